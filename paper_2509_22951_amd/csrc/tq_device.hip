@@ -65,12 +65,6 @@ struct TableWrite {
 };
 static_assert(sizeof(TableWrite) <= 4096, "kernel arguments");
 
-// The stage counters of a staged step start every launch at zero (a fill kernel, not a memset node: the launch may be
-// captured in a HIP graph).
-__global__ __launch_bounds__(256) void k_zero_words(uint32_t* p, uint32_t n) {
-  for (uint32_t i = threadIdx.x; i < n; i += 256) p[i] = 0u;
-}
-
 // Entry t of the table = (description of job t copied from device memory, x, y).  One thread per dword of an entry.
 __global__ __launch_bounds__(64) void k_write_table(TableWrite w) {
   constexpr int kDescDwords = sizeof(DevMat) / 4;
@@ -217,6 +211,11 @@ hipError_t release_dictionary(DictCopy* d) {
 }
 
 constexpr uint32_t kSlotBytes = 2 * kDotWavesMax * 2 * 16 * 4 + 2 * kDotWavesMax * 4;   // (two activation rows at most)
+// slots, their band numbers and, but for two rows of packed weights, the column counts of units shared between wavefronts
+constexpr uint32_t dot_slot_bytes(int waves, int rows, bool counts) { return 2 * waves * rows * 16 * 4 + 2 * waves * 4 + (counts ? waves * 64 * 2 : 0); }
+static_assert(dot_slot_bytes(kDotWaves, 1, true) <= kSlotBytes && dot_slot_bytes(kDotWaves, 2, true) <= kSlotBytes &&
+              dot_slot_bytes(kDotWavesStaged, 2, true) <= kSlotBytes && dot_slot_bytes(kDotWavesPacked, 1, true) <= kSlotBytes &&
+              dot_slot_bytes(kDotWavesPacked, 2, false) <= kSlotBytes, "LDS behind the activation image");
 
 // LDS plan of the product kernel for a set of matrices: dictionary | activation image | partial-sum slots.
 bool plan_matvec_lds(uint32_t dict_words_max, uint32_t x_dwords_max, uint32_t* x_off, uint32_t* slot_off, size_t* total) {
@@ -478,6 +477,56 @@ int fire(const PreparedLaunch& p, hipStream_t stream) {
   return TQ_OK;
 }
 
+// Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
+// that the largest share (bands x columns) is as small as possible.  Returns that share, or 0 when there are more
+// matrices than workgroups or than kMaxAssign.
+constexpr int kMaxAssign = 32;
+uint64_t assign_workgroups(int n, const tq_handle* hs, uint64_t grid, uint32_t* wgs) {
+  if (n > kMaxAssign || (uint64_t)n > grid) return 0;
+  uint64_t total = 0, cols_max = 0;
+  for (int i = 0; i < n; ++i) {
+    if (hs[i]->m.n_bands >= 1u << 23) return 0;   // (share_of_bands multiplies band counts by workgroup counts)
+    total += (uint64_t)hs[i]->m.n_bands * hs[i]->m.cols;
+    cols_max = std::max<uint64_t>(cols_max, hs[i]->m.cols);
+  }
+  auto needed = [&](uint64_t share) {   // workgroups when none takes more than `share`
+    uint64_t sum = 0;
+    for (int i = 0; i < n; ++i) {
+      const uint64_t per = share / hs[i]->m.cols;   // >= 1
+      sum += (hs[i]->m.n_bands + per - 1) / per;
+    }
+    return sum;
+  };
+  uint64_t lo = std::max(cols_max, (total + grid - 1) / grid), hi = lo;
+  while (needed(hi) > grid) hi *= 2;
+  if (hi > lo) {   // needed(lo) > grid >= needed(hi)
+    for (lo = hi / 2; hi - lo > cols_max / 8;) {
+      const uint64_t mid = lo + (hi - lo) / 2;
+      (mid >= cols_max && needed(mid) <= grid ? hi : lo) = mid;
+    }
+  }
+  uint64_t worst = 0;
+  for (int i = 0; i < n; ++i) {
+    const uint64_t bands = hs[i]->m.n_bands, per = hi / hs[i]->m.cols;
+    wgs[i] = (uint32_t)((bands + per - 1) / per);
+    worst = std::max(worst, (bands + wgs[i] - 1) / wgs[i] * hs[i]->m.cols);
+  }
+  return worst;
+}
+// What the busiest workgroup does when the line is cut into `grid` equal parts instead: its part to within half a band,
+// and, with several matrices, a second start (offsets, activations, barriers) in workgroups that get the end of one
+// matrix and the start of the next, worth about kRestartCost of the line (4 us, in which a compute unit streams 100 KB of
+// codes: one LLaMA-3.2-1B layer, 7 matrices, 24.9 us when 6 of the 256 workgroups start twice, 18.4 us in whole workgroups).
+constexpr uint64_t kRestartCost = 6000;
+uint64_t even_cut_cost(int n, const tq_handle* hs, uint64_t grid) {
+  uint64_t total = 0, cols_max = 0;
+  for (int i = 0; i < n; ++i) {
+    total += (uint64_t)hs[i]->m.n_bands * hs[i]->m.cols;
+    cols_max = std::max<uint64_t>(cols_max, hs[i]->m.cols);
+  }
+  return total / grid + cols_max / 2 + (n > 1 ? kRestartCost : 0);
+}
+
 // One kernel launch for hs[0..n), all on one device, total cost below 2^32; n <= kMaxMulti, or n <= kMaxStep when the
 // launch is recorded for a prepared step (rec: its jobs then go to the step's device table, not into the arguments).
 // kMatvec: xs/ys are the activations and outputs; kDecompress: ys are the int8 output matrices, xs is not used.
@@ -538,6 +587,17 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
                : packed ? (batch == 2 ? (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2> : (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1>)
                : batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 2> : (const void*)k_matvec<kDotPiece, kDotWaves, false, 1>;
     p.block = (packed ? kDotWavesPacked : kDotWaves) * 64;
+    uint32_t wgs[kMaxAssign];
+    const uint64_t worst = assign_workgroups(n, hs, std::min<uint64_t>(hs[0]->n_cu, bands), wgs);
+    if (worst && worst <= even_cut_cost(n, hs, p.grid)) {
+      a.by_workgroup = 1;
+      p.grid = 0;
+      for (int i = 0; i < n; ++i) {
+        a.u.cost_long[i] = p.grid;
+        p.grid += wgs[i];
+      }
+      a.u.cost_long[n] = p.grid;
+    }
   } else if (ring) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size: the kernel ORs piece offsets into its
     // address) | the activation tile of one quad.
@@ -788,7 +848,7 @@ struct tq_step {
   // staged steps that run as one launch (all stages in one persistent kernel):
   uint32_t n_stages = 0;
   bool persistent = false;
-  uint32_t* stage_dev = nullptr;    // stage_first[n_stages + 1] | sync[n_stages + 1]
+  uint32_t* stage_dev = nullptr;    // stage_first[n_stages + 1] | the words of the hand-overs (see stage_arrive)
   uint32_t* fault_host = nullptr;   // pinned host word the kernel sets when a hand-over wait gave up
 };
 
@@ -943,15 +1003,39 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
                             : (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 1, false, true>;
     p.block = (packed ? kDotWavesPacked : kDotWavesStaged) * 64;
     p.grid = (unsigned)hs[0]->n_cu;   // one workgroup per compute unit (each takes the whole LDS): all resident together
+    // Whole workgroups per matrix in every stage, if that is the better cut over all stages.
+    std::vector<uint32_t> line((size_t)n + 1, 0);
+    uint64_t whole = 0, even = 0;
+    bool can = true;
+    for (uint32_t k = 0; k < n_stages && can; ++k) {
+      const int f = (int)first[k], cnt = (int)(first[k + 1] - first[k]);
+      uint32_t wgs[kMaxAssign];
+      const uint64_t worst = assign_workgroups(cnt, hs + f, p.grid, wgs);
+      can = worst != 0;
+      whole += worst;
+      even += even_cut_cost(cnt, hs + f, p.grid);
+      uint32_t at = k * p.grid;
+      for (int i = 0; i < cnt && can; ++i) {
+        line[f + i] = at;
+        at += wgs[i];
+      }
+    }
+    line[n] = n_stages * p.grid;   // (workgroups left over in a stage count as its last matrix's)
+    if (can && whole <= even) {
+      a.by_workgroup = 1;
+      std::copy(line.begin(), line.end(), a.u.cost_long);
+    }
     rec.launches.push_back(p);
   }
   s->launches = std::move(rec.launches);
   s->n_entries = rec.entries.size();
   hipError_t e = hipMalloc((void**)&s->table_dev, rec.entries.size() * sizeof(StepEntry));
   if (e == hipSuccess) e = hipMemcpy(s->table_dev, rec.entries.data(), rec.entries.size() * sizeof(StepEntry), hipMemcpyHostToDevice);
+  const size_t sync_at = round_up(n_stages + 1, kLineWords);   // in words, after the list of first jobs
   if (e == hipSuccess && persistent) {
-    e = hipMalloc((void**)&s->stage_dev, (size_t)2 * (n_stages + 1) * 4);
-    if (e == hipSuccess) e = hipMemset(s->stage_dev, 0, (size_t)2 * (n_stages + 1) * 4);
+    const size_t words = sync_at + sync_words(s->launches[0].grid);
+    e = hipMalloc((void**)&s->stage_dev, words * 4);
+    if (e == hipSuccess) e = hipMemset(s->stage_dev, 0, words * 4);   // (every launch leaves the words after the list zero again)
     if (e == hipSuccess) e = hipMemcpy(s->stage_dev, first.data(), (size_t)(n_stages + 1) * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s->fault_host, 64, hipHostMallocMapped);
     if (e == hipSuccess) *s->fault_host = 0;
@@ -965,7 +1049,7 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
     p.a.table = s->table_dev + p.table_first;
     if (persistent) {
       p.a.stage_first = s->stage_dev;
-      p.a.sync = s->stage_dev + n_stages + 1;
+      p.a.sync = s->stage_dev + sync_at;
       void* dp = nullptr;
       e = hipHostGetDevicePointer(&dp, s->fault_host, 0);
       if (e != hipSuccess) return fail(hip_fail("hipHostGetDevicePointer", e));
@@ -987,9 +1071,6 @@ static int tq_step_launch_impl(tq_step_handle s, void* stream) {
                 "resident together?); its results must not be used");
       return TQ_E_HIP;
     }
-    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, (hipStream_t)stream, s->stage_dev + s->n_stages + 1, s->n_stages + 1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail("tq_step_launch: counter reset", e);
   }
   for (const PreparedLaunch& p : s->launches)
     if (int rc = fire(p, (hipStream_t)stream)) return rc;
@@ -1003,7 +1084,7 @@ extern "C" int tq_step_get_info(tq_step_handle s, tq_step_info* out) {
   }
   out->n_matrices = (uint32_t)s->n_matrices;
   out->n_launches = (uint32_t)s->launches.size();
-  out->table_bytes = (uint64_t)s->n_entries * sizeof(StepEntry) + (s->stage_dev ? (uint64_t)(2 * (s->n_stages + 1)) * 4 : 0);
+  out->table_bytes = (uint64_t)s->n_entries * sizeof(StepEntry) + (s->stage_dev ? (uint64_t)(round_up(s->n_stages + 1, kLineWords) + sync_words(s->launches[0].grid)) * 4 : 0);
   out->n_stages = s->n_stages;
   out->persistent = s->persistent ? 1u : 0u;
   out->fault = s->fault_host ? *(volatile uint32_t*)s->fault_host : 0u;

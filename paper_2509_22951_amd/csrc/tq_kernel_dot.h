@@ -6,6 +6,7 @@
 namespace tq {
 // Staging is split in two so that the loads of the dictionary, of the activations and of the first code chunks are
 // all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS.
+constexpr uint32_t kSplitUnits = 4;    // k_matvec splits units between wavefronts in shares of fewer than this many units each
 constexpr int kDictRegs = 16;   // uint4 per thread per round of the tile kernels' dictionary staging
 
 template <int kThreads, int kDictRegs>   // kDictRegs x kThreads x 16 bytes per round (128 KB: the whole dictionary in one)
@@ -28,7 +29,8 @@ __device__ __forceinline__ void commit_dictionary(const DevMat& m, uint32_t base
 
 // LDS image of one activation row: dword (panel * x_span + c) = (x[panel * seg_cols + c], x[panel * seg_cols + c + 1])
 // as two bf16, zero past the end of the row; the gap dwords between panels and the tail are zero.
-// Thread t of a round handles the column pair (2 j, 2 j + 1), j = first_pair + k * 512 + t: it loads x[2j .. 2j+2].
+// Thread t of a round handles the column pair (2 j, 2 j + 1), j = first_pair + k * kThreads + t: it loads x[2j], x[2j + 1];
+// x[2j + 2] is the next lane's, but for the last lane, which loads it (or every lane, when x is not aligned).
 template <bool kAligned, int kThreads, int kXRegs, bool kCoherent = false>   // kXRegs x kThreads x 2 columns per round (8192)
 __device__ __forceinline__ void issue_activations(const DevMat& m, const uint16_t* __restrict__ x, uint32_t first_pair, int tid,
                                                   uint32_t (&lo)[kXRegs], uint32_t (&hi)[kXRegs]) {
@@ -37,10 +39,16 @@ __device__ __forceinline__ void issue_activations(const DevMat& m, const uint16_
     const uint32_t j = first_pair + k * kThreads + tid, col = 2 * j;
     if (kAligned) {   // x is 4-byte aligned and cols is even
       lo[k] = col < m.cols ? x_load<kCoherent>((const uint32_t*)x + j) : 0u;
-      hi[k] = col + 2 < m.cols ? x_load<kCoherent>((const uint32_t*)x + j + 1) : 0u;
     } else {
       lo[k] = (col < m.cols ? x_load<kCoherent>(x + col) : 0u) | (col + 1 < m.cols ? x_load<kCoherent>(x + col + 1) << 16 : 0u);
-      hi[k] = col + 2 < m.cols ? x_load<kCoherent>(x + col + 2) : 0u;
+    }
+    hi[k] = 0u;
+  }
+  if ((tid & 63) == 63) {
+#pragma unroll
+    for (int k = 0; k < kXRegs; ++k) {
+      const uint32_t col = 2 * (first_pair + k * kThreads + tid) + 2;
+      if (col < m.cols) hi[k] = x_load<kCoherent>(x + col);
     }
   }
 }
@@ -51,10 +59,12 @@ __device__ __forceinline__ void commit_activations(const DevMat& m, uint32_t fir
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
     const uint32_t col = 2 * (first_pair + k * kThreads + tid);
+    // the next lane's pair (wave shift by one lane; the last lane keeps what it loaded itself)
+    const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)hi[k], (int)lo[k], 0x130, 0xf, 0xf, false);
     if (col < image_cols) {   // image_cols and seg_cols are even: both dwords of the pair lie in one panel
       const uint32_t i = col + gap * __umulhi(col, m.seg_magic);
       lds_x[i] = lo[k];
-      lds_x[i + 1] = lo[k] >> 16 | hi[k] << 16;
+      lds_x[i + 1] = lo[k] >> 16 | next << 16;
     }
   }
 }
@@ -308,101 +318,259 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   static_assert(kB == 1 || kB == 2, "one activation row or two");
   static_assert(!kLong || (kB == 1 && !kPacked), "runs of 3 and 4 bytes: one activation row of one-weight-per-byte matrices");
   constexpr int kImage = kPacked && kB == 2 ? 2 : 1;   // dwords of the activation image per column
-  constexpr int kThreads = kWaves * 64, kDictRegs = 128 / kWaves, kXRegs = 64 / kWaves;
+  // kSplit: a share of few units is cut into equal runs of chunks, wherever a run starts inside a unit.  (Whole units
+  // leave wavefronts idle: a 2048 x 2048 matrix gives a workgroup two units for its eight wavefronts.)  Where a lane
+  // stands at the start of such a run is the number of columns the wavefronts before it pass in that unit; each counts
+  // its own part while the dictionary is on its way and leaves the counts in LDS, so nothing waits for device memory a
+  // second time.  (2048 x 2048, batch 1: 12.3 -> 10.1 us, decode 5.9 -> 1.9 us of it.)  In shares of kSplitUnits units per
+  // wavefront and more the uneven last unit is no longer worth the counting.
+  constexpr bool kSplit = !kLong && !(kPacked && kB == 2);   // (two rows of packed weights leave no LDS for the counts)
+  constexpr int kCount = 12;   // chunks per round of that count
+  constexpr int kThreads = kWaves * 64, kDictRegs = (kStaged ? 48 : 128) / kWaves, kXRegs = 64 / kWaves;   // (staged: one dictionary for many stages, so few registers)
+  if constexpr (!kStaged) touch_arguments();
   extern __shared__ uint4 lds4[];
   uint32_t* lds_dict = (uint32_t*)lds4;
   uint32_t* lds_x = (uint32_t*)((uint8_t*)lds4 + a.x_off);
   float* slot_val = (float*)((uint8_t*)lds4 + a.slot_off);           // [2 * kWaves][kB][16]
   int* slot_band = (int*)(slot_val + 2 * kWaves * kB * 16);          // [2 * kWaves]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint16_t* lds_count = (uint16_t*)(slot_band + 2 * kWaves);         // kSplit: [kWaves][64] columns of a shared unit, per lane
   const uint32_t* staged = nullptr;
   const uint32_t n_stages = kStaged ? a.n_stages : 1u;
   constexpr uint32_t kNoStage = 0xFFFFFFFFu;
-  uint32_t wait_for = kNoStage;   // staged: the stage whose outputs this workgroup has yet to wait for
-  for (uint32_t stage = 0; stage < n_stages; ++stage) {
-  const int job_first = kStaged ? (int)((const_u32*)a.stage_first)[stage] : 0, job_end = kStaged ? (int)((const_u32*)a.stage_first)[stage + 1] : a.n;
-  const uint32_t cost_first = cost_at(a, job_first);
-  const uint64_t total = cost_at(a, job_end) - cost_first;
-  const uint32_t lo = cost_first + (uint32_t)(total * blockIdx.x / gridDim.x), hi = cost_first + (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
-  for (int i = job_first; i < job_end; ++i) {
-    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb || lo >= ce) continue;
+  uint32_t wait_for = kNoStage;   // staged: the number of stages whose outputs this workgroup has yet to wait for
+  bool lds_used = false;          // an earlier matrix may still be in work
+  // Where the workgroup stands: a stage (the only one unless kStaged), a job of it, its share of the stage's cost line.
+  struct Cursor {
+    uint32_t stage;
+    int i, end;
+    uint32_t lo, hi;
+  };
+  auto enter_stage = [&](Cursor& c) {
+    const int first = kStaged ? (int)((const_u32*)a.stage_first)[c.stage] : 0;
+    c.end = kStaged ? (int)((const_u32*)a.stage_first)[c.stage + 1] : a.n;
+    const uint32_t cost_first = cost_at(a, first);
+    const uint64_t total = cost_at(a, c.end) - cost_first;
+    c.lo = cost_first + (uint32_t)(total * blockIdx.x / gridDim.x);
+    c.hi = cost_first + (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+    c.i = first_job(a, first, c.end, c.lo, lane);
+  };
+  auto settle = [&](Cursor& c) {   // moves on, over stages the workgroup has no share in, to a job it has; false at the end
+    while (c.i >= c.end || cost_at(a, c.i) >= c.hi) {
+      if (++c.stage >= n_stages) return false;
+      enter_stage(c);
+    }
+    return true;
+  };
+  // kStaged: jobs are looked up ahead, so that of the chain table entry -> unit offsets -> code chunks -> decode nothing but
+  // the activations is left behind the hand-over between two stages: while one job is staged, the entry of the job after
+  // the next and the offsets of the next one are requested; when a wavefront has decoded its run it plans its run of the
+  // next job and requests the run's first chunk; the rest of the first piece follows when the workgroup has announced
+  // itself.  (Requested together, ahead of the announcement, they hold it up: the next matrix's pages are new to the
+  // compute unit's address translation, and whatever is issued behind a miss waits for it.)
+  // (Looked up between two stages the chain took 4 to 6 us of every stage of a LLaMA-3.2-3B layer: every stage's matrices
+  // are new to the caches and to address translation.)
+  constexpr uint32_t kEntryDwords = sizeof(StepEntry) / 4;
+  auto request_entry = [&](int i) { return global_load((const uint32_t*)(a.table + i) + min((uint32_t)lane, kEntryDwords - 1)); };
+  auto open_entry = [&](uint32_t entry, Job& job, DevMat& m) {   // entry: dword k in lane k
+    uint32_t w[kEntryDwords];
+#pragma unroll
+    for (uint32_t k = 0; k < kEntryDwords; ++k) w[k] = __builtin_amdgcn_readlane(entry, k);
+    StepEntry v;
+    __builtin_memcpy(&v, w, sizeof v);
+    m = v.m;
+    job.m = nullptr;
+    job.x = v.x;
+    job.y = v.y;
+  };
+  // The unit offsets of a share of few units sit in the lanes: lane k has that of unit k, the lanes behind them the end.
+  constexpr uint32_t kLaneUnits = 64;
+  auto request_offsets = [&](const DevMat& m, uint32_t band_lo, uint32_t band_hi) {
+    const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
+    return n_units < kLaneUnits ? global_load(m.uoff + band_lo * m.n_quads + min((uint32_t)lane, n_units)) : 0u;
+  };
+  // This wavefront's run of a job: the chunks [c0, c_end) of the units [u0, u1).
+  uint32_t uoff_lane = 0;
+  uint32_t unit_lo = 0, u0 = 0, u1 = 0, c0 = 0, c_end = 0, unit_start = 0, split_lo = 0, split_n = 0, part = 0;
+  bool in_lanes = false, split = false, head_shared = false, tail_shared = false;   // the run starts / ends inside a unit
+  uint2 cwa[kPiece], cwb[kPiece];
+  uint2 counted[kCount];   // first chunks of the unit the run leaves unfinished
+  auto offset_of = [&](const DevMat& m, uint32_t u) {
+    if (in_lanes) return (uint32_t)__builtin_amdgcn_readlane(uoff_lane, u - unit_lo);
+    return unit_offset(m, u);
+  };
+  // The chunks of the run come in pieces of at most kPiece that never straddle a unit (a unit, or the part of it that
+  // lies in the run, is cut into equal pieces); two register sets alternate and every piece issues exactly kPiece
+  // loads (those past its end repeat its last chunk), so the loads of the next piece are in flight while this one is
+  // worked on.  A piece runs as straight-line code: the LDS reads of later chunks overlap the dot products of earlier ones.
+  uint32_t wu = 0, wc = 0, w_left = 0, w_base = 0, w_rem = 0;
+  bool w_ends = false;   // the unit in work ends inside the run
+  auto next_piece = [&](const DevMat& m, uint32_t& start, uint32_t& n, bool& ends) {
+    if (w_left == 0) {
+      if (wu == u1) {
+        n = 0;
+        ends = false;
+        start = wc;
+        return;
+      }
+      const uint32_t unit_end = offset_of(m, wu + 1);
+      w_ends = unit_end <= c_end;
+      const uint32_t len = min(unit_end, c_end) - wc;
+      w_left = (len + kPiece - 1) / kPiece;
+      w_base = len / w_left;
+      w_rem = len - w_base * w_left;
+      ++wu;
+    }
+    n = w_base + (w_rem ? 1u : 0u);
+    if (w_rem) --w_rem;
+    start = wc;
+    wc += n;
+    ends = --w_left == 0 && w_ends;
+  };
+  auto load_piece = [&](const DevMat& m, uint2 (&cw)[kPiece], uint32_t start, uint32_t n, bool all = true, bool only_first = false) {
+    const uint32_t last = min(start + max(n, 1u) - 1, c_end - 1);
+#pragma unroll
+    for (int k = 0; k < kPiece; ++k)
+      if (all || (k == 0) == only_first) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
+  };
+  uint32_t sa = 0, na = 0, sb, nb;
+  bool ea = false, eb;
+  // Cuts the share [band_lo, band_hi) of a job and requests the first piece of the wavefront's run (ahead of the staging of
+  // dictionary and activations, so that a small launch does not wait for device memory twice in a row).
+  auto plan_run = [&](const DevMat& m, uint32_t band_lo, uint32_t band_hi) {
+    unit_lo = band_lo * m.n_quads;
+    const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
+    in_lanes = n_units < kLaneUnits;
+    split = kSplit && n_units < kSplitUnits * kWaves && in_lanes && n_units % kWaves != 0;
+    // (values of the two ways meet in local variables and are assigned once: assigned in each branch, the compiler keeps
+    // them in memory)
+    uint32_t first = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves), end = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
+    uint32_t lo = 0, hi = 0, start = 0, shared_from = 0, all_lo = 0, all_n = 0;
+    bool head = false, tail = false;
+    if (split) {   // few units per wavefront: see kSplit above
+      all_lo = offset_of(m, unit_lo);
+      all_n = offset_of(m, unit_lo + n_units) - all_lo;
+      lo = all_lo + all_n * wave / kWaves;
+      hi = all_lo + all_n * (wave + 1) / kWaves;
+      const uint64_t lanes = (2ull << n_units) - 1;   // lanes 0 .. n_units hold the offsets
+      first = unit_lo + (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane <= lo) & lanes) - 1;
+      const uint32_t last = unit_lo + (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane < max(hi, lo + 1)) & lanes) - 1;
+      end = lo < hi ? last + 1 : first;
+      start = offset_of(m, first);
+      const uint32_t last_start = offset_of(m, last), last_end = offset_of(m, last + 1);
+      head = lo > start;
+      tail = lo < hi && hi < last_end;
+      shared_from = tail ? max(lo, last_start) : hi;
+    } else if (first < end) {
+      lo = offset_of(m, first);
+      hi = offset_of(m, end);
+    }
+    u0 = first;
+    u1 = end;
+    c0 = lo;
+    c_end = hi;
+    unit_start = start;
+    part = shared_from;
+    split_lo = all_lo;
+    split_n = all_n;
+    head_shared = head;
+    tail_shared = tail;
+    wu = u0;
+    wc = c0;
+    w_left = 0;
+    na = 0;
+    ea = false;
+    if (u0 < u1) next_piece(m, sa, na, ea);
+  };
+  // Columns every lane passes in this wavefront's part of the unit it leaves unfinished: where the wavefronts after it
+  // start.  (Run lengths follow from the codes alone; an empty run passes nothing.)
+  auto request_count = [&](const DevMat& m, uint32_t from) {
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) counted[k] = load_chunk(m.codes, min(from + k, c_end - 1), lane);
+  };
+  auto count_columns = [&](const DevMat& m) {
+    u16x2 pairs = {0, 0};
+    if (tail_shared) {
+      for (uint32_t from = part;;) {
+#pragma unroll
+        for (int k = 0; k < kCount; ++k)
+          if (from + k < c_end) pairs = count_pairs(count_pairs(pairs, counted[k].x), counted[k].y);
+        from += kCount;
+        if (from >= c_end) break;
+        request_count(m, from);
+      }
+    }
+    lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (c_end - part) + pairs.x + pairs.y);
+  };
+  Cursor at, next;   // (next: one job further, kStaged only)
+  at.stage = 0;
+  enter_stage(at);
+  uint32_t arrived = 0;   // kStaged: the stages this workgroup has announced to have behind it
+  uint32_t entry_at = 0, entry_next = 0, entry_later = 0;
+  bool have = settle(at), have_next = false, have_later = false, planned = false;
+  if (kStaged && have) {
+    entry_at = request_entry(at.i);
+    next = at;
+    ++next.i;
+    have_next = settle(next);
+    if (have_next) entry_next = request_entry(next.i);
+  }
+  Cursor later;
+  auto look_further = [&] {
+    if constexpr (kStaged) {
+      later = next;
+      ++later.i;
+      have_later = have_next && settle(later);
+      if (have_later) entry_later = request_entry(later.i);
+    }
+  };
+  auto advance = [&] {
+    if constexpr (kStaged) {
+      at = next;
+      next = later;
+      have = have_next;
+      have_next = have_later;
+      entry_at = entry_next;
+      entry_next = entry_later;
+    } else {
+      ++at.i;
+      have = settle(at);
+    }
+  };
+  while (have) {
     Job job;
     DevMat m;
-    fetch_job(a, i, job, m);
-    // a band goes to the share that holds its middle
-    const uint32_t bc = m.cols;
-    const uint32_t band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
-    const uint32_t band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
-    if (band_lo >= band_hi) continue;
+    if constexpr (kStaged) open_entry(entry_at, job, m);
+    else fetch_job(a, at.i, job, m);
+    uint32_t band_lo, band_hi;
+    share_of_bands(a, m, cost_at(a, at.i), cost_at(a, at.i + 1), at.lo, at.hi, band_lo, band_hi);
+    if (kStaged && at.stage > arrived) {
+      wait_for_stores();
+      stage_arrive(a, at.stage);
+      wait_for = at.stage;
+      arrived = at.stage;
+    }
+    if (band_lo >= band_hi) {
+      look_further();
+      planned = false;
+      advance();
+      continue;
+    }
     const bool new_dict = m.dict_bf16 != staged;
     staged = m.dict_bf16;
     const uint32_t nq = m.n_quads, n_slots = nq * kUnitPanels, image_cols = n_slots * m.seg_cols;
-    const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
-    const uint32_t u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves);
-    const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
     // lane's panel inside a unit is lane >> 4; quad q adds 4 q panels
     const uint32_t xa_lane = lds_address(lds_x) + 4u * kImage * m.x_span * (uint32_t)(lane >> 4);
     const uint32_t xa_quad = 16u * kImage * m.x_span;
     const bool x_aligned = (kPacked || m.cols % 2 == 0) && ((uintptr_t)job.x % 4 == 0);   // (cols even: a second row is aligned like the first)
-    const uint32_t c0 = u0 < u1 ? unit_offset(m, u0) : 0u, n_chunks = u0 < u1 ? unit_offset(m, u1) - c0 : 0u;
+    if (!planned) uoff_lane = request_offsets(m, band_lo, band_hi);
     {   // one activation row, or two: larger batches run the MFMA kernels
       const uint16_t* xb = job.x;
       float* yb = job.y;
-      // The chunks of the run come in pieces of at most kPiece that never straddle a unit (a unit is cut into equal
-      // pieces); two register sets alternate and every piece issues exactly kPiece loads (those past its end repeat
-      // its last chunk), so the loads of the next piece are in flight while this one is worked on.  A piece of kPiece
-      // or kPiece - 1 chunks (all pieces of a unit of 256-column segments) runs as straight-line code: the LDS reads
-      // of later chunks overlap the dot products of earlier ones.
-      uint32_t wu = u0, wc = c0, w_left = 0, w_base = 0, w_rem = 0;
-      auto next_piece = [&](uint32_t& start, uint32_t& n, bool& ends) {
-        if (w_left == 0) {
-          if (wu == u1) {
-            n = 0;
-            ends = false;
-            start = wc;
-            return;
-          }
-          const uint32_t len = unit_offset(m, wu + 1) - wc;
-          w_left = (len + kPiece - 1) / kPiece;
-          w_base = len / w_left;
-          w_rem = len - w_base * w_left;
-          ++wu;
-        }
-        n = w_base + (w_rem ? 1u : 0u);
-        if (w_rem) --w_rem;
-        start = wc;
-        wc += n;
-        ends = --w_left == 0;
-      };
-      const uint32_t run_last = c0 + n_chunks - 1;
-      auto load_piece = [&](uint2 (&cw)[kPiece], uint32_t start, uint32_t n) {
-        const uint32_t last = min(start + max(n, 1u) - 1, run_last);
-#pragma unroll
-        for (int k = 0; k < kPiece; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
-      };
-      // The first piece of code chunks is requested here, ahead of the staging of dictionary and activations: the
-      // chunks then arrive while the workgroup stages, and a small launch does not wait for device memory twice in a row.
-      uint2 cwa[kPiece], cwb[kPiece];
-      uint32_t sa = c0, na = 0, sb, nb;
-      bool ea = false, eb;
-      if (u0 < u1) {
-        next_piece(sa, na, ea);
-        load_piece(cwa, sa, na);
-      }
-      // the previous dictionary, activation image and slots are no longer in use; staged: nor is anyone still writing
-      // the activations (the wait ends with the same barrier)
-      if (kStaged && wait_for != kNoStage) {
-        stage_wait(a, wait_for);
-        wait_for = kNoStage;
-      } else {
-        __syncthreads();
-      }
-      {
-        uint4 dv[kDictRegs];
-        uint32_t xlo[kXRegs], xhi[kXRegs];
-        const bool dict_now = new_dict;
-        if (dict_now) issue_dictionary<kThreads, kDictRegs>(m, 0, tid, dv);
+      // Dictionary and activations are requested first: their addresses wait for nothing but the description.
+      uint4 dv[kDictRegs];
+      uint32_t xlo[kXRegs], xhi[kXRegs];
+      auto request_activations = [&] {
         if constexpr (kPacked) {
           if (x_aligned) issue_activations_packed<true, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo);
           else issue_activations_packed<false, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo);
@@ -417,15 +585,50 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
           if (x_aligned) issue_activations<true, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
           else issue_activations<false, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
         }
+      };
+      if (new_dict) issue_dictionary<kThreads, kDictRegs>(m, 0, tid, dv);
+      if constexpr (!kStaged) request_activations();   // (staged: they may still be in the making)
+      if (!planned) {
+        plan_run(m, band_lo, band_hi);
+        if (u0 < u1) load_piece(m, cwa, sa, na);
+      } else if (u0 < u1) {
+        load_piece(m, cwa, sa, na, false, false);
+      }
+      if (tail_shared) request_count(m, part);
+      if constexpr (kStaged) {   // while the other workgroups arrive
+        if (lds_used && wait_for == kNoStage) __syncthreads();   // (the counts of the job before are no longer read)
+        if (split) count_columns(m);
+      }
+      // the previous dictionary, activation image and slots are no longer in use; staged: nor is anyone still writing
+      // the activations (the wait ends with the same barrier)
+      if (kStaged && wait_for != kNoStage) {
+        stage_wait(a, wait_for);
+        wait_for = kNoStage;
+      } else if (lds_used) {
+        __syncthreads();
+      }
+      lds_used = true;
+      if constexpr (kStaged) request_activations();
+      look_further();
+      uint32_t uoff_next = 0, next_lo = 0, next_hi = 0;
+      if (kStaged && have_next) {
+        Job next_job;
+        DevMat next_m;
+        open_entry(entry_next, next_job, next_m);
+        share_of_bands(a, next_m, cost_at(a, next.i), cost_at(a, next.i + 1), next.lo, next.hi, next_lo, next_hi);
+        if (next_lo < next_hi) uoff_next = request_offsets(next_m, next_lo, next_hi);
+      }
+      {
         zero_activation_gaps<kThreads, kImage>(m, tid, lds_x, n_slots);
         if (tid < 2 * kWaves) slot_band[tid] = -1;
-        if (dict_now) {
+        if (new_dict) {
           commit_dictionary<kThreads, kDictRegs>(m, 0, tid, dv, lds_dict);
           for (uint32_t base = kDictRegs * kThreads; base < m.dict_words / 4; base += kDictRegs * kThreads) {
             issue_dictionary<kThreads, kDictRegs>(m, base, tid, dv);
             commit_dictionary<kThreads, kDictRegs>(m, base, tid, dv, lds_dict);
           }
         }
+        if (!kStaged && split) count_columns(m);   // (after the dictionary, which was requested first)
         if constexpr (kPacked && kB == 2) {
           commit_activations_packed_two<kThreads, kXRegs>(m, 0, tid, xlo, xhi, lds_x, image_cols);
           for (uint32_t first = kXRegs * kThreads; first < image_cols; first += kXRegs * kThreads) {
@@ -462,11 +665,20 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         }
       }
       __syncthreads();
+      float slot_scale = 0.f;   // row scales of the bands in this wavefront's two slots: the first one's in lanes 0..31
       if (u0 < u1) {
         uint32_t q = u0 % nq, band = u0 / nq;
-        bool whole = q == 0;                             // the current band started inside this wavefront's run
+        bool whole = q == 0 && !head_shared;             // the current band started inside this wavefront's run
         float a0 = 0.f, a1 = 0.f;
         uint32_t xa = xa_lane + q * xa_quad;
+        if (head_shared) {   // the columns of this unit that earlier wavefronts take
+          uint32_t passed = 0;
+          for (int w = wave - 1; w >= 0; --w) {
+            passed += lds_count[w * 64 + lane];
+            if (split_lo + split_n * w / kWaves <= unit_start) break;
+          }
+          xa += 4u * kImage * passed;
+        }
         // the scales of the band in work are requested when the band starts (the array is padded to whole bands)
         float scale = global_load(m.scales + band * kUnitRows + (lane & 15));
         auto finish_band = [&](bool complete) {
@@ -495,6 +707,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             for (int b = 0; b < kB; ++b)
               if (lane < 16) slot_val[(s * kB + b) * 16 + lane] = v[b];
             if (lane == 0) slot_band[s] = (int)band;
+            slot_scale = (lane >= 32) == whole ? scale : slot_scale;
           }
         };
         auto run_piece = [&](const uint2 (&cw)[kPiece], uint32_t n, bool ends) {
@@ -536,18 +749,15 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             straight(std::integral_constant<int, kPiece - 1>{});
           } else if (n == kPiece - 2) {
             straight(std::integral_constant<int, kPiece - 2>{});
-          } else {
-            static_for<kPiece>([&](auto kk) {
-              if ((uint32_t)decltype(kk)::value < n) {
-                read(kk);
-                dot(kk);
-              }
+          } else {   // shorter pieces: ends of shared units, narrow segments
+            static_for<kPiece - 3>([&](auto kk) {
+              if (n == (uint32_t)decltype(kk)::value + 1) straight(std::integral_constant<int, decltype(kk)::value + 1>{});
             });
           }
           if constexpr (!kLong) xa += 16 * kImage * n;   // (the long form keeps xa at the lane's column itself)
           if (ends) {   // every lane restarts at the first column of its next segment
             if (++q == nq) {
-              const bool more = band * nq + nq < u1;
+              const bool more = (band + 1) * nq < u1;
               finish_band(whole);
               q = 0;
               ++band;
@@ -560,41 +770,64 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
           }
         };
         while (na) {
-          next_piece(sb, nb, eb);
-          load_piece(cwb, sb, nb);
+          next_piece(m, sb, nb, eb);
+          load_piece(m, cwb, sb, nb);
           run_piece(cwa, na, ea);
-          next_piece(sa, na, ea);
-          load_piece(cwa, sa, na);
+          next_piece(m, sa, na, ea);
+          load_piece(m, cwa, sa, na);
           run_piece(cwb, nb, eb);
         }
-        if (u1 % nq) finish_band(false);   // the run ends inside a band (a band that ends with the run was finished above)
+        if (u1 % nq || tail_shared) finish_band(false);   // the run ends inside a band (a band that ends with the run was finished above)
+      }
+      planned = kStaged && next_lo < next_hi;
+      if (planned) {
+        Job next_job;
+        DevMat next_m;
+        open_entry(entry_next, next_job, next_m);
+        uoff_lane = uoff_next;
+        plan_run(next_m, next_lo, next_hi);
+        if (u0 < u1) load_piece(next_m, cwa, sa, na, false, true);
       }
       __syncthreads();
-      // Combine the shared bands: the first slot of a band adds the later slots of the same band in slot order.
-      if (tid < 2 * kWaves * kB * 16) {   // one thread per slot, activation row and row of the band
-        const int s = tid / (16 * kB), b = (tid >> 4) % kB, r16 = tid & 15;
-        const int bnd = slot_band[s];
-        bool first = bnd >= 0;
-        for (int t = 0; t < s; ++t) first = first && slot_band[t] != bnd;
-        if (first) {
-          float sum = slot_val[(s * kB + b) * 16 + r16];
-          for (int t = s + 1; t < 2 * kWaves; ++t)
-            if (slot_band[t] == bnd) sum += slot_val[(t * kB + b) * 16 + r16];
+      // Combine the shared bands: the first slot of a band adds the later slots of the same band in slot order.  Every
+      // wavefront sees to its own two slots, whose row scales it still holds; lanes are (slot, activation row, row).
+      {
+        const int slots = lane < 2 * kWaves ? slot_band[lane] : -1;
+        uint64_t same[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int band = __builtin_amdgcn_readlane(slots, 2 * wave + j);
+          same[j] = __builtin_amdgcn_ballot_w64(slots == band && slots >= 0);
+          if (same[j] & ((1ull << (2 * wave + j)) - 1)) same[j] = 0;   // an earlier slot of the band does it
+        }
+        const int j = lane >> 5, b = lane >> 4 & 1, r16 = lane & 15;
+        if (b < kB && (same[0] | same[1])) {
+          double total = 0.;   // (so that the number of wavefronts that share a band adds no rounding)
+#pragma unroll
+          for (int t = 0; t < 2 * kWaves; ++t) {   // all slots are read at once, the ones of other bands dropped
+            const float v = slot_val[(t * kB + b) * 16 + r16];
+            total += (j ? same[1] : same[0]) >> t & 1 ? v : 0.f;
+          }
+          const float sum = (float)total;
+          const int bnd = j ? __builtin_amdgcn_readlane(slots, 2 * wave + 1) : __builtin_amdgcn_readlane(slots, 2 * wave);
+          const bool mine = (j ? same[1] : same[0]) != 0;
           const uint32_t row = (uint32_t)bnd * kUnitRows + r16;
-          if (a.gate_up) {   // the two threads of a pair of rows are neighbours and take this branch together
-            const float t = sum * global_load(m.scales + min(row, m.rows - 1)), other = __shfl_xor(t, 1);
-            if (!(r16 & 1) && row + 1 < m.rows) y_store<kStaged>(yb + (size_t)b * (m.rows / 2) + row / 2, silu_times(t, other));
-          } else if (row < m.rows) {
-            y_store<kStaged>(yb + (size_t)b * m.rows + row, sum * global_load(m.scales + row));
+          const float t = sum * slot_scale;
+          if (a.gate_up) {   // lanes 2r, 2r + 1 hold the gate and the up row of output r
+            const float other = __shfl_xor(t, 1);
+            if (mine && !(r16 & 1) && row + 1 < m.rows) y_store<kStaged>(yb + (size_t)b * (m.rows / 2) + row / 2, silu_times(t, other));
+          } else if (mine && row < m.rows) {
+            y_store<kStaged>(yb + (size_t)b * m.rows + row, t);
           }
         }
       }
     }
+    advance();
   }
-  if (kStaged && stage + 1 < n_stages) {
-    stage_arrive(a, stage);
-    wait_for = stage;
-  }
+  if constexpr (kStaged) {
+    wait_for_stores();
+    if (arrived + 1 < n_stages) stage_arrive(a, n_stages - 1);   // (stages without a share; nobody waits for the last one)
+    stage_end(a);
   }
 }
 

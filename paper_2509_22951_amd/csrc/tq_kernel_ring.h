@@ -214,15 +214,14 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
   const uint32_t* staged = nullptr;
   const int bn = lane & 15, kg = lane >> 4;   // B operand: batch row and k-group (panel) of this lane
   const uint32_t ring = rings + (uint32_t)wave * (64 * kRingBytes) + (uint32_t)lane * kRingBytes;
-  for (int i = 0; i < a.n; ++i) {
+  for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb || lo >= ce) continue;
+    if (hi <= cb) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
-    const uint32_t bc = m.cols;
-    const uint32_t band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
-    const uint32_t band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
+    uint32_t band_lo, band_hi;
+    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     constexpr uint32_t pk = kPacked ? 2u : 1u;             // columns of the weight matrix per stored byte
     const uint32_t nq = m.n_quads, n_win = pk * m.seg_cols / 8;   // activation windows (8 columns) per segment

@@ -23,15 +23,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
   const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
   const uint32_t* staged = nullptr;
   const int bn = lane & 15, kg = lane >> 4;   // B operand: batch row and k-group of this lane
-  for (int i = 0; i < a.n; ++i) {
+  for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb || lo >= ce) continue;
+    if (hi <= cb) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
-    const uint32_t bc = m.cols;
-    const uint32_t band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
-    const uint32_t band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
+    uint32_t band_lo, band_hi;
+    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads;
     const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
@@ -172,15 +171,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
   const uint64_t total = cost_at(a, a.n);
   const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
   const uint32_t* staged = nullptr;
-  for (int i = 0; i < a.n; ++i) {
+  for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb || lo >= ce) continue;
+    if (hi <= cb) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
-    const uint32_t bc = m.cols;
-    const uint32_t band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
-    const uint32_t band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
+    uint32_t band_lo, band_hi;
+    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads;
     const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;

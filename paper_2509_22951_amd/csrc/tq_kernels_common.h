@@ -85,20 +85,22 @@ struct StepEntry {
 };
 constexpr int kMaxStep = 896;        // matrices one launch can serve when the jobs come from a device table
 
-// The launch's cost line: matrix i covers [cost[i], cost[i + 1]), one band of it costs its number of columns.
+// The launch's cost line: matrix i covers [cost[i], cost[i + 1]), one band of it costs its number of columns (by_workgroup:
+// the line counts workgroups instead).
 // The jobs travel in the kernel arguments (up to kMaxMulti of them) or, for a prepared step, sit in a table in device
 // memory (up to kMaxStep); the cost line is in the arguments either way, at the same place.
 struct MatvecArgs {
   int n, batch;
   uint32_t x_off, slot_off;   // byte offsets in LDS of the activation image (or of the tiles) and of the partial-sum slots
   uint32_t tile_area;         // bytes of LDS per wavefront in the tile kernels (the same for every matrix of the launch)
-  uint32_t gate_up;           // 1: rows 2r and 2r + 1 are a gate and an up projection; y[b][r] = silu(row 2r) * (row 2r + 1)
+  uint16_t gate_up;           // 1: rows 2r and 2r + 1 are a gate and an up projection; y[b][r] = silu(row 2r) * (row 2r + 1)
+  uint16_t by_workgroup;      // 1: the cost line counts workgroups (see share_of_bands)
   const StepEntry* table;     // device table of the n jobs, or null: then j and first below hold them
   // A staged step (one launch for products that depend on each other): the jobs come in n_stages groups, jobs
   // stage_first[s] .. stage_first[s + 1] - 1 form stage s, and no workgroup starts a stage before every workgroup has
-  // stored the results of the one before (grid-wide hand-over through sync[s]; sync[n_stages] is set when a wait gave up).
+  // stored the results of the one before (grid-wide hand-over through the words at sync, see stage_arrive).
   const uint32_t* stage_first;   // device, n_stages + 1 entries; null: not staged
-  uint32_t* sync;                // device, n_stages + 1 words, zero at launch
+  uint32_t* sync;                // device, sync_words(gridDim.x) words, zero at launch
   uint32_t* fault_host;          // host memory the device can write: set to 1 when a wait gave up
   uint32_t n_stages;
   uint32_t spin_limit;           // polls of a stage counter before a workgroup gives up
@@ -194,6 +196,47 @@ __device__ __forceinline__ DevMat load_description(const DevMat* p) {
 // Point i of the launch's cost line (the two forms of the arguments keep it at the same place).
 __device__ __forceinline__ uint32_t cost_at(const MatvecArgs& a, int i) { return a.u.cost_long[i]; }
 
+// The lines of the kernel arguments a launch of few matrices looks at - head and cost line, first job, first description -
+// requested together: taken as they are needed, each costs a round trip of its own (0.3 us) before the first load of
+// the matrix can start.
+__device__ __forceinline__ void touch_arguments() {
+  const const_u32* k = (const const_u32*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr size_t job = offsetof(MatvecArgs, u.in.j) / 4, desc = offsetof(MatvecArgs, u.in.first) / 4;
+  const uint32_t v0 = k[0], v1 = k[16], v2 = k[job], v3 = k[desc], v4 = k[desc + 16], v5 = k[desc + sizeof(DevMat) / 4 - 1];
+  asm volatile("" ::"s"(v0), "s"(v1), "s"(v2), "s"(v3), "s"(v4), "s"(v5));
+}
+
+// First job of [first, end) that ends behind point `lo` of the cost line.  A step has up to kMaxStep jobs: looking at
+// them one after the other costs a scalar load's latency each (the last workgroups of a 113-matrix step began 3 us late),
+// so the 64 lanes look at 64 of them at a time.
+__device__ __forceinline__ int first_job(const MatvecArgs& a, int first, int end, uint32_t lo, int lane) {
+  if (end - first <= 4) {
+    while (first < end && cost_at(a, first + 1) <= lo) ++first;
+    return first;
+  }
+  for (; first < end; first += 64) {
+    const uint64_t behind = __builtin_amdgcn_ballot_w64(first + lane < end && cost_at(a, min(first + lane, end - 1) + 1) > lo);
+    if (behind) return first + __builtin_ctzll(behind);
+  }
+  return end;
+}
+
+// The bands of matrix m, at [cb, ce) of the cost line, that belong to the share [lo, hi) of a workgroup.
+// Cost line in weights: a band goes to the share that holds its middle; a workgroup may get the end of one matrix and the
+// start of the next.  Cost line in workgroups (launches of few matrices, see assign_workgroups): [lo, hi) is one
+// workgroup, inside one matrix, which has its bands split evenly over its ce - cb workgroups.
+__device__ __forceinline__ void share_of_bands(const MatvecArgs& a, const DevMat& m, uint32_t cb, uint32_t ce, uint32_t lo, uint32_t hi,
+                                               uint32_t& band_lo, uint32_t& band_hi) {
+  if (a.by_workgroup) {
+    band_lo = (lo - cb) * m.n_bands / (ce - cb);
+    band_hi = (hi - cb) * m.n_bands / (ce - cb);
+  } else {
+    const uint32_t bc = m.cols;
+    band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
+    band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
+  }
+}
+
 // Job i of the launch and the description of its matrix: from the kernel arguments, or from the step's device table
 // (scalar loads, like the descriptions the arguments do not hold by value).
 __device__ __forceinline__ void fetch_job(const MatvecArgs& a, int i, Job& job, DevMat& m) {
@@ -217,41 +260,85 @@ __device__ __forceinline__ void fetch_job(const MatvecArgs& a, int i, Job& job, 
 
 // Grid-wide hand-over between two stages of a staged step.  The stage's outputs were stored with device-coherent
 // stores (y_store<true>); every wavefront waits until its own stores have been acknowledged, the workgroup meets at a
-// barrier, one thread announces the workgroup at the stage's counter and polls it until all gridDim.x workgroups have
-// arrived (relaxed device-scope atomics throughout: the counter and the data are coherent by the way they are accessed,
-// so no cache is written back or invalidated).  The next stage loads its activations coherently too (x_load<true>).
+// barrier and announces itself by writing the number of stages it has behind it to its word of the table at sync, and the
+// first wavefront polls the table until no workgroup is behind (relaxed device-scope atomics throughout: the words
+// and the data are coherent by the way they are accessed, so no cache is written back or invalidated).  The next stage
+// loads its activations coherently too (x_load<true>).
+// There are kSyncCopies copies of the table, each polled by 1 / kSyncCopies of the workgroups.  What this and the layout
+// rest on: workgroups that poll one line keep its memory channel busy, and announcements queue behind them.  Four
+// LLaMA-3.2-3B layers as 16 stages, us: one counter per stage that everybody adds to and polls 272, 2, 4, 8 such counters
+// 250, 237, 231; a table of plain words 227, in 4, 8, 16, 32 copies 219, 216, 222, 223.
 // All workgroups of the launch must be resident together (the host launches at most one per compute unit).  The wait is
 // bounded: after spin_limit polls, or when another workgroup has given up, the workgroup sets the fault words and
 // goes on without waiting - the launch then ends with results that must not be used, and the host reports it.
 // The hand-over comes in two halves so that a workgroup can fetch what its next stage needs and what no other workgroup
 // writes (matrix descriptions, unit offsets, the first code chunks) between the two, while the others still finish.
-// stage_arrive: this workgroup's outputs of `stage` are out.  stage_wait: every workgroup's are; it ends with a
+// stage_arrive: this workgroup's outputs of the stages are out.  stage_wait: every workgroup's are; it ends with a
 // workgroup barrier.  A workgroup that has no share of a stage goes on to the next arrive without waiting: it reads
 // and writes nothing there, and whatever it does later comes after a wait on a later stage.
-__device__ __forceinline__ void stage_arrive(const MatvecArgs& a, uint32_t stage) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores have reached the level the device shares
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_fetch_add(a.sync + stage, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The words are zero when a launch starts: stage_end, the last thing a workgroup does, counts the workgroups out, and the
+// last one clears them (nobody else looks at them any more) for the launch that follows on the stream.
+constexpr uint32_t kSyncCopies = 8, kLineWords = 32;
+__host__ __device__ constexpr uint32_t sync_stride(uint32_t grid) { return (grid + 127) / 128 * 128; }   // words of a copy
+__host__ __device__ constexpr uint32_t fault_word(uint32_t grid) { return kSyncCopies * sync_stride(grid); }
+__host__ __device__ constexpr uint32_t sync_words(uint32_t grid) { return fault_word(grid) + 2; }
+typedef __attribute__((address_space(1))) uint32_t global_u32;
+typedef __attribute__((address_space(1))) uint64_t global_u64;
+
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void stage_arrive(const MatvecArgs& a, uint32_t stages) {   // this workgroup's outputs of stages 0 .. stages - 1
+  __syncthreads();   // every wavefront's stores have reached the level the device shares
+  if (threadIdx.x < kSyncCopies)
+    __hip_atomic_store((global_u32*)a.sync + threadIdx.x * sync_stride(gridDim.x) + blockIdx.x, stages, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void stage_wait(const MatvecArgs& a, uint32_t stage) {
-  if (threadIdx.x == 0) {
-    uint32_t* counter = a.sync + stage;
-    uint32_t* fault = a.sync + a.n_stages;
+__device__ __forceinline__ void stage_wait(const MatvecArgs& a, uint32_t stages) {
+  if (threadIdx.x < 64) {
+    const uint32_t lane = threadIdx.x;
+    const global_u32* mine = (const global_u32*)a.sync + blockIdx.x % kSyncCopies * sync_stride(gridDim.x);
+    global_u32* fault = (global_u32*)a.sync + fault_word(gridDim.x);
     uint32_t polls = 0;
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) {
-      if (++polls > a.spin_limit || __hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-        __hip_atomic_store(fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.fault_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (;;) {
+      bool behind = false;
+      for (uint32_t w = 2 * lane; w < gridDim.x; w += 128) {
+        const uint64_t two = __hip_atomic_load((const global_u64*)(mine + w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        behind = behind || (uint32_t)two < stages || (w + 1 < gridDim.x && (uint32_t)(two >> 32) < stages);
+      }
+      if (__builtin_amdgcn_ballot_w64(behind) == 0) break;
+      ++polls;   // (the fault word, one for all, is looked at now and then)
+      if (polls > a.spin_limit || (polls % 32 == 0 && __hip_atomic_load(fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        if (lane == 0) {
+          __hip_atomic_store(fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(a.fault_host, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(1);
     }
   }
   __syncthreads();
 }
+__device__ __forceinline__ void stage_end(const MatvecArgs& a) {
+  if (threadIdx.x < 64) {
+    global_u32* sync = (global_u32*)a.sync;
+    const uint32_t fault = fault_word(gridDim.x);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this workgroup's announcements are in
+    uint32_t before = 0;
+    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(sync + fault + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) == gridDim.x - 1)
+      for (uint32_t i = threadIdx.x; i < sync_words(gridDim.x); i += 64)
+        if (i != fault) __hip_atomic_store(sync + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
 
 // Byte address inside LDS of a pointer into the workgroup's dynamic shared memory.
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(const lds_u8*)p; }
+
+// 16-bit halves of a packed code pair that are at least 256, as 0 / 1 in either half: the runs of two weights.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 count_pairs(u16x2 acc, uint32_t codes) {
+  const u16x2 high = __builtin_bit_cast(u16x2, codes) >> 8;
+  return acc + __builtin_elementwise_min(high, u16x2{1, 1});
+}
 
 // Pointer forms on purpose: the compiler tracks the outstanding LDS read and places the wait before the first use.
 __device__ __forceinline__ uint32_t lds_read32(uint32_t addr) { return *(lds_cu32*)(size_t)addr; }
