@@ -80,7 +80,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
     if (uoff[u + 1] <= uoff[u] || uoff[u + 1] > h.n_chunks) return bad("unit offsets");
 
   // Codes: in range, pads only at the end of a lane stream, every lane stream's runs sum to its segment's length.
-  std::atomic<uint64_t> first_bad(UINT64_MAX), real_codes(0);
+  std::atomic<uint64_t> first_bad(UINT64_MAX), real_codes(0), wide_units(0);
   std::atomic<uint32_t> overrun(0), spread(0);
   n_threads = std::max(1u, std::min(n_threads, 16u));
   n_threads = (unsigned)std::min<uint64_t>(n_threads, n_units);
@@ -88,6 +88,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   auto work = [&](uint64_t ub, uint64_t ue) {
     uint64_t real = 0;
     uint32_t over = 0, wide = 0;
+    uint64_t last_wide = 0;   // 1 + the last unit of this range whose lanes drift further apart than kWideSpread
     std::vector<uint32_t> reach_lo, reach_hi;   // per chunk count: least / greatest column reached by an unfinished lane
     for (uint64_t u = ub; u < ue && first_bad.load(std::memory_order_relaxed) == UINT64_MAX; ++u) {
       const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
@@ -115,7 +116,10 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
         over = std::max(over, want + pad_advance * pads);
       }
       for (size_t k = 0; ok && k < reach_lo.size(); ++k)
-        if (reach_hi[k] > reach_lo[k] && reach_lo[k] != UINT32_MAX) wide = std::max(wide, reach_hi[k] - reach_lo[k]);
+        if (reach_hi[k] > reach_lo[k] && reach_lo[k] != UINT32_MAX) {
+          wide = std::max(wide, reach_hi[k] - reach_lo[k]);
+          if (reach_hi[k] - reach_lo[k] > kWideSpread) last_wide = u + 1;
+        }
       if (!ok) {
         uint64_t cur = first_bad.load();
         while (u < cur && !first_bad.compare_exchange_weak(cur, u)) {}
@@ -124,6 +128,8 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
     real_codes += real;
     uint32_t cur = overrun.load();
     while (over > cur && !overrun.compare_exchange_weak(cur, over)) {}
+    uint64_t cur_unit = wide_units.load();
+    while (last_wide > cur_unit && !wide_units.compare_exchange_weak(cur_unit, last_wide)) {}
     cur = spread.load();
     while (wide > cur && !spread.compare_exchange_weak(cur, wide)) {}
   };
@@ -144,6 +150,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   if (facts_out) {
     facts_out->max_lane_reach = overrun.load();
     facts_out->max_lane_spread = spread.load();
+    facts_out->wide_units = wide_units.load();
   }
   return TQ_OK;
 }

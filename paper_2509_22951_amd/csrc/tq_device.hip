@@ -39,6 +39,7 @@
 #include "tq_kernel_dot.h"
 #include "tq_strip_decode.h"
 #include "tq_kernel_ring.h"
+#include "tq_kernel_runs.h"
 #include "tq_kernel_strip.h"
 
 using namespace tq;
@@ -278,6 +279,8 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_mfma<false, false, true>,
     (const void*)k_matvec_mfma<true, true, true>,
     (const void*)k_matvec_mfma<false, true, true>,
+    (const void*)k_matvec_runs<kRunWaves, false>,
+    (const void*)k_matvec_runs<kRunWavesPacked, true>,
     (const void*)k_matvec_ring<kRingWaves, 16, false>,
     (const void*)k_matvec_ring<kRingWavesHalf, 8, false>,
     (const void*)k_matvec_ring<kRingWaves, 16, true>,
@@ -286,6 +289,10 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_ring<kRingWavesMore, 8, true>,
     (const void*)k_matvec_ring<kRingWavesQuarter, 4, false>,
     (const void*)k_matvec_ring<kRingWavesQuarter, 4, true>,
+    (const void*)k_matvec_ring<kRingWaves, 16, false, true>,
+    (const void*)k_matvec_ring<kRingWaves, 16, true, true>,
+    (const void*)k_matvec_ring<kRingWaves, 8, false, true>,
+    (const void*)k_matvec_ring<kRingWaves, 8, true, true>,
 };
 
 // Once per matrix creation (cheap): dynamic LDS above 64 KB has to be allowed per kernel function, and the kernels'
@@ -359,7 +366,8 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   // on different LDS banks when seg_cols is a multiple of 32.
   m.x_span = h.seg_cols + (h.seg_cols % 32 == 0 ? 16u : 0u);
   m.seg_magic = (uint32_t)((1ull << 32) / h.seg_cols) + 1;   // exact quotient while col * seg_cols < 2^32
-  m.reserved = long_runs ? 0u : facts.max_lane_spread <= kRingSpread ? 1u : facts.max_lane_spread <= kRingSpreadCareful ? 2u : 0u;
+  // (LZW starts with single bytes: the units whose lanes drift far apart are the first ones of the matrix a dictionary starts with)
+  m.reserved = long_runs || facts.max_lane_spread > kRingSpreadCareful || facts.wide_units > 0xFFFFFFF0ull ? 0u : 1u + (uint32_t)facts.wide_units;
   m.packing = h.packing;
   m.long_runs = long_runs ? 1u : 0u;
   m.class2 = h.class_end[1];
@@ -527,6 +535,10 @@ uint64_t even_cut_cost(int n, const tq_handle* hs, uint64_t grid) {
   return total / grid + cols_max / 2 + (n > 1 ? kRestartCost : 0);
 }
 
+// Whether k_matvec_runs takes a matrix: any but those whose lanes drift too far apart for a ring (or that hold runs of 3 and 4
+// bytes), and those narrower than one activation fragment.
+bool runs_eligible(const tq_matrix* t) { return t->m.reserved != 0 && (t->m.packing ? 2 : 1) * t->m.cols >= 8; }
+
 // One kernel launch for hs[0..n), all on one device, total cost below 2^32; n <= kMaxMulti, or n <= kMaxStep when the
 // launch is recorded for a prepared step (rec: its jobs then go to the step's device table, not into the arguments).
 // kMatvec: xs/ys are the activations and outputs; kDecompress: ys are the int8 output matrices, xs is not used.
@@ -544,6 +556,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   p.what = op == Op::kDecompress ? "tq_decompress launch" : "tq_matvec launch";
   a.table = rec ? (const StepEntry*)(uintptr_t)8 : nullptr;   // (the address follows when the step's table is in device memory)
   uint32_t dict_words_max = 0, x_dwords_max = 0, seg_max = 0, dict16_max = 0;
+  bool runs = op == Op::kMatvec;
   uint64_t cost = 0, bands = 0, band_cost_max = 1;
   bool x_fast = true;
   for (int i = 0; i < n; ++i) {
@@ -565,6 +578,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     dict16_max = std::max(dict16_max, t->lds_dict16);
     x_dwords_max = std::max(x_dwords_max, t->m.x_dwords);
     seg_max = std::max(seg_max, t->m.seg_cols);
+    runs = runs && runs_eligible(t);
     x_fast = x_fast && (t->m.packing ? 2 : 1) * t->m.cols % 8 == 0 && xs && (uintptr_t)xs[i] % 16 == 0;
   }
   a.u.cost_long[n] = (uint32_t)cost;
@@ -577,6 +591,18 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   p.grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)hs[0]->n_cu, bands, cost / band_cost_max}));
   const bool packed = hs[0]->m.packing != 0;   // (all matrices of a product launch hold their weights the same way: launch_all sees to that)
   const bool long_runs = hs[0]->m.long_runs != 0;   // (likewise)
+  auto cut_by_workgroup = [&] {
+    uint32_t wgs[kMaxAssign];
+    const uint64_t worst = assign_workgroups(n, hs, std::min<uint64_t>(hs[0]->n_cu, bands), wgs);
+    if (!worst || worst > even_cut_cost(n, hs, p.grid)) return;
+    a.by_workgroup = 1;
+    p.grid = 0;
+    for (int i = 0; i < n; ++i) {
+      a.u.cost_long[i] = p.grid;
+      p.grid += wgs[i];
+    }
+    a.u.cost_long[n] = p.grid;
+  };
   if (op == Op::kMatvec && dot_kernel_takes(batch, packed, long_runs, dict_words_max, x_dwords_max)) {
     // the dot-product kernel: one activation row or two
     if (!plan_matvec_lds(dict_words_max, (packed && batch == 2 ? 2 : 1) * x_dwords_max, &a.x_off, &a.slot_off, &p.lds)) {
@@ -587,17 +613,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
                : packed ? (batch == 2 ? (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2> : (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1>)
                : batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 2> : (const void*)k_matvec<kDotPiece, kDotWaves, false, 1>;
     p.block = (packed ? kDotWavesPacked : kDotWaves) * 64;
-    uint32_t wgs[kMaxAssign];
-    const uint64_t worst = assign_workgroups(n, hs, std::min<uint64_t>(hs[0]->n_cu, bands), wgs);
-    if (worst && worst <= even_cut_cost(n, hs, p.grid)) {
-      a.by_workgroup = 1;
-      p.grid = 0;
-      for (int i = 0; i < n; ++i) {
-        a.u.cost_long[i] = p.grid;
-        p.grid += wgs[i];
-      }
-      a.u.cost_long[n] = p.grid;
-    }
+    cut_by_workgroup();
   } else if (ring) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size: the kernel ORs piece offsets into its
     // address) | the activation tile of one quad.
@@ -605,21 +621,32 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     a.x_off = (uint32_t)dict16;
     a.tile_area = 64 * kRingBytes;
     const bool half = batch <= 8;   // 8 batch rows in the tile: room for two more wavefronts
-    const bool more = half && dict16 + (size_t)kRingWavesMore * a.tile_area + ring_x_tile(8) + 128 <= kLdsLimit;   // a smaller dictionary leaves room
+    const bool more = half && !gate_up && dict16 + (size_t)kRingWavesMore * a.tile_area + ring_x_tile(8) + 128 <= kLdsLimit;   // a smaller dictionary leaves room
     // batches up to 4 beside a dictionary too large for that: a tile of 4 rows leaves room for one wavefront more
-    const bool quarter = !more && batch <= 4 && dict16 + (size_t)kRingWavesQuarter * a.tile_area + ring_x_tile(4) + 128 <= kLdsLimit;
-    const int waves = more ? kRingWavesMore : quarter ? kRingWavesQuarter : half ? kRingWavesHalf : kRingWaves;
+    const bool quarter = !more && !gate_up && batch <= 4 && dict16 + (size_t)kRingWavesQuarter * a.tile_area + ring_x_tile(4) + 128 <= kLdsLimit;
+    const int waves = more ? kRingWavesMore : quarter ? kRingWavesQuarter : half && !gate_up ? kRingWavesHalf : kRingWaves;   // (gated pairs hold sums in registers)
     a.slot_off = (uint32_t)(dict16 + (size_t)waves * a.tile_area);
     p.lds = a.slot_off + ring_x_tile(quarter ? 4 : half ? 8 : 16) + 128;   // + the band counter
     if (p.lds > kLdsLimit || !x_fast) {
       set_error("internal: ring launch with a dictionary or activations that do not fit it");
       return TQ_E_UNSUPPORTED;
     }
-    if (more) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesMore, 8, true> : (const void*)k_matvec_ring<kRingWavesMore, 8, false>;
+    if (gate_up) {
+      if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 8, true, true> : (const void*)k_matvec_ring<kRingWaves, 8, false, true>;
+      else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true, true> : (const void*)k_matvec_ring<kRingWaves, 16, false, true>;
+    } else if (more) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesMore, 8, true> : (const void*)k_matvec_ring<kRingWavesMore, 8, false>;
     else if (quarter) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesQuarter, 4, true> : (const void*)k_matvec_ring<kRingWavesQuarter, 4, false>;
     else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesHalf, 8, true> : (const void*)k_matvec_ring<kRingWavesHalf, 8, false>;
     else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingWaves, 16, false>;
     p.block = (unsigned)waves * 64;
+  } else if (op == Op::kMatvec && runs) {
+    // LDS: 16-bit dictionary image | one ring per lane (aligned to its size)
+    const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
+    a.x_off = (uint32_t)dict16;
+    p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
+    p.lds = dict16 + (size_t)p.block * kRingBytes;
+    p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true> : (const void*)k_matvec_runs<kRunWaves, false>;
+    cut_by_workgroup();
   } else {
     // Tile decode.  LDS: 16-bit dictionary image | one tile (64 strips) per wavefront, which the batched product reuses
     // for its partial sums (per wavefront two slots of 1 KB and their two band numbers).
@@ -669,11 +696,14 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
   {
     // The kernels are built once per weight format: matrices of packed 4-bit weights, matrices with runs of 3 and 4
     // bytes and the others take separate launches.  (The expansion does not care about packing, only about the runs.)
-    auto kind = [&](const tq_matrix* t) { return (op == Op::kMatvec && t->m.packing ? 1u : 0u) | (t->m.long_runs ? 2u : 0u); };
+    // (Batches for the MFMA kernels: so do the matrices that only the whole-strip kernel takes.)
+    auto kind = [&](const tq_matrix* t) {
+      return (op == Op::kMatvec && t->m.packing ? 1u : 0u) | (t->m.long_runs ? 2u : 0u) | (op == Op::kMatvec && batch > 2 && !runs_eligible(t) ? 4u : 0u);
+    };
     uint32_t seen = 0;
     for (int i = 0; i < n; ++i) seen |= 1u << kind(hs[i]);
     if (seen & (seen - 1)) {   // more than one kind
-      for (uint32_t want = 0; want < 4; ++want) {
+      for (uint32_t want = 0; want < 8; ++want) {
         if (!(seen >> want & 1u)) continue;
         std::vector<tq_handle> h2;
         std::vector<const void*> x2;
@@ -716,7 +746,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
       return TQ_OK;
     }
   }
-  if (op == Op::kMatvec && !dot_call && !ring && !gate_up) {   // (the ring kernel adds partial sums to y: no place for silu)
+  if (op == Op::kMatvec && !dot_call && !ring) {
     // The matrices that can take the ring kernel go there, the others to the whole-strip kernel; the products are
     // independent, so regrouping them changes nothing but the launches.
     // The ring kernel gives whole bands to wavefronts, a quad at a time: it needs many bands per workgroup to keep its
@@ -729,7 +759,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
         ring_bands += hs[i]->m.n_bands;
       }
     if (ring_bands < ring_min_bands_per_cu() * hs[0]->n_cu) n_ring = 0;
-    if (n_ring == n) return launch_all(op, n, hs, xs, ys, batch, stream, true, false, rec);
+    if (n_ring == n) return launch_all(op, n, hs, xs, ys, batch, stream, true, gate_up, rec);
     if (n_ring > 0) {
       std::vector<tq_handle> h2[2];
       std::vector<const void*> x2[2];
@@ -740,7 +770,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
         x2[g].push_back(xs[i]);
         y2[g].push_back(ys[i]);
       }
-      if (int rc = launch_all(op, (int)h2[1].size(), h2[1].data(), x2[1].data(), y2[1].data(), batch, stream, true, false, rec)) return rc;
+      if (int rc = launch_all(op, (int)h2[1].size(), h2[1].data(), x2[1].data(), y2[1].data(), batch, stream, true, gate_up, rec)) return rc;
       n = (int)h2[0].size();
       for (int i = 0; i < n;) {   // the rest, below, with the vectors alive
         int k = 0;
@@ -751,7 +781,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
           cost += c;
           ++k;
         }
-        if (int rc = launch(op, k, h2[0].data() + i, x2[0].data() + i, y2[0].data() + i, batch, stream, false, false, rec)) return rc;
+        if (int rc = launch(op, k, h2[0].data() + i, x2[0].data() + i, y2[0].data() + i, batch, stream, false, gate_up, rec)) return rc;
         i += k;
       }
       return TQ_OK;

@@ -1,0 +1,233 @@
+// Device side of libtq: the batched product with a ring per lane over runs of units (activations from global memory).
+#pragma once
+#include "tq_kernels_common.h"
+#include "tq_kernel_ring.h"
+#include "tq_strip_decode.h"
+
+namespace tq {
+// ---------------------------------------------------------------------------------------------------------------
+// The ring decode of k_matvec_ring without its activation tile: every wavefront takes a contiguous run of units, bands
+// one after the other and a band's quads in order, with the band's sums in registers from its first quad to its last.  No
+// wavefront waits for another, so small launches are cut as finely as whole units allow, and the epilogue sees whole sums
+// (silu(gate) * up needs them; k_matvec_ring adds to y quad by quad).
+// The B operands come from global memory, 16 bytes per lane and MFMA step (they stay in the caches: a band after the other
+// takes the same rows of x), requested a look ahead of their use.  x needs no alignment beyond its elements' (16-byte loads of
+// global memory work at any 2-byte address), and rows need not be whole units: in a unit that reaches past the row's end
+// (or whose segments are no multiple of a group of windows) a fragment is loaded where it still lies inside the row and
+// shifted into place, zeros behind it.
+constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
+constexpr int kRunWavesPacked = 8;   // packed 4-bit weights: two fragments and more conversion per piece, 12 wavefronts leave too few registers
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef __attribute__((address_space(1))) const u32x4_any global_cu128_any;
+
+// The fragment's elements from element `by` on, zeros behind them (by >= 8: all zero).
+__device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
+  const bool four = by & 4u, two = by & 2u;
+  u32x4 r = {four ? v.z : v.x, four ? v.w : v.y, four ? 0u : v.z, four ? 0u : v.w};
+  r = u32x4{two ? r.y : r.x, two ? r.z : r.y, two ? r.w : r.z, two ? 0u : r.w};
+  const uint32_t bits = (by & 1u) << 4;
+  r = u32x4{__builtin_amdgcn_alignbit(r.y, r.x, bits), __builtin_amdgcn_alignbit(r.z, r.y, bits), __builtin_amdgcn_alignbit(r.w, r.z, bits), r.w >> bits};
+  return by >= 8 ? u32x4{0u, 0u, 0u, 0u} : r;
+}
+
+// Decode and multiply the units [u0, u1).  x: the activations, row: the batch row of this lane's B operand (lane & 15, at
+// most the last one); part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
+template <bool kCareful, bool kPacked, typename OnUnit>
+__device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, global_cu16* x, uint32_t row, int lane, uint32_t ring,
+                                                f32x4 (&part)[4], OnUnit&& on_unit) {
+  if (u0 >= u1) return;
+  constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
+  constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
+  const uint32_t sw8 = (uint32_t)(lane & 15) << 3, kg = (uint32_t)lane >> 4;
+  const uint32_t nq = m.n_quads, n_panels = (m.cols + m.seg_cols - 1) / m.seg_cols, x_cols = pk * m.cols;
+  // walker over the pieces of the run
+  uint32_t wu = u0, wc = unit_offset(m, u0), w_left = 0, w_base = 0, w_rem = 0;
+  const uint32_t run_last = unit_offset(m, u1) - 1;
+  auto next_piece = [&](uint32_t& start, uint32_t& n, bool& ends) {
+    if (w_left == 0) {
+      if (wu == u1) {
+        n = 0;
+        ends = false;
+        start = wc;
+        return;
+      }
+      const uint32_t len = unit_offset(m, wu + 1) - wc;
+      w_left = (len + kP - 1) / kP;
+      w_base = len / w_left;
+      w_rem = len - w_base * w_left;
+      ++wu;
+    }
+    n = w_base + (w_rem ? 1u : 0u);
+    if (w_rem) --w_rem;
+    start = wc;
+    wc += n;
+    ends = --w_left == 0;
+  };
+  // every piece issues exactly kP loads (those past its end repeat its last chunk), kRingStep of them at a time
+  auto load_part = [&](uint2 (&cw)[kP], uint32_t start, uint32_t n, int p) {
+    const uint32_t last = min(start + max(n, 1u) - 1, run_last);
+#pragma unroll
+    for (int k = p * kRingStep; k < (p + 1) * kRingStep; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
+  };
+  // the unit in work: its place, the lane's panel (length, first column of x) and segment (none past the last row), the
+  // windows it takes (whole groups)
+  uint32_t band = u0 / nq, quad = u0 - band * nq, panel_len, x_first, seg_len, n_win8, pos = 0, done = 0;
+  bool ragged;
+  uint64_t carry = 0;
+  auto enter_unit = [&] {
+    const uint32_t first = quad * kUnitPanels * m.seg_cols, panel = quad * kUnitPanels + kg;
+    panel_len = panel < n_panels ? min(m.seg_cols, m.cols - panel * m.seg_cols) : 0u;
+    seg_len = band * kUnitRows + (lane & 15) < m.rows ? panel_len : 0u;
+    n_win8 = (min(m.seg_cols, m.cols - first) + 8 * kG - 1) / (8 * kG) * (8 * kG);
+    ragged = first + kUnitPanels * m.seg_cols > m.cols || m.seg_cols % (8 * kG) != 0;
+    x_first = pk * panel * m.seg_cols;
+    pos = 0;
+    done = 0;
+    carry = 0;
+  };
+  u32x4 x8[kG * pk];   // B operands of the next group
+  const uint32_t row_first = row * x_cols;
+  auto request_x = [&] {
+    const uint32_t at = x_first + pk * min(done, n_win8 - 8 * kG);
+#pragma unroll
+    for (uint32_t k = 0; k < kG * pk; ++k) {
+      const uint32_t col = ragged ? min(at + 8 * k, x_cols - 8) : at + 8 * k;
+      x8[k] = *(global_cu128_any*)(x + (row_first + col));
+    }
+  };
+  // One group of MFMA steps if every lane that is still decoding has written the columns [done, done + 8 kG).  The weights
+  // are read before it is known whether the group is ready (volatile: the reads stay ahead of the test).
+  auto multiply_ready = [&]() {
+    const uint32_t at = min(done, n_win8 - 8 * kG);   // at the unit's end: any place inside the ring
+    const uint32_t base = at ^ sw8;
+    // a segment that ends inside a piece: what its last chunk left over is not in the ring yet
+    if (ragged) *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & 0x78u)) = carry;
+    u32x2 a8[kG];
+#pragma unroll
+    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
+    const uint32_t next = done + 8 * kG;
+    if (next > n_win8) return;
+    if (__builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
+    if (ragged) {
+#pragma unroll
+      for (uint32_t k = 0; k < kG * pk; ++k) {
+        const uint32_t in_panel = pk * at + 8 * k, col = x_first + in_panel;
+        x8[k] = drop_elements(x8[k], in_panel >= pk * panel_len ? 8u : col + 8 > x_cols ? col + 8 - x_cols : 0u);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kG; ++k) {
+      if constexpr (kPacked) {
+        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k]), part[k], 0, 0, 0);
+        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[2 * k + 1]), part[k], 0, 0, 0);
+      } else {
+        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k]), part[k], 0, 0, 0);
+      }
+    }
+    done = next;
+  };
+  auto decode_piece = [&](const uint2 (&cw)[kP], uint32_t n, bool ends, uint2 (&cw_next)[kP], uint32_t next_start, uint32_t next_n) {
+    if (n == 0) return;
+    // a look: multiply what is ready, request the operands of the group that follows (again, if it was not)
+    auto look = [&] {
+      multiply_ready();
+      request_x();
+    };
+    if (n >= kP - 1) {
+#pragma unroll
+      for (int k = 0; k < kP - 1; ++k) {
+        append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
+        if (k % kLook == kLook - 1) look();
+        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
+      }
+      if (n == kP) append_chunk_ring(cw[kP - 1], ring, sw8, seg_len, pos, carry);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kP - 2; ++k) {
+        if ((uint32_t)k < n) append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
+        if (k % kLook == kLook - 1 && (uint32_t)k + 1 < n) look();
+        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
+      }
+    }
+    multiply_ready();
+    if (ends) {
+      while (done < n_win8) {   // every lane is complete: whatever is left (at most a group, more in a ragged unit)
+        request_x();
+        multiply_ready();
+      }
+      on_unit(band, quad);
+      if (++quad == nq) {
+        quad = 0;
+        ++band;
+      }
+      if (band * nq + quad < u1) enter_unit();
+    }
+    request_x();
+    load_part(cw_next, next_start, next_n, kP / kRingStep - 1);
+  };
+  uint2 cwa[kP], cwb[kP];
+  uint32_t sa, na, sb, nb;
+  bool ea, eb;
+  enter_unit();
+  next_piece(sa, na, ea);
+  request_x();
+#pragma unroll
+  for (int j = 0; j < kP / kRingStep; ++j) load_part(cwa, sa, na, j);
+  while (na) {   // two register sets: one is decoded while the other is filled
+    next_piece(sb, nb, eb);
+    decode_piece(cwa, na, ea, cwb, sb, nb);
+    next_piece(sa, na, ea);
+    decode_piece(cwb, nb, eb, cwa, sa, na);
+  }
+}
+
+template <int kWaves, bool kPacked>
+__global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
+  constexpr int kRunThreads = kWaves * 64, kRegs = 8;
+  touch_arguments();
+  extern __shared__ uint4 lds4[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t total = cost_at(a, a.n);
+  const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+  const uint32_t* staged = nullptr;
+  const uint32_t rings = a.x_off;   // LDS address (the LDS segment starts at 0)
+  const uint32_t ring = rings + (uint32_t)wave * (64 * kRingBytes) + (uint32_t)lane * kRingBytes;
+  bool lds_used = false;
+  for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
+    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
+    if (hi <= cb) break;
+    Job job;
+    DevMat m;
+    fetch_job(a, i, job, m);
+    uint32_t band_lo, band_hi;
+    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
+    if (band_lo >= band_hi) continue;
+    const uint32_t nq = m.n_quads, unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
+    const uint32_t u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves);
+    const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
+    if (lds_used) __syncthreads();   // the previous matrix's dictionary and partial sums are no longer in use
+    lds_used = true;
+    if (m.dict != staged) {
+      stage_dictionary16<kRegs>(m, (uint16_t*)lds4, tid, kRunThreads);
+      staged = m.dict;
+      __syncthreads();
+    }
+    BandSums sums;
+    sums.start(u0, u1, nq);
+    f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    auto on_unit = [&](uint32_t band, uint32_t quad) {
+      if (quad + 1 != nq && band * nq + quad + 1 != u1) return;
+      sums.finish(a, job, m, band, quad, (part[0] + part[1]) + (part[2] + part[3]), lane);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    const uint32_t row = min((uint32_t)(lane & 15), (uint32_t)a.batch - 1);   // lanes past the batch repeat its last row: their sums are never stored
+    const uint32_t careful = min(max(m.reserved - 1, u0), u1);               // (units whose lanes drift far apart come first: see DevMat::reserved)
+    decode_run_ring<true, kPacked>(m, u0, careful, (global_cu16*)job.x, row, lane, ring, part, on_unit);
+    decode_run_ring<false, kPacked>(m, careful, u1, (global_cu16*)job.x, row, lane, ring, part, on_unit);
+    __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
+    sums.combine(a, job, m, rings, wave, kWaves, lane);
+  }
+}
+
+}  // namespace tq

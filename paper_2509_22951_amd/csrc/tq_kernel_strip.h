@@ -42,61 +42,22 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
       staged = m.dict;
     }
     if (m.dict != staged) {
-      // 16-bit image of the dictionary: the run bytes of every entry (the length follows from the code)
-      const uint4* src = (const uint4*)m.dict;
-      uint2* dst = (uint2*)lds_dict;
-      const uint32_t n4 = m.dict_words / 4;
-      for (uint32_t base = 0; base < n4; base += kDictRegs * n_threads) {
-        uint4 v[kDictRegs];
-#pragma unroll
-        for (int k = 0; k < kDictRegs; ++k) v[k] = global_load(src + min(base + k * n_threads + tid, n4 - 1));
-#pragma unroll
-        for (int k = 0; k < kDictRegs; ++k) {
-          const uint32_t idx = base + k * n_threads + tid;
-          if (idx < n4) dst[idx] = make_uint2((v[k].x & 0xFFFFu) | v[k].y << 16, (v[k].z & 0xFFFFu) | v[k].w << 16);
-        }
-      }
+      stage_dictionary16<kDictRegs>(m, lds_dict, tid, n_threads);
       staged = m.dict;
     }
     __syncthreads();
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, head_acc = {0.f, 0.f, 0.f, 0.f}, tail_acc = {0.f, 0.f, 0.f, 0.f};
-    int head_band = -1, tail_band = -1;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    BandSums sums;
+    sums.start(u0, u1, nq);
     // lanes past the batch repeat its last row: their output columns are never stored
     constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte
     const uint32_t x_cols = pk * m.cols;
     global_cu16* xrow = (global_cu16*)job.x + (size_t)min(bn, a.batch - 1) * x_cols;
-    const uint32_t first_band = u0 / nq;
-    const bool first_whole = u0 % nq == 0;
     // acc holds the sums of the band in work when its last unit (or the run's) has been multiplied
     auto finish_unit = [&](uint32_t band, uint32_t quad) {
-      const bool band_ends = quad + 1 == nq, run_ends = band * nq + quad + 1 == u1;
-      if (band_ends || run_ends) {
-        if (band_ends && (band != first_band || first_whole)) {
-          // the whole band lies in this wavefront's run.  Accumulator register v of lane l: row 4 * (l / 16) + v, batch row l % 16
-          if (a.gate_up) {   // registers 0, 1 and 2, 3 of a lane are gate and up row of two outputs
-#pragma unroll
-            for (int v = 0; v < 4; v += 2) {
-              const uint32_t row = band * kUnitRows + 4 * kg + v;
-              if (bn < a.batch && row + 1 < m.rows)
-                global_store(job.y + (size_t)bn * (m.rows / 2) + row / 2,
-                             silu_times(acc[v] * global_load(m.scales + row), acc[v + 1] * global_load(m.scales + row + 1)));
-            }
-          } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const uint32_t row = band * kUnitRows + 4 * kg + v;
-              if (bn < a.batch && row < m.rows) global_store(job.y + (size_t)bn * m.rows + row, acc[v] * global_load(m.scales + row));
-            }
-          }
-        } else if (band == first_band && !first_whole) {   // band begun by an earlier wavefront
-          head_acc = acc;
-          head_band = (int)band;
-        } else {                                           // band left unfinished
-          tail_acc = acc;
-          tail_band = (int)band;
-        }
-        acc = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+      if (quad + 1 != nq && band * nq + quad + 1 != u1) return;
+      sums.finish(a, job, m, band, quad, acc, lane);
+      acc = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     {
       const uint32_t strip = m.seg_cols + 8;   // bytes between the strips of two lanes
@@ -118,42 +79,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
       });
     }
     __syncthreads();   // every wavefront is done with its tile: the partial sums go over the tile area
-    float* slot_val = (float*)tiles;                                 // [2 * n_waves][256]
-    int* slot_band = (int*)(slot_val + 2 * n_waves * 256);           // [2 * n_waves], also inside the tile area
-    if (lane == 0) {
-      slot_band[2 * wave] = head_band;
-      slot_band[2 * wave + 1] = tail_band;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      slot_val[(2 * wave) * 256 + v * 64 + lane] = head_acc[v];
-      slot_val[(2 * wave + 1) * 256 + v * 64 + lane] = tail_acc[v];
-    }
-    __syncthreads();
-    for (int o = tid; o < 2 * n_waves * 256; o += n_threads) {
-      const int s = o >> 8, e = o & 255;
-      const int bnd = slot_band[s];
-      bool first = bnd >= 0;
-      for (int t = 0; t < s; ++t) first = first && slot_band[t] != bnd;
-      if (first) {
-        auto slot_sum = [&](int el) {
-          float sum = slot_val[s * 256 + el];
-          for (int t = s + 1; t < 2 * n_waves; ++t)
-            if (slot_band[t] == bnd) sum += slot_val[t * 256 + el];
-          return sum;
-        };
-        const int v = e >> 6, l = e & 63;
-        const uint32_t row = (uint32_t)bnd * kUnitRows + 4 * (l >> 4) + v;
-        const int b = l & 15;
-        if (a.gate_up) {   // element e + 64 is the up row that belongs to this gate row
-          if (!(v & 1) && b < a.batch && row + 1 < m.rows)
-            global_store(job.y + (size_t)b * (m.rows / 2) + row / 2,
-                         silu_times(slot_sum(e) * global_load(m.scales + row), slot_sum(e + 64) * global_load(m.scales + row + 1)));
-        } else if (b < a.batch && row < m.rows) {
-          global_store(job.y + (size_t)b * m.rows + row, slot_sum(e) * global_load(m.scales + row));
-        }
-      }
-    }
+    sums.combine(a, job, m, lds_address(tiles), wave, n_waves, lane);
   }
 }
 
@@ -192,19 +118,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
     }
     if (m.dict != staged) {
       __syncthreads();   // nobody reads the previous dictionary any more
-      const uint4* src = (const uint4*)m.dict;
-      uint2* dst = (uint2*)lds_dict;
-      const uint32_t n4 = m.dict_words / 4;
-      for (uint32_t base = 0; base < n4; base += kDictRegs * n_threads) {
-        uint4 v[kDictRegs];
-#pragma unroll
-        for (int k = 0; k < kDictRegs; ++k) v[k] = global_load(src + min(base + k * n_threads + tid, n4 - 1));
-#pragma unroll
-        for (int k = 0; k < kDictRegs; ++k) {
-          const uint32_t idx = base + k * n_threads + tid;
-          if (idx < n4) dst[idx] = make_uint2((v[k].x & 0xFFFFu) | v[k].y << 16, (v[k].z & 0xFFFFu) | v[k].w << 16);
-        }
-      }
+      stage_dictionary16<kDictRegs>(m, lds_dict, tid, n_threads);
       staged = m.dict;
       __syncthreads();
     }

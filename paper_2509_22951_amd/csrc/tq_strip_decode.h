@@ -234,6 +234,93 @@ __device__ __forceinline__ uint4 mask_x_fragment(uint4 v, uint32_t cols, uint32_
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// 16-bit image of the dictionary in LDS: the run bytes of every entry (the length follows from the code).
+template <int kRegs>
+__device__ __forceinline__ void stage_dictionary16(const DevMat& m, uint16_t* lds_dict, int tid, int n_threads) {
+  const uint4* src = (const uint4*)m.dict;
+  uint2* dst = (uint2*)lds_dict;
+  const uint32_t n4 = m.dict_words / 4;
+  for (uint32_t base = 0; base < n4; base += kRegs * n_threads) {
+    uint4 v[kRegs];
+#pragma unroll
+    for (int k = 0; k < kRegs; ++k) v[k] = global_load(src + min(base + k * n_threads + tid, n4 - 1));
+#pragma unroll
+    for (int k = 0; k < kRegs; ++k) {
+      const uint32_t idx = base + k * n_threads + tid;
+      if (idx < n4) dst[idx] = make_uint2((v[k].x & 0xFFFFu) | v[k].y << 16, (v[k].z & 0xFFFFu) | v[k].w << 16);
+    }
+  }
+}
+
+// The sums of the bands of a wavefront's run of units [u0, u1), as MFMA accumulators: register v of lane l is row
+// 4 * (l / 16) + v of the band, batch row l % 16.  A band that lies wholly in the run is scaled and stored at once; one
+// that is shared with the wavefronts before or after goes to LDS at the end, and the wavefront with the band's first
+// part adds the parts in order, so that the result does not depend on timing.
+struct BandSums {
+  f32x4 head_acc, tail_acc;
+  int head_band, tail_band;
+  uint32_t first_band, n_quads;
+  bool first_whole;
+  __device__ __forceinline__ void start(uint32_t u0, uint32_t u1, uint32_t nq) {
+    head_acc = tail_acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    head_band = tail_band = -1;
+    n_quads = nq;
+    first_band = u0 / nq;
+    first_whole = u0 % nq == 0;
+  }
+  __device__ __forceinline__ static void store(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t band, f32x4 acc, int lane) {
+    const int bn = lane & 15;
+    if (bn >= a.batch) return;
+    const uint32_t row0 = band * kUnitRows + 4 * ((uint32_t)lane >> 4);
+    float scale[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) scale[v] = global_load(m.scales + row0 + v);   // (the array is padded to whole bands)
+    if (a.gate_up) {   // registers 0, 1 and 2, 3 of a lane are gate and up row of two outputs
+#pragma unroll
+      for (int v = 0; v < 4; v += 2)
+        if (row0 + v + 1 < m.rows)
+          global_store(job.y + (size_t)bn * (m.rows / 2) + (row0 + v) / 2, silu_times(acc[v] * scale[v], acc[v + 1] * scale[v + 1]));
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (row0 + v < m.rows) global_store(job.y + (size_t)bn * m.rows + row0 + v, acc[v] * scale[v]);
+    }
+  }
+  // acc: the band's sums when unit (band, quad), the last of the band or of the run, has been multiplied
+  __device__ __forceinline__ void finish(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t band, uint32_t quad, f32x4 acc, int lane) {
+    if (quad + 1 == n_quads && (band != first_band || first_whole)) {
+      store(a, job, m, band, acc, lane);
+    } else {
+      const bool head = band == first_band && !first_whole;   // begun by an earlier wavefront, or left unfinished
+      head_acc = head ? acc : head_acc;
+      tail_acc = head ? tail_acc : acc;
+      head_band = head ? (int)band : head_band;
+      tail_band = head ? tail_band : (int)band;
+    }
+  }
+  // area: LDS that nobody uses any more, 2 * n_waves * (1024 + 4) bytes, 16-byte aligned
+  __device__ __forceinline__ void combine(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t area, int wave, int n_waves, int lane) const {
+    typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+    typedef __attribute__((address_space(3))) int lds_int;
+    lds_f32x4* value = (lds_f32x4*)(size_t)area;                             // [2 * n_waves][64]
+    lds_int* band_of = (lds_int*)(size_t)(area + 2 * n_waves * 1024);        // [2 * n_waves]
+    value[(2 * wave) * 64 + lane] = head_acc;
+    value[(2 * wave + 1) * 64 + lane] = tail_acc;
+    if (lane < 2) band_of[2 * wave + lane] = lane ? tail_band : head_band;
+    __syncthreads();
+    const int bands = lane < 2 * n_waves ? band_of[lane] : -1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int s = 2 * wave + j, band = __builtin_amdgcn_readlane(bands, s);
+      uint64_t same = __builtin_amdgcn_ballot_w64(bands == band);
+      if (band < 0 || (same & ((1ull << s) - 1))) continue;   // an earlier slot of the band does it
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+      for (; same; same &= same - 1) sum += value[__builtin_ctzll(same) * 64 + lane];
+      store(a, job, m, (uint32_t)band, sum, lane);
+    }
+  }
+};
+
 constexpr int kMfmaGroup = 8;   // MFMA steps per group: the activation fragments of the next group load while this one runs
 
 // The MFMA steps of one decoded unit: step w multiplies bytes [8 w, 8 w + 8) of every lane's strip (16 rows x 4 panels

@@ -28,6 +28,7 @@ class _Job:
         bits, x = make_activations(spec, batch)
         self.ref = O.gemv_f64(self.Q, s, x)
         self.m = tq.Matrix(tq.tq_encode(W, **opts))
+        self.x_of = lambda shift: torch.from_numpy(np.concatenate([np.zeros(shift, np.int16), bits.view(np.int16).reshape(-1)])).cuda()[shift:]
         self.x = torch.from_numpy(bits.view(np.int16).copy()).cuda()
         self.y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device="cuda")
 
@@ -85,3 +86,54 @@ def test_matrices_of_a_call_get_whole_workgroups(n):
     finally:
         for j in jobs:
             j.m.close()
+
+
+RUNS = [
+    # rows, cols, seg_cols: batches above 2 below the sizes the ring kernel with an activation tile takes
+    (16, 6, 16),           # narrower than an activation fragment: the whole-strip kernel
+    (16, 8, 16),           # one fragment
+    (17, 42, 64),          # a segment that ends inside an 8-byte piece of the ring
+    (33, 300, 48),         # segments of one and a half groups of windows, the last one short
+    (40, 1021, 256),       # one unit per band, row ends inside a fragment
+    (100, 4095, 1024),     # the widest segments
+    (5000, 2999, 256),     # bands shared between wavefronts, a dictionary's start (units that need care)
+]
+
+
+@pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("batch,shift", [(3, 0), (8, 1), (16, 0)])
+@pytest.mark.parametrize("rows,cols,seg_cols", RUNS)
+def test_runs_of_units_in_batches(rows, cols, seg_cols, batch, shift, opts):
+    job = _Job(rows, cols + cols % 2 if opts else cols, batch, seed=rows + cols, seg_cols=seg_cols, **opts)
+    try:
+        x = job.x_of(shift)       # rows of x at odd addresses
+        job.m.matvec(x.data_ptr(), job.y.data_ptr(), batch, _stream())
+        torch.cuda.synchronize()
+        job.check()
+    finally:
+        job.m.close()
+
+
+@pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("batch", [3, 16])
+@pytest.mark.parametrize("rows", [72, 33 * 256 * 8])      # gate rows: one band per workgroup; a pass of 32 bands and one more
+def test_gated_pairs_on_the_ring_kernel(rows, batch, opts):
+    cols = 512 if opts else 256
+    spec = small_case(rows, cols, seed=5)
+    Wg, Wu = make_weights(spec), make_weights(small_case(rows, cols, seed=6))
+    bits, x = make_activations(spec, batch)
+    width = opts.get("bits", 8)
+    ref = O.gate_up_f64(*O.quantize_rows(Wg, width), *O.quantize_rows(Wu, width), x)
+    m = tq.Matrix(tq.tq_encode_gate_up(Wg, Wu, seg_cols=32, **opts))
+    xd = torch.from_numpy(bits.view(np.int16).copy()).cuda()
+    y = torch.full((batch, rows), float("nan"), dtype=torch.float32, device="cuda")
+    tq.tq_set_ring_min_bands_per_cu(0)
+    try:
+        tq.tq_matvec_gate_up(m.handle, xd.data_ptr(), y.data_ptr(), batch, _stream())
+        torch.cuda.synchronize()
+    finally:
+        tq.tq_set_ring_min_bands_per_cu(24)
+        m.close()
+    y = y.cpu().numpy().astype(np.float64)
+    for got, want in zip(y, ref):      # silu adds the rounding of exp and a division in fp32, relative to each output
+        assert np.isfinite(got).all() and np.abs(got - want).max() <= 2 * TOL * np.abs(want).max()
