@@ -139,24 +139,25 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  * batch 1 and batch 2 run the dot-product kernel (activations gathered from an LDS image of x, which holds both rows
  * at batch 2; a matrix whose rows are too long for that image to fit the LDS beside the dictionary - more than 8192
  * columns with a full dictionary, more with a smaller one - goes on as batch 3 does, slower but to the same result);
- * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are two.  The ring kernel keeps 128 bytes of every segment in LDS
- * and multiplies while it decodes; it takes matrices whose lane_spread (tq_info) is at most 113 columns, whose rows
- * are a whole number of units (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x
- * 16-byte aligned, in calls that bring at least 24 bands of 16 rows per compute unit (tq_set_ring_min_bands_per_cu
- * changes that number).  Everything else goes through the
- * whole-strip kernel, which decodes a unit into an LDS tile before it multiplies it.  The ring kernel adds the partial
- * sums of a row's later quads (groups of 4 segments) to y with atomic adds, always in the same order; y must not be
- * read or written by anything else on the device while the call runs (true of any output buffer).
+ * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep 128 bytes of every
+ * segment in LDS and multiply while they decode; they take matrices whose lane_spread (tq_info) is at most 113 columns.
+ * The ring kernel has the activations of a quad (4 segments) in LDS as well: for rows that are a whole number of units
+ * (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x 16-byte aligned, in calls that
+ * bring at least 24 bands of 16 rows per compute unit, 12 for batches above 8 (tq_set_ring_min_bands_per_cu changes
+ * that number).  The runs kernel takes its activations from global memory: any other shape of at least 8 columns, any
+ * x.  Everything else goes through the whole-strip kernel, which decodes a unit into an LDS tile before it multiplies
+ * it.  The ring kernel adds the partial sums of a row's later quads to y with atomic adds, always in the same order; y
+ * must not be read or written by anything else on the device while the call runs (true of any output buffer).
  * Containers of packed 4-bit weights (TQ_PACK_NIBBLES): cols is the number of weights per row, twice the stored bytes;
- * batch 1 and 2 run the dot-product kernel with four weights per dictionary entry, batch 3..16 the same two MFMA
+ * batch 1 and 2 run the dot-product kernel with four weights per dictionary entry, batch 3..16 the same MFMA
  * kernels (the ring kernel then takes segments of at most 128 bytes).
  */
 int tq_matvec(tq_handle h, const void *x, void *y, int batch, void *stream);
 
-/* Tuning knob of the choice between the two MFMA kernels of tq_matvec (see there): the ring kernel hands whole bands
- * of 16 rows to its wavefronts and is taken by launches that bring at least this many bands per compute unit
- * (default 24; 0 = whenever a matrix allows it).  Process-wide, atomic; affects the calls and the prepared steps made
- * after it returns.  Results stay within the tolerance either way (the two kernels add in different orders). */
+/* Tuning knob of the choice between the MFMA kernels of tq_matvec (see there): the ring kernel hands whole bands
+ * of 16 rows to its wavefronts and is taken by launches that bring at least this many bands per compute unit, half as
+ * many for batches above 8 (default 24; 0 = whenever a matrix allows it).  Process-wide, atomic; affects the calls and the prepared steps made
+ * after it returns.  Results stay within the tolerance either way (the kernels add in different orders). */
 int tq_set_ring_min_bands_per_cu(uint32_t bands_per_cu);
 
 /*
@@ -181,7 +182,8 @@ int tq_matvec_multi(int n, const tq_handle *hs, const void *const *xs, void *con
  *   y[b][r] = silu(g) * u,  g = scale[2r] * sum_j Q[2r][j] x[b][j],  u = scale[2r+1] * sum_j Q[2r+1][j] x[b][j],
  *   silu(g) = g / (1 + exp(-g)) in fp32.
  * y: device, fp32 [batch][rows / 2].  Works on any handle with an even number of rows; otherwise as tq_matvec /
- * tq_matvec_multi (batch 1 and 2: dot-product kernel; batch 3..16: the whole-strip MFMA kernel).
+ * tq_matvec_multi (batch 1 and 2: dot-product kernel; batch 3..16: the MFMA kernels; the ring kernel keeps a band's sums
+ * in registers here and adds nothing to y).
  */
 int tq_encode_gate_up(const float *w_gate, const float *w_up, uint32_t rows, uint32_t cols, const tq_encode_opts *opts,
                       void **blob, size_t *blob_bytes);

@@ -13,7 +13,7 @@
 //      (two activation rows are handled the same way, with both rows in the image and one dot product per row;
 //      packed 4-bit weights: four weights per entry as fp8, two conversions and two dot products per code and row),
 //   4. for batches of 3..16 rows and for tq_decompress the lanes append their run bytes to per-lane storage in LDS
-//      instead - a ring of 128 bytes (k_matvec_ring: multiplied by bf16 MFMA, batch = N, while the decode goes on) or
+//      instead - a ring of 128 bytes (k_matvec_ring, k_matvec_runs: multiplied by bf16 MFMA, batch = N, while the decode goes on) or
 //      a strip holding the whole segment (k_matvec_mfma: multiplied when the unit is complete; k_decompress: copied
 //      out row-major).
 // The expanded matrix never exists in HBM on the tq_matvec path.
@@ -640,11 +640,11 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingWaves, 16, false>;
     p.block = (unsigned)waves * 64;
   } else if (op == Op::kMatvec && runs) {
-    // LDS: 16-bit dictionary image | one ring per lane (aligned to its size)
+    // LDS: 16-bit dictionary image | one ring per lane (aligned to its size) | a count per lane
     const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
     a.x_off = (uint32_t)dict16;
     p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
-    p.lds = dict16 + (size_t)p.block * kRingBytes;
+    p.lds = dict16 + (size_t)p.block * kRingBytes + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
     p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true> : (const void*)k_matvec_runs<kRunWaves, false>;
     cut_by_workgroup();
   } else {
@@ -679,7 +679,9 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
 // Bands per CU a launch needs for the ring kernel; tq_set_ring_min_bands_per_cu changes it (tests use 0 to put small
 // matrices through that kernel).
 std::atomic<uint64_t> g_ring_min_bands{kRingMinBandsPerCu};
-uint64_t ring_min_bands_per_cu() { return g_ring_min_bands.load(std::memory_order_relaxed); }
+// (us, ring / runs kernel, LLaMA-3.2-3B layers: 20 bands per CU batch 8 128 / 117, 27 bands batch 4 137 / 140; above 8
+// rows of x the runs kernel pays more for them: 13.5 bands batch 16 92 / 112, 27 bands 139 / 259)
+uint64_t ring_min_bands_per_cu(int batch) { return g_ring_min_bands.load(std::memory_order_relaxed) / (batch > 8 ? 2 : 1); }
 
 bool ring_eligible(const tq_matrix* t, const void* x) {
   const DevMat& m = t->m;
@@ -747,10 +749,10 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
     }
   }
   if (op == Op::kMatvec && !dot_call && !ring) {
-    // The matrices that can take the ring kernel go there, the others to the whole-strip kernel; the products are
+    // The matrices that can take the ring kernel go there, the others to the runs (or whole-strip) kernel; the products are
     // independent, so regrouping them changes nothing but the launches.
     // The ring kernel gives whole bands to wavefronts, a quad at a time: it needs many bands per workgroup to keep its
-    // wavefronts busy (the whole-strip kernel splits single units between them).
+    // wavefronts busy (the runs kernel splits single units between them).
     int n_ring = 0;
     uint64_t ring_bands = 0;
     for (int i = 0; i < n; ++i)
@@ -758,7 +760,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
         ++n_ring;
         ring_bands += hs[i]->m.n_bands;
       }
-    if (ring_bands < ring_min_bands_per_cu() * hs[0]->n_cu) n_ring = 0;
+    if (ring_bands < ring_min_bands_per_cu(batch) * hs[0]->n_cu) n_ring = 0;
     if (n_ring == n) return launch_all(op, n, hs, xs, ys, batch, stream, true, gate_up, rec);
     if (n_ring > 0) {
       std::vector<tq_handle> h2[2];
@@ -834,7 +836,7 @@ static int tq_matvec_impl(tq_handle h, const void* x, void* y, int batch, void* 
   if (int rc = check_call("tq_matvec", 1, &h, &x, &y, batch)) return rc;
   return launch(Op::kMatvec, 1, &h, &x, &y, batch, (hipStream_t)stream,
                 !dot_kernel_takes(batch, h->m.packing != 0, h->m.long_runs != 0, h->m.dict_words, h->m.x_dwords) && ring_eligible(h, x) &&
-                    h->m.n_bands >= ring_min_bands_per_cu() * h->n_cu);
+                    h->m.n_bands >= ring_min_bands_per_cu(batch) * h->n_cu);
 }
 
 static int tq_matvec_multi_impl(int n, const tq_handle* hs, const void* const* xs, void* const* ys, int batch, void* stream) {

@@ -43,7 +43,7 @@ constexpr uint32_t kRingSpread = kRingBytes - 8 * kRingStep - 8 * kRingGroup + 1
 static_assert(kRingSpread == kWideSpread, "what the validator counts as a wide unit");
 constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;   // looking after every chunk, one MFMA step at a time
 constexpr uint32_t kRingMaxSeg = 256;
-constexpr int kRingMinBandsPerCu = 24;   // below that many bands per CU in a launch the whole-strip kernel is used
+constexpr int kRingMinBandsPerCu = 24;   // below that many bands per CU in a launch (half as many above 8 batch rows) k_matvec_runs is faster
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
 static_assert(kRingPiece % kRingStep == 0 && kRingGroup == 4 && kRingStep <= kRingGroup, "ring schedule");
 
@@ -204,7 +204,8 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
 
 // kGateUp: y = silu(gate row) * (up row) needs a band's whole sums, so nothing is added to y: the bands are taken in passes
 // of kGateUpBands per wavefront, each wavefront's bands fixed, with their sums in registers from the first quad to the
-// last.  (The gated pairs of eight LLaMA-3.2-3B blocks, batch 16: 207 us on the whole-strip kernel.)
+// last.  (The gated pairs of eight LLaMA-3.2-3B blocks, batch 16: 154 us; 207 us on the whole-strip
+// kernel, where they went before.)
 constexpr int kGateUpBands = 4;
 template <int kWaves, int kRows, bool kPacked, bool kGateUp = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {

@@ -15,6 +15,10 @@ namespace tq {
 // global memory work at any 2-byte address), and rows need not be whole units: in a unit that reaches past the row's end
 // (or whose segments are no multiple of a group of windows) a fragment is loaded where it still lies inside the row and
 // shifted into place, zeros behind it.
+// Measured, us, whole-strip kernel -> this one: 4099 x 2999 batch 5 41.1 -> 21.5, one LLaMA-3.2-3B layer batch 8 56 -> 44;
+// launches that fill k_matvec_ring stay there (eight such layers, batch 8: 235 us there, 267 here; the gated pairs of
+// eight blocks, batch 16: 154 there, 241 here): 16-byte pieces of up to 16 rows of x from the caches cost more than the
+// tile in LDS (without those loads: 222 and 148).
 constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
 constexpr int kRunWavesPacked = 8;   // packed 4-bit weights: two fragments and more conversion per piece, 12 wavefronts leave too few registers
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
@@ -30,19 +34,21 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
   return by >= 8 ? u32x4{0u, 0u, 0u, 0u} : r;
 }
 
-// Decode and multiply the units [u0, u1).  x: the activations, row: the batch row of this lane's B operand (lane & 15, at
+// Decode and multiply the chunks [c0, c_end) of the units [u0, u1).  The first unit may begin and the last one end outside
+// the run (see kSplit in k_matvec_runs): started says that the lanes stand at column `start` of the first one, and what
+// a lane has not written itself counts as zeros.  x: the activations, row: the batch row of this lane's B operand (lane & 15, at
 // most the last one); part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
 template <bool kCareful, bool kPacked, typename OnUnit>
-__device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, global_cu16* x, uint32_t row, int lane, uint32_t ring,
-                                                f32x4 (&part)[4], OnUnit&& on_unit) {
-  if (u0 >= u1) return;
+__device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, uint32_t start,
+                                                global_cu16* x, uint32_t row, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
+  if (u0 >= u1 || c0 >= c_end) return;
   constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
   constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
   const uint32_t sw8 = (uint32_t)(lane & 15) << 3, kg = (uint32_t)lane >> 4;
   const uint32_t nq = m.n_quads, n_panels = (m.cols + m.seg_cols - 1) / m.seg_cols, x_cols = pk * m.cols;
   // walker over the pieces of the run
-  uint32_t wu = u0, wc = unit_offset(m, u0), w_left = 0, w_base = 0, w_rem = 0;
-  const uint32_t run_last = unit_offset(m, u1) - 1;
+  uint32_t wu = u0, wc = c0, w_left = 0, w_base = 0, w_rem = 0;
+  bool w_ends = false;   // the unit the walker is in ends inside the run
   auto next_piece = [&](uint32_t& start, uint32_t& n, bool& ends) {
     if (w_left == 0) {
       if (wu == u1) {
@@ -51,7 +57,8 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
         start = wc;
         return;
       }
-      const uint32_t len = unit_offset(m, wu + 1) - wc;
+      const uint32_t unit_end = unit_offset(m, wu + 1), len = min(unit_end, c_end) - wc;
+      w_ends = unit_end <= c_end;
       w_left = (len + kP - 1) / kP;
       w_base = len / w_left;
       w_rem = len - w_base * w_left;
@@ -61,11 +68,11 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     if (w_rem) --w_rem;
     start = wc;
     wc += n;
-    ends = --w_left == 0;
+    ends = --w_left == 0 && w_ends;
   };
   // every piece issues exactly kP loads (those past its end repeat its last chunk), kRingStep of them at a time
   auto load_part = [&](uint2 (&cw)[kP], uint32_t start, uint32_t n, int p) {
-    const uint32_t last = min(start + max(n, 1u) - 1, run_last);
+    const uint32_t last = min(start + max(n, 1u) - 1, c_end - 1);
 #pragma unroll
     for (int k = p * kRingStep; k < (p + 1) * kRingStep; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
   };
@@ -97,7 +104,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   };
   // One group of MFMA steps if every lane that is still decoding has written the columns [done, done + 8 kG).  The weights
   // are read before it is known whether the group is ready (volatile: the reads stay ahead of the test).
-  auto multiply_ready = [&]() {
+  auto multiply_ready = [&](bool ready = false) {
     const uint32_t at = min(done, n_win8 - 8 * kG);   // at the unit's end: any place inside the ring
     const uint32_t base = at ^ sw8;
     // a segment that ends inside a piece: what its last chunk left over is not in the ring yet
@@ -107,7 +114,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
     const uint32_t next = done + 8 * kG;
     if (next > n_win8) return;
-    if (__builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
+    if (!ready && __builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
     if (ragged) {
 #pragma unroll
       for (uint32_t k = 0; k < kG * pk; ++k) {
@@ -168,8 +175,15 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   uint2 cwa[kP], cwb[kP];
   uint32_t sa, na, sb, nb;
   bool ea, eb;
+  auto ring_piece = [&](uint32_t col) { return (lds_u64*)(size_t)(ring | ((col ^ sw8) & 0x78u)); };
   enter_unit();
   next_piece(sa, na, ea);
+  if (started) {   // the groups that every lane has passed are others' work; of the next ones, what a lane has passed is zeros here
+    pos = min(start, seg_len);
+    while (done + 8 * kG < n_win8 && __builtin_amdgcn_ballot_w64(pos < min(seg_len, done + 8 * kG)) == 0) done += 8 * kG;
+    for (uint32_t col = done; __builtin_amdgcn_ballot_w64(col < (pos & ~7u)) != 0; col += 8)
+      if (col < (pos & ~7u)) *ring_piece(col) = 0;
+  }
   request_x();
 #pragma unroll
   for (int j = 0; j < kP / kRingStep; ++j) load_part(cwa, sa, na, j);
@@ -179,11 +193,27 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     next_piece(sa, na, ea);
     decode_piece(cwb, nb, eb, cwa, sa, na);
   }
+  if (c_end < unit_offset(m, u1)) {   // the last unit goes on elsewhere: multiply what the lanes have, zeros behind it
+    *ring_piece(pos) = carry;
+    while (__builtin_amdgcn_ballot_w64(pos > done) != 0) {
+#pragma unroll
+      for (int k = 0; k < kG; ++k)
+        if (done + 8 * k > pos) *ring_piece(done + 8 * k) = 0;
+      request_x();
+      multiply_ready(true);
+    }
+  }
 }
 
+// kSplit: as in k_matvec, a share of few units is cut into equal runs of chunks, and each wavefront counts the columns its
+// part of a unit passes while the dictionary is on its way.  A lone wavefront takes 8 us for a unit of 33 chunks, but the
+// windows around a cut are multiplied on both sides of it, each time with zeros for the other side's columns: shares that
+// leave less than half the wavefronts idle are faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 ->
+// 15.5, 700 x 1999 batch 5 20.2 -> 16.8; 6 units of packed weights for 8 wavefronts 18.0 -> 23.2.)
+constexpr uint32_t kRunSplitMin = 4;   // least chunks of a run
 template <int kWaves, bool kPacked>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
-  constexpr int kRunThreads = kWaves * 64, kRegs = 8;
+  constexpr int kRunThreads = kWaves * 64, kRegs = 8, kCount = 12;
   touch_arguments();
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -192,6 +222,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   const uint32_t* staged = nullptr;
   const uint32_t rings = a.x_off;   // LDS address (the LDS segment starts at 0)
   const uint32_t ring = rings + (uint32_t)wave * (64 * kRingBytes) + (uint32_t)lane * kRingBytes;
+  uint16_t* lds_count = (uint16_t*)((uint8_t*)lds4 + rings + kWaves * 64 * kRingBytes);   // [kWaves][64]
   bool lds_used = false;
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
@@ -203,28 +234,61 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads, unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
-    const uint32_t u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves);
-    const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
-    if (lds_used) __syncthreads();   // the previous matrix's dictionary and partial sums are no longer in use
+    EvenRun run;
+    const bool split = 2 * n_units <= kWaves;
+    if (split) {
+      const uint32_t uoff_lane = global_load(m.uoff + unit_lo + min((uint32_t)lane, n_units));
+      run = even_run(uoff_lane, unit_lo, n_units, wave, kWaves, kRunSplitMin);
+    } else {
+      run.u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves);
+      run.u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
+      run.c0 = run.u0 < run.u1 ? unit_offset(m, run.u0) : 0u;
+      run.c_end = run.u0 < run.u1 ? unit_offset(m, run.u1) : 0u;
+      run.head = run.tail = false;
+    }
+    if (lds_used) __syncthreads();   // the previous matrix's dictionary, counts and partial sums are no longer in use
     lds_used = true;
-    if (m.dict != staged) {
-      stage_dictionary16<kRegs>(m, (uint16_t*)lds4, tid, kRunThreads);
-      staged = m.dict;
-      __syncthreads();
+    if (m.dict != staged) stage_dictionary16<kRegs>(m, (uint16_t*)lds4, tid, kRunThreads);
+    if (split) {
+      u16x2 pairs = {0, 0};
+      if (run.tail) {
+        for (uint32_t from = run.part; from < run.c_end; from += kCount) {
+          uint2 cw[kCount];
+#pragma unroll
+          for (int k = 0; k < kCount; ++k) cw[k] = load_chunk(m.codes, min(from + k, run.c_end - 1), lane);
+#pragma unroll
+          for (int k = 0; k < kCount; ++k)
+            if (from + k < run.c_end) pairs = count_pairs(count_pairs(pairs, cw[k].x), cw[k].y);
+        }
+      }
+      lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (run.c_end - run.part) + pairs.x + pairs.y);   // (an empty run passes nothing)
+    }
+    if (split || m.dict != staged) __syncthreads();
+    staged = m.dict;
+    uint32_t start = 0;   // head: the columns of the first unit that earlier wavefronts pass
+    if (run.head) {
+      for (int w = wave - 1; w >= 0; --w) {
+        start += lds_count[w * 64 + lane];
+        if (run.start_of(w) <= run.unit_start) break;
+      }
     }
     BandSums sums;
-    sums.start(u0, u1, nq);
+    sums.start(run.u0, nq, run.head);
     f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     auto on_unit = [&](uint32_t band, uint32_t quad) {
-      if (quad + 1 != nq && band * nq + quad + 1 != u1) return;
-      sums.finish(a, job, m, band, quad, (part[0] + part[1]) + (part[2] + part[3]), lane);
+      if (quad + 1 != nq && band * nq + quad + 1 != run.u1) return;
+      sums.finish(a, job, m, band, quad + 1 == nq, (part[0] + part[1]) + (part[2] + part[3]), lane);
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     const uint32_t row = min((uint32_t)(lane & 15), (uint32_t)a.batch - 1);   // lanes past the batch repeat its last row: their sums are never stored
-    const uint32_t careful = min(max(m.reserved - 1, u0), u1);               // (units whose lanes drift far apart come first: see DevMat::reserved)
-    decode_run_ring<true, kPacked>(m, u0, careful, (global_cu16*)job.x, row, lane, ring, part, on_unit);
-    decode_run_ring<false, kPacked>(m, careful, u1, (global_cu16*)job.x, row, lane, ring, part, on_unit);
+    // units whose lanes drift far apart come first: see DevMat::reserved
+    const uint32_t u_care = min(max(m.reserved - 1, run.u0), run.u1);
+    const uint32_t c_care = u_care == run.u0 ? run.c0 : u_care == run.u1 ? run.c_end : unit_offset(m, u_care);
+    global_cu16* x = (global_cu16*)job.x;
+    decode_run_ring<true, kPacked>(m, run.u0, u_care, run.c0, c_care, run.head, start, x, row, lane, ring, part, on_unit);
+    decode_run_ring<false, kPacked>(m, u_care, run.u1, c_care, run.c_end, run.head && u_care == run.u0, start, x, row, lane, ring, part, on_unit);
+    if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, (part[0] + part[1]) + (part[2] + part[3]), lane);
     __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
     sums.combine(a, job, m, rings, wave, kWaves, lane);
   }

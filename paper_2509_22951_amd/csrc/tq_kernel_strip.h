@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
     __syncthreads();
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     BandSums sums;
-    sums.start(u0, u1, nq);
+    sums.start(u0, nq);
     // lanes past the batch repeat its last row: their output columns are never stored
     constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte
     const uint32_t x_cols = pk * m.cols;
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
     // acc holds the sums of the band in work when its last unit (or the run's) has been multiplied
     auto finish_unit = [&](uint32_t band, uint32_t quad) {
       if (quad + 1 != nq && band * nq + quad + 1 != u1) return;
-      sums.finish(a, job, m, band, quad, acc, lane);
+      sums.finish(a, job, m, band, quad + 1 == nq, acc, lane);
       acc = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     {

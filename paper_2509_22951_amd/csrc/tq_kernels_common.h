@@ -341,6 +341,37 @@ __device__ __forceinline__ u16x2 count_pairs(u16x2 acc, uint32_t codes) {
   return acc + __builtin_elementwise_min(high, u16x2{1, 1});
 }
 
+// One of n_waves equal runs of chunks of a share of n_units < 64 units: chunks [c0, c_end) of the units [u0, u1).
+// uoff_lane: lane k holds the offset of the share's unit k, lanes from n_units on that of its end.
+struct EvenRun {
+  uint32_t u0, u1, c0, c_end;
+  bool head, tail;       // the run starts / ends inside a unit
+  uint32_t unit_start;   // of unit u0
+  uint32_t part;         // tail: where the run's part of the unit it leaves unfinished begins (else c_end)
+  uint32_t all_lo, all_n, n_runs;
+  __device__ __forceinline__ uint32_t start_of(int wave) const { return all_lo + all_n * min((uint32_t)wave, n_runs) / n_runs; }
+};
+__device__ __forceinline__ EvenRun even_run(uint32_t uoff_lane, uint32_t unit_lo, uint32_t n_units, int wave, int n_waves, uint32_t min_chunks) {
+  EvenRun r;
+  r.all_lo = __builtin_amdgcn_readlane(uoff_lane, 0);
+  r.all_n = __builtin_amdgcn_readlane(uoff_lane, n_units) - r.all_lo;
+  r.n_runs = min((uint32_t)n_waves, (r.all_n + min_chunks - 1) / min_chunks);   // the wavefronts behind that many have none
+  r.c0 = r.start_of(wave);
+  r.c_end = r.start_of(wave + 1);
+  const uint64_t lanes = (2ull << n_units) - 1;   // lanes 0 .. n_units hold the offsets
+  const uint32_t first = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane <= r.c0) & lanes) - 1;
+  const uint32_t last = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane < max(r.c_end, r.c0 + 1)) & lanes) - 1;
+  const uint32_t last_start = __builtin_amdgcn_readlane(uoff_lane, last), last_end = __builtin_amdgcn_readlane(uoff_lane, min(last + 1, 63u));
+  const bool empty = r.c0 >= r.c_end;
+  r.u0 = unit_lo + first;
+  r.u1 = empty ? r.u0 : unit_lo + last + 1;
+  r.unit_start = __builtin_amdgcn_readlane(uoff_lane, first);
+  r.head = !empty && r.c0 > r.unit_start;
+  r.tail = !empty && r.c_end < last_end;
+  r.part = r.tail ? max(r.c0, last_start) : r.c_end;
+  return r;
+}
+
 // Pointer forms on purpose: the compiler tracks the outstanding LDS read and places the wait before the first use.
 __device__ __forceinline__ uint32_t lds_read32(uint32_t addr) { return *(lds_cu32*)(size_t)addr; }
 template <int kOff>

@@ -259,14 +259,13 @@ __device__ __forceinline__ void stage_dictionary16(const DevMat& m, uint16_t* ld
 struct BandSums {
   f32x4 head_acc, tail_acc;
   int head_band, tail_band;
-  uint32_t first_band, n_quads;
+  uint32_t first_band;
   bool first_whole;
-  __device__ __forceinline__ void start(uint32_t u0, uint32_t u1, uint32_t nq) {
+  __device__ __forceinline__ void start(uint32_t u0, uint32_t nq, bool inside_unit = false) {   // inside_unit: the run starts within unit u0
     head_acc = tail_acc = f32x4{0.f, 0.f, 0.f, 0.f};
     head_band = tail_band = -1;
-    n_quads = nq;
     first_band = u0 / nq;
-    first_whole = u0 % nq == 0;
+    first_whole = u0 % nq == 0 && !inside_unit;
   }
   __device__ __forceinline__ static void store(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t band, f32x4 acc, int lane) {
     const int bn = lane & 15;
@@ -286,9 +285,9 @@ struct BandSums {
         if (row0 + v < m.rows) global_store(job.y + (size_t)bn * m.rows + row0 + v, acc[v] * scale[v]);
     }
   }
-  // acc: the band's sums when unit (band, quad), the last of the band or of the run, has been multiplied
-  __device__ __forceinline__ void finish(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t band, uint32_t quad, f32x4 acc, int lane) {
-    if (quad + 1 == n_quads && (band != first_band || first_whole)) {
+  // acc: the band's sums when the run has come to the band's end, or to its own (ends: the band's)
+  __device__ __forceinline__ void finish(const MatvecArgs& a, const Job& job, const DevMat& m, uint32_t band, bool ends, f32x4 acc, int lane) {
+    if (ends && (band != first_band || first_whole)) {
       store(a, job, m, band, acc, lane);
     } else {
       const bool head = band == first_band && !first_whole;   // begun by an earlier wavefront, or left unfinished
@@ -314,9 +313,13 @@ struct BandSums {
       const int s = 2 * wave + j, band = __builtin_amdgcn_readlane(bands, s);
       uint64_t same = __builtin_amdgcn_ballot_w64(bands == band);
       if (band < 0 || (same & ((1ull << s) - 1))) continue;   // an earlier slot of the band does it
-      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-      for (; same; same &= same - 1) sum += value[__builtin_ctzll(same) * 64 + lane];
-      store(a, job, m, (uint32_t)band, sum, lane);
+      double sum[4] = {0., 0., 0., 0.};   // (so that the number of wavefronts that share a band adds no rounding)
+      for (; same; same &= same - 1) {
+        const f32x4 v = value[__builtin_ctzll(same) * 64 + lane];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum[k] += v[k];
+      }
+      store(a, job, m, (uint32_t)band, f32x4{(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]}, lane);
     }
   }
 };
