@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -143,6 +144,38 @@ class RunDict {
     }
   }
 
+  // The two-byte runs by their bytes as they lie in memory (first byte low): their code, or kNoPair.
+  static constexpr uint16_t kNoPair = 0xFFFF;
+  std::vector<uint16_t> pair_table() const {
+    std::vector<uint16_t> t(65536, kNoPair);
+    for (uint32_t e = 256; e < size(); ++e)
+      if (len_[e] == 2) t[bytes_[e]] = (uint16_t)e;
+    return t;
+  }
+
+  // parse<true> for runs of at most 2 (lmax 2), with `pairs` kept as pair_table() would give it.
+  uint32_t parse_growing_pairs(const uint8_t* p, uint32_t len, uint16_t* pairs, uint16_t* out) {
+    uint32_t i = 0, n = 0;
+    while (i + 1 < len) {
+      uint16_t key;
+      std::memcpy(&key, p + i, 2);
+      const uint16_t c = pairs[key];
+      if (c != kNoPair) {
+        out[n++] = c;
+        i += 2;
+        continue;
+      }
+      out[n++] = p[i];
+      if (!full()) {
+        pairs[key] = (uint16_t)size();
+        add(p[i], p[i + 1]);
+      }
+      ++i;
+    }
+    if (i < len) out[n++] = p[i];
+    return n;
+  }
+
   // The container's numbering: entries in order of run length, equal lengths in order of creation.
   // final_of[creation code] = container code; class_end[k] = entries of at most k + 1 bytes.
   void final_codes(std::vector<uint16_t>* final_of, std::vector<uint32_t>* words, uint32_t class_end[4]) const {
@@ -209,15 +242,108 @@ int check_opts(const tq_encode_opts* o, uint32_t* max_entries, uint32_t* lmax, u
   return TQ_OK;
 }
 
-// Codes of a contiguous range of units, concatenated in (unit, lane) order; cnt[(u - u_begin) * 64 + lane] codes each.
+// Codes of a contiguous range of units as they come out of a parse that grows the dictionary, concatenated in (unit, lane)
+// order; cnt[u * 64 + lane] codes each.
 struct UnitRange {
-  uint64_t u_begin = 0, u_end = 0;
   std::vector<uint16_t> codes;
   std::vector<uint16_t> cnt;
 };
 
+// The code section of a contiguous range of units, in the container's layout (the offsets follow when all ranges are known).
+struct CodedRange {
+  uint64_t u_begin = 0, u_end = 0, n_real = 0;
+  std::unique_ptr<uint16_t[]> words;   // not initialised: a page that is not written costs nothing
+  size_t used = 0;                     // words
+  std::vector<uint32_t> chunks;        // per unit
+  void start(uint64_t begin, uint64_t end, uint32_t seg_cols) {
+    u_begin = begin;
+    u_end = end;
+    words.reset(new uint16_t[(size_t)(end - begin) * 64 * ((seg_cols + kChunkCodes - 1) / kChunkCodes * kChunkCodes)]);
+    chunks.reserve(end - begin);
+  }
+  // lane l's codes at lanes + l * kMaxSegCols (room to pad them to whole chunks of the longest)
+  void add_unit(uint16_t* lanes, const uint32_t (&cnt)[64], uint16_t pad) {
+    uint32_t mx = 0;
+    for (uint32_t l = 0; l < 64; ++l) {
+      mx = std::max(mx, cnt[l]);
+      n_real += cnt[l];
+    }
+    const uint32_t n = (mx + kChunkCodes - 1) / kChunkCodes;
+    uint16_t* to = words.get() + used;
+    for (uint32_t l = 0; l < 64; ++l) {
+      uint16_t* src = lanes + (size_t)l * kMaxSegCols;
+      std::fill(src + cnt[l], src + n * kChunkCodes, pad);
+      for (uint32_t c = 0; c < n; ++c) std::memcpy(to + (size_t)c * kChunkWords + l * kChunkCodes, src + c * kChunkCodes, kChunkCodes * 2);
+    }
+    used += (size_t)n * kChunkWords;
+    chunks.push_back(n);
+  }
+};
+static_assert(kMaxSegCols % kChunkCodes == 0, "a padded lane stream fits kMaxSegCols codes");
+
+// Longest match over single bytes and pairs, p[0 .. len) -> codes; n = their number.  `pairs`: RunDict::pair_table.
+inline uint32_t parse_pairs(const uint8_t* p, uint32_t i, uint32_t len, const uint16_t* pairs, uint16_t* out, uint32_t n) {
+  while (i + 1 < len) {
+    uint16_t key;
+    std::memcpy(&key, p + i, 2);
+    const uint16_t c = pairs[key];
+    const bool pair = c != RunDict::kNoPair;
+    out[n++] = pair ? c : p[i];
+    i += 1u + pair;
+  }
+  if (i < len) out[n++] = p[i];
+  return n;
+}
+// Four segments of one length side by side: a step waits for its table entry, the four do so together.
+inline void parse_pairs4(const uint8_t* const (&p)[4], uint32_t len, const uint16_t* pairs, uint16_t* const (&out)[4], uint32_t (&n)[4]) {
+  uint32_t i[4] = {0, 0, 0, 0};
+  n[0] = n[1] = n[2] = n[3] = 0;
+  while (std::max(std::max(i[0], i[1]), std::max(i[2], i[3])) + 1 < len) {
+    for (int k = 0; k < 4; ++k) {
+      uint16_t key;
+      std::memcpy(&key, p[k] + i[k], 2);
+      const uint16_t c = pairs[key];
+      const uint32_t pair = c != RunDict::kNoPair;
+      out[k][n[k]++] = pair ? c : (uint16_t)(key & 0xFF);
+      i[k] += 1u + pair;
+    }
+  }
+  for (int k = 0; k < 4; ++k) n[k] = parse_pairs(p[k], i[k], len, pairs, out[k], n[k]);
+}
+
+// One row: the scale, and the values as bytes.  In IEEE fp32 and in this order: amax = max|w|, s = amax / qmax, q = clamp(rne(w / s),
+// -qmax, qmax).  The loops are written for vector instructions: magnitudes compare like their bits, and adding and
+// subtracting 1.5 * 2^23 rounds to nearest, ties to even, for values below 2^22 (|w / s| < 2 qmax).
+float quantize_row(const float* row, uint32_t cols, float qmax, uint8_t* q) {
+  int32_t top = 0;
+  for (uint32_t c = 0; c < cols; ++c) {
+    int32_t bits;
+    std::memcpy(&bits, row + c, 4);
+    bits &= 0x7FFFFFFF;
+    top = bits > top ? bits : top;
+  }
+  float amax;
+  std::memcpy(&amax, &top, 4);
+  if (top > 0x7F800000) {   // a NaN: it counts for nothing
+    amax = 0.f;
+    for (uint32_t c = 0; c < cols; ++c) amax = std::max(amax, std::fabs(row[c]));
+  }
+  const float s = amax / qmax;
+  if (!(s > 0.f)) {   // all-zero row
+    std::memset(q, 0, cols);
+    return s;
+  }
+  for (uint32_t c = 0; c < cols; ++c) {
+    float t = row[c] / s;
+    t = (t + 12582912.f) - 12582912.f;
+    t = std::min(qmax, std::max(-qmax, t));
+    q[c] = (uint8_t)(int8_t)(int)t;
+  }
+  return s;
+}
+
 // Two 4-bit values per byte (low nibble: the even column).  false if a value does not fit or the column count is odd.
-bool pack_nibbles(const std::vector<uint8_t>& Q, uint32_t rows, uint32_t cols, std::vector<uint8_t>* out) {
+bool pack_nibbles(const uint8_t* Q, uint32_t rows, uint32_t cols, std::vector<uint8_t>* out) {
   if (cols % 2) {
     set_error("tq_encode: packing needs an even number of columns");
     return false;
@@ -235,7 +361,7 @@ bool pack_nibbles(const std::vector<uint8_t>& Q, uint32_t rows, uint32_t cols, s
 }
 
 // Q: the byte matrix rows x cols that is coded (for packing 1 the packed one).
-int encode_quantized_matrix(const std::vector<uint8_t>& Q, const std::vector<float>& scales_pad, uint32_t rows, uint32_t cols,
+int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_pad, uint32_t rows, uint32_t cols,
                             const tq_encode_opts* opts, void** blob_out, size_t* bytes_out) {
   uint32_t max_entries, lmax, seg_cols;
   unsigned n_threads;
@@ -274,19 +400,11 @@ int encode_quantized_matrix(const std::vector<uint8_t>& Q, const std::vector<flo
       return TQ_E_INVALID_ARG;
     }
   }
-  auto parse_unit = [&](uint64_t u, bool grow, UnitRange& out) {
+  auto segment_start = [&](uint64_t u, uint32_t lane) {
     const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
-    for (uint32_t lane = 0; lane < 64; ++lane) {
-      const uint32_t len = segment_len(h, band, quad, lane);
-      const size_t before = out.codes.size();
-      if (len) {
-        const uint64_t start = (uint64_t)(band * kUnitRows + (lane & 15)) * cols + (uint64_t)(quad * kUnitPanels + (lane >> 4)) * seg_cols;
-        if (grow) dict.parse<true>(Q.data(), start, start + len, out.codes);
-        else dict.parse<false>(Q.data(), start, start + len, out.codes);
-      }
-      out.cnt.push_back((uint16_t)(out.codes.size() - before));
-    }
+    return (uint64_t)(band * kUnitRows + (lane & 15)) * cols + (uint64_t)(quad * kUnitPanels + (lane >> 4)) * seg_cols;
   };
+  auto segment_length = [&](uint64_t u, uint32_t lane) { return segment_len(h, (uint32_t)(u / h.n_quads), (uint32_t)(u % h.n_quads), lane); };
 
   const bool by_frequency = opts && opts->dictionary == TQ_DICT_FREQUENCY;
   if (by_frequency && !(opts && opts->dict_from) && lmax >= 2 && max_entries > 256) {
@@ -299,7 +417,7 @@ int encode_quantized_matrix(const std::vector<uint8_t>& Q, const std::vector<flo
       for (uint32_t lane = 0; lane < 64; ++lane) {
         const uint32_t len = segment_len(h, band, quad, lane);
         if (len < 2) continue;
-        const uint8_t* seg = Q.data() + (uint64_t)(band * kUnitRows + (lane & 15)) * cols + (uint64_t)(quad * kUnitPanels + (lane >> 4)) * seg_cols;
+        const uint8_t* seg = Q + (uint64_t)(band * kUnitRows + (lane & 15)) * cols + (uint64_t)(quad * kUnitPanels + (lane >> 4)) * seg_cols;
         for (uint32_t i = 0; i + 1 < len; ++i) {
           const uint32_t key = (uint32_t)seg[i] << 8 | seg[i + 1];
           if (count[key]++ == 0) first[key] = seen;
@@ -316,54 +434,106 @@ int encode_quantized_matrix(const std::vector<uint8_t>& Q, const std::vector<flo
   }
 
   // Phase 1 (sequential): units in order while the dictionary can still grow.
-  std::vector<UnitRange> ranges(1 + n_threads);
+  UnitRange grown;
+  std::vector<uint16_t> pairs = lmax <= 2 ? dict.pair_table() : std::vector<uint16_t>();
+  uint16_t segment[kMaxSegCols];
   uint64_t u = 0;
-  for (; !by_frequency && u < n_units && !dict.full(); ++u) parse_unit(u, true, ranges[0]);
-  ranges[0].u_end = u;
+  for (; !by_frequency && u < n_units && !dict.full(); ++u)
+    for (uint32_t lane = 0; lane < 64; ++lane) {
+      const size_t before = grown.codes.size();
+      if (const uint32_t len = segment_length(u, lane)) {
+        const uint64_t start = segment_start(u, lane);
+        if (lmax == 2) grown.codes.insert(grown.codes.end(), segment, segment + dict.parse_growing_pairs(Q + start, len, pairs.data(), segment));
+        else dict.parse<true>(Q, start, start + len, grown.codes);
+      }
+      grown.cnt.push_back((uint16_t)(grown.codes.size() - before));
+    }
   const uint64_t u_frozen = u;
   const uint32_t n_entries = dict.size();
   const uint16_t pad = (uint16_t)n_entries;
-  // The container's code space is sorted by run length; the parse above and below numbers entries as they were created.
+  // The container's code space is sorted by run length; the parse above and below numbers entries as they were created
+  // (which is the same while no run is longer than 2).
   std::vector<uint16_t> final_of;
   std::vector<uint32_t> words;
   dict.final_codes(&final_of, &words, h.class_end);
 
   // Phase 2 (parallel): the dictionary no longer changes, units are independent.
+  std::vector<CodedRange> ranges(1 + n_threads);
   {
+    auto code_unit = [&](uint64_t uu, uint16_t* lanes, std::vector<uint16_t>& buffer, CodedRange& r) {
+      uint32_t cnt[64];
+      for (uint32_t lane = 0; lane < 64; lane += 4) {
+        const uint8_t* p[4];
+        uint16_t* out[4];
+        uint32_t len[4], n[4];
+        for (uint32_t k = 0; k < 4; ++k) {
+          len[k] = segment_length(uu, lane + k);
+          p[k] = Q + (len[k] ? segment_start(uu, lane + k) : 0);
+          out[k] = lanes + (size_t)(lane + k) * kMaxSegCols;
+        }
+        if (lmax <= 2 && len[0] && len[0] == len[1] && len[1] == len[2] && len[2] == len[3]) {
+          parse_pairs4(p, len[0], pairs.data(), out, n);
+        } else {
+          for (uint32_t k = 0; k < 4; ++k) {
+            if (lmax <= 2) {
+              n[k] = parse_pairs(p[k], 0, len[k], pairs.data(), out[k], 0);
+            } else {
+              buffer.clear();
+              if (len[k]) dict.parse<false>(p[k], 0, len[k], buffer);
+              n[k] = (uint32_t)buffer.size();
+              for (uint32_t c = 0; c < n[k]; ++c) out[k][c] = final_of[buffer[c]];
+            }
+          }
+        }
+        for (uint32_t k = 0; k < 4; ++k) cnt[lane + k] = n[k];
+      }
+      r.add_unit(lanes, cnt, pad);
+    };
     const uint64_t rest = n_units - u_frozen, per = (rest + n_threads - 1) / std::max(1u, n_threads);
-    std::vector<std::thread> th;
+    // (what can fail for want of memory is taken here: nothing throws inside the threads but the long-run buffer's growth)
+    const size_t lane_words = (size_t)64 * kMaxSegCols;
+    std::unique_ptr<uint16_t[]> lanes(new uint16_t[lane_words * (1 + n_threads)]);
+    std::vector<std::vector<uint16_t>> buffers(1 + n_threads);
+    ranges[0].start(0, u_frozen, seg_cols);
     for (unsigned t = 0; t < n_threads; ++t) {
-      UnitRange& r = ranges[1 + t];
-      r.u_begin = std::min<uint64_t>(n_units, u_frozen + t * per);
-      r.u_end = std::min<uint64_t>(n_units, r.u_begin + per);
-      if (r.u_begin >= r.u_end) continue;
-      th.emplace_back([&, t] {
-        UnitRange& rr = ranges[1 + t];
-        rr.codes.reserve((rr.u_end - rr.u_begin) * 64 * (seg_cols / 2 + 8));
-        for (uint64_t uu = rr.u_begin; uu < rr.u_end; ++uu) parse_unit(uu, false, rr);
+      const uint64_t b = std::min<uint64_t>(n_units, u_frozen + t * per), e = std::min<uint64_t>(n_units, b + per);
+      ranges[1 + t].start(b, e, seg_cols);
+      if (lmax > 2) buffers[1 + t].reserve(kMaxSegCols);
+    }
+    std::vector<std::thread> th;
+    for (unsigned t = 0; t < n_threads; ++t)
+      if (ranges[1 + t].u_begin < ranges[1 + t].u_end) th.emplace_back([&, t] {
+        CodedRange& r = ranges[1 + t];
+        for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) code_unit(uu, lanes.get() + lane_words * (1 + t), buffers[1 + t], r);
       });
+    const uint16_t* src = grown.codes.data();
+    for (uint64_t uu = 0; uu < u_frozen; ++uu) {   // the units parsed above
+      uint32_t cnt[64];
+      for (uint32_t l = 0; l < 64; ++l) {
+        cnt[l] = grown.cnt[uu * 64 + l];
+        uint16_t* out = lanes.get() + (size_t)l * kMaxSegCols;
+        for (uint32_t k = 0; k < cnt[l]; ++k) out[k] = final_of[src[k]];
+        src += cnt[l];
+      }
+      ranges[0].add_unit(lanes.get(), cnt, pad);
     }
     for (auto& x : th) x.join();
   }
 
-  // Unit lengths in chunks: the longest lane stream, rounded up to whole chunks.
+  // Unit offsets in chunks: a unit is its longest lane stream, rounded up to whole chunks.
   std::vector<uint32_t> uoff(n_units + 1, 0);
   uint64_t acc = 0, n_real = 0;
-  for (const UnitRange& r : ranges)
+  for (const CodedRange& r : ranges) {
+    n_real += r.n_real;
     for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) {
-      const uint16_t* c = r.cnt.data() + (uu - r.u_begin) * 64;
-      uint32_t mx = 0;
-      for (int l = 0; l < 64; ++l) {
-        mx = std::max<uint32_t>(mx, c[l]);
-        n_real += c[l];
-      }
       uoff[uu] = (uint32_t)acc;
-      acc += (mx + kChunkCodes - 1) / kChunkCodes;
+      acc += r.chunks[uu - r.u_begin];
       if (acc >= 0xFFFFFFFFull / kChunkWords) {
         set_error("tq_encode: code stream exceeds 2^32 codes");
         return TQ_E_UNSUPPORTED;
       }
     }
+  }
   uoff[n_units] = (uint32_t)acc;
 
   h.n_entries = n_entries;
@@ -380,36 +550,38 @@ int encode_quantized_matrix(const std::vector<uint8_t>& Q, const std::vector<flo
   h.off_scales = round_up(h.off_codes + h.code_bytes, kSectionAlign);
   h.total_bytes = round_up(h.off_scales + h.scale_bytes, kSectionAlign);
 
-  uint8_t* blob = (uint8_t*)std::calloc(1, h.total_bytes);
+  // Every byte is written below: the sections, and zeros between them (the pad entry is the first of those).
+  uint8_t* blob = (uint8_t*)std::malloc(h.total_bytes);
   if (!blob) {
     set_error("tq_encode: out of host memory");
     return TQ_E_OOM;
   }
+  auto put = [&](uint64_t at, const void* src, uint64_t n, uint64_t next) {
+    std::memcpy(blob + at, src, n);
+    std::memset(blob + at + n, 0, next - at - n);
+  };
   std::memcpy(blob, &h, sizeof h);
-  std::memcpy(blob + h.off_dict, words.data(), (size_t)n_entries * 4);  // pad entry stays zero
-  std::memcpy(blob + h.off_uoff, uoff.data(), uoff.size() * 4);
-  uint16_t* codes = (uint16_t*)(blob + h.off_codes);
+  put(h.off_dict, words.data(), (uint64_t)n_entries * 4, h.off_uoff);
+  put(h.off_uoff, uoff.data(), uoff.size() * 4, h.off_codes);
+  std::memset(blob + h.off_codes + h.code_bytes, 0, h.off_scales - h.off_codes - h.code_bytes);
+  put(h.off_scales, scales_pad.data(), (uint64_t)h.n_bands * kUnitRows * 4, h.total_bytes);
   {
-    // Interleave: code k of lane l of unit u -> codes[(uoff[u] + k / 4) * 256 + l * 4 + k % 4]; pad the rest.
-    auto fill = [&](const UnitRange& r) {
-      const uint16_t* src = r.codes.data();
-      for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) {
-        const uint16_t* c = r.cnt.data() + (uu - r.u_begin) * 64;
-        const uint32_t len = (uoff[uu + 1] - uoff[uu]) * kChunkCodes;
-        uint16_t* base = codes + (uint64_t)uoff[uu] * kChunkWords;
-        for (uint32_t l = 0; l < 64; ++l) {
-          for (uint32_t k = 0; k < len; ++k) base[(uint64_t)(k / kChunkCodes) * kChunkWords + l * kChunkCodes + k % kChunkCodes] = k < c[l] ? final_of[src[k]] : pad;
-          src += c[l];
-        }
-      }
+    uint16_t* codes = (uint16_t*)(blob + h.off_codes);
+    auto copy = [&](const CodedRange& r) {
+      if (r.u_begin < r.u_end) std::memcpy(codes + (uint64_t)uoff[r.u_begin] * kChunkWords, r.words.get(), r.used * 2);
     };
     std::vector<std::thread> th;
-    for (size_t i = 1; i < ranges.size(); ++i)
-      if (ranges[i].u_begin < ranges[i].u_end) th.emplace_back([&, i] { fill(ranges[i]); });
-    fill(ranges[0]);
+    try {
+      for (size_t i = 1; i < ranges.size(); ++i)
+        if (ranges[i].u_begin < ranges[i].u_end) th.emplace_back([&, i] { copy(ranges[i]); });
+    } catch (...) {
+      for (auto& x : th) x.join();
+      std::free(blob);
+      throw;
+    }
+    copy(ranges[0]);
     for (auto& x : th) x.join();
   }
-  std::memcpy(blob + h.off_scales, scales_pad.data(), (size_t)h.n_bands * kUnitRows * 4);
   *blob_out = blob;
   *bytes_out = (size_t)h.total_bytes;
   return TQ_OK;
@@ -429,10 +601,10 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
     }
     const unsigned nt = pick_threads(opts ? opts->n_threads : 0);
     const uint32_t rows_pad = (uint32_t)round_up(rows, kUnitRows);
-    std::vector<uint8_t> Q((size_t)rows * cols, 0);
+    std::unique_ptr<uint8_t[]> Q(new uint8_t[(size_t)rows * cols]);
     std::vector<float> scales(rows_pad, 0.f);
-    // Per row, in IEEE fp32 and in this order: amax = max|w|, s = amax / qmax, q = clamp(rne(w / s), -qmax, qmax),
-    // qmax = 2^(bits - 1) - 1 (paper section 3: a fixed range of levels set by the number of bits; 127 at 8 bits).
+    // Per row (quantize_row), with qmax = 2^(bits - 1) - 1 (paper section 3: a fixed range of levels set by the number of
+    // bits; 127 at 8 bits).
     if (opts && opts->bits != 0 && (opts->bits < 2 || opts->bits > 8)) {
       set_error("tq_encode: bits must be 0 (= 8) or in [2, 8]");
       return TQ_E_INVALID_ARG;
@@ -444,26 +616,14 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
     }
     const float qmax = (float)((1u << ((opts && opts->bits ? opts->bits : 8u) - 1)) - 1u);
     parallel_for(rows, nt, [&](uint64_t rb, uint64_t re, unsigned) {
-      for (uint64_t r = rb; r < re; ++r) {
-        const float* row = w + r * cols;
-        float amax = 0.f;
-        for (uint32_t c = 0; c < cols; ++c) amax = std::max(amax, std::fabs(row[c]));
-        const float s = amax / qmax;
-        scales[r] = s;
-        if (!(s > 0.f)) continue;  // all-zero row: bytes stay 0
-        for (uint32_t c = 0; c < cols; ++c) {
-          float t = std::nearbyintf(row[c] / s);  // default rounding mode: to nearest, ties to even
-          t = std::min(qmax, std::max(-qmax, t));
-          Q[r * cols + c] = (uint8_t)(int8_t)(int)t;
-        }
-      }
+      for (uint64_t r = rb; r < re; ++r) scales[r] = quantize_row(w + r * cols, cols, qmax, Q.get() + r * cols);
     });
     if (packed) {
       std::vector<uint8_t> P;
-      if (!pack_nibbles(Q, rows, cols, &P)) return TQ_E_INVALID_ARG;
-      return encode_quantized_matrix(P, scales, rows, cols / 2, opts, blob, blob_bytes);
+      if (!pack_nibbles(Q.get(), rows, cols, &P)) return TQ_E_INVALID_ARG;
+      return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, blob, blob_bytes);
     }
-    return encode_quantized_matrix(Q, scales, rows, cols, opts, blob, blob_bytes);
+    return encode_quantized_matrix(Q.get(), scales, rows, cols, opts, blob, blob_bytes);
   } catch (const std::bad_alloc&) {
     set_error("tq_encode: out of host memory");
     return TQ_E_OOM;
@@ -478,13 +638,13 @@ extern "C" int tq_encode_quantized(const int8_t* q, const float* scales_in, uint
       return TQ_E_INVALID_ARG;
     }
     const uint32_t rows_pad = (uint32_t)round_up(rows, kUnitRows);
-    std::vector<uint8_t> Q((const uint8_t*)q, (const uint8_t*)q + (size_t)rows * cols);
+    const uint8_t* Q = (const uint8_t*)q;
     std::vector<float> scales(rows_pad, 0.f);
     std::copy(scales_in, scales_in + rows, scales.begin());
     if (opts && opts->packing == TQ_PACK_NIBBLES) {
       std::vector<uint8_t> P;
       if (!pack_nibbles(Q, rows, cols, &P)) return TQ_E_INVALID_ARG;
-      return encode_quantized_matrix(P, scales, rows, cols / 2, opts, blob, blob_bytes);
+      return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, blob, blob_bytes);
     }
     return encode_quantized_matrix(Q, scales, rows, cols, opts, blob, blob_bytes);
   } catch (const std::bad_alloc&) {
