@@ -279,8 +279,12 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_mfma<false, false, true>,
     (const void*)k_matvec_mfma<true, true, true>,
     (const void*)k_matvec_mfma<false, true, true>,
-    (const void*)k_matvec_runs<kRunWaves, false>,
-    (const void*)k_matvec_runs<kRunWavesPacked, true>,
+    (const void*)k_matvec_runs<kRunWaves, false, 1>,
+    (const void*)k_matvec_runs<kRunWaves, false, 2>,
+    (const void*)k_matvec_runs<kRunWaves, false, 4>,
+    (const void*)k_matvec_runs<kRunWavesPacked, true, 1>,
+    (const void*)k_matvec_runs<kRunWavesPacked, true, 2>,
+    (const void*)k_matvec_runs<kRunWavesPacked, true, 4>,
     (const void*)k_matvec_ring<kRingWaves, 16, false>,
     (const void*)k_matvec_ring<kRingWavesHalf, 8, false>,
     (const void*)k_matvec_ring<kRingWaves, 16, true>,
@@ -645,7 +649,9 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     a.x_off = (uint32_t)dict16;
     p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
     p.lds = dict16 + (size_t)p.block * kRingBytes + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
-    p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true> : (const void*)k_matvec_runs<kRunWaves, false>;
+    if (batch <= 4) p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 4> : (const void*)k_matvec_runs<kRunWaves, false, 4>;
+    else if (batch <= 8) p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 2> : (const void*)k_matvec_runs<kRunWaves, false, 2>;
+    else p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 1> : (const void*)k_matvec_runs<kRunWaves, false, 1>;
     cut_by_workgroup();
   } else {
     // Tile decode.  LDS: 16-bit dictionary image | one tile (64 strips) per wavefront, which the batched product reuses

@@ -79,6 +79,7 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
                                                   uint32_t xfrag, OnUnit&& on_unit) {
   if (first_band == kNoBand) return;
   constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
+  constexpr int kFold = kCareful ? 1 : 16 / kRows;   // windows per B operand (fold_sums)
   const uint32_t sw8 = (uint32_t)(lane & 15) << 3;
   const uint32_t n_win8 = m.seg_cols;
   // a row past the end of the matrix has no segment: its lane decodes nothing
@@ -134,23 +135,22 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
     constexpr int kX = kPacked ? 2 : 1;             // activation windows per 8-byte piece of the ring
     const uint32_t xa = xfrag + at * (2 * kRows * kX);   // 16 kRows bytes per window
     u32x2 a8[kG];
-    u32x4 x8[kG * kX];
+    u32x4 x8[kG * kX / kFold];
 #pragma unroll
-    for (int k = 0; k < kG; ++k) {
-      a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
+    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
 #pragma unroll
-      for (int h = 0; h < kX; ++h) x8[k * kX + h] = *(volatile lds_cu128*)(size_t)(xa + 16 * kRows * (k * kX + h));
-    }
+    for (int k = 0; k < kG * kX / kFold; ++k) x8[k] = *(volatile lds_cu128*)(size_t)(xa + 16 * kRows * kFold * k);
     const uint32_t next = done + 8 * kG;
     if (next > n_win8) return;
     if (__builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
 #pragma unroll
     for (int k = 0; k < kG; ++k) {
       if constexpr (kPacked) {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k]), part[k], 0, 0, 0);
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[2 * k + 1]), part[k], 0, 0, 0);
+        f32x4 &p0 = part[2 * k & 3], &p1 = part[(2 * k + 1) & 3];
+        p0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k / kFold]), p0, 0, 0, 0);
+        p1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[(2 * k + 1) / kFold]), p1, 0, 0, 0);
       } else {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k]), part[k], 0, 0, 0);
+        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), part[k], 0, 0, 0);
       }
     }
     done = next;
@@ -178,7 +178,7 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
     if (ends) {   // every lane is complete and at most one whole group was left: the unit has been multiplied
       // the walker is one piece ahead: w_band is the band of the unit that follows, if there is one
       const uint32_t next_band = w_band == cur_band ? kNoBand : w_band;
-      on_unit(cur_band, next_band, (part[0] + part[1]) + (part[2] + part[3]));
+      on_unit(cur_band, next_band, fold_sums<kFold>(part));
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
       cur_band = next_band;
@@ -255,7 +255,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
         return b < n_bands ? band_lo + b : kNoBand;
       }
     };
-    const uint32_t xfrag = xtile + ((uint32_t)kg * n_win * kRows + (bn & (kRows - 1))) * 16;   // lanes past kRows repeat a row: their sums are not stored
+    // 16 columns of a B operand: 16 / kRows windows of kRows rows (fold_sums); the careful form takes one window, its lanes
+    // past kRows repeat a row (their sums are not stored)
+    const uint32_t xfrag = xtile + ((uint32_t)kg * n_win * kRows + bn) * 16, xfrag_careful = xtile + ((uint32_t)kg * n_win * kRows + (bn & (kRows - 1))) * 16;
     // Activation tile of a quad: piece ((panel * n_win + w) * kRows + batch row) holds 8 columns; rows past the batch are
     // zero.  The pieces of the next quad's tile are requested into registers before this quad is decoded and written
     // to LDS when everybody has finished it, so that nobody waits for device memory between two quads.
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
         }
         request_scales(next_band);
       };
-      if (m.reserved - 1 > band_lo * nq) decode_units_ring<true, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
+      if (m.reserved - 1 > band_lo * nq) decode_units_ring<true, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag_careful, finish_unit);
       else decode_units_ring<false, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
     }
     if constexpr (kGateUp) {

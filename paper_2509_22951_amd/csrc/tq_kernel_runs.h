@@ -15,8 +15,10 @@ namespace tq {
 // global memory work at any 2-byte address), and rows need not be whole units: in a unit that reaches past the row's end
 // (or whose segments are no multiple of a group of windows) a fragment is loaded where it still lies inside the row and
 // shifted into place, zeros behind it.
-// Measured, us, whole-strip kernel -> this one: 4099 x 2999 batch 5 41.1 -> 21.5, one LLaMA-3.2-3B layer batch 8 56 -> 44;
-// launches that fill k_matvec_ring stay there (eight such layers, batch 8: 235 us there, 267 here; the gated pairs of
+// Batches of up to 8 rows take two windows per load, up to 4 rows four (fold_sums): one LLaMA-3.2-3B layer batch 8 45.2 -> 42.0,
+// batch 4 43.2 -> 38.8, 8192 x 3072 packed batch 4 16.3 -> 14.8 us.
+// Measured, us, whole-strip kernel -> this one: 4099 x 2999 batch 5 41.1 -> 21.2, that layer batch 8 56 -> 42 (caches warm);
+// launches that fill k_matvec_ring stay there (eight such layers, batch 8: 235 us there, 267 here before two windows were taken per load; the gated pairs of
 // eight blocks, batch 16: 154 there, 241 here): 16-byte pieces of up to 16 rows of x from the caches cost more than the
 // tile in LDS (without those loads: 222 and 148).
 constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
@@ -36,14 +38,17 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
 
 // Decode and multiply the chunks [c0, c_end) of the units [u0, u1).  The first unit may begin and the last one end outside
 // the run (see kSplit in k_matvec_runs): started says that the lanes stand at column `start` of the first one, and what
-// a lane has not written itself counts as zeros.  x: the activations, row: the batch row of this lane's B operand (lane & 15, at
-// most the last one); part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
-template <bool kCareful, bool kPacked, typename OnUnit>
+// a lane has not written itself counts as zeros.  x: the activations, row_first: where the
+// batch row of this lane's B operand starts; part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
+// kFold: windows per B operand (fold_sums); the careful form takes them one by one.
+template <bool kCareful, bool kPacked, int kFoldMost, typename OnUnit>
 __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, uint32_t start,
-                                                global_cu16* x, uint32_t row, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
+                                                global_cu16* x, uint32_t row_first, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
   if (u0 >= u1 || c0 >= c_end) return;
   constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
   constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
+  constexpr uint32_t kFold = kCareful ? 1u : (uint32_t)kFoldMost, kLoads = kG * pk / kFold;
+  const uint32_t behind = (lane & 15) / (16 / kFold) * 8;   // the columns this lane's window lies behind the operand's first
   const uint32_t sw8 = (uint32_t)(lane & 15) << 3, kg = (uint32_t)lane >> 4;
   const uint32_t nq = m.n_quads, n_panels = (m.cols + m.seg_cols - 1) / m.seg_cols, x_cols = pk * m.cols;
   // walker over the pieces of the run
@@ -92,13 +97,12 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     done = 0;
     carry = 0;
   };
-  u32x4 x8[kG * pk];   // B operands of the next group
-  const uint32_t row_first = row * x_cols;
+  u32x4 x8[kLoads];   // B operands of the next group
   auto request_x = [&] {
-    const uint32_t at = x_first + pk * min(done, n_win8 - 8 * kG);
+    const uint32_t at = x_first + pk * min(done, n_win8 - 8 * kG) + behind;
 #pragma unroll
-    for (uint32_t k = 0; k < kG * pk; ++k) {
-      const uint32_t col = ragged ? min(at + 8 * k, x_cols - 8) : at + 8 * k;
+    for (uint32_t k = 0; k < kLoads; ++k) {
+      const uint32_t col = ragged ? min(at + 8 * kFold * k, x_cols - 8) : at + 8 * kFold * k;
       x8[k] = *(global_cu128_any*)(x + (row_first + col));
     }
   };
@@ -117,18 +121,19 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     if (!ready && __builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
     if (ragged) {
 #pragma unroll
-      for (uint32_t k = 0; k < kG * pk; ++k) {
-        const uint32_t in_panel = pk * at + 8 * k, col = x_first + in_panel;
+      for (uint32_t k = 0; k < kLoads; ++k) {
+        const uint32_t in_panel = pk * at + 8 * kFold * k + behind, col = x_first + in_panel;
         x8[k] = drop_elements(x8[k], in_panel >= pk * panel_len ? 8u : col + 8 > x_cols ? col + 8 - x_cols : 0u);
       }
     }
 #pragma unroll
     for (int k = 0; k < kG; ++k) {
       if constexpr (kPacked) {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k]), part[k], 0, 0, 0);
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[2 * k + 1]), part[k], 0, 0, 0);
+        f32x4 &p0 = part[2 * k & 3], &p1 = part[(2 * k + 1) & 3];
+        p0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k / kFold]), p0, 0, 0, 0);
+        p1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[(2 * k + 1) / kFold]), p1, 0, 0, 0);
       } else {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k]), part[k], 0, 0, 0);
+        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), part[k], 0, 0, 0);
       }
     }
     done = next;
@@ -209,9 +214,10 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
 // part of a unit passes while the dictionary is on its way.  A lone wavefront takes 8 us for a unit of 33 chunks, but the
 // windows around a cut are multiplied on both sides of it, each time with zeros for the other side's columns: shares that
 // leave less than half the wavefronts idle are faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 ->
-// 15.5, 700 x 1999 batch 5 20.2 -> 16.8; 6 units of packed weights for 8 wavefronts 18.0 -> 23.2.)
-constexpr uint32_t kRunSplitMin = 4;   // least chunks of a run
-template <int kWaves, bool kPacked>
+// 15.0, 700 x 1999 batch 5 20.2 -> 16.6; 6 units of packed weights for 8 wavefronts 18.0 -> 23.2.)
+constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a unit (4 / 6 / 8 / 11, us: 1024 x 1024 batch 3 14.8 / 14.5 /
+                                        // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
+template <int kWaves, bool kPacked, int kFold>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   constexpr int kRunThreads = kWaves * 64, kRegs = 8, kCount = 12;
   touch_arguments();
@@ -277,18 +283,19 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     auto on_unit = [&](uint32_t band, uint32_t quad) {
       if (quad + 1 != nq && band * nq + quad + 1 != run.u1) return;
-      sums.finish(a, job, m, band, quad + 1 == nq, (part[0] + part[1]) + (part[2] + part[3]), lane);
+      sums.finish(a, job, m, band, quad + 1 == nq, fold_sums<kFold>(part), lane);
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    const uint32_t row = min((uint32_t)(lane & 15), (uint32_t)a.batch - 1);   // lanes past the batch repeat its last row: their sums are never stored
     // units whose lanes drift far apart come first: see DevMat::reserved
     const uint32_t u_care = min(max(m.reserved - 1, run.u0), run.u1);
     const uint32_t c_care = u_care == run.u0 ? run.c0 : u_care == run.u1 ? run.c_end : unit_offset(m, u_care);
     global_cu16* x = (global_cu16*)job.x;
-    decode_run_ring<true, kPacked>(m, run.u0, u_care, run.c0, c_care, run.head, start, x, row, lane, ring, part, on_unit);
-    decode_run_ring<false, kPacked>(m, u_care, run.u1, c_care, run.c_end, run.head && u_care == run.u0, start, x, row, lane, ring, part, on_unit);
-    if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, (part[0] + part[1]) + (part[2] + part[3]), lane);
+    // lanes past the batch repeat its last row: their sums are never stored
+    const uint32_t row_first = min((uint32_t)(lane & 15) % (16 / kFold), (uint32_t)a.batch - 1) * (kPacked ? 2 : 1) * m.cols;
+    decode_run_ring<true, kPacked, kFold>(m, run.u0, u_care, run.c0, c_care, run.head, start, x, row_first, lane, ring, part, on_unit);
+    decode_run_ring<false, kPacked, kFold>(m, u_care, run.u1, c_care, run.c_end, run.head && u_care == run.u0, start, x, row_first, lane, ring, part, on_unit);
+    if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, fold_sums<kFold>(part), lane);
     __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
     sums.combine(a, job, m, rings, wave, kWaves, lane);
   }

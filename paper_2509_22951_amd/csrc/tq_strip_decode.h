@@ -324,6 +324,29 @@ struct BandSums {
   }
 };
 
+// Batches of at most 16 / kFold rows: a B operand has 16 columns, one per batch row, so one load of it can bring kFold
+// consecutive windows, window j in columns 16 / kFold * j on.  The MFMA step of a window takes the operand as it is: the
+// columns of its own window are right, the others are products with another window's activations and are dropped.  A
+// window's step adds to part[window % 4], so every accumulator has its right columns in one place; here they are moved to
+// the first columns and added.
+template <int kFold>
+__device__ __forceinline__ f32x4 fold_sums(const f32x4 (&part)[4]) {
+  f32x4 moved[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int from = k % kFold * (16 / kFold);   // (compile-time: the loop is unrolled) lane c of a row of 16 takes lane c + from
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int bits = __float_as_int(part[k][v]);
+      moved[k][v] = __int_as_float(from == 0   ? bits
+                                   : from == 4 ? __builtin_amdgcn_update_dpp(0, bits, 0x12C, 0xf, 0xf, true)
+                                   : from == 8 ? __builtin_amdgcn_update_dpp(0, bits, 0x128, 0xf, 0xf, true)
+                                               : __builtin_amdgcn_update_dpp(0, bits, 0x124, 0xf, 0xf, true));
+    }
+  }
+  return (moved[0] + moved[1]) + (moved[2] + moved[3]);
+}
+
 constexpr int kMfmaGroup = 8;   // MFMA steps per group: the activation fragments of the next group load while this one runs
 
 // The MFMA steps of one decoded unit: step w multiplies bytes [8 w, 8 w + 8) of every lane's strip (16 rows x 4 panels
