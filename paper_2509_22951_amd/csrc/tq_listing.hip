@@ -23,11 +23,13 @@
 
 #include "../../include/tq.h"
 #include "tq_format.h"
+#include "tq_plan.h"
 
 namespace tq {
 namespace {
 
 constexpr uint32_t kSeq = TQ_LISTING_SEQ;
+static_assert(kSeq == 4, "listing_output");
 constexpr uint32_t kMarker = 0xFFFFu;
 constexpr int kThreadWords = 8;     // words per thread: one 16-byte load
 constexpr int kListingThreads = 256;
@@ -109,8 +111,8 @@ __global__ __launch_bounds__(kListingThreads) void k_listing_decompress(const ui
     first += v < wave ? wave_tokens[v] : 0u;
     tokens += wave_tokens[v];
   }
-  const uint32_t skew = base & 3;   // the block's output starts this many dwords into a 16-byte piece
-  uint32_t* to = lds_out + skew + first;
+  const ListingOutput o = listing_output(base, tokens, n_values);
+  uint32_t* to = lds_out + o.lo / 4 + first;
   for (; starts; starts &= starts - 1) {
     const uint32_t j = (uint32_t)__builtin_ctz(starts);
     const uint32_t* at = lds_words + 4 + 4 * tid + (j >> 1);
@@ -122,9 +124,8 @@ __global__ __launch_bounds__(kListingThreads) void k_listing_decompress(const ui
     *to++ = v4;
   }
   __syncthreads();
-  const uint64_t first_byte = (uint64_t)base * kSeq, end_byte = min(first_byte + (uint64_t)tokens * kSeq, n_values);   // (the last token may have fewer values)
-  uint8_t* piece0 = out + (first_byte - skew * 4);   // where lds_out[0] belongs
-  const uint32_t lo = skew * 4, hi = lo + (uint32_t)(end_byte - first_byte);   // bytes of lds_out that are output
+  uint8_t* piece0 = out + o.piece0;
+  const uint32_t lo = o.lo, hi = o.hi;
   if (((uintptr_t)out & 15) == 0) {
     for (uint32_t p = (uint32_t)tid * 16; p < hi; p += kListingThreads * 16) {
       if (p >= lo && p + 16 <= hi) {

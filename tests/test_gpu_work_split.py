@@ -137,3 +137,27 @@ def test_gated_pairs_on_the_ring_kernel(rows, batch, opts):
     y = y.cpu().numpy().astype(np.float64)
     for got, want in zip(y, ref):      # silu adds the rounding of exp and a division in fp32, relative to each output
         assert np.isfinite(got).all() and np.abs(got - want).max() <= 2 * TOL * np.abs(want).max()
+
+
+@pytest.mark.parametrize("shift", [0, 4, 1])              # 16-, 4- and 1-byte stores
+@pytest.mark.parametrize("escapes", [0, 3])
+@pytest.mark.parametrize("marker,raw", [(2047, 1), (2047, 2), (2047, 3), (2046, 2), (2046, 3), (2045, 3), (2044, 3), (4095, 3)])
+def test_listing_streams_whose_last_block_starts_no_token(marker, raw, escapes, shift):
+    """Streams of 2048-word blocks that end in a marker at word `marker` with `raw` values, which lie in a block of their own
+    (one block earlier for (2044, 3): the block ends with them).  Bytes around the output stay as they are."""
+    table = np.full((1, 4), 7, np.uint8)
+    values = np.concatenate([np.arange(4 * escapes, dtype=np.uint8), np.full(4 * (marker - 5 * escapes), 7, np.uint8),
+                             np.arange(raw, dtype=np.uint8)])
+    words = tq.tq_listing_compress(values, table)
+    assert words[marker] == 0xFFFF and words.size == marker + 1 + raw
+    h = tq.Listing(words, table)
+    guard = 64
+    buf = torch.full((guard + shift + values.size + guard,), 99, dtype=torch.uint8, device="cuda")
+    try:
+        h.decompress(buf[guard + shift:].data_ptr(), _stream())
+        torch.cuda.synchronize()
+    finally:
+        h.close()
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[guard + shift:guard + shift + values.size], values)
+    assert (got[:guard + shift] == 99).all() and (got[guard + shift + values.size:] == 99).all()

@@ -1,0 +1,31 @@
+"""The index arithmetic that kernels and launch plans share (csrc/tq_plan.h), run over its range on the CPU by a small C++
+driver (plan_driver.cpp).  No GPU involved."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "driver")
+    build = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=undefined", "-fno-sanitize-recover=all", os.path.join(HERE, "plan_driver.cpp"),
+                            "-o", exe], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-3000:]
+
+    def run(what):
+        r = subprocess.run([exe, what], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, (r.stdout + r.stderr)[-2000:]
+        return r.stdout
+
+    return run
+
+
+def test_blocks_of_a_listing_stream_write_every_value_once_and_nothing_else(driver):
+    """Blocks that hold no token start (raw values of the block before's last marker) among them."""
+    assert "listing streams" in driver("listing")
