@@ -36,6 +36,7 @@
 #include "../../include/tq.h"
 #include "tq_format.h"
 #include "tq_kernels_common.h"
+#include "tq_plan.h"
 #include "tq_kernel_dot.h"
 #include "tq_strip_decode.h"
 #include "tq_kernel_ring.h"
@@ -489,47 +490,18 @@ int fire(const PreparedLaunch& p, hipStream_t stream) {
   return TQ_OK;
 }
 
-// Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
-// that the largest share (bands x columns) is as small as possible.  Returns that share, or 0 when there are more
-// matrices than workgroups or than kMaxAssign.
-constexpr int kMaxAssign = 32;
-uint64_t assign_workgroups(int n, const tq_handle* hs, uint64_t grid, uint32_t* wgs) {
-  if (n > kMaxAssign || (uint64_t)n > grid) return 0;
-  uint64_t total = 0, cols_max = 0;
-  for (int i = 0; i < n; ++i) {
-    if (hs[i]->m.n_bands >= 1u << 23) return 0;   // (share_of_bands multiplies band counts by workgroup counts)
-    total += (uint64_t)hs[i]->m.n_bands * hs[i]->m.cols;
-    cols_max = std::max<uint64_t>(cols_max, hs[i]->m.cols);
-  }
-  auto needed = [&](uint64_t share) {   // workgroups when none takes more than `share`
-    uint64_t sum = 0;
-    for (int i = 0; i < n; ++i) {
-      const uint64_t per = share / hs[i]->m.cols;   // >= 1
-      sum += (hs[i]->m.n_bands + per - 1) / per;
-    }
-    return sum;
-  };
-  uint64_t lo = std::max(cols_max, (total + grid - 1) / grid), hi = lo;
-  while (needed(hi) > grid) hi *= 2;
-  if (hi > lo) {   // needed(lo) > grid >= needed(hi)
-    for (lo = hi / 2; hi - lo > cols_max / 8;) {
-      const uint64_t mid = lo + (hi - lo) / 2;
-      (mid >= cols_max && needed(mid) <= grid ? hi : lo) = mid;
-    }
-  }
-  uint64_t worst = 0;
-  for (int i = 0; i < n; ++i) {
-    const uint64_t bands = hs[i]->m.n_bands, per = hi / hs[i]->m.cols;
-    wgs[i] = (uint32_t)((bands + per - 1) / per);
-    worst = std::max(worst, (bands + wgs[i] - 1) / wgs[i] * hs[i]->m.cols);
-  }
-  return worst;
-}
 // What the busiest workgroup does when the line is cut into `grid` equal parts instead: its part to within half a band,
 // and, with several matrices, a second start (offsets, activations, barriers) in workgroups that get the end of one
 // matrix and the start of the next, worth about kRestartCost of the line (4 us, in which a compute unit streams 100 KB of
 // codes: one LLaMA-3.2-1B layer, 7 matrices, 24.9 us when 6 of the 256 workgroups start twice, 18.4 us in whole workgroups).
 constexpr uint64_t kRestartCost = 6000;
+constexpr int kMaxAssign = 32;
+uint64_t assign_workgroups(int n, const tq_handle* hs, uint64_t grid, uint32_t* wgs) {   // 0: not so (see tq_plan.h)
+  BandCount m[kMaxAssign];
+  if (n > kMaxAssign) return 0;
+  for (int i = 0; i < n; ++i) m[i] = {hs[i]->m.n_bands, hs[i]->m.cols};
+  return assign_workgroups(n, m, grid, wgs);
+}
 uint64_t even_cut_cost(int n, const tq_handle* hs, uint64_t grid) {
   uint64_t total = 0, cols_max = 0;
   for (int i = 0; i < n; ++i) {

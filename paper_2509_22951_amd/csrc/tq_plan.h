@@ -1,6 +1,7 @@
 // Index arithmetic that the kernels and their launches rest on and that needs no GPU: host and device code share it, and
 // the host tests run it over its whole range.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 
 #if defined(__HIPCC__)
@@ -24,6 +25,46 @@ TQ_HD ListingOutput listing_output(uint32_t base, uint32_t tokens, uint64_t n_va
   const uint32_t lo = (base & 3u) * 4u;
   const uint64_t first = (uint64_t)base * 4u, end = first + (uint64_t)tokens * 4u, stop = end < n_values ? end : n_values;
   return {first - lo, lo, lo + (uint32_t)(stop > first ? stop - first : 0u)};
+}
+
+// Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
+// that the largest share (bands x columns) is as small as possible, to within an eighth of the widest row.  Returns that
+// share, or 0 when there are more matrices than workgroups (or a matrix is too tall for the kernels' cut).
+struct BandCount {
+  uint32_t n_bands, cols;   // of a matrix, both at least 1
+};
+inline uint64_t assign_workgroups(int n, const BandCount* m, uint64_t grid, uint32_t* wgs) {
+  if ((uint64_t)n > grid) return 0;
+  uint64_t total = 0, cols_max = 0;
+  for (int i = 0; i < n; ++i) {
+    if (m[i].n_bands >= 1u << 23) return 0;   // (share_of_bands multiplies band counts by workgroup counts)
+    total += (uint64_t)m[i].n_bands * m[i].cols;
+    cols_max = std::max<uint64_t>(cols_max, m[i].cols);
+  }
+  auto needed = [&](uint64_t share) {   // workgroups when none takes more than `share`
+    uint64_t sum = 0;
+    for (int i = 0; i < n; ++i) {
+      const uint64_t per = share / m[i].cols;   // >= 1
+      sum += (m[i].n_bands + per - 1) / per;
+    }
+    return sum;
+  };
+  uint64_t lo = std::max(cols_max, (total + grid - 1) / grid), hi = lo;
+  while (needed(hi) > grid) hi *= 2;
+  if (hi > lo) {   // needed(lo) > grid >= needed(hi), and so it stays; hi - lo >= 2 inside the loop, so that it shrinks every time
+    const uint64_t close = std::max<uint64_t>(1, cols_max / 8);   // (an eighth of a row below 8 columns is nothing)
+    for (lo = hi / 2; hi - lo > close;) {
+      const uint64_t mid = lo + (hi - lo) / 2;
+      (mid >= cols_max && needed(mid) <= grid ? hi : lo) = mid;
+    }
+  }
+  uint64_t worst = 0;
+  for (int i = 0; i < n; ++i) {
+    const uint64_t bands = m[i].n_bands, per = hi / m[i].cols;
+    wgs[i] = (uint32_t)((bands + per - 1) / per);
+    worst = std::max(worst, (bands + wgs[i] - 1) / wgs[i] * m[i].cols);
+  }
+  return worst;
 }
 
 }  // namespace tq

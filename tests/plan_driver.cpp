@@ -54,9 +54,45 @@ static void listing() {
   std::printf("%d listing streams\n", n);
 }
 
+// One to three matrices of any number of bands and narrow and ordinary widths on grids of several sizes: the search ends, every
+// matrix gets workgroups, no more than there are, and the largest share is near the least possible one.
+static void assign() {
+  int n = 0;
+  auto one = [&](const std::vector<tq::BandCount>& m, uint64_t grid) {
+    uint32_t wgs[4] = {};
+    const uint64_t worst = tq::assign_workgroups((int)m.size(), m.data(), grid, wgs);
+    uint64_t sum = 0, share = 0, total = 0, cols_max = 0;
+    for (size_t i = 0; i < m.size(); ++i) {
+      CHECK(wgs[i] >= 1 && wgs[i] <= m[i].n_bands, "matrix %zu: %u workgroups", i, wgs[i]);
+      sum += wgs[i];
+      share = std::max<uint64_t>(share, (uint64_t)((m[i].n_bands + wgs[i] - 1) / wgs[i]) * m[i].cols);
+      total += (uint64_t)m[i].n_bands * m[i].cols;
+      cols_max = std::max<uint64_t>(cols_max, m[i].cols);
+    }
+    CHECK(sum <= grid && worst == share, "%zu matrices, first %u x %u, grid %lu: %lu workgroups, share %lu", m.size(), m[0].n_bands, m[0].cols, grid, sum, worst);
+    // a share of twice the mean part and a band always suffices (a matrix then needs less than half its mean's
+    // workgroups, rounded up) while the matrices are few against the grid; the search ends an eighth of a row above the least
+    CHECK(worst <= 2 * ((total + grid - 1) / grid) + 2 * cols_max, "share %lu of %lu on %lu", worst, total, grid);
+    ++n;
+  };
+  for (uint64_t grid : {16, 255, 256, 304})
+    for (uint32_t cols = 1; cols <= 20; ++cols)
+      for (uint32_t bands = 1; bands < 3000; bands += bands < 600 ? 1 : 7) {
+        one({{bands, cols}}, grid);
+        if (bands % 5 == 0) one({{bands, cols}, {bands / 3 + 1, 1 + (cols * 3) % 7}, {3 * bands, 1 + cols % 7}}, grid);
+      }
+  for (uint32_t bands : {1u, 255u, 257u, 1000u, 8016u, (1u << 23) - 1})
+    for (uint32_t cols : {1u, 7u, 8u, 9u, 63u, 3072u, 8191u, 1u << 20}) one({{bands, cols}}, 256);
+  uint32_t wgs[4];
+  const tq::BandCount tall = {1u << 23, 4}, three[3] = {{5, 4}, {5, 4}, {5, 4}};
+  CHECK(tq::assign_workgroups(1, &tall, 256, wgs) == 0 && tq::assign_workgroups(3, three, 2, wgs) == 0, "refused cuts");
+  std::printf("%d cuts\n", n);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
+  else if (!std::strcmp(what, "assign")) assign();
   else return 2;
   return 0;
 }

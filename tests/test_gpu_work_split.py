@@ -88,6 +88,31 @@ def test_matrices_of_a_call_get_whole_workgroups(n):
             j.m.close()
 
 
+# More bands than compute units, fewer than 8 stored columns: whole workgroups per matrix at the narrow end.
+NARROW = [(6, {}), (3, {}), (1, {}), (10, {"bits": 4, "pack": True}), (14, {"bits": 4, "pack": True})]
+
+
+@pytest.mark.parametrize("cols,opts", NARROW)
+@pytest.mark.parametrize("rows", [4800, 4099 * 3])
+def test_narrow_matrices_with_more_bands_than_workgroups(rows, cols, opts):
+    for batch in (1, 2, 3):       # the dot-product kernel, the runs kernel (or, narrower than a fragment, the whole-strip kernel)
+        job = _Job(rows, cols, batch, seed=rows + cols, seg_cols=16, **opts)
+        try:
+            job.m.matvec(job.x.data_ptr(), job.y.data_ptr(), batch, _stream())
+            torch.cuda.synchronize()
+            job.check()
+            if batch == 1:
+                job.y.fill_(float("nan"))
+                step = tq.Step([job.m.handle], [job.x.data_ptr()], [job.y.data_ptr()], 1, stages=[0])
+                assert step.info["persistent"] == 1
+                step.launch(_stream())
+                torch.cuda.synchronize()
+                step.close()
+                job.check()
+        finally:
+            job.m.close()
+
+
 RUNS = [
     # rows, cols, seg_cols: batches above 2 below the sizes the ring kernel with an activation tile takes
     (16, 6, 16),           # narrower than an activation fragment: the whole-strip kernel

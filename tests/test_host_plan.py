@@ -29,3 +29,8 @@ def driver(tmp_path_factory):
 def test_blocks_of_a_listing_stream_write_every_value_once_and_nothing_else(driver):
     """Blocks that hold no token start (raw values of the block before's last marker) among them."""
     assert "listing streams" in driver("listing")
+
+
+def test_whole_workgroups_per_matrix_for_every_width(driver):
+    """The search for the smallest largest share ends below 8 columns too (an eighth of such a row is no step at all)."""
+    assert "cuts" in driver("assign")
