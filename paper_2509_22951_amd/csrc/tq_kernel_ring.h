@@ -1,6 +1,7 @@
 // Device side of libtq: the batched product with a ring per lane (decode and MFMA interleaved).
 #pragma once
 #include "tq_kernels_common.h"
+#include "tq_plan.h"
 #include "tq_strip_decode.h"
 
 namespace tq {
@@ -13,11 +14,11 @@ namespace tq {
 // unfinished lane has passed the next kRingGroup windows (one compare and a look at the condition mask) and, if so,
 // multiplies them; a lane advances by at most 8 columns per chunk, so one group per look keeps up.  Bytes of the ring
 // are reused kRingBytes columns later: a lane writes 8-byte piece q only when q + 8 - kRingBytes <= done, which holds
-// whenever no two unfinished lanes are ever more than kRingSpread columns apart; the host checks that for every unit
-// when the container is loaded.  A matrix that does not keep it is decoded in a careful mode - a look after every chunk
-// and one MFMA step at a time, which absorbs a distance of kRingSpreadCareful columns (the first units of a matrix that
-// starts a dictionary, where early segments are still all single bytes, need that) - or, beyond that, goes to the
-// whole-strip kernel.
+// whenever no two unfinished lanes are ever more than kRingSpread columns apart (derived in tq_plan.h); the host checks that
+// for every unit when the container is loaded.  Units that do not keep it are decoded in a careful mode - a look after every
+// chunk and one MFMA step at a time, which absorbs a distance of kRingSpreadCareful columns (the first units of a matrix
+// that starts a dictionary, where early segments are still all single bytes, need that); a matrix with a unit beyond that
+// goes to the whole-strip kernel.
 // Piece p (8 bytes) of lane l lives at p ^ (l & 15) within the lane's ring: when the 64 lanes read the same window, the
 // 16 lanes served together hit different banks.
 //
@@ -31,21 +32,13 @@ namespace tq {
 // one workgroup barrier apart from each other, so the result does not depend on timing.
 // Needs rows of a whole number of units (a multiple of 4 * seg_cols columns), segments of 32..256 columns in
 // multiples of 32 (packed 4-bit weights: 32..128 bytes), and 16-byte aligned activations.
-constexpr int kRingBytes = 128;
 constexpr int kRingWaves = 8;       // with an activation tile of 16 batch rows
 constexpr int kRingWavesHalf = 10;  // with one of 8 batch rows (batches up to 8): more wavefronts fit next to the smaller tile
 constexpr int kRingWavesMore = 12;  // the same beside a dictionary of at most 24,512 entries
 constexpr int kRingWavesQuarter = 11;   // with a tile of 4 batch rows (batches up to 4) beside a full dictionary
-constexpr int kRingPiece = 12;    // chunks per piece of the code stream (two register sets)
-constexpr int kRingStep = 4;      // chunks between two looks at the lanes' progress
-constexpr int kRingGroup = 4;     // MFMA steps per group
-constexpr uint32_t kRingSpread = kRingBytes - 8 * kRingStep - 8 * kRingGroup + 1;
-static_assert(kRingSpread == kWideSpread, "what the validator counts as a wide unit");
-constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;   // looking after every chunk, one MFMA step at a time
 constexpr uint32_t kRingMaxSeg = 256;
 constexpr int kRingMinBandsPerCu = 24;   // below that many bands per CU in a launch (half as many above 8 batch rows) k_matvec_runs is faster
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
-static_assert(kRingPiece % kRingStep == 0 && kRingGroup == 4 && kRingStep <= kRingGroup, "ring schedule");
 
 // append_chunk for the ring: the complete 8-byte piece goes to its swizzled place; sw8 = 8 * (lane & 15).
 // pos never passes seg_len (pad codes fall off the end), and a piece is complete when pos crosses a multiple of 8.

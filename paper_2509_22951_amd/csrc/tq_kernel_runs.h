@@ -112,7 +112,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     const uint32_t at = min(done, n_win8 - 8 * kG);   // at the unit's end: any place inside the ring
     const uint32_t base = at ^ sw8;
     // a segment that ends inside a piece: what its last chunk left over is not in the ring yet
-    if (ragged) *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & 0x78u)) = carry;
+    if (ragged && ring_leftover(pos)) *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & 0x78u)) = carry;
     u32x2 a8[kG];
 #pragma unroll
     for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));

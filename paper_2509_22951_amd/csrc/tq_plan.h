@@ -4,6 +4,8 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "tq_format.h"
+
 #if defined(__HIPCC__)
 #define TQ_HD __host__ __device__ __forceinline__
 #else
@@ -26,6 +28,33 @@ TQ_HD ListingOutput listing_output(uint32_t base, uint32_t tokens, uint64_t n_va
   const uint64_t first = (uint64_t)base * 4u, end = first + (uint64_t)tokens * 4u, stop = end < n_values ? end : n_values;
   return {first - lo, lo, lo + (uint32_t)(stop > first ? stop - first : 0u)};
 }
+
+// The schedule of the ring kernels.  A lane keeps kRingBytes of its segment; every kRingStep chunks the wavefront looks whether
+// all unfinished lanes have passed the next kRingGroup windows of 8 columns, and multiplies them if so (the careful
+// form looks after every chunk and takes one window).
+constexpr int kRingBytes = 128;
+constexpr int kRingPiece = 12;    // chunks per piece of the code stream (two register sets)
+constexpr int kRingStep = 4;      // chunks between two looks at the lanes' progress
+constexpr int kRingGroup = 4;     // MFMA steps per group
+static_assert(kRingPiece % kRingStep == 0 && kRingGroup == 4 && kRingStep <= kRingGroup, "ring schedule");
+// How far apart two unfinished lanes may be.  With `done` columns multiplied, a lane at column p may store into the 8-byte
+// piece of p only if that piece's place holds columns below done: p - p % 8 <= done + kRingBytes - 8.
+//  - After a look the slowest unfinished lane is less than a group past done: between two looks it gains at most a group
+//    (8 columns a chunk), and a look takes a group that is ready.
+//  - A lane stores where it stands before a chunk.  Before the last of the chunks between two looks it has gained 8 columns
+//    in each of the others and stands at most at done + (8 group - 1) + spread + 8 (step - 1): the limits below make
+//    that done + kRingBytes - 8.
+//  - A lane that completes its segment stays at its end and goes on storing there (pad codes).  It was at most `spread` ahead
+//    with the chunk before, the slowest lane gains at least 4 columns in a chunk: from the next look on it is at most
+//    (8 group - 1) + spread + 4 past done, which is no further piece, and until then the bound above holds.
+//  - At a look, after the last chunk, a lane can stand at done + kRingBytes: at a piece's start, and that piece's place
+//    still holds columns the look is about to multiply.  Nothing of the lane lies in that piece yet: see ring_leftover.
+constexpr uint32_t kRingSpread = kRingBytes - 8 * kRingStep - 8 * kRingGroup + 1;
+constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;
+static_assert(kRingSpread == kWideSpread, "what the validator counts as a wide unit");
+// Whether a lane that stands at column pos holds bytes of a piece it has not stored (see append_chunk_ring): a unit whose
+// segments end inside pieces stores those at every look - those only, never the piece that begins at pos.
+TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }
 
 // Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
 // that the largest share (bands x columns) is as small as possible, to within an eighth of the widest row.  Returns that

@@ -1,5 +1,6 @@
 // Host-only exercise of the index arithmetic in csrc/tq_plan.h over its range.  Prints what was checked; the first
 // violation ends the program with status 1.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -89,10 +90,207 @@ static void assign() {
   std::printf("%d cuts\n", n);
 }
 
+// The ring kernels' decode of one unit by its schedule, column numbers in place of bytes: a piece of a lane's ring holds the
+// columns it was stored with, and every group a look multiplies has to hold the lane's own columns of the run in their places
+// and zeros (number 0) elsewhere.
+struct LaneStream {
+  uint32_t panel_len;              // columns of its segment
+  std::vector<uint32_t> advance;   // columns per chunk: 4..8 until it is complete (the last one whatever is left), then pads
+};
+struct Unit {
+  std::vector<LaneStream> lanes;
+  uint32_t n_chunks, n_win8;   // windows are taken up to n_win8, in whole groups
+  bool ragged, careful;
+};
+
+// Largest distance between two lanes that are both unfinished after the same number of chunks, as the validator takes it.
+static uint32_t spread_of(const std::vector<LaneStream>& lanes, uint32_t n_chunks) {
+  std::vector<uint32_t> lo(n_chunks, ~0u), hi(n_chunks, 0);
+  for (const LaneStream& l : lanes)
+    for (uint32_t k = 0, pos = 0; k < l.advance.size(); ++k) {
+      pos += l.advance[k];
+      if (pos < l.panel_len) {
+        lo[k] = std::min(lo[k], pos);
+        hi[k] = std::max(hi[k], pos);
+      }
+    }
+  uint32_t wide = 0;
+  for (uint32_t k = 0; k < n_chunks; ++k)
+    if (hi[k] > lo[k]) wide = std::max(wide, hi[k] - lo[k]);
+  return wide;
+}
+
+// Chunks [c0, c_end) of the unit.  taken[lane][column] counts how often a column was multiplied; returns the places that held
+// something else than they should.  always_store: the leftover goes to the ring whether there is one or not.
+static int decode(const Unit& u, uint32_t c0, uint32_t c_end, bool always_store, std::vector<std::vector<int>>& taken) {
+  const uint32_t kG = u.careful ? 1 : tq::kRingGroup, kLook = u.careful ? 1 : tq::kRingStep;
+  struct Lane {
+    uint32_t pos = 0, first = 0;                 // first: the column the run starts at
+    uint32_t ring[tq::kRingBytes] = {}, carry[8] = {};
+  };
+  std::vector<Lane> lanes(u.lanes.size());
+  uint32_t done = 0;
+  int wrong = 0;
+  auto store = [&](Lane& l, uint32_t col, const uint32_t* v) { std::memcpy(l.ring + (col & 0x78u), v, 32); };
+  const uint32_t zeros[8] = {};
+  auto append = [&](size_t i, uint32_t chunk) {
+    Lane& l = lanes[i];
+    const LaneStream& s = u.lanes[i];
+    uint32_t both[16] = {};
+    std::memcpy(both, l.carry, 32);
+    const uint32_t n = chunk < s.advance.size() ? s.advance[chunk] : 0;   // (pads are zeros behind the end)
+    for (uint32_t k = 0; k < n; ++k) both[(l.pos & 7) + k] = l.pos + k + 1;
+    const uint32_t after = std::min(l.pos + (n ? n : 8), s.panel_len);
+    store(l, l.pos, both);
+    std::memcpy(l.carry, (after ^ l.pos) >= 8 ? both + 8 : both, 32);
+    l.pos = after;
+  };
+  auto multiply_ready = [&](bool ready) {
+    if (u.ragged)
+      for (Lane& l : lanes)
+        if (always_store || tq::ring_leftover(l.pos)) store(l, l.pos, l.carry);
+    if (done + 8 * kG > u.n_win8) return;
+    for (size_t i = 0; i < lanes.size() && !ready; ++i)
+      if (lanes[i].pos < std::min(u.lanes[i].panel_len, done + 8 * kG)) return;
+    for (size_t i = 0; i < lanes.size(); ++i)
+      for (uint32_t col = done; col < std::min(done + 8 * kG, u.lanes[i].panel_len); ++col) {   // (activations are zero behind the panel)
+        const uint32_t got = lanes[i].ring[col % tq::kRingBytes], want = col >= lanes[i].first && col < lanes[i].pos ? col + 1 : 0;
+        wrong += got != want;
+        taken[i][col] += want != 0;
+      }
+    done += 8 * kG;
+  };
+  if (c0) {   // the run starts inside the unit
+    for (size_t i = 0; i < lanes.size(); ++i) {
+      for (uint32_t k = 0; k < c0; ++k) lanes[i].pos += k < u.lanes[i].advance.size() ? u.lanes[i].advance[k] : 0;
+      lanes[i].first = lanes[i].pos;
+    }
+    auto passed = [&] {
+      for (size_t i = 0; i < lanes.size(); ++i)
+        if (lanes[i].pos < std::min(u.lanes[i].panel_len, done + 8 * kG)) return false;
+      return true;
+    };
+    while (done + 8 * kG < u.n_win8 && passed()) done += 8 * kG;
+    for (Lane& l : lanes)
+      for (uint32_t col = done; col < (l.pos & ~7u); col += 8) store(l, col, zeros);
+  }
+  const uint32_t len = c_end - c0, pieces = (len + tq::kRingPiece - 1) / tq::kRingPiece;
+  uint32_t at = c0;
+  for (uint32_t p = 0; p < pieces; ++p) {
+    const uint32_t n = len / pieces + (p < len % pieces ? 1 : 0);
+    for (uint32_t k = 0; k < n; ++k) {
+      for (size_t i = 0; i < lanes.size(); ++i) append(i, at + k);
+      if (k % kLook == kLook - 1 && (n >= (uint32_t)tq::kRingPiece - 1 ? k + 1 < (uint32_t)tq::kRingPiece : k + 1 < n)) multiply_ready(false);
+    }
+    multiply_ready(false);
+    at += n;
+  }
+  if (c_end == u.n_chunks) {
+    for (uint32_t before = ~0u; done < u.n_win8 && done != before;) {
+      before = done;
+      multiply_ready(false);
+    }
+    CHECK(done == u.n_win8, "unit left at column %u of %u", done, u.n_win8);
+  } else {   // the unit goes on elsewhere: what the lanes have, zeros behind it
+    for (Lane& l : lanes) store(l, l.pos, l.carry);
+    for (;;) {
+      bool left = false;
+      for (const Lane& l : lanes) left = left || l.pos > done;
+      if (!left) break;
+      for (Lane& l : lanes)
+        for (uint32_t k = 0; k < kG; ++k)
+          if (done + 8 * k > l.pos) store(l, done + 8 * k, zeros);
+      multiply_ready(true);
+    }
+  }
+  return wrong;
+}
+
+// Streams whose lanes come to exactly the distance a form of the decode takes and stay there for a while: a fast lane, a slow
+// one, others in between; whole panels, and a shorter one in every ragged unit; units as a whole and cut into runs.
+static void ring() {
+  uint64_t state = 88172645463325252ull;
+  auto random = [&](uint32_t n) {
+    state ^= state << 13, state ^= state >> 7, state ^= state << 17;
+    return (uint32_t)(state % n);
+  };
+  int at_limit[2] = {0, 0}, units = 0, planted[2] = {0, 0};
+  for (int trial = 0; trial < 20000; ++trial) {
+    const bool careful = trial & 1, ragged = trial % 8 != 0;
+    const uint32_t limit = careful ? tq::kRingSpreadCareful : tq::kRingSpread;
+    const uint32_t seg = ragged ? 16 * (16 + random(49)) : 32 * (8 + random(25));   // 256..1024
+    const uint32_t shorter = ragged ? 1 + random(seg) : seg, hold = random(40), wobble = random(3);
+    Unit u;
+    u.careful = careful;
+    u.ragged = ragged;
+    u.lanes.assign(6, LaneStream{seg, {}});
+    if (ragged) u.lanes[4].panel_len = u.lanes[5].panel_len = shorter;
+    std::vector<uint32_t> pos(6, 0);
+    uint32_t held = 0, gap = 0, burst = 0;
+    for (bool busy = true; busy;) {
+      uint32_t step[6];
+      if (gap < limit) {
+        step[1] = 4 + (random(4) < wobble);
+        step[0] = std::min(8u, step[1] + (limit - gap));
+        gap += step[0] - step[1];
+      } else if (held++ < hold || pos[0] < seg) {
+        if (burst) --burst;
+        else if (random(4) == 0) burst = 6;   // pairs alone for a while: the most a lane gains between two looks
+        step[0] = step[1] = burst ? 8 : 4 + random(5);
+      }
+      if (gap >= limit && held >= hold) step[0] = 4 + random(5), step[1] = 4 + random(5);
+      for (int i : {2, 3, 4, 5}) {   // between the two (equal steps keep them there)
+        const uint32_t low = pos[1] + step[1], high = std::min(pos[0], pos[1] + gap) + step[0];
+        const uint32_t least = std::max(low, pos[i] + 4), most = std::min(high, pos[i] + 8);
+        step[i] = least <= most ? least - pos[i] + random(most - least + 1) : least > pos[i] + 8 ? 8 : 4;
+      }
+      busy = false;
+      for (int i = 0; i < 6; ++i) {
+        const uint32_t len = u.lanes[i].panel_len;
+        if (pos[i] >= len) continue;
+        const uint32_t n = std::min(step[i], len - pos[i]);
+        u.lanes[i].advance.push_back(n);
+        pos[i] += n;
+        busy = true;
+      }
+    }
+    u.n_chunks = 0;
+    for (const LaneStream& l : u.lanes) u.n_chunks = std::max<uint32_t>(u.n_chunks, l.advance.size());
+    const uint32_t group = 8 * (careful ? 1 : tq::kRingGroup), spread = spread_of(u.lanes, u.n_chunks);
+    u.n_win8 = (seg + group - 1) / group * group;
+    if (spread > limit) continue;
+    at_limit[careful] += spread == limit && ragged;
+    ++units;
+    for (int cuts = 0; cuts < 3; ++cuts) {
+      std::vector<uint32_t> cut = {0, u.n_chunks};
+      for (int c = 0; c < cuts; ++c) cut.push_back(1 + random(u.n_chunks - 1));
+      std::sort(cut.begin(), cut.end());
+      std::vector<std::vector<int>> taken;
+      for (const LaneStream& l : u.lanes) taken.emplace_back(l.panel_len, 0);
+      for (size_t c = 0; c + 1 < cut.size(); ++c)
+        if (cut[c] < cut[c + 1]) {
+          const int wrong = decode(u, cut[c], cut[c + 1], false, taken);
+          CHECK(wrong == 0, "trial %d, spread %u (%s), segments of %u and %u, chunks %u..%u of %u: %d columns wrong", trial, spread,
+                careful ? "careful" : "fast", seg, shorter, cut[c], cut[c + 1], u.n_chunks, wrong);
+        }
+      for (size_t i = 0; i < taken.size(); ++i)
+        for (size_t col = 0; col < taken[i].size(); ++col) CHECK(taken[i][col] == 1, "trial %d, lane %zu, column %zu taken %d times", trial, i, col, taken[i][col]);
+    }
+    std::vector<std::vector<int>> taken;
+    for (const LaneStream& l : u.lanes) taken.emplace_back(l.panel_len, 0);
+    planted[careful] += decode(u, 0, u.n_chunks, true, taken) != 0;
+  }
+  CHECK(at_limit[0] > 500 && at_limit[1] > 500, "%d, %d ragged units at the limits", at_limit[0], at_limit[1]);
+  // the streams reach the edge: a store of the empty leftover is found in both forms
+  CHECK(planted[0] > 0 && planted[1] > 0, "%d, %d units with the planted mistake wrong", planted[0], planted[1]);
+  std::printf("%d units decoded, %d and %d ragged ones at the limits, %d and %d wrong with the mistake\n", units, at_limit[0], at_limit[1], planted[0], planted[1]);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
   else if (!std::strcmp(what, "assign")) assign();
+  else if (!std::strcmp(what, "ring")) ring();
   else return 2;
   return 0;
 }

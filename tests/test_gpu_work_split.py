@@ -139,6 +139,73 @@ def test_runs_of_units_in_batches(rows, cols, seg_cols, batch, shift, opts):
         job.m.close()
 
 
+def _bytes_at_the_limit(seed, cols, seg_cols, limit):
+    """One band of bytes whose last unit's lanes drift exactly `limit` columns apart when it is coded with the pairs (p, p + 32),
+    p = 64..95, and single bytes: its first row takes pairs and the others single bytes until they are that far apart, then
+    all take the same number of columns per chunk of 4 codes, in bursts of pairs among others.  The units before hold single
+    bytes alone.  -> bytes [16, cols]"""
+    rng = np.random.default_rng(seed)
+    Q = rng.integers(1, 64, (16, cols), dtype=np.uint8)
+    steps, slow, gap, burst = [], 0, 0, 0       # columns per chunk of the first row and the others, the same in all panels
+    while slow < seg_cols:
+        a = b = 4
+        if gap < limit:
+            a = min(8, b + limit - gap)
+            gap += a - b
+        else:
+            burst = burst - 1 if burst else (6 if rng.integers(4) == 0 else 0)
+            a = b = 8 if burst else int(rng.integers(4, 9))
+        steps.append((a, b))
+        slow += b
+    unit = (cols - 1) // (4 * seg_cols) * (4 * seg_cols)
+    for first in range(unit, cols, seg_cols):
+        end = min(cols, first + seg_cols)
+        for r in range(16):
+            at = first
+            for step in steps:                  # a chunk: pairs for the columns beyond 4, then single bytes
+                n = min(step[min(r, 1)], end - at)
+                for k in range(max(0, n - 4)):
+                    Q[r, at + 2 * k] = rng.integers(64, 96)
+                    Q[r, at + 2 * k + 1] = Q[r, at + 2 * k] + 32
+                at += n
+    return Q
+
+
+@pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("limit", [65, 113])              # the fast and the careful form of the ring decode
+@pytest.mark.parametrize("cols,seg_cols,seed", [
+    # seven units for one workgroup, taken whole: the last one ends inside a piece of the ring.  (With this seed the first row
+    # stands 128 columns past what has been multiplied at 1 look per panel of the fast form, 21 of the careful one.)
+    (7 * 4 * 1008 - 12, 1008, 2),
+    (500, 512, 2),                 # one unit, cut between the wavefronts
+])
+def test_lanes_as_far_apart_as_the_ring_takes(cols, seg_cols, seed, limit, opts):
+    Qb = _bytes_at_the_limit(seed, cols, seg_cols, limit)
+    pairs = np.array([[p, p + 32] for p in range(64, 96)], np.uint8).view(np.int8)
+    ones = np.ones(32, np.float32)
+    d = tq.tq_encode_quantized(pairs, ones, max_entries=288, dictionary="frequency")
+    Q = Qb.view(np.int8)
+    if opts:   # byte j of a row holds columns 2j and 2j + 1 as 4-bit values
+        Q = np.stack([((Qb & 15) ^ 8).astype(np.int8) - 8, ((Qb >> 4) ^ 8).astype(np.int8) - 8], axis=2).reshape(Qb.shape[0], -1)
+    scales = np.linspace(0.5, 1.5, Q.shape[0]).astype(np.float32)
+    blob = tq.tq_encode_quantized(Q, scales, max_entries=288, seg_cols=seg_cols, dict_from=d, dictionary="frequency", **opts)
+    assert tq.tq_validate_blob(blob)["lane_spread"] == limit
+    m = tq.Matrix(blob)
+    try:
+        for batch in (3, 8, 16):
+            bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
+            ref = O.gemv_f64(Q, scales, x)
+            xd = torch.from_numpy(bits.view(np.int16).copy()).cuda()
+            y = torch.full((batch, Q.shape[0]), float("nan"), dtype=torch.float32, device="cuda")
+            for _ in range(2):
+                m.matvec(xd.data_ptr(), y.data_ptr(), batch, _stream())
+            torch.cuda.synchronize()
+            for got, want in zip(y.cpu().numpy().astype(np.float64), ref):
+                assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL * np.abs(want).max()
+    finally:
+        m.close()
+
+
 @pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
 @pytest.mark.parametrize("batch", [3, 16])
 @pytest.mark.parametrize("rows", [72, 33 * 256 * 8])      # gate rows: one band per workgroup; a pass of 32 bands and one more

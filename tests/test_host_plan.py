@@ -34,3 +34,10 @@ def test_blocks_of_a_listing_stream_write_every_value_once_and_nothing_else(driv
 def test_whole_workgroups_per_matrix_for_every_width(driver):
     """The search for the smallest largest share ends below 8 columns too (an eighth of such a row is no step at all)."""
     assert "cuts" in driver("assign")
+
+
+def test_ring_decode_at_the_distances_it_takes(driver):
+    """Lanes exactly as far apart as the fast and the careful form allow, also in segments that end inside a piece."""
+    out = driver("ring")
+    print(out)
+    assert "units decoded" in out
