@@ -278,7 +278,8 @@ __device__ __forceinline__ void fetch_job(const MatvecArgs& a, int i, Job& job, 
 // workgroup barrier.  A workgroup that has no share of a stage goes on to the next arrive without waiting: it reads
 // and writes nothing there, and whatever it does later comes after a wait on a later stage.
 // The words are zero when a launch starts: stage_end, the last thing a workgroup does, counts the workgroups out, and the
-// last one clears them (nobody else looks at them any more) for the launch that follows on the stream.
+// last one clears them (nobody else looks at them any more) for the launch that follows on the stream.  The fault word is
+// among them: the report to the host stays, but a captured launch that is replayed after it waits as it should.
 constexpr uint32_t kSyncCopies = 8, kLineWords = 32;
 __host__ __device__ constexpr uint32_t sync_stride(uint32_t grid) { return (grid + 127) / 128 * 128; }   // words of a copy
 __host__ __device__ constexpr uint32_t fault_word(uint32_t grid) { return kSyncCopies * sync_stride(grid); }
@@ -322,12 +323,11 @@ __device__ __forceinline__ void stage_end(const MatvecArgs& a) {
   if (threadIdx.x < 64) {
     global_u32* sync = (global_u32*)a.sync;
     const uint32_t fault = fault_word(gridDim.x);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this workgroup's announcements are in
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this workgroup's announcements (and its fault, if it gave up) are in
     uint32_t before = 0;
     if (threadIdx.x == 0) before = __hip_atomic_fetch_add(sync + fault + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane(before) == gridDim.x - 1)
-      for (uint32_t i = threadIdx.x; i < sync_words(gridDim.x); i += 64)
-        if (i != fault) __hip_atomic_store(sync + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (uint32_t i = threadIdx.x; i < sync_words(gridDim.x); i += 64) __hip_atomic_store(sync + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

@@ -253,3 +253,47 @@ def test_listing_streams_whose_last_block_starts_no_token(marker, raw, escapes, 
     got = buf.cpu().numpy()
     assert np.array_equal(got[guard + shift:guard + shift + values.size], values)
     assert (got[:guard + shift] == 99).all() and (got[guard + shift + values.size:] == 99).all()
+
+
+def test_replayed_staged_step_waits_again_after_one_that_gave_up():
+    """A staged step whose last product reads what the one before it wrote (an fp32 output of small whole numbers is, read as
+    bf16, zeros and those numbers in turn), behind stages that keep one workgroup busy for longer than the others
+    would poll in a launch that has given up.  Captured, launched once with no polls allowed, replayed: the replay waits."""
+    rng = np.random.default_rng(4)
+    jobs = [_Job(16, 16384, 1, seed=40 + i, seg_cols=256, max_entries=600) for i in range(4)]
+    Qb = rng.integers(-1, 2, (16, 512)).astype(np.int8)
+    xb = np.where(np.arange(512) < 100, np.uint16(0x3F80), np.uint16(0))      # bf16 1.0 a hundred times
+    Qc = rng.integers(-100, 101, (4096, 32)).astype(np.int8)
+    b = tq.Matrix(tq.tq_encode_quantized(Qb, np.ones(16, np.float32), max_entries=600))
+    c = tq.Matrix(tq.tq_encode_quantized(Qc, np.ones(4096, np.float32), max_entries=600))
+    yb_ref = Qb[:, :100].astype(np.int64).sum(axis=1)
+    yc_ref = Qc[:, 1::2].astype(np.int64) @ yb_ref
+    xbd = torch.from_numpy(xb.view(np.int16)).cuda()
+    yb = torch.zeros(16, dtype=torch.float32, device="cuda")
+    yc = torch.zeros(4096, dtype=torch.float32, device="cuda")
+    busy = [jobs[i % 4] for i in range(60)]
+    step = tq.Step([j.m.handle for j in busy] + [b.handle, c.handle], [j.x.data_ptr() for j in busy] + [xbd.data_ptr(), yb.data_ptr()],
+                   [j.y.data_ptr() for j in busy] + [yb.data_ptr(), yc.data_ptr()], 1, stages=list(range(62)))
+    try:
+        assert step.info["persistent"] == 1
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            step.launch(_stream())
+        for gave_up in (False, True, True):
+            if gave_up:
+                tq.tq_step_set_spin_limit(step.handle, 0)
+                if tq.tq_step_get_info(step.handle)["fault"] == 0:
+                    step.launch(_stream())
+                torch.cuda.synchronize()
+                assert tq.tq_step_get_info(step.handle)["fault"] == 1
+            yb.zero_()
+            yc.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(yb.cpu().numpy(), yb_ref) and np.array_equal(yc.cpu().numpy(), yc_ref)
+        del graph
+    finally:
+        step.close()
+        for m in [j.m for j in jobs] + [b, c]:
+            m.close()
