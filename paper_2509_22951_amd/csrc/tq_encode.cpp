@@ -255,10 +255,11 @@ struct CodedRange {
   std::unique_ptr<uint16_t[]> words;   // not initialised: a page that is not written costs nothing
   size_t used = 0;                     // words
   std::vector<uint32_t> chunks;        // per unit
-  void start(uint64_t begin, uint64_t end, uint32_t seg_cols) {
+  // longest: of the segments' lengths (a matrix narrower than its segments would otherwise ask for many times its size)
+  void start(uint64_t begin, uint64_t end, uint32_t longest) {
     u_begin = begin;
     u_end = end;
-    words.reset(new uint16_t[(size_t)(end - begin) * 64 * ((seg_cols + kChunkCodes - 1) / kChunkCodes * kChunkCodes)]);
+    words.reset(new uint16_t[(size_t)(end - begin) * 64 * ((longest + kChunkCodes - 1) / kChunkCodes * kChunkCodes)]);
     chunks.reserve(end - begin);
   }
   // lane l's codes at lanes + l * kMaxSegCols (room to pad them to whole chunks of the longest)
@@ -494,10 +495,11 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
     const size_t lane_words = (size_t)64 * kMaxSegCols;
     std::unique_ptr<uint16_t[]> lanes(new uint16_t[lane_words * (1 + n_threads)]);
     std::vector<std::vector<uint16_t>> buffers(1 + n_threads);
-    ranges[0].start(0, u_frozen, seg_cols);
+    const uint32_t longest = std::min(seg_cols, cols);
+    ranges[0].start(0, u_frozen, longest);
     for (unsigned t = 0; t < n_threads; ++t) {
       const uint64_t b = std::min<uint64_t>(n_units, u_frozen + t * per), e = std::min<uint64_t>(n_units, b + per);
-      ranges[1 + t].start(b, e, seg_cols);
+      ranges[1 + t].start(b, e, longest);
       if (lmax > 2) buffers[1 + t].reserve(kMaxSegCols);
     }
     std::vector<std::thread> th;

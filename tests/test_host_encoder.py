@@ -385,3 +385,24 @@ def test_bench_launch_plans_group_what_a_layer_can_run_side_by_side():
         assert flat == list(range(197))
     first = bench.launch_groups(specs, "independent")[:4]
     assert [[specs[i].name.split(".")[-1] for i in g] for g in first] == [["q_proj", "k_proj", "v_proj"], ["o_proj"], ["gate_proj", "up_proj"], ["down_proj"]]
+
+
+def test_a_matrix_narrower_than_its_segments_takes_memory_by_its_width():
+    """400,000 rows of 8 columns in segments of 256, with 600 MB of address space to go: the encoder's working memory follows
+    the length of the segments there are, not the one they may have."""
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = """
+import resource
+import numpy as np
+import paper_2509_22951_amd as tq
+tq.load()
+q = np.random.default_rng(0).integers(-127, 128, (400_000, 8), dtype=np.int8)
+s = np.ones(q.shape[0], np.float32)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + 600_000_000,) * 2)
+print("container of", len(tq.tq_encode_quantized(q, s, n_threads=1)))
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    assert r.returncode == 0 and "container of" in r.stdout, r.stderr[-1000:]
