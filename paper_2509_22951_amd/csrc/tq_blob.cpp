@@ -4,7 +4,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/tq.h"
@@ -136,13 +135,12 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   if (n_threads <= 1) {
     work(0, n_units);
   } else {
-    std::vector<std::thread> th;
+    Threads th;
     uint64_t per = (n_units + n_threads - 1) / n_threads;
     for (unsigned t = 0; t < n_threads; ++t) {
       uint64_t b = std::min(n_units, t * per), e = std::min(n_units, b + per);
-      if (b < e) th.emplace_back(work, b, e);
+      if (b < e) th.start(work, b, e);
     }
-    for (auto& x : th) x.join();
   }
   if (first_bad.load() != UINT64_MAX) return bad("code stream of unit " + std::to_string(first_bad.load()));
   if (real_codes.load() != h.n_real_codes) return bad("count of non-padding codes");

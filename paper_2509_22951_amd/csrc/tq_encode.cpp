@@ -8,7 +8,6 @@
 #include <cstring>
 #include <memory>
 #include <new>
-#include <thread>
 #include <vector>
 
 #include "../../include/tq.h"
@@ -34,13 +33,13 @@ void parallel_for(uint64_t n, unsigned n_threads, F&& body) {  // body(begin, en
     body(0, n, 0);
     return;
   }
-  std::vector<std::thread> th;
+  Threads th;
   uint64_t per = (n + n_threads - 1) / n_threads;
   for (unsigned t = 0; t < n_threads; ++t) {
     uint64_t b = std::min<uint64_t>(n, t * per), e = std::min<uint64_t>(n, b + per);
-    th.emplace_back([=, &body] { body(b, e, t); });
+    th.start([=, &body] { body(b, e, t); });
   }
-  for (auto& x : th) x.join();
+  th.join();
 }
 
 // Dictionary of runs of up to 4 bytes, in the order LZW creates them (the container's code space is that order sorted by
@@ -502,9 +501,9 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
       ranges[1 + t].start(b, e, longest);
       if (lmax > 2) buffers[1 + t].reserve(kMaxSegCols);
     }
-    std::vector<std::thread> th;
+    Threads th;
     for (unsigned t = 0; t < n_threads; ++t)
-      if (ranges[1 + t].u_begin < ranges[1 + t].u_end) th.emplace_back([&, t] {
+      if (ranges[1 + t].u_begin < ranges[1 + t].u_end) th.start([&, t] {
         CodedRange& r = ranges[1 + t];
         for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) code_unit(uu, lanes.get() + lane_words * (1 + t), buffers[1 + t], r);
       });
@@ -519,7 +518,7 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
       }
       ranges[0].add_unit(lanes.get(), cnt, pad);
     }
-    for (auto& x : th) x.join();
+    th.join();
   }
 
   // Unit offsets in chunks: a unit is its longest lane stream, rounded up to whole chunks.
@@ -553,7 +552,8 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   h.total_bytes = round_up(h.off_scales + h.scale_bytes, kSectionAlign);
 
   // Every byte is written below: the sections, and zeros between them (the pad entry is the first of those).
-  uint8_t* blob = (uint8_t*)std::malloc(h.total_bytes);
+  std::unique_ptr<uint8_t, void (*)(void*)> owned((uint8_t*)std::malloc(h.total_bytes), std::free);
+  uint8_t* blob = owned.get();
   if (!blob) {
     set_error("tq_encode: out of host memory");
     return TQ_E_OOM;
@@ -572,19 +572,12 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
     auto copy = [&](const CodedRange& r) {
       if (r.u_begin < r.u_end) std::memcpy(codes + (uint64_t)uoff[r.u_begin] * kChunkWords, r.words.get(), r.used * 2);
     };
-    std::vector<std::thread> th;
-    try {
-      for (size_t i = 1; i < ranges.size(); ++i)
-        if (ranges[i].u_begin < ranges[i].u_end) th.emplace_back([&, i] { copy(ranges[i]); });
-    } catch (...) {
-      for (auto& x : th) x.join();
-      std::free(blob);
-      throw;
-    }
+    Threads th;
+    for (size_t i = 1; i < ranges.size(); ++i)
+      if (ranges[i].u_begin < ranges[i].u_end) th.start([&, i] { copy(ranges[i]); });
     copy(ranges[0]);
-    for (auto& x : th) x.join();
   }
-  *blob_out = blob;
+  *blob_out = owned.release();
   *bytes_out = (size_t)h.total_bytes;
   return TQ_OK;
 }
@@ -629,6 +622,9 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
   } catch (const std::bad_alloc&) {
     set_error("tq_encode: out of host memory");
     return TQ_E_OOM;
+  } catch (...) {
+    set_error("tq_encode: unexpected internal error (could a thread not be started?)");
+    return TQ_E_HIP;
   }
 }
 
@@ -652,6 +648,9 @@ extern "C" int tq_encode_quantized(const int8_t* q, const float* scales_in, uint
   } catch (const std::bad_alloc&) {
     set_error("tq_encode_quantized: out of host memory");
     return TQ_E_OOM;
+  } catch (...) {
+    set_error("tq_encode_quantized: unexpected internal error (could a thread not be started?)");
+    return TQ_E_HIP;
   }
 }
 
@@ -671,6 +670,9 @@ extern "C" int tq_encode_gate_up(const float* w_gate, const float* w_up, uint32_
   } catch (const std::bad_alloc&) {
     set_error("tq_encode_gate_up: out of host memory");
     return TQ_E_OOM;
+  } catch (...) {
+    set_error("tq_encode_gate_up: unexpected internal error (could a thread not be started?)");
+    return TQ_E_HIP;
   }
 }
 

@@ -28,6 +28,9 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <thread>
+#include <utility>
+#include <vector>
 
 struct tq_info;
 
@@ -83,6 +86,21 @@ inline uint32_t segment_len(const Header& h, uint32_t band, uint32_t quad, uint3
 }
 
 void set_error(const std::string& msg);   // thread-local last-error text
+
+// Host threads that are waited for wherever their block ends, also when one of them cannot be started (std::thread throws then).
+class Threads {
+ public:
+  ~Threads() { join(); }
+  template <typename... A>
+  void start(A&&... a) { threads_.emplace_back(std::forward<A>(a)...); }
+  void join() {
+    for (auto& t : threads_) t.join();
+    threads_.clear();
+  }
+
+ private:
+  std::vector<std::thread> threads_;
+};
 
 // What validation learns about a container beyond the header.
 struct BlobFacts {

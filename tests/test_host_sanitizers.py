@@ -25,3 +25,16 @@ def test_encoder_and_validator_are_clean_under_asan_and_ubsan():
     run = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
     assert run.returncode == 0, (run.stdout + run.stderr)[-3000:]
     assert "containers encoded and validated" in run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_encoder_and_validator_come_back_when_a_thread_cannot_be_started():
+    """The same two sources with a pthread_create that refuses from the n-th call on, for every n (threads_driver.cpp)."""
+    folder = tempfile.mkdtemp(prefix="tq_thr_")
+    exe = os.path.join(folder, "driver")
+    build = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", os.path.join(HERE, "threads_driver.cpp"),
+                            os.path.join(CSRC, "tq_encode.cpp"), os.path.join(CSRC, "tq_blob.cpp"), "-ldl", "-o", exe], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, (run.stdout + run.stderr)[-3000:]
+    assert "came back" in run.stdout
