@@ -336,7 +336,7 @@ def test_multi_launch_matches_single_launches_and_oracle(dev, shared_dictionary)
 
 def test_multi_launch_splits_into_ring_and_whole_strip_launches(dev, ring_for_small_launches):
     """One call whose matrices go partly to the ring kernel (inherited dictionary, whole units, aligned activations) and
-    partly to the whole-strip kernel (300 columns: no whole units)."""
+    partly to the runs kernel (300 columns: no whole units)."""
     shapes = [(192, 768, 64), (64, 768, 64), (64, 768, 192), (40, 300, 32), (512, 768, 192), (192, 2048, 256), (100, 1024, 128)]
     for batch in (3, 8, 16):
         _multi_case(dev, shapes, batch, True)
@@ -459,7 +459,7 @@ RING_SPREAD_LIMIT = 65   # lane_spread up to which the batched product keeps a 1
 
 def test_batched_product_ring_and_whole_strip_kernels_agree(dev, ring_for_small_launches):
     """A matrix encoded with an inherited, full dictionary keeps its 64 lanes close together (lane_spread small): with
-    16-byte aligned activations its batched product runs on the ring kernel, with misaligned ones on the whole-strip
+    16-byte aligned activations its batched product runs on the ring kernel, with misaligned ones on the runs
     kernel.  Both must match the oracle, for every batch size that takes these kernels, over several bands, several
     quads, rows past the last band's end, and 1, 2 and 8 windows per segment."""
     first = tq.tq_encode(make_weights(small_case(256, 1024, seed=900)), max_entries=3000, seg_cols=64)
@@ -559,7 +559,7 @@ def test_packed_four_bit_weights(dev, rows, cols, width, seg_cols, dictionary):
 
 def test_packed_weights_on_the_ring_kernel(dev, ring_for_small_launches):
     """Whole units of packed bytes with the lanes close together: aligned activations take the ring kernel (two MFMA steps
-    per 8-byte piece), misaligned ones the whole-strip kernel; both match the oracle.  The first matrix starts its
+    per 8-byte piece), misaligned ones the runs kernel; both match the oracle.  The first matrix starts its
     dictionary (lanes further apart: careful mode or whole strips), the others inherit a full one."""
     first_spec = small_case(256, 1024, seed=995)
     first = tq.tq_encode(make_weights(first_spec), bits=4, seg_cols=64, pack=True)
@@ -676,7 +676,7 @@ def test_two_activation_rows_of_packed_weights(dev):
 
 def test_rows_too_long_for_the_activation_image_run_on_the_batched_kernels(dev, monkeypatch):
     """A row whose LDS image does not fit beside the dictionary is not refused: batch 1 and 2 then run on the kernels that
-    serve the larger batches (whole-strip, or ring when the launch is large enough).  Alone, as a prepared step, mixed
+    serve the larger batches (the runs kernel, or the ring kernel when the launch is large enough).  Alone, as a prepared step, mixed
     with ordinary matrices in one call (the call is split), as a gate/up pair, packed."""
     cases = [(96, 28672, 256, 12000, 8, False), (64, 65536, 256, 2000, 8, False), (48, 98304, 128, 4000, 4, True)]
     for rows, cols, seg, me, width, pack in cases:
@@ -805,7 +805,7 @@ def _gpu_gate_up(m, bits, dev, rows):
 @pytest.mark.parametrize("rows,cols,seg_cols", [(8, 64, 16), (100, 768, 64), (1027, 2048, 256), (520, 1000, 128)])
 def test_gate_up_product_with_fused_silu(dev, rows, cols, seg_cols):
     """silu(W_gate x) * (W_up x) from one container of interleaved rows, against the float64 definition: batch 1
-    (dot-product kernel) and batched (whole-strip MFMA kernel), bands that end in the middle of a pair's band included."""
+    (dot-product kernel) and batched (MFMA kernels), bands that end in the middle of a pair's band included."""
     sg, su = small_case(rows, cols, seed=70), small_case(rows, cols, seed=71)
     Wg, Wu = make_weights(sg), make_weights(su)
     Qg, scg = O.quantize_rows(Wg)
@@ -850,7 +850,7 @@ def test_gate_up_multi_and_argument_errors(dev):
 def test_frequency_dictionary_containers_on_the_device(dev, ring_for_small_launches):
     """Same container, same kernels: a dictionary picked by frequency decodes bit-exactly and multiplies within
     tolerance (dot-product kernel, ring kernel - such a matrix has no start-up phase of single bytes, its lanes stay
-    close - and whole-strip kernel through misaligned activations)."""
+    close - and runs kernel through misaligned activations)."""
     spec = small_case(256, 2048, seed=61)
     W = make_weights(spec)
     blob = tq.tq_encode(W, dictionary="frequency")
@@ -984,7 +984,7 @@ def test_prepared_step_serves_more_matrices_per_launch_than_the_kernel_arguments
 
 
 def test_prepared_step_with_ring_whole_strip_and_packed_matrices(dev, ring_for_small_launches):
-    """One step whose matrices go to different kernels: ring (whole units), whole strip (300 columns), packed 4-bit."""
+    """One step whose matrices go to different kernels: ring (whole units), runs (300 columns), packed 4-bit."""
     shapes = [(192, 768, 64), (64, 768, 64), (64, 768, 192), (40, 300, 32), (512, 768, 192), (192, 2048, 256), (100, 1024, 128)]
     for batch in (1, 3, 16):
         n = _step_case(dev, shapes, batch, max_entries=3000, widths=[(8, False), (8, False), (4, True)])
@@ -1073,7 +1073,7 @@ def test_staged_step_runs_dependent_products_in_one_launch(dev, batch, pack):
 
 
 def test_staged_step_in_a_hip_graph(dev):
-    """The staged launch (a fill kernel for the stage counters, then the persistent kernel) captured into a graph and
+    """The staged launch (the persistent kernel alone: it leaves its hand-over words clear) captured into a graph and
     replayed, with eager launches of the same step between the replays: every replay against the oracle."""
     layer = [[(256, 512), (64, 512), (64, 512)], [(256, 256)], [(1024, 256), (1024, 256)], [(256, 1024)]]
     mats, xs, ys, refs, stages = _staged_case(dev, 1, layer + layer, 15000)

@@ -171,6 +171,20 @@ def _bytes_at_the_limit(seed, cols, seg_cols, limit):
     return Q
 
 
+def _drifting(seed, cols, seg_cols, limit, opts):
+    """_bytes_at_the_limit as a container -> (weights, scales, matrix)."""
+    Qb = _bytes_at_the_limit(seed, cols, seg_cols, limit)
+    pairs = np.array([[p, p + 32] for p in range(64, 96)], np.uint8).view(np.int8)
+    d = tq.tq_encode_quantized(pairs, np.ones(32, np.float32), max_entries=288, dictionary="frequency")
+    Q = Qb.view(np.int8)
+    if opts:   # byte j of a row holds columns 2j and 2j + 1 as 4-bit values
+        Q = np.stack([((Qb & 15) ^ 8).astype(np.int8) - 8, ((Qb >> 4) ^ 8).astype(np.int8) - 8], axis=2).reshape(Qb.shape[0], -1)
+    scales = np.linspace(0.005, 0.015, Q.shape[0]).astype(np.float32)
+    blob = tq.tq_encode_quantized(Q, scales, max_entries=288, seg_cols=seg_cols, dict_from=d, dictionary="frequency", **opts)
+    assert tq.tq_validate_blob(blob)["lane_spread"] == limit
+    return Q, scales, tq.Matrix(blob)
+
+
 @pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
 @pytest.mark.parametrize("limit", [65, 113])              # the fast and the careful form of the ring decode
 @pytest.mark.parametrize("cols,seg_cols,seed", [
@@ -180,17 +194,7 @@ def _bytes_at_the_limit(seed, cols, seg_cols, limit):
     (500, 512, 2),                 # one unit, cut between the wavefronts
 ])
 def test_lanes_as_far_apart_as_the_ring_takes(cols, seg_cols, seed, limit, opts):
-    Qb = _bytes_at_the_limit(seed, cols, seg_cols, limit)
-    pairs = np.array([[p, p + 32] for p in range(64, 96)], np.uint8).view(np.int8)
-    ones = np.ones(32, np.float32)
-    d = tq.tq_encode_quantized(pairs, ones, max_entries=288, dictionary="frequency")
-    Q = Qb.view(np.int8)
-    if opts:   # byte j of a row holds columns 2j and 2j + 1 as 4-bit values
-        Q = np.stack([((Qb & 15) ^ 8).astype(np.int8) - 8, ((Qb >> 4) ^ 8).astype(np.int8) - 8], axis=2).reshape(Qb.shape[0], -1)
-    scales = np.linspace(0.5, 1.5, Q.shape[0]).astype(np.float32)
-    blob = tq.tq_encode_quantized(Q, scales, max_entries=288, seg_cols=seg_cols, dict_from=d, dictionary="frequency", **opts)
-    assert tq.tq_validate_blob(blob)["lane_spread"] == limit
-    m = tq.Matrix(blob)
+    Q, scales, m = _drifting(seed, cols, seg_cols, limit, opts)
     try:
         for batch in (3, 8, 16):
             bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
@@ -202,6 +206,29 @@ def test_lanes_as_far_apart_as_the_ring_takes(cols, seg_cols, seed, limit, opts)
             torch.cuda.synchronize()
             for got, want in zip(y.cpu().numpy().astype(np.float64), ref):
                 assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL * np.abs(want).max()
+    finally:
+        m.close()
+
+
+@pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("cols,seg_cols,limit", [(2048, 512, 114), (4096, 512, 200), (500, 512, 150)])
+def test_lanes_further_apart_than_the_ring_takes(cols, seg_cols, limit, opts):
+    """The whole-strip kernel: whole units and a ragged one, 16-byte aligned x and x at odd addresses, products and gated pairs."""
+    Q, scales, m = _drifting(3, cols, seg_cols, limit, opts)
+    try:
+        for batch, shift in ((3, 0), (5, 1), (16, 0)):
+            bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
+            ref = O.gemv_f64(Q, scales, x)
+            gated = ref[:, 0::2] / (1.0 + np.exp(-ref[:, 0::2])) * ref[:, 1::2]
+            xd = torch.from_numpy(np.concatenate([np.zeros(shift, np.int16), bits.view(np.int16).reshape(-1)])).cuda()[shift:]
+            y = torch.full((batch, 16), float("nan"), dtype=torch.float32, device="cuda")
+            g = torch.full((batch, 8), float("nan"), dtype=torch.float32, device="cuda")
+            m.matvec(xd.data_ptr(), y.data_ptr(), batch, _stream())
+            tq.tq_matvec_gate_up(m.handle, xd.data_ptr(), g.data_ptr(), batch, _stream())
+            torch.cuda.synchronize()
+            for got, want, tol in ((y, ref, TOL), (g, gated, 2 * TOL)):
+                got = got.cpu().numpy().astype(np.float64)
+                assert np.isfinite(got).all() and (np.abs(got - want).max(axis=1) <= tol * np.abs(want).max(axis=1)).all()
     finally:
         m.close()
 
