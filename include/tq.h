@@ -211,8 +211,7 @@ int tq_matvec_gate_up_multi(int n, const tq_handle *hs, const void *const *xs, v
                                  NULL and batch is not used */
 typedef struct tq_step *tq_step_handle;
 typedef struct tq_step_info {
-  uint32_t n_matrices, n_launches; /* kernel launches one tq_step_launch makes (a staged step that runs as one kernel: 1,
-                                      not counting the small launch that clears its stage counters) */
+  uint32_t n_matrices, n_launches; /* kernel launches one tq_step_launch makes (a staged step that runs as one kernel: 1) */
   uint64_t table_bytes;            /* device memory the step holds */
   uint32_t n_stages;               /* staged steps: number of stages, else 0 */
   uint32_t persistent;             /* 1: all stages run in one kernel launch with device-side hand-over between them */
@@ -233,18 +232,20 @@ int tq_step_create(int n, const tq_handle *hs, const void *const *xs, void *cons
  * caller's, as in tq_step_create; this call only orders the products.
  * When every matrix takes the dot-product kernel (batch 1 or 2; ordinary or packed weights; rows that fit its LDS image;
  * no runs longer than 2 bytes) the whole step is one kernel launch: one workgroup per compute unit walks the stages, the
- * dictionary stays in LDS across them, and between two stages the workgroups hand over through a counter in device
- * memory (outputs and activations of such a step are stored and loaded device-coherently).  That needs all workgroups resident together, which holds when nothing
- * else occupies the GPU's compute units while the step runs; a wait is bounded (tq_step_set_spin_limit; about two
- * seconds by default): a workgroup that gives up sets a fault flag, every other wait of that launch ends at once, the
- * results must not be used, tq_step_get_info reports fault = 1 and later launches return TQ_E_HIP.
+ * dictionary stays in LDS across them, and between two stages the workgroups hand over through a table of words in device
+ * memory, one per workgroup, which every launch finds and leaves zero (outputs and activations of such a step are stored
+ * and loaded device-coherently).  That needs all workgroups resident together, which holds when nothing else occupies the
+ * GPU's compute units while the step runs; a wait is bounded (tq_step_set_spin_limit; about two seconds by default): a
+ * workgroup that gives up sets a fault flag, every other wait of that launch ends within 32 polls, the results must not
+ * be used, tq_step_get_info reports fault = 1 from then on and later calls of tq_step_launch return TQ_E_HIP (a captured
+ * launch that is replayed all the same starts afresh).
  * Otherwise (larger batches, long runs, mixed kinds) each stage gets the launches tq_matvec_multi would make, in order
  * on the stream.  Results equal tq_matvec_multi's for the same products up to the order of fp32 additions.
  * flags: none defined yet, pass 0.  Launch with tq_step_launch, release with tq_step_destroy.
  */
 int tq_step_create_staged(int n, const tq_handle *hs, const void *const *xs, void *const *ys, const int *stage, int batch,
                           uint32_t flags, tq_step_handle *out);
-/* Polls of a stage counter (a microsecond or two each) after which a workgroup of a staged step gives up waiting. */
+/* Polls of the hand-over table (a microsecond or two each) after which a workgroup of a staged step gives up waiting. */
 int tq_step_set_spin_limit(tq_step_handle s, uint32_t polls);
 int tq_step_launch(tq_step_handle s, void *stream);
 int tq_step_get_info(tq_step_handle s, tq_step_info *out);

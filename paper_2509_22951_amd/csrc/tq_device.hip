@@ -657,8 +657,9 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
 // Bands per CU a launch needs for the ring kernel; tq_set_ring_min_bands_per_cu changes it (tests use 0 to put small
 // matrices through that kernel).
 std::atomic<uint64_t> g_ring_min_bands{kRingMinBandsPerCu};
-// (us, ring / runs kernel, LLaMA-3.2-3B layers: 20 bands per CU batch 8 128 / 117, 27 bands batch 4 137 / 140; above 8
-// rows of x the runs kernel pays more for them: 13.5 bands batch 16 92 / 112, 27 bands 139 / 259)
+// (us, ring / runs kernel, LLaMA-3.2-3B layers as one step: batch 8 20 bands per CU 127 / 109, 27 bands 135 / 142, 54 bands
+// 230 / 250; above 8 rows of x the runs kernel pays more for them: batch 16 13.5 bands 91 / 95, 27 bands 138 / 254.  Batches
+// of up to 4 rows would have the line further up: 27 bands 133 / 122, 54 bands 225 / 217, packed weights 99 / 96 and 176 / 200)
 uint64_t ring_min_bands_per_cu(int batch) { return g_ring_min_bands.load(std::memory_order_relaxed) / (batch > 8 ? 2 : 1); }
 
 bool ring_eligible(const tq_matrix* t, const void* x) {
@@ -862,7 +863,7 @@ struct tq_step {
   uint32_t* fault_host = nullptr;   // pinned host word the kernel sets when a hand-over wait gave up
 };
 
-constexpr uint32_t kDefaultSpinLimit = 1u << 20;   // polls of a stage counter (a microsecond or two each) before a workgroup gives up
+constexpr uint32_t kDefaultSpinLimit = 1u << 20;   // polls of the hand-over table (a microsecond or two each) before a workgroup gives up
 
 static int tq_step_create_impl(int n, const tq_handle* hs, const void* const* xs, void* const* ys, int batch, uint32_t flags,
                               tq_step_handle* out) {

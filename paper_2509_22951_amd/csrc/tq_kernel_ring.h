@@ -278,57 +278,57 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
     };
     request_tile(0);
     for (; pass_lo < band_hi; pass_lo = pass_hi) {
-    pass_hi = min(band_hi, pass_lo + pass_bands);
-    f32x4 acc[kGateUpBands];   // kGateUp: the sums of this wavefront's bands of the pass
+      pass_hi = min(band_hi, pass_lo + pass_bands);
+      f32x4 acc[kGateUpBands];   // kGateUp: the sums of this wavefront's bands of the pass
 #pragma unroll
-    for (int k = 0; k < kGateUpBands; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (uint32_t q = 0; q < nq; ++q) {
-      if (q || pass_lo != band_lo) __syncthreads();   // everybody has finished the previous quad: its activation tile can go
-      if (!kGateUp && tid == 0) *next_band_counter = kWaves;   // bands 0 .. kWaves - 1 are the wavefronts' first ones
-      commit_tile();
-      if (q + 1 < nq || pass_hi < band_hi) request_tile(q + 1 < nq ? q + 1 : 0);
-      __syncthreads();
-      // Sums of lane l: rows 4 * (l / 16) + v of the band, batch row l % 16.  The scales of the next band are requested
-      // when this one's have been used, a unit ahead of their use: waiting for them is then not a wait for the code
-      // chunks requested in between.
-      const uint32_t band0 = (uint32_t)wave < pass_hi - pass_lo ? pass_lo + wave : kNoBand;
-      own_band = pass_lo + wave;
-      float scale[4];
-      auto request_scales = [&](uint32_t band) {
+      for (int k = 0; k < kGateUpBands; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (uint32_t q = 0; q < nq; ++q) {
+        if (q || pass_lo != band_lo) __syncthreads();   // everybody has finished the previous quad: its activation tile can go
+        if (!kGateUp && tid == 0) *next_band_counter = kWaves;   // bands 0 .. kWaves - 1 are the wavefronts' first ones
+        commit_tile();
+        if (q + 1 < nq || pass_hi < band_hi) request_tile(q + 1 < nq ? q + 1 : 0);
+        __syncthreads();
+        // Sums of lane l: rows 4 * (l / 16) + v of the band, batch row l % 16.  The scales of the next band are requested
+        // when this one's have been used, a unit ahead of their use: waiting for them is then not a wait for the code
+        // chunks requested in between.
+        const uint32_t band0 = (uint32_t)wave < pass_hi - pass_lo ? pass_lo + wave : kNoBand;
+        own_band = pass_lo + wave;
+        float scale[4];
+        auto request_scales = [&](uint32_t band) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) scale[v] = global_load(m.scales + min(band, m.n_bands - 1) * kUnitRows + 4 * kg + v);
-      };
-      if constexpr (!kGateUp) request_scales(band0);
-      auto finish_unit = [&](uint32_t band, uint32_t next_band, f32x4 sums) {
-        if constexpr (kGateUp) {
-          const uint32_t mine = (band - pass_lo) / kWaves;
+          for (int v = 0; v < 4; ++v) scale[v] = global_load(m.scales + min(band, m.n_bands - 1) * kUnitRows + 4 * kg + v);
+        };
+        if constexpr (!kGateUp) request_scales(band0);
+        auto finish_unit = [&](uint32_t band, uint32_t next_band, f32x4 sums) {
+          if constexpr (kGateUp) {
+            const uint32_t mine = (band - pass_lo) / kWaves;
 #pragma unroll
-          for (int k = 0; k < kGateUpBands; ++k)   // (a sum of selected values: indexed, the array would go to memory)
+            for (int k = 0; k < kGateUpBands; ++k)   // (a sum of selected values: indexed, the array would go to memory)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[k][v] += mine == (uint32_t)k ? sums[v] : 0.f;
-          return;
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const uint32_t row = band * kUnitRows + 4 * kg + v;
-          if (bn < a.batch && row < m.rows) {
-            float* y = job.y + (size_t)bn * m.rows + row;
-            if (q == 0) global_store(y, sums[v] * scale[v]);
-            else (void)__builtin_amdgcn_global_atomic_fadd_f32((__attribute__((address_space(1))) float*)y, sums[v] * scale[v]);
+              for (int v = 0; v < 4; ++v) acc[k][v] += mine == (uint32_t)k ? sums[v] : 0.f;
+            return;
           }
-        }
-        request_scales(next_band);
-      };
-      if (m.reserved - 1 > band_lo * nq) decode_units_ring<true, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag_careful, finish_unit);
-      else decode_units_ring<false, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
-    }
-    if constexpr (kGateUp) {
 #pragma unroll
-      for (int k = 0; k < kGateUpBands; ++k) {
-        const uint32_t band = pass_lo + k * kWaves + wave;
-        if (band < pass_hi) BandSums::store(a, job, m, band, acc[k], lane);
+          for (int v = 0; v < 4; ++v) {
+            const uint32_t row = band * kUnitRows + 4 * kg + v;
+            if (bn < a.batch && row < m.rows) {
+              float* y = job.y + (size_t)bn * m.rows + row;
+              if (q == 0) global_store(y, sums[v] * scale[v]);
+              else (void)__builtin_amdgcn_global_atomic_fadd_f32((__attribute__((address_space(1))) float*)y, sums[v] * scale[v]);
+            }
+          }
+          request_scales(next_band);
+        };
+        if (m.reserved - 1 > band_lo * nq) decode_units_ring<true, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag_careful, finish_unit);
+        else decode_units_ring<false, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
       }
-    }
+      if constexpr (kGateUp) {
+#pragma unroll
+        for (int k = 0; k < kGateUpBands; ++k) {
+          const uint32_t band = pass_lo + k * kWaves + wave;
+          if (band < pass_hi) BandSums::store(a, job, m, band, acc[k], lane);
+        }
+      }
     }
   }
 }

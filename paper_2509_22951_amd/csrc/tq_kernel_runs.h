@@ -15,12 +15,14 @@ namespace tq {
 // global memory work at any 2-byte address), and rows need not be whole units: in a unit that reaches past the row's end
 // (or whose segments are no multiple of a group of windows) a fragment is loaded where it still lies inside the row and
 // shifted into place, zeros behind it.
-// Batches of up to 8 rows take two windows per load, up to 4 rows four (fold_sums): one LLaMA-3.2-3B layer batch 8 45.2 -> 42.0,
-// batch 4 43.2 -> 38.8, 8192 x 3072 packed batch 4 16.3 -> 14.8 us.
-// Measured, us, whole-strip kernel -> this one: 4099 x 2999 batch 5 41.1 -> 21.2, that layer batch 8 56 -> 42 (caches warm);
-// launches that fill k_matvec_ring stay there (eight such layers, batch 8: 235 us there, 267 here before two windows were taken per load; the gated pairs of
-// eight blocks, batch 16: 154 there, 241 here): 16-byte pieces of up to 16 rows of x from the caches cost more than the
-// tile in LDS (without those loads: 222 and 148).
+// Batches of up to 8 rows take two windows per load, up to 4 rows four (fold_sums).
+// Measured, us, buffers warm in the caches (in brackets: the whole-strip kernel, which took these launches before): 4099 x
+// 2999 batch 5 19.7 (41), one LLaMA-3.2-3B layer batch 8 42.2 (56), batch 4 41.8, batch 16 55.7, 8192 x 3072 packed batch 4 14.1.
+// Launches that fill k_matvec_ring go there: eight such layers, batch 8, 230 us there, 250 here; the gated pairs of eight
+// blocks, batch 16, 128 there, 253 here.  What they differ in is x.  Counters of the eight layers at batch 8, M cycles
+// summed over the compute units, there / here: busy 122 / 136, address unit of the vector memory path busy 58 / 109 (39 / 89 M
+// cache accesses), vector instructions issued 86 / 90, LDS pipe busy 71 / 68.  The 16-byte pieces of up to 16 rows of x keep
+// the address unit busy four fifths of the time here; with 16 rows in place of 8 there are twice as many of them.
 constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
 constexpr int kRunWavesPacked = 8;   // packed 4-bit weights: two fragments and more conversion per piece, 12 wavefronts leave too few registers
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));

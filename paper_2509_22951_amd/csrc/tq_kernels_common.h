@@ -104,7 +104,7 @@ struct MatvecArgs {
   uint32_t* sync;                // device, sync_words(gridDim.x) words, zero at launch
   uint32_t* fault_host;          // host memory the device can write: set to 1 when a wait gave up
   uint32_t n_stages;
-  uint32_t spin_limit;           // polls of a stage counter before a workgroup gives up
+  uint32_t spin_limit;           // polls of the hand-over table before a workgroup gives up
   union {
     struct {
       uint32_t cost[kMaxMulti + 1];

@@ -68,7 +68,8 @@ __device__ __forceinline__ bf16x8 nib8_to_bf16x8(uint32_t d) {
 
 // The runs of one chunk (4 codes) as one string of 4..8 bytes in (s0, s1), n = its length.  The 4 entries (1 or 2 bytes
 // each; the length follows from the code; the byte after a single is zero in the dictionary image) are joined with
-// byte-granular funnel shifts.  Bytes of the string past n are not zero in general.
+// byte-granular funnel shifts.  Bytes of the string past n are zero (k_matvec_runs multiplies what a unit's last chunk left in
+// the carry of append_chunk_ring as it is).
 __device__ __forceinline__ void chunk_string(uint2 c, uint32_t& s0, uint32_t& s1, uint32_t& n) {
   const uint32_t e0 = lds_read16(half_offset_lo(c.x)), e1 = lds_read16(half_offset_hi(c.x));
   const uint32_t e2 = lds_read16(half_offset_lo(c.y)), e3 = lds_read16(half_offset_hi(c.y));
