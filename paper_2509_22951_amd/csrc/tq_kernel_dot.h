@@ -6,7 +6,7 @@
 namespace tq {
 // Staging is split in two so that the loads of the dictionary, of the activations and of the first code chunks are
 // all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS.
-constexpr uint32_t kSplitUnits = 4;    // k_matvec splits units between wavefronts in shares of fewer than this many units each
+constexpr uint32_t kSplitWaves = 4;    // k_matvec splits units between wavefronts in shares that leave each unit at least this many
 constexpr int kDictRegs = 16;   // uint4 per thread per round of the tile kernels' dictionary staging
 
 template <int kThreads, int kDictRegs>   // kDictRegs x kThreads x 16 bytes per round (128 KB: the whole dictionary in one)
@@ -322,8 +322,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   // leave wavefronts idle: a 2048 x 2048 matrix gives a workgroup two units for its eight wavefronts.)  Where a lane
   // stands at the start of such a run is the number of columns the wavefronts before it pass in that unit; each counts
   // its own part while the dictionary is on its way and leaves the counts in LDS, so nothing waits for device memory a
-  // second time.  (2048 x 2048, batch 1: 12.3 -> 10.1 us, decode 5.9 -> 1.9 us of it.)  In shares of kSplitUnits units per
-  // wavefront and more the uneven last unit is no longer worth the counting.
+  // second time.  (2048 x 2048, batch 1: 12.3 -> 10.1 us, decode 5.9 -> 1.9 us of it.)  The counts and the sums of the
+  // shared bands cost 2 to 4 us, most where the codes come from HBM: they pay in shares of kWaves / kSplitWaves units and no
+  // more.  (us, split / whole units, from HBM | from the caches: 8 wavefronts, 1 unit 9.3 / 9.8 | 8.6 / 9.4, 2 units 10.1 / 10.9 |
+  // 9.1 / 10.5, 3 units 11.9 / 10.7 | 10.5 / 10.1, 6 units (8192 x 3072) 15.7 / 12.5 | 13.6 / 11.6, 15 units 22.1 / 19.0 | 19.1 / 17.1;
+  // two rows, 2 units 9.7 / 12.2, 3 units 11.7 / 11.5; packed, 12 wavefronts, 3 units 10.3 / 11.2, 4 units 11.1 / 10.6.)
   constexpr bool kSplit = !kLong && !(kPacked && kB == 2);   // (two rows of packed weights leave no LDS for the counts)
   constexpr int kCount = 12;   // chunks per round of that count
   constexpr int kThreads = kWaves * 64, kDictRegs = (kStaged ? 48 : 128) / kWaves, kXRegs = 64 / kWaves;   // (staged: one dictionary for many stages, so few registers)
@@ -441,7 +444,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     unit_lo = band_lo * m.n_quads;
     const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
     in_lanes = n_units < kLaneUnits;
-    split = kSplit && n_units < kSplitUnits * kWaves && in_lanes && n_units % kWaves != 0;
+    split = kSplit && kSplitWaves * n_units <= kWaves;
+    static_assert(kWaves / kSplitWaves < kLaneUnits, "the offsets of a split share are in the lanes");
     // (values of the two ways meet in local variables and are assigned once: assigned in each branch, the compiler keeps
     // them in memory)
     uint32_t first = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves), end = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);

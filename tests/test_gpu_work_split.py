@@ -42,9 +42,13 @@ SHARES = [
     # rows, cols, seg_cols: units of a workgroup's share (whole bands of quads) and their length
     (16, 8, 16),          # one unit of two chunks for 8 or 12 wavefronts: most runs are empty
     (16, 250, 64),        # one unit
+    (16, 500, 64),        # two units (packed: one): the most that are shared between 8 wavefronts
+    (16, 700, 64),        # three units (packed: two): whole
+    (16, 1500, 64),       # six units (packed: three, the most that are shared between 12 wavefronts)
+    (16, 2000, 64),       # eight units (packed: four: whole)
     (16, 3000, 64),       # one band of 12 units, the last one part empty
-    (16, 4096, 32),       # one band of 32 units: as many as are never shared
-    (16, 3968, 32),       # 31 units: still shared between 8 wavefronts
+    (16, 4096, 32),       # one band of 32 units
+    (16, 3968, 32),       # 31 units: one wavefront has one less
     (4099, 1500, 128),    # one or two bands of 3 units, ragged rows and columns
     (8192, 512, 32),      # two bands of 4 units: a whole unit each for 8 wavefronts
 ]
