@@ -111,8 +111,7 @@ __global__ __launch_bounds__(kListingThreads) void k_listing_decompress(const ui
     first += v < wave ? wave_tokens[v] : 0u;
     tokens += wave_tokens[v];
   }
-  const ListingOutput o = listing_output(base, tokens, n_values);
-  uint32_t* to = lds_out + o.lo / 4 + first;
+  uint32_t* to = lds_out + (base & 3u) + first;   // (see listing_output)
   for (; starts; starts &= starts - 1) {
     const uint32_t j = (uint32_t)__builtin_ctz(starts);
     const uint32_t* at = lds_words + 4 + 4 * tid + (j >> 1);
@@ -124,6 +123,7 @@ __global__ __launch_bounds__(kListingThreads) void k_listing_decompress(const ui
     *to++ = v4;
   }
   __syncthreads();
+  const ListingOutput o = listing_output(base, tokens, n_values);
   uint8_t* piece0 = out + o.piece0;
   const uint32_t lo = o.lo, hi = o.hi;
   if (((uintptr_t)out & 15) == 0) {

@@ -26,7 +26,8 @@ struct ListingOutput {
 TQ_HD ListingOutput listing_output(uint32_t base, uint32_t tokens, uint64_t n_values) {
   const uint32_t lo = (base & 3u) * 4u;
   const uint64_t first = (uint64_t)base * 4u, end = first + (uint64_t)tokens * 4u, stop = end < n_values ? end : n_values;
-  return {first - lo, lo, lo + (uint32_t)(stop > first ? stop - first : 0u)};
+  const uint32_t hi = lo + (uint32_t)(stop - first);   // (a token that starts in the block stands for at least one value: first < stop)
+  return {first - lo, lo, tokens ? hi : lo};
 }
 
 // The schedule of the ring kernels.  A lane keeps kRingBytes of its segment; every kRingStep chunks the wavefront looks whether
