@@ -2,12 +2,14 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
 
 #include "../../include/tq.h"
 #include "tq_format.h"
+#include "tq_plan.h"
 
 namespace tq {
 
@@ -79,16 +81,19 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
     if (uoff[u + 1] <= uoff[u] || uoff[u + 1] > h.n_chunks) return bad("unit offsets");
 
   // Codes: in range, pads only at the end of a lane stream, every lane stream's runs sum to its segment's length.
-  std::atomic<uint64_t> first_bad(UINT64_MAX), real_codes(0), wide_units(0);
+  std::atomic<uint64_t> first_bad(UINT64_MAX), real_codes(0);
   std::atomic<uint32_t> overrun(0), spread(0);
+  std::mutex wide_mutex;
+  std::vector<uint32_t> wide_units;
   n_threads = std::max(1u, std::min(n_threads, 16u));
   n_threads = (unsigned)std::min<uint64_t>(n_threads, n_units);
   const uint32_t pad_advance = h.lmax > 2 ? 4u : 2u;   // columns a pad code moves a lane's activation index in the product kernel
   auto work = [&](uint64_t ub, uint64_t ue) {
     uint64_t real = 0;
     uint32_t over = 0, wide = 0;
-    uint64_t last_wide = 0;   // 1 + the last unit of this range whose lanes drift further apart than kWideSpread
+    std::vector<uint32_t> mine;                 // the units of this range that level_unit has to see
     std::vector<uint32_t> reach_lo, reach_hi;   // per chunk count: least / greatest column reached by an unfinished lane
+    std::vector<uint32_t> reach_on;             // the greatest column any lane reaches, finished lanes going on by one a code
     for (uint64_t u = ub; u < ue && first_bad.load(std::memory_order_relaxed) == UINT64_MAX; ++u) {
       const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
       const uint32_t steps = (uoff[u + 1] - uoff[u]) * kChunkCodes;
@@ -96,29 +101,37 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
       bool ok = true;
       reach_lo.assign(steps / kChunkCodes, UINT32_MAX);
       reach_hi.assign(steps / kChunkCodes, 0);
+      reach_on.assign(steps / kChunkCodes, 0);
       for (uint32_t l = 0; l < 64 && ok; ++l) {
         const uint32_t want = segment_len(h, band, quad, l);
         uint32_t sum = 0, pads = 0;
         for (uint32_t k = 0; k < steps; ++k) {
           const uint32_t c = cb[(uint64_t)(k / kChunkCodes) * kChunkWords + l * kChunkCodes + k % kChunkCodes];
           if (c > h.n_entries) { ok = false; break; }
-          if (c == h.n_entries) { ++pads; continue; }
-          if (pads) { ok = false; break; }   // a real code after a pad
-          sum += run_length(h, c);
-          if (k % kChunkCodes == kChunkCodes - 1 && sum < want) {   // a whole chunk taken, segment not complete
-            reach_lo[k / kChunkCodes] = std::min(reach_lo[k / kChunkCodes], sum);
-            reach_hi[k / kChunkCodes] = std::max(reach_hi[k / kChunkCodes], sum);
+          if (c == h.n_entries) {
+            ++pads;
+          } else {
+            if (pads) { ok = false; break; }   // a real code after a pad
+            sum += run_length(h, c);
+          }
+          if (k % kChunkCodes == kChunkCodes - 1) {   // a whole chunk taken
+            reach_on[k / kChunkCodes] = std::max(reach_on[k / kChunkCodes], sum + pads);
+            if (sum < want) {                         // segment not complete
+              reach_lo[k / kChunkCodes] = std::min(reach_lo[k / kChunkCodes], sum);
+              reach_hi[k / kChunkCodes] = std::max(reach_hi[k / kChunkCodes], sum);
+            }
           }
         }
         if (sum != want) ok = false;
         real += steps - pads;
         over = std::max(over, want + pad_advance * pads);
       }
-      for (size_t k = 0; ok && k < reach_lo.size(); ++k)
-        if (reach_hi[k] > reach_lo[k] && reach_lo[k] != UINT32_MAX) {
-          wide = std::max(wide, reach_hi[k] - reach_lo[k]);
-          if (reach_hi[k] - reach_lo[k] > kWideSpread) last_wide = u + 1;
-        }
+      bool apart = false;
+      for (size_t k = 0; ok && k < reach_lo.size() && reach_lo[k] != UINT32_MAX; ++k) {   // (until all are finished)
+        wide = std::max(wide, reach_hi[k] - reach_lo[k]);
+        apart = apart || reach_on[k] > reach_lo[k] + kRingSpread;
+      }
+      if (apart) mine.push_back((uint32_t)u);
       if (!ok) {
         uint64_t cur = first_bad.load();
         while (u < cur && !first_bad.compare_exchange_weak(cur, u)) {}
@@ -127,10 +140,12 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
     real_codes += real;
     uint32_t cur = overrun.load();
     while (over > cur && !overrun.compare_exchange_weak(cur, over)) {}
-    uint64_t cur_unit = wide_units.load();
-    while (last_wide > cur_unit && !wide_units.compare_exchange_weak(cur_unit, last_wide)) {}
     cur = spread.load();
     while (wide > cur && !spread.compare_exchange_weak(cur, wide)) {}
+    if (!mine.empty()) {
+      std::lock_guard<std::mutex> lock(wide_mutex);
+      wide_units.insert(wide_units.end(), mine.begin(), mine.end());
+    }
   };
   if (n_threads <= 1) {
     work(0, n_units);
@@ -148,7 +163,8 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   if (facts_out) {
     facts_out->max_lane_reach = overrun.load();
     facts_out->max_lane_spread = spread.load();
-    facts_out->wide_units = wide_units.load();
+    std::sort(wide_units.begin(), wide_units.end());
+    facts_out->wide_units = std::move(wide_units);
   }
   return TQ_OK;
 }

@@ -35,6 +35,7 @@
 
 #include "../../include/tq.h"
 #include "tq_format.h"
+#include "tq_level.h"
 #include "tq_kernels_common.h"
 #include "tq_plan.h"
 #include "tq_kernel_dot.h"
@@ -80,6 +81,18 @@ __global__ __launch_bounds__(64) void k_write_table(TableWrite w) {
     const uint64_t px = (uint64_t)w.j[t].x, py = (uint64_t)w.j[t].y;
     const uint32_t tail[4] = {(uint32_t)px, (uint32_t)(px >> 32), (uint32_t)py, (uint32_t)(py >> 32)};
     dst[k] = tail[k - kDescDwords];
+  }
+}
+
+// The pads of a matrix with runs of at most 2 bytes become code 0, a single byte of value 0: a lane that has finished goes on
+// by a column a code, no faster than any other lane, and never gets further ahead of them than it was (see tq_plan.h).
+__global__ __launch_bounds__(256) void k_replace_pads(uint4* codes, uint64_t n16, uint32_t pad) {
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (uint64_t)gridDim.x * 256) {
+    uint4 v = codes[i];
+    uint32_t* w = (uint32_t*)&v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = ((w[k] & 0xFFFFu) == pad ? 0u : w[k] & 0xFFFFu) | (w[k] >> 16 == pad ? 0u : w[k] & 0xFFFF0000u);
+    codes[i] = v;
   }
 }
 
@@ -371,8 +384,22 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   // on different LDS banks when seg_cols is a multiple of 32.
   m.x_span = h.seg_cols + (h.seg_cols % 32 == 0 ? 16u : 0u);
   m.seg_magic = (uint32_t)((1ull << 32) / h.seg_cols) + 1;   // exact quotient while col * seg_cols < 2^32
-  // (LZW starts with single bytes: the units whose lanes drift far apart are the first ones of the matrix a dictionary starts with)
-  m.reserved = long_runs || facts.max_lane_spread > kRingSpreadCareful || facts.wide_units > 0xFFFFFFF0ull ? 0u : 1u + (uint32_t)facts.wide_units;
+  // The units whose lanes are further apart than the ring kernels take are brought closer together (level_unit).
+  const uint32_t* blob_uoff = (const uint32_t*)((const uint8_t*)blob + h.off_uoff);
+  std::vector<uint16_t> level;
+  m.ring = !long_runs;
+  if (m.ring) {
+    size_t words = 0;
+    for (uint32_t u : facts.wide_units) words += (size_t)(blob_uoff[u + 1] - blob_uoff[u]) * kChunkWords;
+    level.resize(words);
+    words = 0;
+    for (uint32_t u : facts.wide_units) {
+      const uint32_t chunks = blob_uoff[u + 1] - blob_uoff[u];
+      m.ring = m.ring && level_unit((const uint16_t*)((const uint8_t*)blob + h.off_codes) + (uint64_t)blob_uoff[u] * kChunkWords, chunks, h.n_entries,
+                                    (const uint32_t*)((const uint8_t*)blob + h.off_dict), kRingSpread, level.data() + words);
+      words += (size_t)chunks * kChunkWords;
+    }
+  }
   m.packing = h.packing;
   m.long_runs = long_runs ? 1u : 0u;
   m.class2 = h.class_end[1];
@@ -432,6 +459,21 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   e = hipMemcpy(base + o_uoff, src + h.off_uoff, h.uoff_bytes, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(base + o_codes, src + h.off_codes, h.code_bytes, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(base + o_scales, src + h.off_scales, h.scale_bytes, hipMemcpyHostToDevice);
+  if (m.ring) {
+    // (units in a row go up together: they are the first of the matrix a dictionary starts with)
+    size_t at = 0;
+    for (size_t i = 0, j; i < facts.wide_units.size() && e == hipSuccess; i = j) {
+      for (j = i + 1; j < facts.wide_units.size() && facts.wide_units[j] == facts.wide_units[j - 1] + 1;) ++j;
+      const uint64_t first = blob_uoff[facts.wide_units[i]], n = blob_uoff[facts.wide_units[j - 1] + 1] - first;
+      e = hipMemcpy(base + o_codes + first * kChunkWords * 2, level.data() + at, n * kChunkWords * 2, hipMemcpyHostToDevice);
+      at += n * kChunkWords;
+    }
+  }
+  if (!long_runs && e == hipSuccess) {
+    const uint64_t n16 = h.code_bytes / 16;
+    hipLaunchKernelGGL(k_replace_pads, dim3((unsigned)std::min<uint64_t>((n16 + 255) / 256, 4096)), dim3(256), 0, nullptr, (uint4*)(base + o_codes), n16, h.pad_code);
+    e = hipGetLastError();
+  }
   m.dict = dict->dev;
   m.dict_bf16 = dict->dev_bf16;
   m.uoff = (const uint32_t*)(base + o_uoff);
@@ -513,7 +555,7 @@ uint64_t even_cut_cost(int n, const tq_handle* hs, uint64_t grid) {
 
 // Whether k_matvec_runs takes a matrix: any but those whose lanes drift too far apart for a ring (or that hold runs of 3 and 4
 // bytes), and those narrower than one activation fragment.
-bool runs_eligible(const tq_matrix* t) { return t->m.reserved != 0 && (t->m.packing ? 2 : 1) * t->m.cols >= 8; }
+bool runs_eligible(const tq_matrix* t) { return t->m.ring && (t->m.packing ? 2 : 1) * t->m.cols >= 8; }
 
 // One kernel launch for hs[0..n), all on one device, total cost below 2^32; n <= kMaxMulti, or n <= kMaxStep when the
 // launch is recorded for a prepared step (rec: its jobs then go to the step's device table, not into the arguments).
@@ -665,7 +707,7 @@ uint64_t ring_min_bands_per_cu(int batch) { return g_ring_min_bands.load(std::me
 bool ring_eligible(const tq_matrix* t, const void* x) {
   const DevMat& m = t->m;
   const uint32_t seg_weights = (m.packing ? 2u : 1u) * m.seg_cols;   // what the activation tile of a quad is sized by
-  return m.reserved != 0 && m.cols % (kUnitPanels * m.seg_cols) == 0 && m.seg_cols % (8 * kRingGroup) == 0 &&
+  return m.ring && m.cols % (kUnitPanels * m.seg_cols) == 0 && m.seg_cols % (8 * kRingGroup) == 0 &&
          seg_weights <= kRingMaxSeg && (uintptr_t)x % 16 == 0 &&
          round_up((uint64_t)m.dict_words * 2, kRingBytes) + (size_t)kRingWaves * 64 * kRingBytes + ring_x_tile(16) + 128 <= kLdsLimit;
 }

@@ -110,9 +110,8 @@ struct BlobFacts {
   uint32_t max_lane_spread;  // the 64 lanes of a unit take their chunks in step; after any number of chunks, the lanes whose
                              // segment is not yet complete have reached different columns of it: the largest difference
                              // between two of them, over all units and all chunk counts
-  uint64_t wide_units;       // units up to and including the last one in which that difference exceeds kWideSpread
+  std::vector<uint32_t> wide_units;   // the units whose lanes are further apart than the ring kernels take (see level_unit)
 };
-constexpr uint32_t kWideSpread = 65;   // columns between a unit's lanes that the ring kernels' fast form stands
 
 // Host-side structural validation; fills *hdr_out with a copy of the header on success.
 int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* facts_out, unsigned n_threads);

@@ -14,11 +14,8 @@ namespace tq {
 // unfinished lane has passed the next kRingGroup windows (one compare and a look at the condition mask) and, if so,
 // multiplies them; a lane advances by at most 8 columns per chunk, so one group per look keeps up.  Bytes of the ring
 // are reused kRingBytes columns later: a lane writes 8-byte piece q only when q + 8 - kRingBytes <= done, which holds
-// whenever no two unfinished lanes are ever more than kRingSpread columns apart (derived in tq_plan.h); the host checks that
-// for every unit when the container is loaded.  Units that do not keep it are decoded in a careful mode - a look after every
-// chunk and one MFMA step at a time, which absorbs a distance of kRingSpreadCareful columns (the first units of a matrix
-// that starts a dictionary, where early segments are still all single bytes, need that); a matrix with a unit beyond that
-// goes to the whole-strip kernel.
+// whenever no lane is ever more than kRingSpread columns ahead of an unfinished one (derived in tq_plan.h); the host sees to
+// that for every unit when the container is loaded (level_unit); a matrix where it cannot goes to the whole-strip kernel.
 // Piece p (8 bytes) of lane l lives at p ^ (l & 15) within the lane's ring: when the 64 lanes read the same window, the
 // 16 lanes served together hit different banks.
 //
@@ -67,12 +64,12 @@ typedef __attribute__((address_space(3))) const u32x4 lds_cu128;
 constexpr uint32_t kNoBand = 0xFFFFFFFFu;
 // kPacked: the ring holds packed 4-bit weights; an 8-byte piece is then two MFMA steps (16 columns), and the activation
 // tile has two windows per piece.
-template <bool kCareful, int kRows, bool kPacked, typename Claim, typename OnUnit>
+template <int kRows, bool kPacked, typename Claim, typename OnUnit>
 __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad, uint32_t first_band, Claim&& claim, int lane, uint32_t ring,
                                                   uint32_t xfrag, OnUnit&& on_unit) {
   if (first_band == kNoBand) return;
-  constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
-  constexpr int kFold = kCareful ? 1 : 16 / kRows;   // windows per B operand (fold_sums)
+  constexpr int kP = kRingPiece, kG = kRingGroup, kLook = kRingStep;
+  constexpr int kFold = 16 / kRows;   // windows per B operand (fold_sums)
   const uint32_t sw8 = (uint32_t)(lane & 15) << 3;
   const uint32_t n_win8 = m.seg_cols;
   // a row past the end of the matrix has no segment: its lane decodes nothing
@@ -248,9 +245,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
         return b < n_bands ? band_lo + b : kNoBand;
       }
     };
-    // 16 columns of a B operand: 16 / kRows windows of kRows rows (fold_sums); the careful form takes one window, its lanes
-    // past kRows repeat a row (their sums are not stored)
-    const uint32_t xfrag = xtile + ((uint32_t)kg * n_win * kRows + bn) * 16, xfrag_careful = xtile + ((uint32_t)kg * n_win * kRows + (bn & (kRows - 1))) * 16;
+    // 16 columns of a B operand: 16 / kRows windows of kRows rows (fold_sums)
+    const uint32_t xfrag = xtile + ((uint32_t)kg * n_win * kRows + bn) * 16;
     // Activation tile of a quad: piece ((panel * n_win + w) * kRows + batch row) holds 8 columns; rows past the batch are
     // zero.  The pieces of the next quad's tile are requested into registers before this quad is decoded and written
     // to LDS when everybody has finished it, so that nobody waits for device memory between two quads.
@@ -319,8 +315,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
           }
           request_scales(next_band);
         };
-        if (m.reserved - 1 > band_lo * nq) decode_units_ring<true, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag_careful, finish_unit);
-        else decode_units_ring<false, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
+        decode_units_ring<kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
       }
       if constexpr (kGateUp) {
 #pragma unroll

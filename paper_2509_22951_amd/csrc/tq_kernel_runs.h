@@ -42,14 +42,14 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
 // the run (see kSplit in k_matvec_runs): started says that the lanes stand at column `start` of the first one, and what
 // a lane has not written itself counts as zeros.  x: the activations, row_first: where the
 // batch row of this lane's B operand starts; part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
-// kFold: windows per B operand (fold_sums); the careful form takes them one by one.
-template <bool kCareful, bool kPacked, int kFoldMost, typename OnUnit>
+// kFold: windows per B operand (fold_sums).
+template <bool kPacked, int kFold, typename OnUnit>
 __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, uint32_t start,
                                                 global_cu16* x, uint32_t row_first, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
   if (u0 >= u1 || c0 >= c_end) return;
-  constexpr int kP = kRingPiece, kG = kCareful ? 1 : kRingGroup, kLook = kCareful ? 1 : kRingStep;
+  constexpr int kP = kRingPiece, kG = kRingGroup, kLook = kRingStep;
   constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
-  constexpr uint32_t kFold = kCareful ? 1u : (uint32_t)kFoldMost, kLoads = kG * pk / kFold;
+  constexpr uint32_t kLoads = kG * pk / kFold;
   const uint32_t behind = (lane & 15) / (16 / kFold) * 8;   // the columns this lane's window lies behind the operand's first
   const uint32_t sw8 = (uint32_t)(lane & 15) << 3, kg = (uint32_t)lane >> 4;
   const uint32_t nq = m.n_quads, n_panels = (m.cols + m.seg_cols - 1) / m.seg_cols, x_cols = pk * m.cols;
@@ -289,14 +289,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    // units whose lanes drift far apart come first: see DevMat::reserved
-    const uint32_t u_care = min(max(m.reserved - 1, run.u0), run.u1);
-    const uint32_t c_care = u_care == run.u0 ? run.c0 : u_care == run.u1 ? run.c_end : unit_offset(m, u_care);
     global_cu16* x = (global_cu16*)job.x;
     // lanes past the batch repeat its last row: their sums are never stored
     const uint32_t row_first = min((uint32_t)(lane & 15) % (16 / kFold), (uint32_t)a.batch - 1) * (kPacked ? 2 : 1) * m.cols;
-    decode_run_ring<true, kPacked, kFold>(m, run.u0, u_care, run.c0, c_care, run.head, start, x, row_first, lane, ring, part, on_unit);
-    decode_run_ring<false, kPacked, kFold>(m, u_care, run.u1, c_care, run.c_end, run.head && u_care == run.u0, start, x, row_first, lane, ring, part, on_unit);
+    decode_run_ring<kPacked, kFold>(m, run.u0, run.u1, run.c0, run.c_end, run.head, start, x, row_first, lane, ring, part, on_unit);
     if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, fold_sums<kFold>(part), lane);
     __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
     sums.combine(a, job, m, rings, wave, kWaves, lane);

@@ -1,0 +1,74 @@
+// The code stream of a unit as the device keeps it, where that differs from the container's.  Host code, no GPU needed.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+#include "tq_format.h"
+
+namespace tq {
+
+// Lanes close together.  The ring kernels hold a short stretch of every lane's segment and multiply what all lanes of a unit
+// have passed, so the lanes may not be further apart than the ring is long.  In the first units of a matrix that starts a
+// dictionary they are: some segments are still all single bytes, others all pairs.  A lane that is ahead can wait: any pair
+// may be written as its two single bytes (codes 0..255 are the single bytes), which takes a code more for the same columns,
+// and a lane that is ahead has codes to spare, for its stream is filled up with pads to the length of the longest.  So the
+// unit keeps its length and its weights; only which of its codes are pairs changes.
+//
+// codes: the unit's n_chunks chunks as the container holds them (valid, runs of at most 2 bytes); word: the dictionary's.
+// out: the same chunks with no lane ever more than `limit` columns ahead of an unfinished one after a chunk, lanes that have
+// finished going on by a column a code, as the device's pads do (code 0, a single byte of value 0).  False when that cannot be
+// done within the unit's length (a lane that is ahead now and slower than the others later on).
+inline bool level_unit(const uint16_t* codes, uint32_t n_chunks, uint32_t n_entries, const uint32_t* word, uint32_t limit, uint16_t* out) {
+  struct Lane {
+    uint32_t next = 0, n = 0;   // codes taken, codes there are
+    uint32_t pos = 0;           // columns passed
+    int half = -1;              // second byte of a pair of which the first has been written
+    bool finished() const { return next == n && half < 0; }
+  };
+  Lane lane[64];
+  auto code = [&](uint32_t l, uint32_t k) { return codes[(size_t)(k / kChunkCodes) * kChunkWords + l * kChunkCodes + k % kChunkCodes]; };
+  for (uint32_t l = 0; l < 64; ++l)
+    while (lane[l].n < n_chunks * kChunkCodes && code(l, lane[l].n) != n_entries) ++lane[l].n;
+  // One chunk of a lane that may come to column `most`; false: it has no codes to spare for that.
+  auto take = [&](uint32_t l, uint32_t chunk, uint64_t most, Lane& s) {
+    for (uint32_t j = 0; j < kChunkCodes; ++j) {
+      const uint32_t left = kChunkCodes - 1 - j;   // codes of the chunk that follow, of at least a column each
+      uint16_t c = 0;
+      if (s.half >= 0) {
+        c = (uint16_t)s.half;
+        s.half = -1;
+      } else if (s.next < s.n) {
+        c = code(l, s.next++);
+        if (c >= 256 && s.pos + 2 + left > most) {
+          if (s.n - s.next >= (n_chunks - chunk) * kChunkCodes - 1 - j) return false;   // (two codes in the place of one must fit)
+          s.half = (int)(word[c] >> 8 & 0xFF);
+          c = (uint16_t)(word[c] & 0xFF);
+        }
+      }
+      s.pos += c >= 256 ? 2 : 1;
+      out[(size_t)chunk * kChunkWords + l * kChunkCodes + j] = c;
+    }
+    return true;
+  };
+  for (uint32_t chunk = 0; chunk < n_chunks; ++chunk) {
+    Lane before[64];
+    std::copy(lane, lane + 64, before);
+    uint32_t least = UINT32_MAX;
+    for (uint32_t l = 0; l < 64; ++l) {
+      take(l, chunk, UINT64_MAX, lane[l]);
+      if (!lane[l].finished()) least = std::min(least, lane[l].pos);
+    }
+    if (least == UINT32_MAX) continue;   // (all finished; what follows is pads)
+    for (uint32_t l = 0; l < 64; ++l)
+      if (lane[l].pos > least + limit) {
+        lane[l] = before[l];
+        if (!take(l, chunk, (uint64_t)least + limit, lane[l]) || lane[l].pos > least + limit) return false;
+      }
+  }
+  for (const Lane& l : lane)
+    if (!l.finished()) return false;
+  return true;
+}
+
+}  // namespace tq

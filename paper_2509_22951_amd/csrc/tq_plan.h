@@ -7,7 +7,7 @@
 #include "tq_format.h"
 
 #if defined(__HIPCC__)
-#define TQ_HD __host__ __device__ __forceinline__
+#define TQ_HD __host__ __device__ inline __attribute__((always_inline))
 #else
 #define TQ_HD inline
 #endif
@@ -52,7 +52,6 @@ static_assert(kRingPiece % kRingStep == 0 && kRingGroup == 4 && kRingStep <= kRi
 //    still holds columns the look is about to multiply.  Nothing of the lane lies in that piece yet: see ring_leftover.
 constexpr uint32_t kRingSpread = kRingBytes - 8 * kRingStep - 8 * kRingGroup + 1;
 constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;
-static_assert(kRingSpread == kWideSpread, "what the validator counts as a wide unit");
 // Whether a lane that stands at column pos holds bytes of a piece it has not stored (see append_chunk_ring): a unit whose
 // segments end inside pieces stores those at every look - those only, never the piece that begins at pos.
 TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }

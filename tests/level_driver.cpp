@@ -1,0 +1,98 @@
+// Host-only exercise of level_unit (csrc/tq_level.h): units whose lanes run apart, brought closer together.  Every lane has to
+// stand for the same bytes, and no lane may be more than the limit ahead of an unfinished one after any chunk.
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "../paper_2509_22951_amd/csrc/tq_level.h"
+
+using Codes = std::vector<uint16_t>;
+static uint64_t state = 88172645463325252ull;
+static uint32_t rnd(uint32_t n) {
+  state ^= state << 13, state ^= state >> 7, state ^= state << 17;
+  return (uint32_t)(state % n);
+}
+
+int main() {
+  const uint32_t n_entries = 1000, pad = n_entries;
+  std::vector<uint32_t> word(n_entries + 1, 0);
+  for (uint32_t c = 0; c < n_entries; ++c) word[c] = c < 256 ? c : rnd(65536);
+  int levelled = 0, refused = 0, late = 0;
+  for (int trial = 0; trial < 4000; ++trial) {
+    const uint32_t limit = trial % 3 == 0 ? 65 : 36, seg = 16 * (1 + rnd(64)), shorter = rnd(4) ? seg : rnd(seg);
+    const uint32_t turn = trial % 4 == 3 ? seg / 2 : seg;   // some units: the lanes change places half way
+    // lane l takes pairs with a probability of its own
+    std::vector<std::vector<uint16_t>> lane(64);
+    uint32_t longest = 1;
+    for (uint32_t l = 0; l < 64; ++l) {
+      const uint32_t len = trial % 5 == 0 && l % 16 == 15 ? 0 : l >= 48 ? shorter : seg, share = trial % 2 ? rnd(101) : l * 100 / 63;
+      for (uint32_t pos = 0; pos < len;) {
+        const bool pair = pos + 2 <= len && rnd(100) < (pos < turn ? share : 100 - share);
+        lane[l].push_back((uint16_t)(pair ? 256 + rnd(n_entries - 256) : rnd(256)));
+        pos += pair ? 2 : 1;
+      }
+      longest = std::max<uint32_t>(longest, lane[l].size());
+    }
+    const uint32_t n_chunks = (longest + 3) / 4 + (rnd(8) == 0);
+    Codes in((size_t)n_chunks * tq::kChunkWords, (uint16_t)pad), out(in.size(), 0xFFFF);
+    auto at = [](uint32_t l, uint32_t k) { return (size_t)(k / 4) * tq::kChunkWords + 4 * l + k % 4; };
+    for (uint32_t l = 0; l < 64; ++l)
+      for (uint32_t k = 0; k < lane[l].size(); ++k) in[at(l, k)] = lane[l][k];
+    if (!tq::level_unit(in.data(), n_chunks, n_entries, word.data(), limit, out.data())) {
+      ++refused;
+      if (turn == seg) {   // a lane that is ahead to the end can always wait
+        std::printf("trial %d: refused\n", trial);
+        return 1;
+      }
+      continue;
+    }
+    std::vector<uint32_t> pos(64, 0), len(64, 0);
+    for (uint32_t l = 0; l < 64; ++l) {
+      std::vector<uint8_t> want, got;
+      for (uint16_t c : lane[l]) {
+        want.push_back((uint8_t)word[c]);
+        if (c >= 256) want.push_back((uint8_t)(word[c] >> 8));
+      }
+      for (uint32_t k = 0; k < 4 * n_chunks; ++k) {
+        const uint16_t c = out[at(l, k)];
+        if (c >= n_entries || (got.size() >= want.size() && c != 0)) {
+          std::printf("trial %d, lane %u, code %u: %u\n", trial, l, k, c);
+          return 1;
+        }
+        got.push_back((uint8_t)word[c]);
+        if (c >= 256) got.push_back((uint8_t)(word[c] >> 8));
+      }
+      len[l] = want.size();
+      if (got.size() < want.size() || !std::equal(want.begin(), want.end(), got.begin())) {
+        std::printf("trial %d, lane %u: other bytes\n", trial, l);
+        return 1;
+      }
+    }
+    uint32_t far = 0, before = 0;
+    std::vector<uint32_t> was(64, 0);
+    for (uint32_t chunk = 0; chunk < n_chunks; ++chunk) {
+      uint32_t least = UINT32_MAX, most = 0, least0 = UINT32_MAX, most0 = 0;
+      for (uint32_t l = 0; l < 64; ++l) {
+        for (uint32_t k = 4 * chunk; k < 4 * chunk + 4; ++k) {
+          pos[l] += out[at(l, k)] >= 256 ? 2 : 1;
+          was[l] += k < lane[l].size() && lane[l][k] >= 256 ? 2 : 1;
+        }
+        most = std::max(most, pos[l]);
+        most0 = std::max(most0, was[l]);
+        if (pos[l] < len[l]) least = std::min(least, pos[l]);
+        if (was[l] < len[l]) least0 = std::min(least0, was[l]);
+      }
+      if (least != UINT32_MAX) far = std::max(far, most - least);
+      if (least0 != UINT32_MAX) before = std::max(before, most0 - least0);
+    }
+    if (far > limit) {
+      std::printf("trial %d: %u columns apart, %u before, limit %u\n", trial, far, before, limit);
+      return 1;
+    }
+    levelled += before > limit;
+    late += before > limit && turn < seg;
+  }
+  std::printf("%d units brought together (%d of them with lanes that change places), %d refused\n", levelled, late, refused);
+  return levelled > 1000 && refused > 0 ? 0 : 1;
+}
