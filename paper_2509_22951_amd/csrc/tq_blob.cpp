@@ -129,7 +129,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
       bool apart = false;
       for (size_t k = 0; ok && k < reach_lo.size() && reach_lo[k] != UINT32_MAX; ++k) {   // (until all are finished)
         wide = std::max(wide, reach_hi[k] - reach_lo[k]);
-        apart = apart || reach_on[k] > reach_lo[k] + kRingSpread;
+        apart = apart || reach_on[k] > reach_lo[k] + kSmallRingSpread;
       }
       if (apart) mine.push_back((uint32_t)u);
       if (!ok) {

@@ -299,18 +299,26 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_runs<kRunWavesPacked, true, 1>,
     (const void*)k_matvec_runs<kRunWavesPacked, true, 2>,
     (const void*)k_matvec_runs<kRunWavesPacked, true, 4>,
-    (const void*)k_matvec_ring<kRingWaves, 16, false>,
-    (const void*)k_matvec_ring<kRingWavesHalf, 8, false>,
-    (const void*)k_matvec_ring<kRingWaves, 16, true>,
-    (const void*)k_matvec_ring<kRingWavesHalf, 8, true>,
-    (const void*)k_matvec_ring<kRingWavesMore, 8, false>,
-    (const void*)k_matvec_ring<kRingWavesMore, 8, true>,
-    (const void*)k_matvec_ring<kRingWavesQuarter, 4, false>,
-    (const void*)k_matvec_ring<kRingWavesQuarter, 4, true>,
-    (const void*)k_matvec_ring<kRingWaves, 16, false, true>,
-    (const void*)k_matvec_ring<kRingWaves, 16, true, true>,
-    (const void*)k_matvec_ring<kRingWaves, 8, false, true>,
-    (const void*)k_matvec_ring<kRingWaves, 8, true, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, false>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, false>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, false>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, false, true>,
+    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, true, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, false>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, false>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, false, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, true, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, false, true>,
+    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, true, true>,
 };
 
 // Once per matrix creation (cheap): dynamic LDS above 64 KB has to be allowed per kernel function, and the kernels'
@@ -387,18 +395,23 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   // The units whose lanes are further apart than the ring kernels take are brought closer together (level_unit).
   const uint32_t* blob_uoff = (const uint32_t*)((const uint8_t*)blob + h.off_uoff);
   std::vector<uint16_t> level;
-  m.ring = !long_runs;
-  if (m.ring) {
+  m.ring = 0;
+  if (!long_runs) {
     size_t words = 0;
     for (uint32_t u : facts.wide_units) words += (size_t)(blob_uoff[u + 1] - blob_uoff[u]) * kChunkWords;
     level.resize(words);
-    words = 0;
-    for (uint32_t u : facts.wide_units) {
-      const uint32_t chunks = blob_uoff[u + 1] - blob_uoff[u];
-      m.ring = m.ring && level_unit((const uint16_t*)((const uint8_t*)blob + h.off_codes) + (uint64_t)blob_uoff[u] * kChunkWords, chunks, h.n_entries,
-                                    (const uint32_t*)((const uint8_t*)blob + h.off_dict), kRingSpread, level.data() + words);
-      words += (size_t)chunks * kChunkWords;
-    }
+    auto level_to = [&](uint32_t limit) {
+      size_t at = 0;
+      for (uint32_t u : facts.wide_units) {
+        const uint32_t chunks = blob_uoff[u + 1] - blob_uoff[u];
+        if (!level_unit((const uint16_t*)((const uint8_t*)blob + h.off_codes) + (uint64_t)blob_uoff[u] * kChunkWords, chunks, h.n_entries,
+                        (const uint32_t*)((const uint8_t*)blob + h.off_dict), limit, level.data() + at))
+          return false;
+        at += (size_t)chunks * kChunkWords;
+      }
+      return true;
+    };
+    m.ring = level_to(kSmallRingSpread) ? 2u : level_to(kRingSpread) ? 1u : 0u;
   }
   m.packing = h.packing;
   m.long_runs = long_runs ? 1u : 0u;
@@ -574,7 +587,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   p.what = op == Op::kDecompress ? "tq_decompress launch" : "tq_matvec launch";
   a.table = rec ? (const StepEntry*)(uintptr_t)8 : nullptr;   // (the address follows when the step's table is in device memory)
   uint32_t dict_words_max = 0, x_dwords_max = 0, seg_max = 0, dict16_max = 0;
-  bool runs = op == Op::kMatvec;
+  bool runs = op == Op::kMatvec, small = true;
   uint64_t cost = 0, bands = 0, band_cost_max = 1;
   bool x_fast = true;
   for (int i = 0; i < n; ++i) {
@@ -597,6 +610,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     x_dwords_max = std::max(x_dwords_max, t->m.x_dwords);
     seg_max = std::max(seg_max, t->m.seg_cols);
     runs = runs && runs_eligible(t);
+    small = small && t->m.ring == 2;
     x_fast = x_fast && (t->m.packing ? 2 : 1) * t->m.cols % 8 == 0 && xs && (uintptr_t)xs[i] % 16 == 0;
   }
   a.u.cost_long[n] = (uint32_t)cost;
@@ -637,25 +651,30 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     // address) | the activation tile of one quad.
     const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
     a.x_off = (uint32_t)dict16;
-    a.tile_area = 64 * kRingBytes;
-    const bool half = batch <= 8;   // 8 batch rows in the tile: room for two more wavefronts
-    const bool more = half && !gate_up && dict16 + (size_t)kRingWavesMore * a.tile_area + ring_x_tile(8) + 128 <= kLdsLimit;   // a smaller dictionary leaves room
+    a.tile_area = 64 * (small ? kSmallRingBytes : kRingBytes);
+    const bool half = batch <= 8;   // 8 batch rows in the tile: room for two more wavefronts beside large rings
+    const bool more = !small && half && !gate_up && dict16 + (size_t)kRingWavesMore * a.tile_area + ring_x_tile(8) + 128 <= kLdsLimit;   // a smaller dictionary leaves room
     // batches up to 4 beside a dictionary too large for that: a tile of 4 rows leaves room for one wavefront more
-    const bool quarter = !more && !gate_up && batch <= 4 && dict16 + (size_t)kRingWavesQuarter * a.tile_area + ring_x_tile(4) + 128 <= kLdsLimit;
-    const int waves = more ? kRingWavesMore : quarter ? kRingWavesQuarter : half && !gate_up ? kRingWavesHalf : kRingWaves;   // (gated pairs hold sums in registers)
+    const bool quarter = !small && !more && !gate_up && batch <= 4 && dict16 + (size_t)kRingWavesQuarter * a.tile_area + ring_x_tile(4) + 128 <= kLdsLimit;
+    const int waves = small ? (gate_up ? kRingWavesSmallGated : kRingWavesSmall) : more ? kRingWavesMore : quarter ? kRingWavesQuarter : half && !gate_up ? kRingWavesHalf : kRingWaves;   // (gated pairs hold sums in registers)
     a.slot_off = (uint32_t)(dict16 + (size_t)waves * a.tile_area);
     p.lds = a.slot_off + ring_x_tile(quarter ? 4 : half ? 8 : 16) + 128;   // + the band counter
     if (p.lds > kLdsLimit || !x_fast) {
       set_error("internal: ring launch with a dictionary or activations that do not fit it");
       return TQ_E_UNSUPPORTED;
     }
-    if (gate_up) {
-      if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 8, true, true> : (const void*)k_matvec_ring<kRingWaves, 8, false, true>;
-      else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true, true> : (const void*)k_matvec_ring<kRingWaves, 16, false, true>;
-    } else if (more) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesMore, 8, true> : (const void*)k_matvec_ring<kRingWavesMore, 8, false>;
-    else if (quarter) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesQuarter, 4, true> : (const void*)k_matvec_ring<kRingWavesQuarter, 4, false>;
-    else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesHalf, 8, true> : (const void*)k_matvec_ring<kRingWavesHalf, 8, false>;
-    else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingWaves, 16, false>;
+    if (small) {
+      if (gate_up && half) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, true, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, false, true>;
+      else if (gate_up) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, true, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, false, true>;
+      else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, false>;
+      else p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, false>;
+    } else if (gate_up) {
+      if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, true, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, false, true>;
+      else p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false, true>;
+    } else if (more) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, false>;
+    else if (quarter) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, false>;
+    else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, false>;
+    else p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false>;
     p.block = (unsigned)waves * 64;
   } else if (op == Op::kMatvec && runs) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size) | a count per lane

@@ -6,17 +6,18 @@
 
 namespace tq {
 // ---------------------------------------------------------------------------------------------------------------
-// The batched product with a ring of kRingBytes per lane in place of the whole strip, and the activations in LDS.
+// The batched product with a ring of kRing bytes per lane (128, or 64) in place of the whole strip, and the activations in LDS.
 //
 // The 16 rows of a band take their codes in step but reach different columns, so some per-lane storage has to bring
 // them back into line before an MFMA can take 8 columns of all of them; what it has to hold is only the distance
-// between the slowest and the fastest lane, not the segment.  Every kRingStep chunks the wavefront asks whether every
-// unfinished lane has passed the next kRingGroup windows (one compare and a look at the condition mask) and, if so,
+// between the slowest and the fastest lane, not the segment.  Every ring_step chunks the wavefront asks whether every
+// lane has passed the next ring_group windows (one compare and a look at the condition mask) and, if so,
 // multiplies them; a lane advances by at most 8 columns per chunk, so one group per look keeps up.  Bytes of the ring
-// are reused kRingBytes columns later: a lane writes 8-byte piece q only when q + 8 - kRingBytes <= done, which holds
-// whenever no lane is ever more than kRingSpread columns ahead of an unfinished one (derived in tq_plan.h); the host sees to
-// that for every unit when the container is loaded (level_unit); a matrix where it cannot goes to the whole-strip kernel.
-// Piece p (8 bytes) of lane l lives at p ^ (l & 15) within the lane's ring: when the 64 lanes read the same window, the
+// are reused kRing columns later: a lane writes 8-byte piece q only when q + 8 - kRing <= done, which holds
+// whenever no lane is ever more than ring_spread columns ahead of an unfinished one (derived in tq_plan.h); the host sees to
+// that for every unit when the container is loaded (level_unit): 33 columns for the small ring, which nearly every matrix
+// keeps, else 65; a matrix where it cannot goes to the whole-strip kernel.
+// Piece p (8 bytes) of lane l lives at p ^ swizzle(l) within the lane's ring: when the 64 lanes read the same window, the
 // 16 lanes served together hit different banks.
 //
 // With 8 KB of ring per wavefront, 8 wavefronts leave room for the activations of one quad (4 panels) in LDS, laid out
@@ -33,23 +34,35 @@ constexpr int kRingWaves = 8;       // with an activation tile of 16 batch rows
 constexpr int kRingWavesHalf = 10;  // with one of 8 batch rows (batches up to 8): more wavefronts fit next to the smaller tile
 constexpr int kRingWavesMore = 12;  // the same beside a dictionary of at most 24,512 entries
 constexpr int kRingWavesQuarter = 11;   // with a tile of 4 batch rows (batches up to 4) beside a full dictionary
+// With rings of 64 bytes (kSmallRingBytes) there is LDS for 16 wavefronts, and the vector ALUs, which 10 wavefronts keep busy
+// for 75 % of the time, have more to choose from.  Gated pairs keep sums in registers, 16 wavefronts of them spill.  us, rings of 128
+// bytes -> 64 with 16 | 12 wavefronts: eight LLaMA-3.2-3B layers batch 4 225 -> 203 | 222, batch 8 228 -> 208 | 223, batch 16 252 ->
+// 228 | 239, packed weights batch 8 182 -> 151 | 169, batch 16 202 -> 183 | 189; gated pairs of eight blocks batch 8 116 -> 103 |
+// 99, batch 16 119 -> 113 | 102, packed batch 8 92 -> 80 | 77, batch 16 94 -> 90 | 79.  (Two accumulators per wavefront instead of
+// four, which the groups of two windows suggest, made the sums 8 % less exact: hence the turns in multiply_ready.)
+constexpr int kRingWavesSmall = 16, kRingWavesSmallGated = 12;
 constexpr uint32_t kRingMaxSeg = 256;
 constexpr int kRingMinBandsPerCu = 24;   // below that many bands per CU in a launch (half as many above 8 batch rows) k_matvec_runs is faster
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
 
+// 8 * swizzle(lane): lanes 2 (4) apart start on the same bank when a ring is 128 (64) bytes
+template <int kRing>
+__device__ __forceinline__ uint32_t ring_swizzle(int lane) { return (kRing == 128 ? (uint32_t)lane & 15u : (uint32_t)lane >> 2 & 7u) << 3; }
+
 // append_chunk for the ring: the complete 8-byte piece goes to its swizzled place; sw8 = 8 * (lane & 15).
-// pos never passes seg_len (pad codes fall off the end), and a piece is complete when pos crosses a multiple of 8.
+// kClamp: pos never passes seg_len (pad codes fall off the end).  A piece is complete when pos crosses a multiple of 8.
+template <int kRing, bool kClamp>
 __device__ __forceinline__ void append_chunk_ring(uint2 c, uint32_t ring, uint32_t sw8, uint32_t seg_len, uint32_t& pos, uint64_t& carry) {
   uint32_t s0, s1, n;
   chunk_string(c, s0, s1, n);                                           // the 4..8 bytes of the chunk, zero above them
   const uint64_t str = (uint64_t)s1 << 32 | s0;
-  const uint32_t after = min(pos + n, seg_len);
+  const uint32_t after = kClamp ? min(pos + n, seg_len) : pos + n;
   const uint32_t sh = (pos & 7u) << 3;
   const uint64_t lo = carry | str << sh, hi = (str >> 1) >> (63 - sh);  // the 16 bytes carry + string; hi is 0 when pos % 8 == 0
   const bool full = (after ^ pos) >= 8;
   // stored whether the piece is complete or not (an incomplete one holds zeros above its bytes and is stored again,
   // complete, by a later chunk; nobody reads a piece before every lane has passed it): no branch in the chunk's code
-  *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & 0x78u)) = lo;
+  *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & (kRing - 8u))) = lo;
   carry = full ? hi : lo;
   pos = after;
 }
@@ -64,17 +77,18 @@ typedef __attribute__((address_space(3))) const u32x4 lds_cu128;
 constexpr uint32_t kNoBand = 0xFFFFFFFFu;
 // kPacked: the ring holds packed 4-bit weights; an 8-byte piece is then two MFMA steps (16 columns), and the activation
 // tile has two windows per piece.
-template <int kRows, bool kPacked, typename Claim, typename OnUnit>
+template <int kRing, int kRows, bool kPacked, typename Claim, typename OnUnit>
 __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad, uint32_t first_band, Claim&& claim, int lane, uint32_t ring,
                                                   uint32_t xfrag, OnUnit&& on_unit) {
   if (first_band == kNoBand) return;
-  constexpr int kP = kRingPiece, kG = kRingGroup, kLook = kRingStep;
+  constexpr int kP = ring_piece(kRing), kG = ring_group(kRing), kLook = ring_step(kRing), kParts = (kP + kLook - 1) / kLook;
+  static_assert((kP - 1) / kLook == kParts - 1 && (kP - 2) / kLook >= kParts - 2, "the parts of a piece that the loops below request");
   constexpr int kFold = 16 / kRows;   // windows per B operand (fold_sums)
-  const uint32_t sw8 = (uint32_t)(lane & 15) << 3;
+  const uint32_t sw8 = ring_swizzle<kRing>(lane);
   const uint32_t n_win8 = m.seg_cols;
-  // a row past the end of the matrix has no segment: its lane decodes nothing
-  auto segment_length = [&](uint32_t band) { return band != kNoBand && band * kUnitRows + (lane & 15) < m.rows ? m.seg_cols : 0u; };
-  uint32_t cur_band = first_band, seg_len = segment_length(first_band);
+  // A row past the end of the matrix has no segment: its lane holds pads alone and stands behind the last window from the start.
+  auto first_column = [&](uint32_t band) { return band != kNoBand && band * kUnitRows + (lane & 15) < m.rows ? 0u : n_win8; };
+  uint32_t cur_band = first_band;
   // walker over the pieces: the band it is in (the decoder is at most one band behind), pieces left in it, next chunk
   uint32_t w_band = kNoBand, wc = 0, w_left = 0, w_base = 0, w_rem = 0;
   bool w_started = false;
@@ -107,19 +121,21 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
     wc += n;
     ends = --w_left == 0;
   };
-  // Every piece issues exactly kP loads (those past its end repeat its last chunk), kRingStep of them at a time.
+  // Every piece issues exactly kP loads (those past its end repeat its last chunk), kLook of them at a time.
   auto load_part = [&](uint2 (&cw)[kP], uint32_t start, uint32_t n, int part) {
     const uint32_t last = n ? start + n - 1 : start - 1;   // n == 0 (past the last unit, start >= 1): the chunk before, never used
 #pragma unroll
-    for (int k = part * kRingStep; k < (part + 1) * kRingStep; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
+    for (int k = part * kLook; k < (part + 1) * kLook && k < kP; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
   };
-  uint32_t pos = 0, done = 0;
+  uint32_t pos = first_column(first_band), done = 0;
   uint64_t carry = 0;
   f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
   // One group of MFMA steps if every lane that is still decoding has written the columns [done, done + 8 kG).
   // The operands are read before it is known whether the group is ready (volatile: the reads stay ahead of the test),
   // so that their latency overlaps the test; an unready group just reads them again at the next look.
-  auto multiply_ready = [&]() {
+  // look: the looks take the accumulators in turn where a group has fewer windows than there are of them.
+  auto multiply_ready = [&](auto look) {
+    constexpr int kFirst = decltype(look)::value * kG;
     const uint32_t at = min(done, n_win8 - 8 * kG);   // at the unit's end: any place inside the ring and the tile
     const uint32_t base = at ^ sw8;
     constexpr int kX = kPacked ? 2 : 1;             // activation windows per 8-byte piece of the ring
@@ -127,12 +143,12 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
     u32x2 a8[kG];
     u32x4 x8[kG * kX / kFold];
 #pragma unroll
-    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
+    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & (kRing - 8u)));
 #pragma unroll
     for (int k = 0; k < kG * kX / kFold; ++k) x8[k] = *(volatile lds_cu128*)(size_t)(xa + 16 * kRows * kFold * k);
     const uint32_t next = done + 8 * kG;
     if (next > n_win8) return;
-    if (__builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
+    if (__builtin_amdgcn_ballot_w64(pos < next) != 0) return;
 #pragma unroll
     for (int k = 0; k < kG; ++k) {
       if constexpr (kPacked) {
@@ -140,31 +156,38 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
         p0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k / kFold]), p0, 0, 0, 0);
         p1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[(2 * k + 1) / kFold]), p1, 0, 0, 0);
       } else {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), part[k], 0, 0, 0);
+        f32x4& p = part[(kFirst + k) & 3];
+        p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), p, 0, 0, 0);
       }
     }
     done = next;
   };
-  auto decode_piece = [&](const uint2 (&cw)[kP], uint32_t n, bool ends, uint2 (&cw_next)[kP], uint32_t next_start, uint32_t next_n) {
+  auto decode_piece = [&](auto turn, const uint2 (&cw)[kP], uint32_t n, bool ends, uint2 (&cw_next)[kP], uint32_t next_start, uint32_t next_n) {
     if (n == 0) return;
+    constexpr int kTurn = decltype(turn)::value;
     if (n >= kP - 1) {
-#pragma unroll
-      for (int k = 0; k < kP - 1; ++k) {
-        append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
-        if (k % kLook == kLook - 1) multiply_ready();
-        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
-      }
-      if (n == kP) append_chunk_ring(cw[kP - 1], ring, sw8, seg_len, pos, carry);
+      static_for<kP - 1>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        append_chunk_ring<kRing, false>(cw[k], ring, sw8, 0u, pos, carry);
+        if constexpr (k % kLook == kLook - 1) {
+          multiply_ready(std::integral_constant<int, kTurn + k / kLook>{});
+          load_part(cw_next, next_start, next_n, k / kLook);
+        }
+      });
+      if (n == kP) append_chunk_ring<kRing, false>(cw[kP - 1], ring, sw8, 0u, pos, carry);
     } else {
-#pragma unroll
-      for (int k = 0; k < kP - 2; ++k) {
-        if ((uint32_t)k < n) append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
-        if (k % kLook == kLook - 1 && (uint32_t)k + 1 < n) multiply_ready();
-        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
-      }
+      static_for<kP - 2>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        if ((uint32_t)k < n) append_chunk_ring<kRing, false>(cw[k], ring, sw8, 0u, pos, carry);
+        if constexpr (k % kLook == kLook - 1) {
+          if ((uint32_t)k + 1 < n) multiply_ready(std::integral_constant<int, kTurn + k / kLook>{});
+          load_part(cw_next, next_start, next_n, k / kLook);
+        }
+      });
+      if constexpr ((kP - 2) / kLook < kParts - 1) load_part(cw_next, next_start, next_n, kParts - 2);
     }
-    multiply_ready();
-    load_part(cw_next, next_start, next_n, kP / kRingStep - 1);
+    multiply_ready(std::integral_constant<int, kTurn + kParts - 1>{});
+    load_part(cw_next, next_start, next_n, kParts - 1);
     if (ends) {   // every lane is complete and at most one whole group was left: the unit has been multiplied
       // the walker is one piece ahead: w_band is the band of the unit that follows, if there is one
       const uint32_t next_band = w_band == cur_band ? kNoBand : w_band;
@@ -172,8 +195,7 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = f32x4{0.f, 0.f, 0.f, 0.f};
       cur_band = next_band;
-      seg_len = segment_length(cur_band);
-      pos = 0;
+      pos = first_column(cur_band);
       carry = 0;
       done = 0;
     }
@@ -183,23 +205,22 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
   bool ea, eb;
   next_piece(sa, na, ea);
 #pragma unroll
-  for (int j = 0; j < kP / kRingStep; ++j) load_part(cwa, sa, na, j);
+  for (int j = 0; j < kParts; ++j) load_part(cwa, sa, na, j);
   while (na) {   // two register sets: one is decoded while the other is filled
     next_piece(sb, nb, eb);
-    decode_piece(cwa, na, ea, cwb, sb, nb);
+    decode_piece(std::integral_constant<int, 0>{}, cwa, na, ea, cwb, sb, nb);
     next_piece(sa, na, ea);
-    decode_piece(cwb, nb, eb, cwa, sa, na);
+    decode_piece(std::integral_constant<int, kParts & 1>{}, cwb, nb, eb, cwa, sa, na);
   }
 }
 
 // kGateUp: y = silu(gate row) * (up row) needs a band's whole sums, so nothing is added to y: the bands are taken in passes
 // of kGateUpBands per wavefront, each wavefront's bands fixed, with their sums in registers from the first quad to the
-// last.  (The gated pairs of eight LLaMA-3.2-3B blocks, batch 16: 154 us; 207 us on the whole-strip
-// kernel, where they went before.)
-constexpr int kGateUpBands = 4;
-template <int kWaves, int kRows, bool kPacked, bool kGateUp = false>
+// last.  A pass takes 32 bands at least (gated pairs of eight LLaMA-3.2-3B blocks, batch 16, 12 wavefronts: 102 us in one pass of
+// 36 bands, 121 in two of 24).
+template <int kRing, int kWaves, int kRows, bool kPacked, bool kGateUp = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
-  constexpr int kRingThreads = kWaves * 64;
+  constexpr int kRingThreads = kWaves * 64, kGateUpBands = (32 + kWaves - 1) / kWaves;
   constexpr uint32_t kRingXTile = ring_x_tile(kRows);
   extern __shared__ uint4 lds4[];
   uint16_t* lds_dict = (uint16_t*)lds4;
@@ -209,7 +230,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
   const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
   const uint32_t* staged = nullptr;
   const int bn = lane & 15, kg = lane >> 4;   // B operand: batch row and k-group (panel) of this lane
-  const uint32_t ring = rings + (uint32_t)wave * (64 * kRingBytes) + (uint32_t)lane * kRingBytes;
+  const uint32_t ring = rings + (uint32_t)wave * (64 * kRing) + (uint32_t)lane * kRing;
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
     if (hi <= cb) break;
@@ -315,7 +336,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
           }
           request_scales(next_band);
         };
-        decode_units_ring<kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
+        decode_units_ring<kRing, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
       }
       if constexpr (kGateUp) {
 #pragma unroll

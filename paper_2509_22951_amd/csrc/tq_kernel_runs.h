@@ -150,15 +150,15 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     if (n >= kP - 1) {
 #pragma unroll
       for (int k = 0; k < kP - 1; ++k) {
-        append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
+        append_chunk_ring<kRingBytes, true>(cw[k], ring, sw8, seg_len, pos, carry);
         if (k % kLook == kLook - 1) look();
         if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
       }
-      if (n == kP) append_chunk_ring(cw[kP - 1], ring, sw8, seg_len, pos, carry);
+      if (n == kP) append_chunk_ring<kRingBytes, true>(cw[kP - 1], ring, sw8, seg_len, pos, carry);
     } else {
 #pragma unroll
       for (int k = 0; k < kP - 2; ++k) {
-        if ((uint32_t)k < n) append_chunk_ring(cw[k], ring, sw8, seg_len, pos, carry);
+        if ((uint32_t)k < n) append_chunk_ring<kRingBytes, true>(cw[k], ring, sw8, seg_len, pos, carry);
         if (k % kLook == kLook - 1 && (uint32_t)k + 1 < n) look();
         if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
       }

@@ -45,12 +45,23 @@ static_assert(kRingPiece % kRingStep == 0 && kRingGroup == 4 && kRingStep <= kRi
 //  - A lane stores where it stands before a chunk.  Before the last of the chunks between two looks it has gained 8 columns
 //    in each of the others and stands at most at done + (8 group - 1) + spread + 8 (step - 1): the limits below make
 //    that done + kRingBytes - 8.
-//  - A lane that completes its segment stays at its end and goes on storing there (pad codes).  It was at most `spread` ahead
-//    with the chunk before, the slowest lane gains at least 4 columns in a chunk: from the next look on it is at most
+//  - A lane that completes its segment goes on with pad codes, on the device code 0: a column a code, 4 in a chunk, no faster
+//    than an unfinished lane, and the host counts it among the lanes that may be `spread` ahead.  In k_matvec_ring it really
+//    moves on; in k_matvec_runs it stays at the segment's end and goes on storing there: from the next look on it is at most
 //    (8 group - 1) + spread + 4 past done, which is no further piece, and until then the bound above holds.
+//  - When the last lane has finished, less than two groups are left, and none or one after the look that follows.
 //  - At a look, after the last chunk, a lane can stand at done + kRingBytes: at a piece's start, and that piece's place
 //    still holds columns the look is about to multiply.  Nothing of the lane lies in that piece yet: see ring_leftover.
-constexpr uint32_t kRingSpread = kRingBytes - 8 * kRingStep - 8 * kRingGroup + 1;
+constexpr uint32_t ring_spread(int bytes, int step, int group) { return bytes - 8 * step - 8 * group + 1; }
+constexpr uint32_t kRingSpread = ring_spread(kRingBytes, kRingStep, kRingGroup);
+// The small form: half the ring, looks twice as often at half the windows.  Pieces of 9 chunks: a unit of 33..36 chunks, or of
+// 17 (packed), is cut into pieces of 8 and 9, and 18 of them in registers leave room for 16 wavefronts.
+constexpr int kSmallRingBytes = 64, kSmallRingStep = 2, kSmallRingGroup = 2, kSmallRingPiece = 9;
+constexpr uint32_t kSmallRingSpread = ring_spread(kSmallRingBytes, kSmallRingStep, kSmallRingGroup);
+static_assert(kSmallRingStep <= kSmallRingGroup, "ring schedule");
+constexpr int ring_step(int bytes) { return bytes == kSmallRingBytes ? kSmallRingStep : kRingStep; }
+constexpr int ring_group(int bytes) { return bytes == kSmallRingBytes ? kSmallRingGroup : kRingGroup; }
+constexpr int ring_piece(int bytes) { return bytes == kSmallRingBytes ? kSmallRingPiece : kRingPiece; }
 constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;
 // Whether a lane that stands at column pos holds bytes of a piece it has not stored (see append_chunk_ring): a unit whose
 // segments end inside pieces stores those at every look - those only, never the piece that begins at pos.
