@@ -107,12 +107,12 @@ int hip_fail(const char* what, hipError_t e) {
 struct DictCopy {
   int device;
   std::vector<uint32_t> words;   // host copy for the comparison
-  uint32_t* dev;        // container words
+  uint32_t* dev;        // the bytes of every entry, two to an entry (packed weights: bytes of two weights all the same)
   uint32_t* dev_bf16;   // (bf16(b0), bf16(b1)) per entry; a single-byte entry has a zero second weight, the pad entry two.
                         // Packed 4-bit weights: the four nibbles of (b0, b1) as fp8 e4m3, in column order.
   uint32_t packing;
   uint32_t long_runs, class2, class3;   // containers with runs of 3 and 4 bytes: dev and dev_bf16 are slot images (long_slot)
-  uint32_t image_bytes;                 // long_runs: size of the byte image at dev
+  uint32_t image_bytes;                 // size of the image at dev, a multiple of 16
   uint32_t dict_words_bf16;             // dwords of the image at dev_bf16 (a multiple of 4)
   int refs;
 };
@@ -160,17 +160,16 @@ int acquire_dictionary(int device, const uint32_t* words, uint32_t n_words, cons
   d->long_runs = long_runs;
   d->class2 = class2;
   d->class3 = class3;
-  d->image_bytes = 0;
   d->dev = d->dev_bf16 = nullptr;
   // bytes past an entry's length are zero in the container, so the conversions need no length test
   std::vector<uint32_t> first, second;   // what dev and dev_bf16 will hold
   if (!long_runs) {
-    // dev: the container words (the kernels take the low 16 bits); dev_bf16: one dword per entry
+    // dev: the two bytes of every entry; dev_bf16: one dword per entry
     const uint32_t n_pad = (uint32_t)round_up(n_words, 4);
-    first.assign(n_pad, 0u);
+    first.assign(round_up(n_pad * 2, 16) / 4, 0u);
     second.assign(n_pad, 0u);
     for (uint32_t i = 0; i < n_words; ++i) {
-      first[i] = words[i];
+      first[i / 2] |= (words[i] & 0xFFFFu) << 16 * (i % 2);
       if (packing) {
         for (uint32_t k = 0; k < 4; ++k) second[i] |= nibble_to_fp8_bits(words[i] >> (4 * k) & 15u) << (8 * k);
       } else {
@@ -197,8 +196,8 @@ int acquire_dictionary(int device, const uint32_t* words, uint32_t n_words, cons
     }
     first.assign(bytes_img.size() / 2, 0u);
     std::memcpy(first.data(), bytes_img.data(), bytes_img.size() * 2);
-    d->image_bytes = (uint32_t)(bytes_img.size() * 2);
   }
+  d->image_bytes = (uint32_t)(first.size() * 4);
   hipError_t e = hipMalloc((void**)&d->dev, first.size() * 4);
   if (e == hipSuccess) e = hipMalloc((void**)&d->dev_bf16, second.size() * 4);
   if (e == hipSuccess) e = hipMemcpy(d->dev, first.data(), first.size() * 4, hipMemcpyHostToDevice);
@@ -453,10 +452,8 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   const uint8_t* src = (const uint8_t*)blob;
   DictCopy* dict = nullptr;
   if (int rc = acquire_dictionary(dev, (const uint32_t*)(src + h.off_dict), h.n_entries + 1, h, &dict)) return rc;
-  if (long_runs) {
-    m.dict_words = dict->dict_words_bf16;
-    m.dict16_bytes = dict->image_bytes;
-  }
+  if (long_runs) m.dict_words = dict->dict_words_bf16;
+  m.dict16_bytes = dict->image_bytes;
 
   const uint64_t sz_uoff = round_up(h.uoff_bytes, kSectionAlign), sz_codes = round_up(h.code_bytes, kSectionAlign),
                  sz_scales = round_up(h.scale_bytes, kSectionAlign);
@@ -508,7 +505,7 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   t->m_dev = (const DevMat*)(base + o_desc);
   t->dict = dict;
   t->dev_base = base;
-  t->lds_dict16 = long_runs ? dict->image_bytes : (uint32_t)round_up((uint64_t)m.dict_words * 2, 16);
+  t->lds_dict16 = dict->image_bytes;
   t->device = dev;
   t->n_cu = prop.multiProcessorCount;
   *out = t;

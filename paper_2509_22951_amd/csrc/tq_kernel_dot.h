@@ -7,7 +7,6 @@ namespace tq {
 // Staging is split in two so that the loads of the dictionary, of the activations and of the first code chunks are
 // all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS.
 constexpr uint32_t kSplitWaves = 4;    // k_matvec splits units between wavefronts in shares that leave each unit at least this many
-constexpr int kDictRegs = 16;   // uint4 per thread per round of the tile kernels' dictionary staging
 
 template <int kThreads, int kDictRegs>   // kDictRegs x kThreads x 16 bytes per round (128 KB: the whole dictionary in one)
 __device__ __forceinline__ void issue_dictionary(const DevMat& m, uint32_t base, int tid, uint4 (&v)[kDictRegs]) {

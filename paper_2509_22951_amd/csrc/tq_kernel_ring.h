@@ -223,7 +223,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
   constexpr int kRingThreads = kWaves * 64, kGateUpBands = (32 + kWaves - 1) / kWaves;
   constexpr uint32_t kRingXTile = ring_x_tile(kRows);
   extern __shared__ uint4 lds4[];
-  uint16_t* lds_dict = (uint16_t*)lds4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t rings = a.x_off, xtile = a.slot_off;   // LDS addresses (the LDS segment starts at 0)
   const uint64_t total = cost_at(a, a.n);
@@ -244,7 +243,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
     const uint32_t nq = m.n_quads, n_win = pk * m.seg_cols / 8;   // activation windows (8 columns) per segment
     __syncthreads();   // the previous matrix's dictionary and activation tile are no longer in use
     if (m.dict != staged) {
-      stage_dictionary16<kDictRegs>(m, lds_dict, tid, kRingThreads);
+      stage_image<kRingThreads>(m, tid, lds4);
       staged = m.dict;
     }
     // Bands are handed out one at a time, per quad, through a counter in LDS: wavefront w starts with band w of the

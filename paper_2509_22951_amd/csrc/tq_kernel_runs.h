@@ -221,7 +221,7 @@ constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a u
                                         // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
 template <int kWaves, bool kPacked, int kFold>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
-  constexpr int kRunThreads = kWaves * 64, kRegs = 8, kCount = 12;
+  constexpr int kRunThreads = kWaves * 64, kCount = 12;
   touch_arguments();
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -254,9 +254,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
       run.c_end = run.u0 < run.u1 ? unit_offset(m, run.u1) : 0u;
       run.head = run.tail = false;
     }
+    const bool new_dict = m.dict != staged;
     if (lds_used) __syncthreads();   // the previous matrix's dictionary, counts and partial sums are no longer in use
     lds_used = true;
-    if (m.dict != staged) stage_dictionary16<kRegs>(m, (uint16_t*)lds4, tid, kRunThreads);
+    if (new_dict) stage_image<kRunThreads>(m, tid, lds4);
     if (split) {
       u16x2 pairs = {0, 0};
       if (run.tail) {
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
       }
       lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (run.c_end - run.part) + pairs.x + pairs.y);   // (an empty run passes nothing)
     }
-    if (split || m.dict != staged) __syncthreads();
+    if (split || new_dict) __syncthreads();
     staged = m.dict;
     uint32_t start = 0;   // head: the columns of the first unit that earlier wavefronts pass
     if (run.head) {

@@ -4,18 +4,10 @@
 #include "tq_strip_decode.h"
 
 namespace tq {
-// Stage a dictionary image that is already laid out the way the kernel reads it (containers with runs of 3 and 4 bytes).
-__device__ __forceinline__ void stage_image(const uint32_t* image, uint32_t bytes, uint16_t* lds_dict, int tid, int n_threads) {
-  const uint4* src = (const uint4*)image;
-  uint4* dst = (uint4*)lds_dict;
-  for (uint32_t i = tid; i < bytes / 16; i += n_threads) dst[i] = global_load(src + i);
-}
-
 // kLong: the matrices of the launch hold runs of up to 4 bytes (append_chunk_long).
 template <bool kXFast, bool kPacked, bool kLong = false>
 __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
   extern __shared__ uint4 lds4[];
-  uint16_t* lds_dict = (uint16_t*)lds4;
   uint8_t* tiles = (uint8_t*)lds4 + a.x_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_threads = blockDim.x, n_waves = n_threads >> 6;
@@ -37,12 +29,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
     const uint32_t u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / n_waves);
     const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / n_waves);
     __syncthreads();   // the previous matrix's dictionary and partial sums are no longer in use
-    if (kLong && m.dict != staged) {
-      stage_image(m.dict, m.dict16_bytes, lds_dict, tid, n_threads);
-      staged = m.dict;
-    }
     if (m.dict != staged) {
-      stage_dictionary16<kDictRegs>(m, lds_dict, tid, n_threads);
+      stage_image<kThreads>(m, tid, lds4, n_threads);
       staged = m.dict;
     }
     __syncthreads();
@@ -91,7 +79,6 @@ template <bool kLong = false>
 __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
   touch_arguments();   // (one 8192 x 3072 matrix 24.2 -> 23.5 us: the job is looked up by an index, so each of its lines would cost a round trip)
   extern __shared__ uint4 lds4[];
-  uint16_t* lds_dict = (uint16_t*)lds4;
   uint8_t* tiles = (uint8_t*)lds4 + a.x_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_threads = blockDim.x, n_waves = n_threads >> 6;
@@ -111,15 +98,9 @@ __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
     const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
     const uint32_t u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / n_waves);
     const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / n_waves);
-    if (kLong && m.dict != staged) {
-      __syncthreads();   // nobody reads the previous dictionary any more
-      stage_image(m.dict, m.dict16_bytes, lds_dict, tid, n_threads);
-      staged = m.dict;
-      __syncthreads();
-    }
     if (m.dict != staged) {
       __syncthreads();   // nobody reads the previous dictionary any more
-      stage_dictionary16<kDictRegs>(m, lds_dict, tid, n_threads);
+      stage_image<kThreads>(m, tid, lds4, n_threads);
       staged = m.dict;
       __syncthreads();
     }

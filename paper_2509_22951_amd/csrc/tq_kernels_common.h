@@ -38,7 +38,7 @@ constexpr int kInlineDescriptions = 4;
 
 // What the kernels need to know about one matrix.
 struct DevMat {
-  const uint32_t* dict;    // container dictionary words (run bytes + length), dict_words of them, zero filled past the pad entry
+  const uint32_t* dict;    // the dictionary's byte image, as the batched kernels and the expansion keep it in LDS: 2 bytes per entry, zeros past the pad entry
   const uint32_t* dict_bf16;   // the same entries as two bf16 weights each (second one zero for a single byte): the form the
                                // batch-1 kernel keeps in LDS, made once when the dictionary is uploaded
   const uint32_t* uoff;    // n_units + 1 unit offsets, in chunks
@@ -56,7 +56,7 @@ struct DevMat {
   uint32_t long_runs;      // 1: runs of 3 and 4 bytes exist (lmax > 2): the code space classes below apply, and dict / dict_bf16
                            // point to images with two slots for every entry from `class2` on (see long_slot)
   uint32_t class2, class3; // codes from class2 on are runs of at least 3 bytes, from class3 on of 4 (sorted code space)
-  uint32_t dict16_bytes;   // long_runs: size of the byte image at `dict` (a multiple of 16)
+  uint32_t dict16_bytes;   // size of the byte image at `dict` (a multiple of 16)
 };
 static_assert(sizeof(DevMat) % 8 == 0, "copied as whole dwords, kept 8-byte aligned in tables");
 

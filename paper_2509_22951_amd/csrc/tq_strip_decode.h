@@ -235,21 +235,20 @@ __device__ __forceinline__ uint4 mask_x_fragment(uint4 v, uint32_t cols, uint32_
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// 16-bit image of the dictionary in LDS: the run bytes of every entry (the length follows from the code).
-template <int kRegs>
-__device__ __forceinline__ void stage_dictionary16(const DevMat& m, uint16_t* lds_dict, int tid, int n_threads) {
-  const uint4* src = (const uint4*)m.dict;
-  uint2* dst = (uint2*)lds_dict;
-  const uint32_t n4 = m.dict_words / 4;
-  for (uint32_t base = 0; base < n4; base += kRegs * n_threads) {
+// The dictionary's byte image goes to LDS as it is.  kThreads: of the workgroup, or the most it may have (n_threads then says how
+// many it has); a full dictionary is one round of loads.
+constexpr uint32_t kImageBytes = 61440;
+template <int kThreads>
+__device__ __forceinline__ void stage_image(const DevMat& m, int tid, uint4* lds_dict, int n_threads = kThreads) {
+  constexpr int kRegs = (kImageBytes / 16 + kThreads - 1) / kThreads;
+  const uint32_t n = m.dict16_bytes / 16;
+  for (uint32_t base = tid; base < n; base += kRegs * n_threads) {
     uint4 v[kRegs];
 #pragma unroll
-    for (int k = 0; k < kRegs; ++k) v[k] = global_load(src + min(base + k * n_threads + tid, n4 - 1));
+    for (int k = 0; k < kRegs; ++k) v[k] = global_load((const uint4*)m.dict + min(base + k * n_threads, n - 1));
 #pragma unroll
-    for (int k = 0; k < kRegs; ++k) {
-      const uint32_t idx = base + k * n_threads + tid;
-      if (idx < n4) dst[idx] = make_uint2((v[k].x & 0xFFFFu) | v[k].y << 16, (v[k].z & 0xFFFFu) | v[k].w << 16);
-    }
+    for (int k = 0; k < kRegs; ++k)
+      if (base + k * n_threads < n) lds_dict[base + k * n_threads] = v[k];
   }
 }
 
