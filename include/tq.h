@@ -139,8 +139,8 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  * batch 1 and batch 2 run the dot-product kernel (activations gathered from an LDS image of x, which holds both rows
  * at batch 2; a matrix whose rows are too long for that image to fit the LDS beside the dictionary - more than 8192
  * columns with a full dictionary, more with a smaller one - goes on as batch 3 does, slower but to the same result);
- * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep 128 bytes of every
- * segment in LDS and multiply while they decode; they take matrices whose lane_spread (tq_info) is at most 113 columns.
+ * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep 64 or 128 bytes of every
+ * segment in LDS and multiply while they decode; they take every matrix whose lanes can be brought within 65 columns.
  * The ring kernel has the activations of a quad (4 segments) in LDS as well: for rows that are a whole number of units
  * (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x 16-byte aligned, in calls that
  * bring at least 24 bands of 16 rows per compute unit, 12 for batches above 8 (tq_set_ring_min_bands_per_cu changes

@@ -292,12 +292,14 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_mfma<false, false, true>,
     (const void*)k_matvec_mfma<true, true, true>,
     (const void*)k_matvec_mfma<false, true, true>,
-    (const void*)k_matvec_runs<kRunWaves, false, 1>,
-    (const void*)k_matvec_runs<kRunWaves, false, 2>,
-    (const void*)k_matvec_runs<kRunWaves, false, 4>,
-    (const void*)k_matvec_runs<kRunWavesPacked, true, 1>,
-    (const void*)k_matvec_runs<kRunWavesPacked, true, 2>,
-    (const void*)k_matvec_runs<kRunWavesPacked, true, 4>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4>,
     (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false>,
     (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, false>,
     (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true>,
@@ -677,11 +679,15 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size) | a count per lane
     const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
     a.x_off = (uint32_t)dict16;
+    uint64_t units = 0;
+    for (int i = 0; i < n; ++i) units += (uint64_t)hs[i]->m.n_bands * hs[i]->m.n_quads;
+    const bool less = small && !packed && batch > 4 && units <= (uint64_t)kRunSmallUnits * p.grid;
     p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
-    p.lds = dict16 + (size_t)p.block * kRingBytes + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
-    if (batch <= 4) p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 4> : (const void*)k_matvec_runs<kRunWaves, false, 4>;
-    else if (batch <= 8) p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 2> : (const void*)k_matvec_runs<kRunWaves, false, 2>;
-    else p.kernel = packed ? (const void*)k_matvec_runs<kRunWavesPacked, true, 1> : (const void*)k_matvec_runs<kRunWaves, false, 1>;
+    p.lds = dict16 + (size_t)p.block * (less ? kSmallRingBytes : kRingBytes) + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
+    if (less) p.kernel = batch <= 8 ? (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2> : (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1>;
+    else if (batch <= 4) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4>;
+    else if (batch <= 8) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2>;
+    else p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1>;
     cut_by_workgroup();
   } else {
     // Tile decode.  LDS: 16-bit dictionary image | one tile (64 strips) per wavefront, which the batched product reuses

@@ -24,6 +24,7 @@ namespace tq {
 // cache accesses), vector instructions issued 86 / 90, LDS pipe busy 71 / 68.  The 16-byte pieces of up to 16 rows of x keep
 // the address unit busy four fifths of the time here; with 16 rows in place of 8 there are twice as many of them.
 constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
+constexpr int kRunSmallUnits = 6;    // units per workgroup up to which the rings are 64 bytes (batches above 4, one weight per byte)
 constexpr int kRunWavesPacked = 8;   // packed 4-bit weights: two fragments and more conversion per piece, 12 wavefronts leave too few registers
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef __attribute__((address_space(1))) const u32x4_any global_cu128_any;
@@ -43,15 +44,15 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
 // a lane has not written itself counts as zeros.  x: the activations, row_first: where the
 // batch row of this lane's B operand starts; part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
 // kFold: windows per B operand (fold_sums).
-template <bool kPacked, int kFold, typename OnUnit>
+template <int kRing, bool kPacked, int kFold, typename OnUnit>
 __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, uint32_t start,
                                                 global_cu16* x, uint32_t row_first, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
   if (u0 >= u1 || c0 >= c_end) return;
-  constexpr int kP = kRingPiece, kG = kRingGroup, kLook = kRingStep;
+  constexpr int kP = ring_piece(kRing), kG = ring_group(kRing), kLook = ring_step(kRing), kParts = (kP + kLook - 1) / kLook;
   constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
   constexpr uint32_t kLoads = kG * pk / kFold;
   const uint32_t behind = (lane & 15) / (16 / kFold) * 8;   // the columns this lane's window lies behind the operand's first
-  const uint32_t sw8 = (uint32_t)(lane & 15) << 3, kg = (uint32_t)lane >> 4;
+  const uint32_t sw8 = ring_swizzle<kRing>(lane), kg = (uint32_t)lane >> 4;
   const uint32_t nq = m.n_quads, n_panels = (m.cols + m.seg_cols - 1) / m.seg_cols, x_cols = pk * m.cols;
   // walker over the pieces of the run
   uint32_t wu = u0, wc = c0, w_left = 0, w_base = 0, w_rem = 0;
@@ -77,11 +78,11 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
     wc += n;
     ends = --w_left == 0 && w_ends;
   };
-  // every piece issues exactly kP loads (those past its end repeat its last chunk), kRingStep of them at a time
+  // every piece issues exactly kP loads (those past its end repeat its last chunk), kLook of them at a time
   auto load_part = [&](uint2 (&cw)[kP], uint32_t start, uint32_t n, int p) {
     const uint32_t last = min(start + max(n, 1u) - 1, c_end - 1);
 #pragma unroll
-    for (int k = p * kRingStep; k < (p + 1) * kRingStep; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
+    for (int k = p * kLook; k < (p + 1) * kLook && k < kP; ++k) cw[k] = load_chunk(m.codes, min(start + k, last), lane);
   };
   // the unit in work: its place, the lane's panel (length, first column of x) and segment (none past the last row), the
   // windows it takes (whole groups)
@@ -110,14 +111,15 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   };
   // One group of MFMA steps if every lane that is still decoding has written the columns [done, done + 8 kG).  The weights
   // are read before it is known whether the group is ready (volatile: the reads stay ahead of the test).
-  auto multiply_ready = [&](bool ready = false) {
+  auto multiply_ready = [&](auto look, bool ready = false) {   // look: see k_matvec_ring's
+    constexpr int kFirst = decltype(look)::value * kG;
     const uint32_t at = min(done, n_win8 - 8 * kG);   // at the unit's end: any place inside the ring
     const uint32_t base = at ^ sw8;
     // a segment that ends inside a piece: what its last chunk left over is not in the ring yet
-    if (ragged && ring_leftover(pos)) *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & 0x78u)) = carry;
+    if (ragged && ring_leftover(pos)) *(lds_u64*)(size_t)(ring | ((pos ^ sw8) & (kRing - 8u))) = carry;
     u32x2 a8[kG];
 #pragma unroll
-    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & 0x78u));
+    for (int k = 0; k < kG; ++k) a8[k] = *(volatile lds_cu64*)(size_t)(ring | ((base ^ (8u * k)) & (kRing - 8u)));
     const uint32_t next = done + 8 * kG;
     if (next > n_win8) return;
     if (!ready && __builtin_amdgcn_ballot_w64(pos < min(seg_len, next)) != 0) return;
@@ -135,39 +137,47 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
         p0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].x), __builtin_bit_cast(bf16x8, x8[2 * k / kFold]), p0, 0, 0, 0);
         p1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nib8_to_bf16x8(a8[k].y), __builtin_bit_cast(bf16x8, x8[(2 * k + 1) / kFold]), p1, 0, 0, 0);
       } else {
-        part[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), part[k], 0, 0, 0);
+        f32x4& p = part[(kFirst + k) & 3];
+        p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i8x8_to_bf16x8(make_uint2(a8[k].x, a8[k].y)), __builtin_bit_cast(bf16x8, x8[k / kFold]), p, 0, 0, 0);
       }
     }
     done = next;
   };
-  auto decode_piece = [&](const uint2 (&cw)[kP], uint32_t n, bool ends, uint2 (&cw_next)[kP], uint32_t next_start, uint32_t next_n) {
+  typedef std::integral_constant<int, 0> First;
+  auto decode_piece = [&](auto turn, const uint2 (&cw)[kP], uint32_t n, bool ends, uint2 (&cw_next)[kP], uint32_t next_start, uint32_t next_n) {
     if (n == 0) return;
+    constexpr int kTurn = decltype(turn)::value;
     // a look: multiply what is ready, request the operands of the group that follows (again, if it was not)
-    auto look = [&] {
-      multiply_ready();
+    auto look = [&](auto number) {
+      multiply_ready(number);
       request_x();
     };
     if (n >= kP - 1) {
-#pragma unroll
-      for (int k = 0; k < kP - 1; ++k) {
-        append_chunk_ring<kRingBytes, true>(cw[k], ring, sw8, seg_len, pos, carry);
-        if (k % kLook == kLook - 1) look();
-        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
-      }
-      if (n == kP) append_chunk_ring<kRingBytes, true>(cw[kP - 1], ring, sw8, seg_len, pos, carry);
+      static_for<kP - 1>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        append_chunk_ring<kRing, true>(cw[k], ring, sw8, seg_len, pos, carry);
+        if constexpr (k % kLook == kLook - 1) {
+          look(std::integral_constant<int, kTurn + k / kLook>{});
+          load_part(cw_next, next_start, next_n, k / kLook);
+        }
+      });
+      if (n == kP) append_chunk_ring<kRing, true>(cw[kP - 1], ring, sw8, seg_len, pos, carry);
     } else {
-#pragma unroll
-      for (int k = 0; k < kP - 2; ++k) {
-        if ((uint32_t)k < n) append_chunk_ring<kRingBytes, true>(cw[k], ring, sw8, seg_len, pos, carry);
-        if (k % kLook == kLook - 1 && (uint32_t)k + 1 < n) look();
-        if (k % kRingStep == kRingStep - 1) load_part(cw_next, next_start, next_n, k / kRingStep);
-      }
+      static_for<kP - 2>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        if ((uint32_t)k < n) append_chunk_ring<kRing, true>(cw[k], ring, sw8, seg_len, pos, carry);
+        if constexpr (k % kLook == kLook - 1) {
+          if ((uint32_t)k + 1 < n) look(std::integral_constant<int, kTurn + k / kLook>{});
+          load_part(cw_next, next_start, next_n, k / kLook);
+        }
+      });
+      if constexpr ((kP - 2) / kLook < kParts - 1) load_part(cw_next, next_start, next_n, kParts - 2);
     }
-    multiply_ready();
+    multiply_ready(std::integral_constant<int, kTurn + kParts - 1>{});
     if (ends) {
       while (done < n_win8) {   // every lane is complete: whatever is left (at most a group, more in a ragged unit)
         request_x();
-        multiply_ready();
+        multiply_ready(First{});
       }
       on_unit(band, quad);
       if (++quad == nq) {
@@ -177,12 +187,12 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
       if (band * nq + quad < u1) enter_unit();
     }
     request_x();
-    load_part(cw_next, next_start, next_n, kP / kRingStep - 1);
+    load_part(cw_next, next_start, next_n, kParts - 1);
   };
   uint2 cwa[kP], cwb[kP];
   uint32_t sa, na, sb, nb;
   bool ea, eb;
-  auto ring_piece = [&](uint32_t col) { return (lds_u64*)(size_t)(ring | ((col ^ sw8) & 0x78u)); };
+  auto ring_piece = [&](uint32_t col) { return (lds_u64*)(size_t)(ring | ((col ^ sw8) & (kRing - 8u))); };
   enter_unit();
   next_piece(sa, na, ea);
   if (started) {   // the groups that every lane has passed are others' work; of the next ones, what a lane has passed is zeros here
@@ -193,12 +203,12 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   }
   request_x();
 #pragma unroll
-  for (int j = 0; j < kP / kRingStep; ++j) load_part(cwa, sa, na, j);
+  for (int j = 0; j < kParts; ++j) load_part(cwa, sa, na, j);
   while (na) {   // two register sets: one is decoded while the other is filled
     next_piece(sb, nb, eb);
-    decode_piece(cwa, na, ea, cwb, sb, nb);
+    decode_piece(First{}, cwa, na, ea, cwb, sb, nb);
     next_piece(sa, na, ea);
-    decode_piece(cwb, nb, eb, cwa, sa, na);
+    decode_piece(std::integral_constant<int, kParts & 1>{}, cwb, nb, eb, cwa, sa, na);
   }
   if (c_end < unit_offset(m, u1)) {   // the last unit goes on elsewhere: multiply what the lanes have, zeros behind it
     *ring_piece(pos) = carry;
@@ -207,7 +217,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
       for (int k = 0; k < kG; ++k)
         if (done + 8 * k > pos) *ring_piece(done + 8 * k) = 0;
       request_x();
-      multiply_ready(true);
+      multiply_ready(First{}, true);
     }
   }
 }
@@ -215,11 +225,18 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
 // kSplit: as in k_matvec, a share of few units is cut into equal runs of chunks, and each wavefront counts the columns its
 // part of a unit passes while the dictionary is on its way.  A lone wavefront takes 8 us for a unit of 33 chunks, but the
 // windows around a cut are multiplied on both sides of it, each time with zeros for the other side's columns: shares that
-// leave less than half the wavefronts idle are faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 ->
-// 15.0, 700 x 1999 batch 5 20.2 -> 16.6; 6 units of packed weights for 8 wavefronts 18.0 -> 23.2.)
+// leave less than half the wavefronts idle (above 8 batch rows, where the operands are twice as many loads: two thirds) are
+// faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 -> 15.0, 700 x 1999 batch 5 20.2 -> 16.6; 6 units of
+// packed weights for 8 wavefronts 18.0 -> 23.2; batch 16, 6 units for 12 wavefronts: 4099 x 2999 27.7 -> 33.8, 8192 x 3072 22.7 -> 26.4.)
+// Rings of 64 bytes take such shares (kRunSmallUnits): groups of two windows leave half as much around a cut to be multiplied
+// twice, and in ragged units.  us, rings of 128 -> 64 bytes: 4099 x 2999 batch 5 19.7 -> 18.6, 700 x 1999 batch 8 17.6 -> 16.7, batch 16 26.2 ->
+// 22.9, 2048 x 2048 batch 16 15.5 -> 14.3, 3072 x 3072 batch 16 18.8 -> 16.4; larger shares equal or slower (16384 x 3072 batch 8 21.2 -> 22.6), and
+// so are batches of up to 4 rows, whose operands then bring two windows instead of four (2048 x 2048 batch 3 12.4 -> 12.8).
 constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a unit (4 / 6 / 8 / 11, us: 1024 x 1024 batch 3 14.8 / 14.5 /
                                         // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
-template <int kWaves, bool kPacked, int kFold>
+constexpr uint32_t kRunSplitMinSmall = 9;   // with rings of 64 bytes, whose pieces are 9 chunks (11 / 9, us: 1024 x 1024 batch 8 10.8 / 10.1, 2048 x 2048 12.9 /
+                                            // 12.5, 700 x 1999 15.9 / 16.7; batch 16 14.3 / 14.5)
+template <int kRing, int kWaves, bool kPacked, int kFold>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   constexpr int kRunThreads = kWaves * 64, kCount = 12;
   touch_arguments();
@@ -229,8 +246,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
   const uint32_t* staged = nullptr;
   const uint32_t rings = a.x_off;   // LDS address (the LDS segment starts at 0)
-  const uint32_t ring = rings + (uint32_t)wave * (64 * kRingBytes) + (uint32_t)lane * kRingBytes;
-  uint16_t* lds_count = (uint16_t*)((uint8_t*)lds4 + rings + kWaves * 64 * kRingBytes);   // [kWaves][64]
+  const uint32_t ring = rings + (uint32_t)wave * (64 * kRing) + (uint32_t)lane * kRing;
+  uint16_t* lds_count = (uint16_t*)((uint8_t*)lds4 + rings + kWaves * 64 * kRing);   // [kWaves][64]
   bool lds_used = false;
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
     const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
@@ -243,10 +260,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads, unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
     EvenRun run;
-    const bool split = 2 * n_units <= kWaves;
+    const bool split = (kFold == 1 && !kPacked ? 3 : 2) * n_units <= kWaves;
     if (split) {
       const uint32_t uoff_lane = global_load(m.uoff + unit_lo + min((uint32_t)lane, n_units));
-      run = even_run(uoff_lane, unit_lo, n_units, wave, kWaves, kRunSplitMin);
+      run = even_run(uoff_lane, unit_lo, n_units, wave, kWaves, kRing == kSmallRingBytes && kFold > 1 ? kRunSplitMinSmall : kRunSplitMin);
     } else {
       run.u0 = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves);
       run.u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
@@ -293,7 +310,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     global_cu16* x = (global_cu16*)job.x;
     // lanes past the batch repeat its last row: their sums are never stored
     const uint32_t row_first = min((uint32_t)(lane & 15) % (16 / kFold), (uint32_t)a.batch - 1) * (kPacked ? 2 : 1) * m.cols;
-    decode_run_ring<kPacked, kFold>(m, run.u0, run.u1, run.c0, run.c_end, run.head, start, x, row_first, lane, ring, part, on_unit);
+    decode_run_ring<kRing, kPacked, kFold>(m, run.u0, run.u1, run.c0, run.c_end, run.head, start, x, row_first, lane, ring, part, on_unit);
     if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, fold_sums<kFold>(part), lane);
     __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
     sums.combine(a, job, m, rings, wave, kWaves, lane);
