@@ -143,8 +143,8 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  * segment in LDS and multiply while they decode; they take every matrix whose lanes can be brought within 65 columns.
  * The ring kernel has the activations of a quad (4 segments) in LDS as well: for rows that are a whole number of units
  * (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x 16-byte aligned, in calls that
- * bring at least 24 bands of 16 rows per compute unit, 12 for batches above 8 (tq_set_ring_min_bands_per_cu changes
- * that number).  The runs kernel takes its activations from global memory: any other shape of at least 8 columns, any
+ * bring enough bands of 16 rows per compute unit: about 24 of LLaMA-3.2-3B layers, 12 for batches above 8, more of matrices
+ * with few bands and many quads (tq_set_ring_min_bands_per_cu scales that: 24 is the default, 0 is always).  The runs kernel takes its activations from global memory: any other shape of at least 8 columns, any
  * x.  Everything else goes through the whole-strip kernel, which decodes a unit into an LDS tile before it multiplies
  * it.  The ring kernel adds the partial sums of a row's later quads to y with atomic adds, always in the same order; y
  * must not be read or written by anything else on the device while the call runs (true of any output buffer).
@@ -155,8 +155,8 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
 int tq_matvec(tq_handle h, const void *x, void *y, int batch, void *stream);
 
 /* Tuning knob of the choice between the MFMA kernels of tq_matvec (see there): the ring kernel hands whole bands
- * of 16 rows to its wavefronts and is taken by launches that bring at least this many bands per compute unit, half as
- * many for batches above 8 (default 24; 0 = whenever a matrix allows it).  Process-wide, atomic; affects the calls and the prepared steps made
+ * of 16 rows to its wavefronts and is taken where an estimate of both kernels' times says that it pays; the estimate for the
+ * ring kernel counts bands_per_cu / 24 times (default 24; 0 = whenever a matrix allows it).  Process-wide, atomic; affects the calls and the prepared steps made
  * after it returns.  Results stay within the tolerance either way (the kernels add in different orders). */
 int tq_set_ring_min_bands_per_cu(uint32_t bands_per_cu);
 

@@ -718,20 +718,60 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
 }
 
 // Whether the batched product of this matrix can keep a ring per lane instead of the whole strip.
-// Bands per CU a launch needs for the ring kernel; tq_set_ring_min_bands_per_cu changes it (tests use 0 to put small
-// matrices through that kernel).
-std::atomic<uint64_t> g_ring_min_bands{kRingMinBandsPerCu};
-// (us, ring / runs kernel, LLaMA-3.2-3B layers as one step: batch 8 20 bands per CU 127 / 109, 27 bands 135 / 142, 54 bands
-// 230 / 250; above 8 rows of x the runs kernel pays more for them: batch 16 13.5 bands 91 / 95, 27 bands 138 / 254.  Batches
-// of up to 4 rows would have the line further up: 27 bands 133 / 122, 54 bands 225 / 217, packed weights 99 / 96 and 176 / 200)
-uint64_t ring_min_bands_per_cu(int batch) { return g_ring_min_bands.load(std::memory_order_relaxed) / (batch > 8 ? 2 : 1); }
-
 bool ring_eligible(const tq_matrix* t, const void* x) {
   const DevMat& m = t->m;
   const uint32_t seg_weights = (m.packing ? 2u : 1u) * m.seg_cols;   // what the activation tile of a quad is sized by
   return m.ring && m.cols % (kUnitPanels * m.seg_cols) == 0 && m.seg_cols % (8 * kRingGroup) == 0 &&
          seg_weights <= kRingMaxSeg && (uintptr_t)x % 16 == 0 &&
          round_up((uint64_t)m.dict_words * 2, kRingBytes) + (size_t)kRingWaves * 64 * kRingBytes + ring_x_tile(16) + 128 <= kLdsLimit;
+}
+
+// (what tq_set_ring_min_bands_per_cu sets; tests use 0 to put small matrices through the ring kernel)
+std::atomic<uint64_t> g_ring_min_bands{kRingMinBandsPerCu};
+
+// Whether the ring kernel is the faster one for a launch of these matrices (all eligible, of one packing).  It walks the quads of a
+// workgroup's bands one after the other with a barrier between them, which few bands do not fill: a quad of n bands takes a + b n
+// us and c n at least, a workgroup that gets the end of one matrix and the start of the next a little more.  The runs kernel
+// takes time by the units alone, more for more rows of x, and most where the codes come from HBM and not from the 256 MB
+// cache behind the L2.  The figures are for units of 16 x 1024 weights, fitted to 24 sizes of launch: LLaMA-3.2-1B and -3B layers as
+// one step and gated pairs, batch 3, 4, 5, 8, 9, 16.  us, ring / runs: one 3B layer batch 8 69 / 33, two 87 / 57, three 126 / 102, four
+// 123 / 127, batch 4 122 / 112; six 1B layers batch 8 144 / 122, batch 16 154 / 224; two 3B layers batch 9 92 / 61, batch 16 95 / 93;
+// packed, four 3B layers batch 8 90 / 101, gated pairs of four blocks batch 8 42 / 52, of two blocks batch 16 29 / 41.  (By bands per
+// compute unit alone, as the line was drawn before, the 1B layers and batch 9 took the wrong one.)
+bool ring_pays(int n, const tq_handle* hs, const void* const* xs, int batch) {
+  const uint64_t weight = g_ring_min_bands.load(std::memory_order_relaxed);
+  if (weight == 0) return true;
+  const bool packed = hs[0]->m.packing != 0;
+  double total = 0, units = 0, bytes = 0, quads_min = 1e9;
+  uint64_t bands_all = 0;
+  int taken = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!ring_eligible(hs[i], xs[i])) continue;
+    const DevMat& m = hs[i]->m;
+    const double unit = (packed ? 2. : 1.) * m.seg_cols / 256;
+    total += (double)m.n_bands * m.cols;
+    bands_all += m.n_bands;
+    units += (double)m.n_bands * m.n_quads * unit;
+    bytes += (double)hs[i]->h.code_bytes;
+    quads_min = std::min(quads_min, m.n_quads * unit);
+    ++taken;
+  }
+  if (4 * bands_all < weight * hs[0]->n_cu) return false;   // (6 bands per compute unit: no smaller launch was measured faster)
+  const double share = total / hs[0]->n_cu;
+  const double a = packed ? 4.6 : 6., b = packed ? .56 : .75, c = packed ? .8 : 1.05, rows = batch <= 8 ? 1. : packed ? 1.1 + .014 * (batch - 9) : 1.05;
+  double ring = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!ring_eligible(hs[i], xs[i])) continue;
+    const DevMat& m = hs[i]->m;
+    const double unit = (packed ? 2. : 1.) * m.seg_cols / 256, cost = (double)m.n_bands * m.cols, bands = std::min((double)m.n_bands, share / m.cols);
+    ring = std::max(ring, m.n_quads * unit * std::max(a + b * bands, c * bands) * std::max(1., share / cost));   // (of a small matrix: and others like it)
+  }
+  ring = ring * rows + (taken > 1 ? (packed ? 1. : 2.) * quads_min : 0.);
+  const bool from_hbm = bytes > 240e6;
+  const double per_unit = packed ? (batch <= 4 ? .91 : batch <= 8 ? .97 : 1.06 + .056 * (batch - 9))
+                          : from_hbm ? (batch <= 4 ? 1.09 : batch <= 8 ? 1.24 : 1.52 + .13 * (batch - 9))
+                                     : (batch <= 8 ? 1.03 : 1.15 + .09 * (batch - 9));
+  return ring * weight <= (8. + per_unit * units / hs[0]->n_cu) * kRingMinBandsPerCu;
 }
 
 // As few launches as the kernel-argument size and the 32-bit cost line allow.
@@ -794,23 +834,16 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
   if (op == Op::kMatvec && !dot_call && !ring) {
     // The matrices that can take the ring kernel go there, the others to the runs (or whole-strip) kernel; the products are
     // independent, so regrouping them changes nothing but the launches.
-    // The ring kernel gives whole bands to wavefronts, a quad at a time: it needs many bands per workgroup to keep its
-    // wavefronts busy (the runs kernel splits single units between them).
     int n_ring = 0;
-    uint64_t ring_bands = 0;
-    for (int i = 0; i < n; ++i)
-      if (ring_eligible(hs[i], xs[i])) {
-        ++n_ring;
-        ring_bands += hs[i]->m.n_bands;
-      }
-    if (ring_bands < ring_min_bands_per_cu(batch) * hs[0]->n_cu) n_ring = 0;
+    for (int i = 0; i < n; ++i) n_ring += ring_eligible(hs[i], xs[i]) ? 1 : 0;
+    if (n_ring > 0 && !ring_pays(n, hs, xs, batch)) n_ring = 0;
     if (n_ring == n) return launch_all(op, n, hs, xs, ys, batch, stream, true, gate_up, rec);
     if (n_ring > 0) {
       std::vector<tq_handle> h2[2];
       std::vector<const void*> x2[2];
       std::vector<void*> y2[2];
       for (int i = 0; i < n; ++i) {
-        const int g = ring_eligible(hs[i], xs[i]) ? 1 : 0;   // n_ring > 0: the eligible ones have enough bands together
+        const int g = ring_eligible(hs[i], xs[i]) ? 1 : 0;   // n_ring > 0: the eligible ones together are worth a launch of that kernel
         h2[g].push_back(hs[i]);
         x2[g].push_back(xs[i]);
         y2[g].push_back(ys[i]);
@@ -879,7 +912,7 @@ static int tq_matvec_impl(tq_handle h, const void* x, void* y, int batch, void* 
   if (int rc = check_call("tq_matvec", 1, &h, &x, &y, batch)) return rc;
   return launch(Op::kMatvec, 1, &h, &x, &y, batch, (hipStream_t)stream,
                 !dot_kernel_takes(batch, h->m.packing != 0, h->m.long_runs != 0, h->m.dict_words, h->m.x_dwords) && ring_eligible(h, x) &&
-                    h->m.n_bands >= ring_min_bands_per_cu(batch) * h->n_cu);
+                    ring_pays(1, &h, &x, batch));
 }
 
 static int tq_matvec_multi_impl(int n, const tq_handle* hs, const void* const* xs, void* const* ys, int batch, void* stream) {

@@ -42,7 +42,7 @@ constexpr int kRingWavesQuarter = 11;   // with a tile of 4 batch rows (batches 
 // four, which the groups of two windows suggest, made the sums 8 % less exact: hence the turns in multiply_ready.)
 constexpr int kRingWavesSmall = 16, kRingWavesSmallGated = 12;
 constexpr uint32_t kRingMaxSeg = 256;
-constexpr int kRingMinBandsPerCu = 24;   // below that many bands per CU in a launch (half as many above 8 batch rows) k_matvec_runs is faster
+constexpr int kRingMinBandsPerCu = 24;   // tq_set_ring_min_bands_per_cu's default, see ring_pays
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
 
 // 8 * swizzle(lane): lanes 2 (4) apart start on the same bank when a ring is 128 (64) bytes
