@@ -13,7 +13,7 @@
 //      (two activation rows are handled the same way, with both rows in the image and one dot product per row;
 //      packed 4-bit weights: four weights per entry as fp8, two conversions and two dot products per code and row),
 //   4. for batches of 3..16 rows and for tq_decompress the lanes append their run bytes to per-lane storage in LDS
-//      instead - a ring of 128 bytes (k_matvec_ring, k_matvec_runs: multiplied by bf16 MFMA, batch = N, while the decode goes on) or
+//      instead - a ring of 64 or 128 bytes (k_matvec_ring, k_matvec_runs: multiplied by bf16 MFMA, batch = N, while the decode goes on) or
 //      a strip holding the whole segment (k_matvec_mfma: multiplied when the unit is complete; k_decompress: copied
 //      out row-major).
 // The expanded matrix never exists in HBM on the tq_matvec path.

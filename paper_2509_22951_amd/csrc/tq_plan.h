@@ -31,8 +31,7 @@ TQ_HD ListingOutput listing_output(uint32_t base, uint32_t tokens, uint64_t n_va
 }
 
 // The schedule of the ring kernels.  A lane keeps kRingBytes of its segment; every kRingStep chunks the wavefront looks whether
-// all unfinished lanes have passed the next kRingGroup windows of 8 columns, and multiplies them if so (the careful
-// form looks after every chunk and takes one window).
+// all unfinished lanes have passed the next kRingGroup windows of 8 columns, and multiplies them if so.
 constexpr int kRingBytes = 128;
 constexpr int kRingPiece = 12;    // chunks per piece of the code stream (two register sets)
 constexpr int kRingStep = 4;      // chunks between two looks at the lanes' progress
@@ -62,7 +61,7 @@ static_assert(kSmallRingStep <= kSmallRingGroup, "ring schedule");
 constexpr int ring_step(int bytes) { return bytes == kSmallRingBytes ? kSmallRingStep : kRingStep; }
 constexpr int ring_group(int bytes) { return bytes == kSmallRingBytes ? kSmallRingGroup : kRingGroup; }
 constexpr int ring_piece(int bytes) { return bytes == kSmallRingBytes ? kSmallRingPiece : kRingPiece; }
-constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;
+constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;   // of a schedule that looks after every chunk (no kernel takes it; the host test of the bound does)
 // Whether a lane that stands at column pos holds bytes of a piece it has not stored (see append_chunk_ring): a unit whose
 // segments end inside pieces stores those at every look - those only, never the piece that begins at pos.
 TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }
