@@ -83,12 +83,13 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   // Codes: in range, pads only at the end of a lane stream, every lane stream's runs sum to its segment's length.
   std::atomic<uint64_t> first_bad(UINT64_MAX), real_codes(0);
   std::atomic<uint32_t> overrun(0), spread(0);
+  std::atomic<bool> out_of_memory(false);
   std::mutex wide_mutex;
   std::vector<uint32_t> wide_units;
   n_threads = std::max(1u, std::min(n_threads, 16u));
   n_threads = (unsigned)std::min<uint64_t>(n_threads, n_units);
   const uint32_t pad_advance = h.lmax > 2 ? 4u : 2u;   // columns a pad code moves a lane's activation index in the product kernel
-  auto work = [&](uint64_t ub, uint64_t ue) {
+  auto check_units = [&](uint64_t ub, uint64_t ue) {
     uint64_t real = 0;
     uint32_t over = 0, wide = 0;
     std::vector<uint32_t> mine;                 // the units of this range that level_unit has to see
@@ -147,6 +148,13 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
       wide_units.insert(wide_units.end(), mine.begin(), mine.end());
     }
   };
+  auto work = [&](uint64_t ub, uint64_t ue) {   // (an exception that leaves a thread ends the process)
+    try {
+      check_units(ub, ue);
+    } catch (const std::bad_alloc&) {
+      out_of_memory = true;
+    }
+  };
   if (n_threads <= 1) {
     work(0, n_units);
   } else {
@@ -157,6 +165,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
       if (b < e) th.start(work, b, e);
     }
   }
+  if (out_of_memory) throw std::bad_alloc();
   if (first_bad.load() != UINT64_MAX) return bad("code stream of unit " + std::to_string(first_bad.load()));
   if (real_codes.load() != h.n_real_codes) return bad("count of non-padding codes");
   if (hdr_out) *hdr_out = h;

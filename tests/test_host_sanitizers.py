@@ -38,3 +38,16 @@ def test_encoder_and_validator_come_back_when_a_thread_cannot_be_started():
     run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0, (run.stdout + run.stderr)[-3000:]
     assert "came back" in run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_validator_comes_back_when_an_allocation_is_refused():
+    """For every allocation there is, those in its threads among them (alloc_driver.cpp)."""
+    folder = tempfile.mkdtemp(prefix="tq_alloc_")
+    exe = os.path.join(folder, "driver")
+    build = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", os.path.join(HERE, "alloc_driver.cpp"),
+                            os.path.join(CSRC, "tq_encode.cpp"), os.path.join(CSRC, "tq_blob.cpp"), "-o", exe], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, (run.stdout + run.stderr)[-3000:]
+    assert "came back" in run.stdout
