@@ -21,7 +21,7 @@ static int bad(const std::string& why) {
   return TQ_E_BAD_BLOB;
 }
 
-int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* facts_out, unsigned n_threads) {
+int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* facts_out, std::vector<uint32_t>* wide_units_out, unsigned n_threads) {
   if (!blob) {
     set_error("null container pointer");
     return TQ_E_INVALID_ARG;
@@ -172,8 +172,10 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   if (facts_out) {
     facts_out->max_lane_reach = overrun.load();
     facts_out->max_lane_spread = spread.load();
+  }
+  if (wide_units_out) {
     std::sort(wide_units.begin(), wide_units.end());
-    facts_out->wide_units = std::move(wide_units);
+    *wide_units_out = std::move(wide_units);
   }
   return TQ_OK;
 }
@@ -207,7 +209,7 @@ extern "C" int tq_validate_blob(const void* blob, size_t blob_bytes, tq_info* in
   tq::BlobFacts facts;
   try {   // no C++ exception leaves the library
     unsigned hw = std::thread::hardware_concurrency();
-    int rc = tq::validate_blob(blob, blob_bytes, &h, &facts, hw ? hw : 1);
+    int rc = tq::validate_blob(blob, blob_bytes, &h, &facts, nullptr, hw ? hw : 1);
     if (rc == TQ_OK && info) tq::fill_info(h, facts, info);
     return rc;
   } catch (const std::bad_alloc&) {

@@ -377,8 +377,9 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   *out = nullptr;
   Header h;
   BlobFacts facts;
+  std::vector<uint32_t> wide_units;
   unsigned hw = std::thread::hardware_concurrency();
-  if (int rc = validate_blob(blob, blob_bytes, &h, &facts, hw ? hw : 1)) return rc;
+  if (int rc = validate_blob(blob, blob_bytes, &h, &facts, &wide_units, hw ? hw : 1)) return rc;
 
   DevMat m;
   std::memset(&m, 0, sizeof m);
@@ -399,11 +400,11 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   m.ring = 0;
   if (!long_runs) {
     size_t words = 0;
-    for (uint32_t u : facts.wide_units) words += (size_t)(blob_uoff[u + 1] - blob_uoff[u]) * kChunkWords;
+    for (uint32_t u : wide_units) words += (size_t)(blob_uoff[u + 1] - blob_uoff[u]) * kChunkWords;
     level.resize(words);
     auto level_to = [&](uint32_t limit) {
       size_t at = 0;
-      for (uint32_t u : facts.wide_units) {
+      for (uint32_t u : wide_units) {
         const uint32_t chunks = blob_uoff[u + 1] - blob_uoff[u];
         if (!level_unit((const uint16_t*)((const uint8_t*)blob + h.off_codes) + (uint64_t)blob_uoff[u] * kChunkWords, chunks, h.n_entries,
                         (const uint32_t*)((const uint8_t*)blob + h.off_dict), limit, level.data() + at))
@@ -474,9 +475,9 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   if (m.ring) {
     // (units in a row go up together: they are the first of the matrix a dictionary starts with)
     size_t at = 0;
-    for (size_t i = 0, j; i < facts.wide_units.size() && e == hipSuccess; i = j) {
-      for (j = i + 1; j < facts.wide_units.size() && facts.wide_units[j] == facts.wide_units[j - 1] + 1;) ++j;
-      const uint64_t first = blob_uoff[facts.wide_units[i]], n = blob_uoff[facts.wide_units[j - 1] + 1] - first;
+    for (size_t i = 0, j; i < wide_units.size() && e == hipSuccess; i = j) {
+      for (j = i + 1; j < wide_units.size() && wide_units[j] == wide_units[j - 1] + 1;) ++j;
+      const uint64_t first = blob_uoff[wide_units[i]], n = blob_uoff[wide_units[j - 1] + 1] - first;
       e = hipMemcpy(base + o_codes + first * kChunkWords * 2, level.data() + at, n * kChunkWords * 2, hipMemcpyHostToDevice);
       at += n * kChunkWords;
     }

@@ -391,7 +391,7 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   if (opts && opts->dict_from) {
     // One LZW dictionary over a sequence of matrices: start from the entries the earlier container ended with.
     Header fh;
-    if (int rc = validate_blob(opts->dict_from, (size_t)opts->dict_from_bytes, &fh, nullptr, n_threads)) return rc;
+    if (int rc = validate_blob(opts->dict_from, (size_t)opts->dict_from_bytes, &fh, nullptr, nullptr, n_threads)) return rc;
     std::vector<uint8_t> lens(fh.n_entries);
     for (uint32_t e = 0; e < fh.n_entries; ++e) lens[e] = (uint8_t)run_length(fh, e);
     if (fh.lmax > lmax || fh.n_entries > max_entries ||

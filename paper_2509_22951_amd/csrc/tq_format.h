@@ -29,6 +29,7 @@
 #include <cstdint>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -110,11 +111,12 @@ struct BlobFacts {
   uint32_t max_lane_spread;  // the 64 lanes of a unit take their chunks in step; after any number of chunks, the lanes whose
                              // segment is not yet complete have reached different columns of it: the largest difference
                              // between two of them, over all units and all chunk counts
-  std::vector<uint32_t> wide_units;   // the units whose lanes are further apart than the ring kernels take (see level_unit)
 };
+static_assert(std::is_trivially_copyable<BlobFacts>::value, "kept with every matrix: a copy that cannot fail");
 
-// Host-side structural validation; fills *hdr_out with a copy of the header on success.
-int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* facts_out, unsigned n_threads);
+// Host-side structural validation; on success fills *hdr_out with a copy of the header and *wide_units_out with the units, in
+// order, whose lanes are further apart than the ring kernels take (see level_unit).  Each of the three may be null.
+int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* facts_out, std::vector<uint32_t>* wide_units_out, unsigned n_threads);
 void fill_info(const Header& h, const BlobFacts& facts, ::tq_info* out);
 
 }  // namespace tq
