@@ -26,6 +26,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -396,22 +397,12 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   m.seg_magic = (uint32_t)((1ull << 32) / h.seg_cols) + 1;   // exact quotient while col * seg_cols < 2^32
   // The units whose lanes are further apart than the ring kernels take are brought closer together (level_unit).
   const uint32_t* blob_uoff = (const uint32_t*)((const uint8_t*)blob + h.off_uoff);
-  std::vector<uint16_t> level;
+  std::unique_ptr<uint16_t[]> level;
   m.ring = 0;
   if (!long_runs) {
-    size_t words = 0;
-    for (uint32_t u : wide_units) words += (size_t)(blob_uoff[u + 1] - blob_uoff[u]) * kChunkWords;
-    level.resize(words);
     auto level_to = [&](uint32_t limit) {
-      size_t at = 0;
-      for (uint32_t u : wide_units) {
-        const uint32_t chunks = blob_uoff[u + 1] - blob_uoff[u];
-        if (!level_unit((const uint16_t*)((const uint8_t*)blob + h.off_codes) + (uint64_t)blob_uoff[u] * kChunkWords, chunks, h.n_entries,
-                        (const uint32_t*)((const uint8_t*)blob + h.off_dict), limit, level.data() + at))
-          return false;
-        at += (size_t)chunks * kChunkWords;
-      }
-      return true;
+      return level_units((const uint16_t*)((const uint8_t*)blob + h.off_codes), blob_uoff, wide_units, h.n_entries, (const uint32_t*)((const uint8_t*)blob + h.off_dict),
+                         limit, hw ? hw : 1, level);
     };
     m.ring = level_to(kSmallRingSpread) ? 2u : level_to(kRingSpread) ? 1u : 0u;
   }
@@ -478,7 +469,7 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
     for (size_t i = 0, j; i < wide_units.size() && e == hipSuccess; i = j) {
       for (j = i + 1; j < wide_units.size() && wide_units[j] == wide_units[j - 1] + 1;) ++j;
       const uint64_t first = blob_uoff[wide_units[i]], n = blob_uoff[wide_units[j - 1] + 1] - first;
-      e = hipMemcpy(base + o_codes + first * kChunkWords * 2, level.data() + at, n * kChunkWords * 2, hipMemcpyHostToDevice);
+      e = hipMemcpy(base + o_codes + first * kChunkWords * 2, level.get() + at, n * kChunkWords * 2, hipMemcpyHostToDevice);
       at += n * kChunkWords;
     }
   }

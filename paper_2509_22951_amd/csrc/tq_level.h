@@ -1,7 +1,9 @@
 // The code stream of a unit as the device keeps it, where that differs from the container's.  Host code, no GPU needed.
 #pragma once
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "tq_format.h"
@@ -28,8 +30,8 @@ inline bool level_unit(const uint16_t* codes, uint32_t n_chunks, uint32_t n_entr
   };
   Lane lane[64];
   auto code = [&](uint32_t l, uint32_t k) { return codes[(size_t)(k / kChunkCodes) * kChunkWords + l * kChunkCodes + k % kChunkCodes]; };
-  for (uint32_t l = 0; l < 64; ++l)
-    while (lane[l].n < n_chunks * kChunkCodes && code(l, lane[l].n) != n_entries) ++lane[l].n;
+  for (uint32_t k = 0; k < n_chunks * kChunkCodes; ++k)
+    for (uint32_t l = 0; l < 64; ++l) lane[l].n += code(l, k) != n_entries;   // (pads only follow)
   // One chunk of a lane that may come to column `most`; false: it has no codes to spare for that.
   auto take = [&](uint32_t l, uint32_t chunk, uint64_t most, Lane& s) {
     for (uint32_t j = 0; j < kChunkCodes; ++j) {
@@ -40,7 +42,7 @@ inline bool level_unit(const uint16_t* codes, uint32_t n_chunks, uint32_t n_entr
         s.half = -1;
       } else if (s.next < s.n) {
         c = code(l, s.next++);
-        if (c >= 256 && s.pos + 2 + left > most) {
+        if (s.pos + 2 + left > most && c >= 256) {
           if (s.n - s.next >= (n_chunks - chunk) * kChunkCodes - 1 - j) return false;   // (two codes in the place of one must fit)
           s.half = (int)(word[c] >> 8 & 0xFF);
           c = (uint16_t)(word[c] & 0xFF);
@@ -69,6 +71,34 @@ inline bool level_unit(const uint16_t* codes, uint32_t n_chunks, uint32_t n_entr
   for (const Lane& l : lane)
     if (!l.finished()) return false;
   return true;
+}
+
+// The units `units` of a container (codes, uoff: its sections), levelled one behind the other into out by up to n_threads threads.
+// False when one of them cannot be.  (A matrix in which all units are wide - every second row zero, say - is as much work as its
+// validation: 8192 x 3072 of that kind 85 ms on one thread and 15 on 8, its validation 15 on 8.)
+inline bool level_units(const uint16_t* codes, const uint32_t* uoff, const std::vector<uint32_t>& units, uint32_t n_entries, const uint32_t* word,
+                        uint32_t limit, unsigned n_threads, std::unique_ptr<uint16_t[]>& out) {
+  std::vector<size_t> at(units.size() + 1, 0);   // where in out, in chunks
+  for (size_t i = 0; i < units.size(); ++i) at[i + 1] = at[i] + (uoff[units[i] + 1] - uoff[units[i]]);
+  out.reset(new uint16_t[at.back() * kChunkWords]);
+  constexpr size_t kTake = 8;   // units a thread takes at a time (half a millisecond)
+  std::atomic<size_t> next(0);
+  std::atomic<bool> refused(false);
+  auto work = [&] {
+    for (size_t i0; (i0 = next.fetch_add(kTake)) < units.size();)
+      for (size_t i = i0; i < std::min(i0 + kTake, units.size()); ++i) {
+        if (refused.load(std::memory_order_relaxed)) return;
+        if (!level_unit(codes + (size_t)uoff[units[i]] * kChunkWords, (uint32_t)(at[i + 1] - at[i]), n_entries, word, limit, out.get() + at[i] * kChunkWords))
+          refused = true;
+      }
+  };
+  {
+    Threads th;
+    const size_t more = std::min<size_t>({n_threads, 16, (units.size() + kTake - 1) / kTake});
+    for (size_t t = 1; t < more; ++t) th.start(work);   // (2 to 8 units, as most matrices have at the start of a dictionary: this thread alone)
+    work();
+  }
+  return !refused;
 }
 
 }  // namespace tq
