@@ -301,26 +301,14 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1>,
     (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2>,
     (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, false>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, false>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, false>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, false, true>,
-    (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, true, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, false>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, false>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, false, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, true, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, false, true>,
-    (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, true, true>,
+    (const void*)k_matvec_ring<kRingWaves, 16, false>,
+    (const void*)k_matvec_ring<kRingWaves, 8, false>,
+    (const void*)k_matvec_ring<kRingWaves, 16, true>,
+    (const void*)k_matvec_ring<kRingWaves, 8, true>,
+    (const void*)k_matvec_ring<kRingWavesGated, 16, false, true>,
+    (const void*)k_matvec_ring<kRingWavesGated, 16, true, true>,
+    (const void*)k_matvec_ring<kRingWavesGated, 8, false, true>,
+    (const void*)k_matvec_ring<kRingWavesGated, 8, true, true>,
 };
 
 // Once per matrix creation (cheap): dynamic LDS above 64 KB has to be allowed per kernel function, and the kernels'
@@ -398,14 +386,7 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   // The units whose lanes are further apart than the ring kernels take are brought closer together (level_unit).
   const uint32_t* blob_uoff = (const uint32_t*)((const uint8_t*)blob + h.off_uoff);
   std::unique_ptr<uint16_t[]> level;
-  m.ring = 0;
-  if (!long_runs) {
-    auto level_to = [&](uint32_t limit) {
-      return level_units((const uint16_t*)((const uint8_t*)blob + h.off_codes), blob_uoff, wide_units, h.n_entries, (const uint32_t*)((const uint8_t*)blob + h.off_dict),
-                         limit, hw ? hw : 1, level);
-    };
-    m.ring = level_to(kSmallRingSpread) ? 2u : level_to(kRingSpread) ? 1u : 0u;
-  }
+  m.ring = ring_class(blob, h, wide_units, hw ? hw : 1, level);
   m.packing = h.packing;
   m.long_runs = long_runs ? 1u : 0u;
   m.class2 = h.class_end[1];
@@ -642,30 +623,19 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     // address) | the activation tile of one quad.
     const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
     a.x_off = (uint32_t)dict16;
-    a.tile_area = 64 * (small ? kSmallRingBytes : kRingBytes);
-    const bool half = batch <= 8;   // 8 batch rows in the tile: room for two more wavefronts beside large rings
-    const bool more = !small && half && !gate_up && dict16 + (size_t)kRingWavesMore * a.tile_area + ring_x_tile(8) + 128 <= kLdsLimit;   // a smaller dictionary leaves room
-    // batches up to 4 beside a dictionary too large for that: a tile of 4 rows leaves room for one wavefront more
-    const bool quarter = !small && !more && !gate_up && batch <= 4 && dict16 + (size_t)kRingWavesQuarter * a.tile_area + ring_x_tile(4) + 128 <= kLdsLimit;
-    const int waves = small ? (gate_up ? kRingWavesSmallGated : kRingWavesSmall) : more ? kRingWavesMore : quarter ? kRingWavesQuarter : half && !gate_up ? kRingWavesHalf : kRingWaves;   // (gated pairs hold sums in registers)
+    a.tile_area = 64 * kSmallRingBytes;
+    const bool half = batch <= 8;   // 8 batch rows in the tile
+    const int waves = gate_up ? kRingWavesGated : kRingWaves;   // (gated pairs hold sums in registers)
     a.slot_off = (uint32_t)(dict16 + (size_t)waves * a.tile_area);
-    p.lds = a.slot_off + ring_x_tile(quarter ? 4 : half ? 8 : 16) + 128;   // + the band counter
-    if (p.lds > kLdsLimit || !x_fast) {
-      set_error("internal: ring launch with a dictionary or activations that do not fit it");
+    p.lds = a.slot_off + ring_x_tile(half ? 8 : 16) + 128;   // + the band counter
+    if (p.lds > kLdsLimit || !x_fast || !small) {
+      set_error("internal: ring launch with a dictionary, activations or matrices that do not fit it");
       return TQ_E_UNSUPPORTED;
     }
-    if (small) {
-      if (gate_up && half) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, true, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 8, false, true>;
-      else if (gate_up) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, true, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmallGated, 16, false, true>;
-      else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 8, false>;
-      else p.kernel = packed ? (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, true> : (const void*)k_matvec_ring<kSmallRingBytes, kRingWavesSmall, 16, false>;
-    } else if (gate_up) {
-      if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, true, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 8, false, true>;
-      else p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false, true>;
-    } else if (more) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesMore, 8, false>;
-    else if (quarter) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesQuarter, 4, false>;
-    else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, true> : (const void*)k_matvec_ring<kRingBytes, kRingWavesHalf, 8, false>;
-    else p.kernel = packed ? (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingBytes, kRingWaves, 16, false>;
+    if (gate_up && half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesGated, 8, true, true> : (const void*)k_matvec_ring<kRingWavesGated, 8, false, true>;
+    else if (gate_up) p.kernel = packed ? (const void*)k_matvec_ring<kRingWavesGated, 16, true, true> : (const void*)k_matvec_ring<kRingWavesGated, 16, false, true>;
+    else if (half) p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 8, true> : (const void*)k_matvec_ring<kRingWaves, 8, false>;
+    else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingWaves, 16, false>;
     p.block = (unsigned)waves * 64;
   } else if (op == Op::kMatvec && runs) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size) | a count per lane
@@ -709,13 +679,13 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   return fire(p, stream);
 }
 
-// Whether the batched product of this matrix can keep a ring per lane instead of the whole strip.
+// Whether k_matvec_ring takes a matrix (and x).  Any dictionary fits it.
+static_assert(2 * (size_t)(TQ_MAX_ENTRIES_DEVICE + 1) + (size_t)kRingWaves * 64 * kSmallRingBytes + ring_x_tile(16) + 128 <= kLdsLimit, "LDS of k_matvec_ring");
 bool ring_eligible(const tq_matrix* t, const void* x) {
   const DevMat& m = t->m;
   const uint32_t seg_weights = (m.packing ? 2u : 1u) * m.seg_cols;   // what the activation tile of a quad is sized by
-  return m.ring && m.cols % (kUnitPanels * m.seg_cols) == 0 && m.seg_cols % (8 * kRingGroup) == 0 &&
-         seg_weights <= kRingMaxSeg && (uintptr_t)x % 16 == 0 &&
-         round_up((uint64_t)m.dict_words * 2, kRingBytes) + (size_t)kRingWaves * 64 * kRingBytes + ring_x_tile(16) + 128 <= kLdsLimit;
+  return m.ring == 2 && m.cols % (kUnitPanels * m.seg_cols) == 0 && m.seg_cols % 32 == 0 && seg_weights <= kRingMaxSeg &&
+         (uintptr_t)x % 16 == 0;
 }
 
 // (what tq_set_ring_min_bands_per_cu sets; tests use 0 to put small matrices through the ring kernel)

@@ -6,21 +6,24 @@
 
 namespace tq {
 // ---------------------------------------------------------------------------------------------------------------
-// The batched product with a ring of kRing bytes per lane (128, or 64) in place of the whole strip, and the activations in LDS.
+// The batched product with a ring of 64 bytes per lane in place of the whole strip, and the activations in LDS.
 //
 // The 16 rows of a band take their codes in step but reach different columns, so some per-lane storage has to bring
 // them back into line before an MFMA can take 8 columns of all of them; what it has to hold is only the distance
 // between the slowest and the fastest lane, not the segment.  Every ring_step chunks the wavefront asks whether every
 // lane has passed the next ring_group windows (one compare and a look at the condition mask) and, if so,
 // multiplies them; a lane advances by at most 8 columns per chunk, so one group per look keeps up.  Bytes of the ring
-// are reused kRing columns later: a lane writes 8-byte piece q only when q + 8 - kRing <= done, which holds
+// are reused 64 columns later: a lane writes 8-byte piece q only when q + 8 - 64 <= done, which holds
 // whenever no lane is ever more than ring_spread columns ahead of an unfinished one (derived in tq_plan.h); the host sees to
-// that for every unit when the container is loaded (level_unit): 33 columns for the small ring, which nearly every matrix
-// keeps, else 65; a matrix where it cannot goes to the whole-strip kernel.
-// Piece p (8 bytes) of lane l lives at p ^ swizzle(l) within the lane's ring: when the 64 lanes read the same window, the
+// that for every unit when the container is loaded (level_unit): 33 columns.  A matrix where it cannot (its lanes change places:
+// one ahead now and slower than the others later on, without a code to spare) goes to the runs kernel, whose rings of 128 bytes take
+// 65 columns, and beyond that to the whole-strip kernel.  (Of 320 containers of the encoder, normal and Student-t weights in all widths,
+// segments and dictionaries, none has such a matrix with segments of up to 256 columns.  One made for it, lanes 40 columns apart,
+// eight times 8192 x 3072: 104 us at batch 8 and 198 at batch 16, 83 and 97 by a form of this kernel with rings of 128 bytes.)
+// Piece p (8 bytes) of lane l lives at p ^ ring_swizzle(l) within the lane's ring: when the 64 lanes read the same window, the
 // 16 lanes served together hit different banks.
 //
-// With 8 KB of ring per wavefront, 8 wavefronts leave room for the activations of one quad (4 panels) in LDS, laid out
+// With 4 KB of ring per wavefront, 16 wavefronts leave room for the activations of one quad (4 panels) in LDS, laid out
 // as the B operands the MFMA steps take: [panel][window][batch row 0..15][8 columns], 16 bytes per lane and step, read
 // with one ds_read_b128.  (Taken from global memory, every step's fragment load touches 4 panels x batch rows
 // different cache lines; that, not the decode, then bounds the kernel.)  All wavefronts of a workgroup therefore work
@@ -30,17 +33,15 @@ namespace tq {
 // one workgroup barrier apart from each other, so the result does not depend on timing.
 // Needs rows of a whole number of units (a multiple of 4 * seg_cols columns), segments of 32..256 columns in
 // multiples of 32 (packed 4-bit weights: 32..128 bytes), and 16-byte aligned activations.
-constexpr int kRingWaves = 8;       // with an activation tile of 16 batch rows
-constexpr int kRingWavesHalf = 10;  // with one of 8 batch rows (batches up to 8): more wavefronts fit next to the smaller tile
-constexpr int kRingWavesMore = 12;  // the same beside a dictionary of at most 24,512 entries
-constexpr int kRingWavesQuarter = 11;   // with a tile of 4 batch rows (batches up to 4) beside a full dictionary
-// With rings of 64 bytes (kSmallRingBytes) there is LDS for 16 wavefronts, and the vector ALUs, which 10 wavefronts keep busy
-// for 75 % of the time, have more to choose from.  Gated pairs keep sums in registers, 16 wavefronts of them spill.  us, rings of 128
-// bytes -> 64 with 16 | 12 wavefronts: eight LLaMA-3.2-3B layers batch 4 225 -> 203 | 222, batch 8 228 -> 208 | 223, batch 16 252 ->
-// 228 | 239, packed weights batch 8 182 -> 151 | 169, batch 16 202 -> 183 | 189; gated pairs of eight blocks batch 8 116 -> 103 |
-// 99, batch 16 119 -> 113 | 102, packed batch 8 92 -> 80 | 77, batch 16 94 -> 90 | 79.  (Two accumulators per wavefront instead of
-// four, which the groups of two windows suggest, made the sums 8 % less exact: hence the turns in multiply_ready.)
-constexpr int kRingWavesSmall = 16, kRingWavesSmallGated = 12;
+//
+// 16 wavefronts: with rings of 128 bytes there is LDS for 10, which keep the vector ALUs busy for 75 % of the time.  12 of gated pairs,
+// whose sums stay in registers (16 would spill them); of the plain forms the one for packed weights and 9 to 16 rows of x spills 11
+// registers and is still faster with 16.  us, rings of 128 bytes -> 64 with 16 | 12 wavefronts: eight LLaMA-3.2-3B layers batch 4
+// 225 -> 203 | 222, batch 8 228 -> 208 | 223, batch 16 252 -> 228 | 239, packed weights batch 8 182 -> 151 | 169, batch 16 202 ->
+// 183 | 189; gated pairs of eight blocks batch 8 116 -> 103 | 99, batch 16 119 -> 113 | 102, packed batch 8 92 -> 80 | 77, batch 16
+// 94 -> 90 | 79.  (Two accumulators per wavefront instead of four, which the groups of two windows suggest, made the sums 8 % less
+// exact: hence the turns in multiply_ready.)
+constexpr int kRingWaves = 16, kRingWavesGated = 12;
 constexpr uint32_t kRingMaxSeg = 256;
 constexpr int kRingMinBandsPerCu = 24;   // tq_set_ring_min_bands_per_cu's default, see ring_pays
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
@@ -49,7 +50,7 @@ constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * ro
 template <int kRing>
 __device__ __forceinline__ uint32_t ring_swizzle(int lane) { return (kRing == 128 ? (uint32_t)lane & 15u : (uint32_t)lane >> 2 & 7u) << 3; }
 
-// append_chunk for the ring: the complete 8-byte piece goes to its swizzled place; sw8 = 8 * (lane & 15).
+// append_chunk for the ring: the complete 8-byte piece goes to its swizzled place; sw8 = ring_swizzle(lane).
 // kClamp: pos never passes seg_len (pad codes fall off the end).  A piece is complete when pos crosses a multiple of 8.
 template <int kRing, bool kClamp>
 __device__ __forceinline__ void append_chunk_ring(uint2 c, uint32_t ring, uint32_t sw8, uint32_t seg_len, uint32_t& pos, uint64_t& carry) {
@@ -77,10 +78,11 @@ typedef __attribute__((address_space(3))) const u32x4 lds_cu128;
 constexpr uint32_t kNoBand = 0xFFFFFFFFu;
 // kPacked: the ring holds packed 4-bit weights; an 8-byte piece is then two MFMA steps (16 columns), and the activation
 // tile has two windows per piece.
-template <int kRing, int kRows, bool kPacked, typename Claim, typename OnUnit>
+template <int kRows, bool kPacked, typename Claim, typename OnUnit>
 __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad, uint32_t first_band, Claim&& claim, int lane, uint32_t ring,
                                                   uint32_t xfrag, OnUnit&& on_unit) {
   if (first_band == kNoBand) return;
+  constexpr int kRing = kSmallRingBytes;
   constexpr int kP = ring_piece(kRing), kG = ring_group(kRing), kLook = ring_step(kRing), kParts = (kP + kLook - 1) / kLook;
   static_assert((kP - 1) / kLook == kParts - 1 && (kP - 2) / kLook >= kParts - 2, "the parts of a piece that the loops below request");
   constexpr int kFold = 16 / kRows;   // windows per B operand (fold_sums)
@@ -218,9 +220,9 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
 // of kGateUpBands per wavefront, each wavefront's bands fixed, with their sums in registers from the first quad to the
 // last.  A pass takes 32 bands at least (gated pairs of eight LLaMA-3.2-3B blocks, batch 16, 12 wavefronts: 102 us in one pass of
 // 36 bands, 121 in two of 24).
-template <int kRing, int kWaves, int kRows, bool kPacked, bool kGateUp = false>
+template <int kWaves, int kRows, bool kPacked, bool kGateUp = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
-  constexpr int kRingThreads = kWaves * 64, kGateUpBands = (32 + kWaves - 1) / kWaves;
+  constexpr int kRing = kSmallRingBytes, kRingThreads = kWaves * 64, kGateUpBands = (32 + kWaves - 1) / kWaves;
   constexpr uint32_t kRingXTile = ring_x_tile(kRows);
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
           }
           request_scales(next_band);
         };
-        decode_units_ring<kRing, kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
+        decode_units_ring<kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
       }
       if constexpr (kGateUp) {
 #pragma unroll

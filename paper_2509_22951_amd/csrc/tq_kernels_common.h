@@ -50,7 +50,7 @@ struct DevMat {
   uint32_t x_span;         // dwords per panel in the LDS image of x: seg_cols plus a gap that spreads the 4 panels of a unit over the banks
   uint32_t x_dwords;       // size of that image, including the columns lanes can reach while they consume pad codes
   uint32_t seg_magic;      // floor(2^32 / seg_cols) + 1: col / seg_cols == mulhi(col, seg_magic) for every column index in use
-  uint32_t ring;           // the lanes of every unit stay as close together as rings of 128 bytes (1), or of 64 bytes too (2), need; else 0
+  uint32_t ring;           // the lanes of every unit stay as close together as rings of 128 bytes (1), or of 64 bytes too (2), need; else 0 (ring_class)
   uint32_t packing;        // 1: every byte holds two 4-bit weights (columns 2j and 2j + 1 of a matrix of 2 * cols columns); rows,
                            // cols and seg_cols describe the byte matrix, and dict_bf16 holds four fp8 (e4m3) weights per entry
   uint32_t long_runs;      // 1: runs of 3 and 4 bytes exist (lmax > 2): the code space classes below apply, and dict / dict_bf16

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "tq_format.h"
+#include "tq_plan.h"
 
 namespace tq {
 
@@ -99,6 +100,19 @@ inline bool level_units(const uint16_t* codes, const uint32_t* uoff, const std::
     work();
   }
   return !refused;
+}
+
+// What the ring kernels can do with a valid container whose units `wide` have lanes further apart than the small ring takes:
+// 2 - k_matvec_ring and k_matvec_runs with rings of either size, 1 - k_matvec_runs with rings of 128 bytes, 0 - neither.  codes:
+// for 2 and 1, what takes the place of those units' codes, one unit behind the other.
+inline uint32_t ring_class(const void* blob, const Header& h, const std::vector<uint32_t>& wide, unsigned n_threads, std::unique_ptr<uint16_t[]>& codes) {
+  if (h.lmax > 2) return 0;   // (runs of 3 and 4 bytes)
+  const uint8_t* base = (const uint8_t*)blob;
+  auto level_to = [&](uint32_t limit) {
+    return level_units((const uint16_t*)(base + h.off_codes), (const uint32_t*)(base + h.off_uoff), wide, h.n_entries, (const uint32_t*)(base + h.off_dict), limit,
+                       n_threads, codes);
+  };
+  return level_to(kSmallRingSpread) ? 2u : level_to(kRingSpread) ? 1u : 0u;
 }
 
 }  // namespace tq

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import paper_2509_22951_amd as tq
+from drifting import ring_class
 from inputs import make_activations, make_weights, small_case
 from oracle import oracle as O
 
@@ -334,7 +335,7 @@ def test_multi_launch_matches_single_launches_and_oracle(dev, shared_dictionary)
         _multi_case(dev, shapes, batch, shared_dictionary)
 
 
-def test_multi_launch_splits_into_ring_and_whole_strip_launches(dev, ring_for_small_launches):
+def test_multi_launch_splits_into_ring_and_runs_launches(dev, ring_for_small_launches):
     """One call whose matrices go partly to the ring kernel (inherited dictionary, whole units, aligned activations) and
     partly to the runs kernel (300 columns: no whole units)."""
     shapes = [(192, 768, 64), (64, 768, 64), (64, 768, 192), (40, 300, 32), (512, 768, 192), (192, 2048, 256), (100, 1024, 128)]
@@ -407,6 +408,7 @@ def test_full_size_shapes_in_the_benchmarks_launch_configuration_every_row(dev, 
     for spec in specs:
         W = make_weights(spec)
         prev = tq.tq_encode(W, dict_from=prev, bits=0 if width == 8 else width, pack=pack)
+        first = prev if not mats else first
         mats.append(tq.Matrix(prev))
         parts = _oracle_by_row_blocks(lambda a, b: O.quantize_rows(W[a:b], bits=width), spec.rows)
         q_ref.append(np.concatenate([p[0] for p in parts]))
@@ -425,7 +427,7 @@ def test_full_size_shapes_in_the_benchmarks_launch_configuration_every_row(dev, 
             assert torch.equal(o, torch.from_numpy(Qs).to(dev))          # the whole matrix, bit for bit
         del outs
         if config == 4 and not pack:
-            assert all(m.info["lane_spread"] <= 113 for m in mats)   # none of them needs the whole-strip kernel
+            assert ring_class(first) == 2 and all(m.info["lane_spread"] <= RING_SPREAD_LIMIT for m in mats[1:])
         for batch in batches:
             xs, ys, refs = [], [], []
             for sp, Qs, ss in zip(specs, q_ref, s_ref):
@@ -454,10 +456,10 @@ def test_full_size_shapes_in_the_benchmarks_launch_configuration_every_row(dev, 
             m.close()
 
 
-RING_SPREAD_LIMIT = 65   # lane_spread up to which the batched product keeps a 128-byte ring per lane instead of the whole segment
+RING_SPREAD_LIMIT = 65   # lane_spread up to which the batched product keeps a ring per lane (of 128 bytes) as the container has it
 
 
-def test_batched_product_ring_and_whole_strip_kernels_agree(dev, ring_for_small_launches):
+def test_batched_product_ring_and_runs_kernels_agree(dev, ring_for_small_launches):
     """A matrix encoded with an inherited, full dictionary keeps its 64 lanes close together (lane_spread small): with
     16-byte aligned activations its batched product runs on the ring kernel, with misaligned ones on the runs
     kernel.  Both must match the oracle, for every batch size that takes these kernels, over several bands, several
@@ -468,7 +470,7 @@ def test_batched_product_ring_and_whole_strip_kernels_agree(dev, ring_for_small_
         W = make_weights(spec)
         blob = tq.tq_encode(W, max_entries=3000, seg_cols=seg, dict_from=first)
         info = tq.tq_validate_blob(blob)
-        assert info["lane_spread"] <= RING_SPREAD_LIMIT and cols % (4 * seg) == 0, info
+        assert info["lane_spread"] <= RING_SPREAD_LIMIT and ring_class(blob) == 2 and cols % (4 * seg) == 0, info
         Qo, so = O.quantize_rows(W)
         m = tq.Matrix(blob)
         try:
@@ -485,15 +487,14 @@ def test_batched_product_ring_and_whole_strip_kernels_agree(dev, ring_for_small_
             m.close()
 
 
-def test_matrix_that_starts_a_dictionary_takes_the_careful_ring_mode(dev, ring_for_small_launches):
+def test_matrix_that_starts_a_dictionary_on_the_ring_kernel(dev, ring_for_small_launches):
     """The first segments of a matrix that starts from the 256 single bytes are nearly all singles, later ones nearly all
-    pairs: the lanes of the first units are further apart than the ring absorbs in groups of 4 windows, but not further
-    than it absorbs window by window."""
+    pairs: the lanes of the first units are further apart than any ring absorbs.  They are brought together when the matrix is
+    loaded, and it takes the ring kernel."""
     spec = small_case(128, 1024, seed=950)
     W = make_weights(spec)
     blob = tq.tq_encode(W, seg_cols=256)
-    spread = tq.tq_validate_blob(blob)["lane_spread"]
-    assert RING_SPREAD_LIMIT < spread <= 113, spread
+    assert tq.tq_validate_blob(blob)["lane_spread"] > RING_SPREAD_LIMIT and ring_class(blob) == 2
     Qo, so = O.quantize_rows(W)
     m = tq.Matrix(blob)
     try:
@@ -560,7 +561,7 @@ def test_packed_four_bit_weights(dev, rows, cols, width, seg_cols, dictionary):
 def test_packed_weights_on_the_ring_kernel(dev, ring_for_small_launches):
     """Whole units of packed bytes with the lanes close together: aligned activations take the ring kernel (two MFMA steps
     per 8-byte piece), misaligned ones the runs kernel; both match the oracle.  The first matrix starts its
-    dictionary (lanes further apart: careful mode or whole strips), the others inherit a full one."""
+    dictionary, the others inherit a full one."""
     first_spec = small_case(256, 1024, seed=995)
     first = tq.tq_encode(make_weights(first_spec), bits=4, seg_cols=64, pack=True)
     cases = [(first_spec, first)]
@@ -571,6 +572,7 @@ def test_packed_weights_on_the_ring_kernel(dev, ring_for_small_launches):
     for spec, blob in cases:
         info = tq.tq_validate_blob(blob)
         spreads.append(info["lane_spread"])
+        assert ring_class(blob) == 2
         assert (spec.cols // 2) % (4 * info["seg_cols"]) == 0
         Qo, so = O.quantize_rows(make_weights(spec), bits=4)
         m = tq.Matrix(blob)
@@ -586,7 +588,7 @@ def test_packed_weights_on_the_ring_kernel(dev, ring_for_small_launches):
                 assert np.array_equal(ring, gpu_matvec(m, bits, dev))
         finally:
             m.close()
-    assert min(spreads[1:]) <= RING_SPREAD_LIMIT, spreads       # at least these run in groups of four pieces
+    assert max(spreads) <= RING_SPREAD_LIMIT, spreads
 
 
 def test_two_activation_rows_on_the_dot_product_kernel(dev):
@@ -870,10 +872,10 @@ def test_frequency_dictionary_containers_on_the_device(dev, ring_for_small_launc
         m.close()
 
 
-def test_lanes_far_apart_fall_back_to_the_whole_strip_kernel(dev):
+def test_zero_rows_beside_rows_of_single_bytes(dev):
     """All-zero rows (every code a pair once the dictionary knows the pair of zeros) next to rows of values the small
-    frozen dictionary has no pairs for (every code a single): the lanes of a unit drift far apart, lane_spread exceeds
-    what a ring can absorb, and the batched product must still be exact through the whole-strip kernel."""
+    frozen dictionary has no pairs for (every code a single): the lanes of every unit drift as far apart as they can.  Those that
+    are ahead have half their codes to spare, so all units are brought together when the matrix is loaded."""
     rng = np.random.default_rng(5)
     rows, cols = 64, 2048
     Q = rng.integers(-127, 128, size=(rows, cols), dtype=np.int8)
@@ -881,7 +883,7 @@ def test_lanes_far_apart_fall_back_to_the_whole_strip_kernel(dev):
     scales = rng.uniform(0.5, 2.0, rows).astype(np.float32)
     blob = tq.tq_encode_quantized(Q, scales, max_entries=300, seg_cols=256)
     info = tq.tq_validate_blob(blob)
-    assert info["lane_spread"] > 113, info   # more than the ring absorbs even window by window
+    assert info["lane_spread"] > 113 and ring_class(blob) == 2, info
     spec = small_case(rows, cols, seed=77)
     m = tq.Matrix(blob)
     try:
@@ -983,7 +985,7 @@ def test_prepared_step_serves_more_matrices_per_launch_than_the_kernel_arguments
     assert _step_case(dev, shapes, 4) == 1
 
 
-def test_prepared_step_with_ring_whole_strip_and_packed_matrices(dev, ring_for_small_launches):
+def test_prepared_step_with_ring_runs_and_packed_matrices(dev, ring_for_small_launches):
     """One step whose matrices go to different kernels: ring (whole units), runs (300 columns), packed 4-bit."""
     shapes = [(192, 768, 64), (64, 768, 64), (64, 768, 192), (40, 300, 32), (512, 768, 192), (192, 2048, 256), (100, 1024, 128)]
     for batch in (1, 3, 16):

@@ -1,41 +1,42 @@
-"""The ring kernel with rings of 64 and of 128 bytes, around the distance between lanes where one takes over from the other."""
+"""The batched kernels around the distance between lanes up to which rings of 64 bytes do, and the runs kernel with such rings."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2509_22951_amd as tq
+from drifting import drifting, ring_class
 from inputs import make_activations, make_weights, small_case
 from oracle import oracle as O
-from test_gpu_work_split import TOL, _drifting, _stream
+from test_gpu_work_split import TOL, _gated, _stream
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("cols,seg_cols,opts", [(2048, 256, {}), (384, 96, {}), (1024, 128, {"pack": True})], ids=["256", "96", "packed"])
-@pytest.mark.parametrize("limit", [32, 33, 34, 40])
-def test_lanes_around_the_limit_of_the_small_ring(cols, seg_cols, opts, limit):
-    Q, scales, m = _drifting(5, cols, seg_cols, limit, opts)
+@pytest.mark.parametrize("limit,spare,kind", [(32, True, 2), (33, True, 2), (34, True, 2), (40, True, 2), (32, False, 2), (33, False, 2), (34, False, 1), (40, False, 1)])
+def test_lanes_around_the_limit_of_the_small_ring(cols, seg_cols, opts, limit, spare, kind):
+    """Lanes that can wait are brought within 33 columns when the matrix is loaded, whatever they were, and take the ring kernel; so do
+    lanes that cannot but are no further apart; beyond that the runs kernel takes the matrix, with rings of 128 bytes."""
+    if not spare and seg_cols < 3 * limit + 8:
+        pytest.skip("a segment too short for such lanes")
+    Q, scales, blob = drifting(1, cols, seg_cols, limit, opts, spare)
+    assert ring_class(blob) == kind
+    m = tq.Matrix(blob)
     tq.tq_set_ring_min_bands_per_cu(0)
     try:
         for batch in (3, 8, 16):
             bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
             ref = O.gemv_f64(Q, scales, x)
-            gate, up = ref[:, 0::2], ref[:, 1::2]
-            gated = gate / (1.0 + np.exp(-gate)) * up
-            # Both sums are within e = TOL * max |ref| of a batch row; |silu'| <= 1.1 and |silu(g)| <= |g|, so the gated product is
-            # within e * (1.1 |up| + |gate|) (and e^2).  (Relative to the row's largest output it may be far off: where every
-            # gate of a batch row is well below zero, silu(g) ~ g exp(g) turns an error of the sum into a factor.)
-            e = TOL * np.abs(ref).max(axis=1, keepdims=True)
-            limits = (e, e * (1.1 * np.abs(up) + np.abs(gate) + e))
+            gated, most = _gated(ref)
             xd = torch.from_numpy(bits.view(np.int16).copy()).cuda()
             y = torch.full((batch, 16), float("nan"), dtype=torch.float32, device="cuda")
             g = torch.full((batch, 8), float("nan"), dtype=torch.float32, device="cuda")
             m.matvec(xd.data_ptr(), y.data_ptr(), batch, _stream())
             tq.tq_matvec_gate_up(m.handle, xd.data_ptr(), g.data_ptr(), batch, _stream())
             torch.cuda.synchronize()
-            for got, want, most in ((y, ref, limits[0]), (g, gated, limits[1])):
+            for got, want, limits in ((y, ref, TOL * np.abs(ref).max(axis=1, keepdims=True)), (g, gated, most)):
                 got = got.cpu().numpy().astype(np.float64)
-                assert np.isfinite(got).all() and (np.abs(got - want) <= most).all()
+                assert np.isfinite(got).all() and (np.abs(got - want) <= limits).all()
     finally:
         tq.tq_set_ring_min_bands_per_cu(24)
         m.close()

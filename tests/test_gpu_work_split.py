@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2509_22951_amd as tq
+from drifting import drifting, ring_class
 from inputs import make_activations, make_weights, small_case
 from oracle import oracle as O
 
@@ -125,7 +126,7 @@ RUNS = [
     (33, 300, 48),         # segments of one and a half groups of windows, the last one short
     (40, 1021, 256),       # one unit per band, row ends inside a fragment
     (100, 4095, 1024),     # the widest segments
-    (5000, 2999, 256),     # bands shared between wavefronts, a dictionary's start (units that need care)
+    (5000, 2999, 256),     # bands shared between wavefronts, a dictionary's start (units that are levelled)
 ]
 
 
@@ -143,62 +144,27 @@ def test_runs_of_units_in_batches(rows, cols, seg_cols, batch, shift, opts):
         job.m.close()
 
 
-def _bytes_at_the_limit(seed, cols, seg_cols, limit):
-    """One band of bytes whose last unit's lanes drift exactly `limit` columns apart when it is coded with the pairs (p, p + 32),
-    p = 64..95, and single bytes: its first row takes pairs and the others single bytes until they are that far apart, then
-    all take the same number of columns per chunk of 4 codes, in bursts of pairs among others.  The units before hold single
-    bytes alone.  -> bytes [16, cols]"""
-    rng = np.random.default_rng(seed)
-    Q = rng.integers(1, 64, (16, cols), dtype=np.uint8)
-    steps, slow, gap, burst = [], 0, 0, 0       # columns per chunk of the first row and the others, the same in all panels
-    while slow < seg_cols:
-        a = b = 4
-        if gap < limit:
-            a = min(8, b + limit - gap)
-            gap += a - b
-        else:
-            burst = burst - 1 if burst else (6 if rng.integers(4) == 0 else 0)
-            a = b = 8 if burst else int(rng.integers(4, 9))
-        steps.append((a, b))
-        slow += b
-    unit = (cols - 1) // (4 * seg_cols) * (4 * seg_cols)
-    for first in range(unit, cols, seg_cols):
-        end = min(cols, first + seg_cols)
-        for r in range(16):
-            at = first
-            for step in steps:                  # a chunk: pairs for the columns beyond 4, then single bytes
-                n = min(step[min(r, 1)], end - at)
-                for k in range(max(0, n - 4)):
-                    Q[r, at + 2 * k] = rng.integers(64, 96)
-                    Q[r, at + 2 * k + 1] = Q[r, at + 2 * k] + 32
-                at += n
-    return Q
-
-
-def _drifting(seed, cols, seg_cols, limit, opts):
-    """_bytes_at_the_limit as a container -> (weights, scales, matrix)."""
-    Qb = _bytes_at_the_limit(seed, cols, seg_cols, limit)
-    pairs = np.array([[p, p + 32] for p in range(64, 96)], np.uint8).view(np.int8)
-    d = tq.tq_encode_quantized(pairs, np.ones(32, np.float32), max_entries=288, dictionary="frequency")
-    Q = Qb.view(np.int8)
-    if opts:   # byte j of a row holds columns 2j and 2j + 1 as 4-bit values
-        Q = np.stack([((Qb & 15) ^ 8).astype(np.int8) - 8, ((Qb >> 4) ^ 8).astype(np.int8) - 8], axis=2).reshape(Qb.shape[0], -1)
-    scales = np.linspace(0.005, 0.015, Q.shape[0]).astype(np.float32)
-    blob = tq.tq_encode_quantized(Q, scales, max_entries=288, seg_cols=seg_cols, dict_from=d, dictionary="frequency", **opts)
-    assert tq.tq_validate_blob(blob)["lane_spread"] == limit
-    return Q, scales, tq.Matrix(blob)
-
-
 @pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
-@pytest.mark.parametrize("limit", [65, 113])              # the fast and the careful form of the ring decode
-@pytest.mark.parametrize("cols,seg_cols,seed", [
-    # seven units for one workgroup, taken whole: the last one ends inside a piece of the ring.  (With this seed the first row
-    # stands 128 columns past what has been multiplied at 1 look per panel of the fast form, 21 of the careful one.)
-    (7 * 4 * 1008 - 12, 1008, 2),
-    (500, 512, 2),                 # one unit, cut between the wavefronts
+@pytest.mark.parametrize("cols,seg_cols,limit,spare,kind", [
+    # Seven units for one workgroup, taken whole: the last one ends inside a piece of the ring.  (With this seed the first row stands
+    # a whole ring past what has been multiplied at 1 look per panel of 128 bytes, 5 of 64.)  Lanes that can wait are brought
+    # together when the matrix is loaded; those that cannot stand as far apart as the rings of 64 and of 128 bytes take.
+    (7 * 4 * 1008 - 12, 1008, 65, True, 2),
+    (7 * 4 * 1008 - 12, 1008, 113, True, 2),
+    (7 * 4 * 1008 - 12, 1008, 33, False, 2),
+    (7 * 4 * 1008 - 12, 1008, 34, False, 1),
+    (7 * 4 * 1008 - 12, 1008, 65, False, 1),
+    # one unit, cut between the wavefronts
+    (500, 512, 65, True, 2),
+    (500, 512, 113, True, 2),
+    (500, 512, 33, False, 2),
+    (500, 512, 66, False, 1),      # (the rows end ahead of the last chunk: a few codes to spare)
 ])
-def test_lanes_as_far_apart_as_the_ring_takes(cols, seg_cols, seed, limit, opts):
-    Q, scales, m = _drifting(seed, cols, seg_cols, limit, opts)
+def test_lanes_as_far_apart_as_the_rings_take(cols, seg_cols, limit, spare, kind, opts):
+    """k_matvec_runs with rings of 128 bytes (kind 1) and of either size (kind 2)."""
+    Q, scales, blob = drifting(2, cols, seg_cols, limit, opts, spare)
+    assert ring_class(blob) == kind
+    m = tq.Matrix(blob)
     try:
         for batch in (3, 8, 16):
             bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
@@ -214,27 +180,82 @@ def test_lanes_as_far_apart_as_the_ring_takes(cols, seg_cols, seed, limit, opts)
         m.close()
 
 
+def _gated(ref):
+    """silu(gate) * up of the even and odd rows of a product, and how far it may be off: both sums are within e = TOL * max |ref| of a
+    batch row; |silu'| <= 1.1 and |silu(g)| <= |g|, so the gated product is within e * (1.1 |up| + |gate|) (and e^2)."""
+    gate, up = ref[:, 0::2], ref[:, 1::2]
+    e = TOL * np.abs(ref).max(axis=1, keepdims=True)
+    return gate / (1.0 + np.exp(-gate)) * up, e * (1.1 * np.abs(up) + np.abs(gate) + e)
+
+
 @pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
-@pytest.mark.parametrize("cols,seg_cols,limit", [(2048, 512, 114), (4096, 512, 200), (500, 512, 150)])
-def test_lanes_further_apart_than_the_ring_takes(cols, seg_cols, limit, opts):
+@pytest.mark.parametrize("cols,seg_cols,limit", [(2048, 512, 66), (2048, 512, 114), (4096, 512, 150), (500, 512, 150)])
+def test_lanes_further_apart_than_the_rings_take(cols, seg_cols, limit, opts):
     """The whole-strip kernel: whole units and a ragged one, 16-byte aligned x and x at odd addresses, products and gated pairs."""
-    Q, scales, m = _drifting(3, cols, seg_cols, limit, opts)
+    Q, scales, blob = drifting(3, cols, seg_cols, limit, opts, spare=False)
+    assert ring_class(blob) == 0
+    m = tq.Matrix(blob)
     try:
         for batch, shift in ((3, 0), (5, 1), (16, 0)):
             bits, x = make_activations(small_case(16, Q.shape[1], seed=batch), batch)
             ref = O.gemv_f64(Q, scales, x)
-            gated = ref[:, 0::2] / (1.0 + np.exp(-ref[:, 0::2])) * ref[:, 1::2]
+            gated, most = _gated(ref)
             xd = torch.from_numpy(np.concatenate([np.zeros(shift, np.int16), bits.view(np.int16).reshape(-1)])).cuda()[shift:]
             y = torch.full((batch, 16), float("nan"), dtype=torch.float32, device="cuda")
             g = torch.full((batch, 8), float("nan"), dtype=torch.float32, device="cuda")
             m.matvec(xd.data_ptr(), y.data_ptr(), batch, _stream())
             tq.tq_matvec_gate_up(m.handle, xd.data_ptr(), g.data_ptr(), batch, _stream())
             torch.cuda.synchronize()
-            for got, want, tol in ((y, ref, TOL), (g, gated, 2 * TOL)):
+            for got, want, limits in ((y, ref, TOL * np.abs(ref).max(axis=1, keepdims=True)), (g, gated, most)):
                 got = got.cpu().numpy().astype(np.float64)
-                assert np.isfinite(got).all() and (np.abs(got - want).max(axis=1) <= tol * np.abs(want).max(axis=1)).all()
+                assert np.isfinite(got).all() and (np.abs(got - want) <= limits).all()
     finally:
         m.close()
+
+
+@pytest.mark.parametrize("opts", [{}, {"pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("gate_up", [False, True])
+def test_matrices_for_all_three_batched_kernels_in_one_call(gate_up, opts):
+    """Lanes 33, 65 and 80 columns apart that cannot wait, several bands each: a launch of the ring kernel, one of the runs kernel
+    (which takes the second matrix, and the first too where the first's x is at an odd address) and one of the whole-strip kernel."""
+    most = (1024, 128) if opts else (2048, 256)      # the widest segments of the ring kernel
+    mats = [drifting(20 + i, *(most if limit == 33 else (2048, 256)), limit, opts, spare=False, rows=rows)
+            for i, (limit, rows) in enumerate([(33, 96), (65, 80), (80, 48), (33, 16), (34, 4112)])]
+    assert [ring_class(blob) for _, _, blob in mats] == [2, 1, 0, 2, 1]
+    hs = [tq.Matrix(blob) for _, _, blob in mats]
+    tq.tq_set_ring_min_bands_per_cu(0)
+    try:
+        for batch in (3, 8, 16):
+            for shift in (0, 1):
+                xs, ys, refs = [], [], []
+                for i, (Q, scales, _) in enumerate(mats):
+                    bits, x = make_activations(small_case(16, Q.shape[1], seed=10 * batch + i), batch)
+                    odd = shift if i in (0, 3) else 0
+                    xs.append(torch.from_numpy(np.concatenate([np.zeros(odd, np.int16), bits.view(np.int16).reshape(-1)])).cuda()[odd:])
+                    refs.append(O.gemv_f64(Q, scales, x))
+                    ys.append(torch.full((batch, Q.shape[0] // (2 if gate_up else 1)), float("nan"), dtype=torch.float32, device="cuda"))
+                args = [h.handle for h in hs], [x.data_ptr() for x in xs], [y.data_ptr() for y in ys], batch
+                step = tq.Step(*args, gate_up=gate_up)
+                assert step.info["n_launches"] == (2 if shift else 3)
+                for through_step in (True, False):
+                    for y in ys:
+                        y.fill_(float("nan"))
+                    if through_step:
+                        step.launch(_stream())
+                    elif gate_up:
+                        tq.tq_matvec_gate_up_multi(*args, _stream())
+                    else:
+                        tq.tq_matvec_multi(*args, _stream())
+                    torch.cuda.synchronize()
+                    for y, ref in zip(ys, refs):
+                        want, most = _gated(ref) if gate_up else (ref, TOL * np.abs(ref).max(axis=1, keepdims=True))
+                        got = y.cpu().numpy().astype(np.float64)
+                        assert np.isfinite(got).all() and (np.abs(got - want) <= most).all()
+                step.close()
+    finally:
+        tq.tq_set_ring_min_bands_per_cu(24)
+        for h in hs:
+            h.close()
 
 
 @pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
