@@ -139,13 +139,15 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  * batch 1 and batch 2 run the dot-product kernel (activations gathered from an LDS image of x, which holds both rows
  * at batch 2; a matrix whose rows are too long for that image to fit the LDS beside the dictionary - more than 8192
  * columns with a full dictionary, more with a smaller one - goes on as batch 3 does, slower but to the same result);
- * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep 64 or 128 bytes of every
- * segment in LDS and multiply while they decode; they take every matrix whose lanes can be brought within 65 columns.
- * The ring kernel has the activations of a quad (4 segments) in LDS as well: for rows that are a whole number of units
- * (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x 16-byte aligned, in calls that
- * bring enough bands of 16 rows per compute unit: about 24 of LLaMA-3.2-3B layers, 12 for batches above 8, more of matrices
- * with few bands and many quads (tq_set_ring_min_bands_per_cu scales that: 24 is the default, 0 is always).  The runs kernel takes its activations from global memory: any other shape of at least 8 columns, any
- * x.  Everything else goes through the whole-strip kernel, which decodes a unit into an LDS tile before it multiplies
+ * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep the last 64 or 128 bytes of
+ * every segment in LDS and multiply while they decode; how far apart the lanes of a matrix are, which tq_info's lane_spread
+ * tells of the container, they are brought closer on the device where their codes leave room for it.  The ring kernel
+ * takes matrices whose lanes are then within 33 columns, and has the activations of a quad (4 segments) in LDS as well: for
+ * rows that are a whole number of units (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x
+ * 16-byte aligned, in calls where an estimate of both kernels' times says that it is the faster one (many bands of 16 rows
+ * per compute unit, few sums to add; tq_set_ring_min_bands_per_cu puts a line of the caller's in its place).  The runs kernel
+ * takes its activations from global memory: any other shape of at least 8 columns, any x, lanes within 65 columns.
+ * Everything else goes through the whole-strip kernel, which decodes a unit into an LDS tile before it multiplies
  * it.  The ring kernel adds the partial sums of a row's later quads to y with atomic adds, always in the same order; y
  * must not be read or written by anything else on the device while the call runs (true of any output buffer).
  * Containers of packed 4-bit weights (TQ_PACK_NIBBLES): cols is the number of weights per row, twice the stored bytes;
@@ -154,10 +156,10 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  */
 int tq_matvec(tq_handle h, const void *x, void *y, int batch, void *stream);
 
-/* Tuning knob of the choice between the MFMA kernels of tq_matvec (see there): the ring kernel hands whole bands
- * of 16 rows to its wavefronts and is taken where an estimate of both kernels' times says that it pays; the estimate for the
- * ring kernel counts bands_per_cu / 24 times (default 24; 0 = whenever a matrix allows it).  Process-wide, atomic; affects the calls and the prepared steps made
- * after it returns.  Results stay within the tolerance either way (the kernels add in different orders). */
+/* Tuning knob of the choice between the MFMA kernels of tq_matvec (see there): with any value but 24, the default, the ring kernel
+ * is taken by launches that bring at least this many bands of 16 rows per compute unit, half as many for batches above 8 (0 =
+ * whenever a matrix allows it); 24 leaves the choice to the estimate of both kernels' times.  Process-wide, atomic; affects the calls
+ * and the prepared steps made after it returns.  Results stay within the tolerance either way (the kernels add in different orders). */
 int tq_set_ring_min_bands_per_cu(uint32_t bands_per_cu);
 
 /*

@@ -36,6 +36,7 @@
 
 #include "../../include/tq.h"
 #include "tq_format.h"
+#include "tq_choice.h"
 #include "tq_level.h"
 #include "tq_kernels_common.h"
 #include "tq_plan.h"
@@ -517,26 +518,13 @@ int fire(const PreparedLaunch& p, hipStream_t stream) {
   return TQ_OK;
 }
 
-// What the busiest workgroup does when the line is cut into `grid` equal parts instead: its part to within half a band,
-// and, with several matrices, a second start (offsets, activations, barriers) in workgroups that get the end of one
-// matrix and the start of the next, worth about kRestartCost of the line (4 us, in which a compute unit streams 100 KB of
-// codes: one LLaMA-3.2-1B layer, 7 matrices, 24.9 us when 6 of the 256 workgroups start twice, 18.4 us in whole workgroups).
-constexpr uint64_t kRestartCost = 6000;
-constexpr int kMaxAssign = 32;
-uint64_t assign_workgroups(int n, const tq_handle* hs, uint64_t grid, uint32_t* wgs) {   // 0: not so (see tq_plan.h)
+// (of matrices on the cost line; n <= kMaxAssign)
+struct BandCounts {
   BandCount m[kMaxAssign];
-  if (n > kMaxAssign) return 0;
-  for (int i = 0; i < n; ++i) m[i] = {hs[i]->m.n_bands, hs[i]->m.cols};
-  return assign_workgroups(n, m, grid, wgs);
-}
-uint64_t even_cut_cost(int n, const tq_handle* hs, uint64_t grid) {
-  uint64_t total = 0, cols_max = 0;
-  for (int i = 0; i < n; ++i) {
-    total += (uint64_t)hs[i]->m.n_bands * hs[i]->m.cols;
-    cols_max = std::max<uint64_t>(cols_max, hs[i]->m.cols);
+  BandCounts(int n, const tq_handle* hs) {
+    for (int i = 0; i < n; ++i) m[i] = {hs[i]->m.n_bands, hs[i]->m.cols};
   }
-  return total / grid + cols_max / 2 + (n > 1 ? kRestartCost : 0);
-}
+};
 
 // Whether k_matvec_runs takes a matrix: any but those whose lanes drift too far apart for a ring (or that hold runs of 3 and 4
 // bytes), and those narrower than one activation fragment.
@@ -597,8 +585,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   const bool long_runs = hs[0]->m.long_runs != 0;   // (likewise)
   auto cut_by_workgroup = [&] {
     uint32_t wgs[kMaxAssign];
-    const uint64_t worst = assign_workgroups(n, hs, std::min<uint64_t>(hs[0]->n_cu, bands), wgs);
-    if (!worst || worst > even_cut_cost(n, hs, p.grid)) return;
+    if (n > kMaxAssign || !cut_in_workgroups(n, BandCounts(n, hs).m, std::min<uint64_t>(hs[0]->n_cu, bands), p.grid, wgs)) return;
     a.by_workgroup = 1;
     p.grid = 0;
     for (int i = 0; i < n; ++i) {
@@ -691,49 +678,25 @@ bool ring_eligible(const tq_matrix* t, const void* x) {
 // (what tq_set_ring_min_bands_per_cu sets; tests use 0 to put small matrices through the ring kernel)
 std::atomic<uint64_t> g_ring_min_bands{kRingMinBandsPerCu};
 
-// Whether the ring kernel is the faster one for a launch of these matrices (all eligible, of one packing).  It walks the quads of a
-// workgroup's bands one after the other with a barrier between them, which few bands do not fill: a quad of n bands takes a + b n
-// us and c n at least, a workgroup that gets the end of one matrix and the start of the next a little more.  The runs kernel
-// takes time by the units alone, more for more rows of x, and most where the codes come from HBM and not from the 256 MB
-// cache behind the L2.  The figures are for units of 16 x 1024 weights, fitted to 24 sizes of launch: LLaMA-3.2-1B and -3B layers as
-// one step and gated pairs, batch 3, 4, 5, 8, 9, 16.  us, ring / runs: one 3B layer batch 8 69 / 33, two 87 / 57, three 126 / 102, four
-// 123 / 127, batch 4 122 / 112; six 1B layers batch 8 144 / 122, batch 16 154 / 224; two 3B layers batch 9 92 / 61, batch 16 95 / 93;
-// packed, four 3B layers batch 8 90 / 101, gated pairs of four blocks batch 8 42 / 52, of two blocks batch 16 29 / 41.  (By bands per
-// compute unit alone, as the line was drawn before, the 1B layers and batch 9 took the wrong one.)
-bool ring_pays(int n, const tq_handle* hs, const void* const* xs, int batch) {
-  const uint64_t weight = g_ring_min_bands.load(std::memory_order_relaxed);
-  if (weight == 0) return true;
+// Whether the matrices of a call that the ring kernel can take should go there and leave the others, if there are any, a launch of
+// their own, or all of them to the runs kernel.  (All of one packing, none for the whole-strip kernel.)
+bool ring_pays(int n, const tq_handle* hs, const void* const* xs, int batch, bool gate_up) {
+  const uint64_t min_bands = g_ring_min_bands.load(std::memory_order_relaxed), n_cu = hs[0]->n_cu;
+  uint64_t bands = 0;
+  for (int i = 0; i < n; ++i) bands += ring_eligible(hs[i], xs[i]) ? hs[i]->m.n_bands : 0;
+  if (min_bands != kRingMinBandsPerCu) return bands >= min_bands / (batch > 8 ? 2 : 1) * n_cu;   // the caller's own line
+  if (bands < 2 * n_cu) return false;   // (no launch of so few was measured faster there)
+  std::vector<BatchedMatrix> m;   // those it can take first
+  m.reserve(n);
+  int n_ring = 0;
+  for (int rest = 0; rest < 2; ++rest) {
+    for (int i = 0; i < n; ++i)
+      if (ring_eligible(hs[i], xs[i]) != (rest != 0)) m.push_back({hs[i]->m.n_bands, hs[i]->m.cols, hs[i]->m.n_quads, hs[i]->m.seg_cols, hs[i]->h.code_bytes});
+    if (!rest) n_ring = (int)m.size();
+  }
   const bool packed = hs[0]->m.packing != 0;
-  double total = 0, units = 0, bytes = 0, quads_min = 1e9;
-  uint64_t bands_all = 0;
-  int taken = 0;
-  for (int i = 0; i < n; ++i) {
-    if (!ring_eligible(hs[i], xs[i])) continue;
-    const DevMat& m = hs[i]->m;
-    const double unit = (packed ? 2. : 1.) * m.seg_cols / 256;
-    total += (double)m.n_bands * m.cols;
-    bands_all += m.n_bands;
-    units += (double)m.n_bands * m.n_quads * unit;
-    bytes += (double)hs[i]->h.code_bytes;
-    quads_min = std::min(quads_min, m.n_quads * unit);
-    ++taken;
-  }
-  if (4 * bands_all < weight * hs[0]->n_cu) return false;   // (6 bands per compute unit: no smaller launch was measured faster)
-  const double share = total / hs[0]->n_cu;
-  const double a = packed ? 4.6 : 6., b = packed ? .56 : .75, c = packed ? .8 : 1.05, rows = batch <= 8 ? 1. : packed ? 1.1 + .014 * (batch - 9) : 1.05;
-  double ring = 0;
-  for (int i = 0; i < n; ++i) {
-    if (!ring_eligible(hs[i], xs[i])) continue;
-    const DevMat& m = hs[i]->m;
-    const double unit = (packed ? 2. : 1.) * m.seg_cols / 256, cost = (double)m.n_bands * m.cols, bands = std::min((double)m.n_bands, share / m.cols);
-    ring = std::max(ring, m.n_quads * unit * std::max(a + b * bands, c * bands) * std::max(1., share / cost));   // (of a small matrix: and others like it)
-  }
-  ring = ring * rows + (taken > 1 ? (packed ? 1. : 2.) * quads_min : 0.);
-  const bool from_hbm = bytes > 240e6;
-  const double per_unit = packed ? (batch <= 4 ? .91 : batch <= 8 ? .97 : 1.06 + .056 * (batch - 9))
-                          : from_hbm ? (batch <= 4 ? 1.09 : batch <= 8 ? 1.24 : 1.52 + .13 * (batch - 9))
-                                     : (batch <= 8 ? 1.03 : 1.15 + .09 * (batch - 9));
-  return ring * weight <= (8. + per_unit * units / hs[0]->n_cu) * kRingMinBandsPerCu;
+  return ring_time(n_ring, m.data(), n_cu, batch, packed, gate_up) + (n_ring < n ? runs_time(n - n_ring, m.data() + n_ring, n_cu, batch, packed) : 0.) <=
+         runs_time(n, m.data(), n_cu, batch, packed);
 }
 
 // As few launches as the kernel-argument size and the 32-bit cost line allow.
@@ -798,7 +761,7 @@ int launch_all(Op op, int n, const tq_handle* hs, const void* const* xs, void* c
     // independent, so regrouping them changes nothing but the launches.
     int n_ring = 0;
     for (int i = 0; i < n; ++i) n_ring += ring_eligible(hs[i], xs[i]) ? 1 : 0;
-    if (n_ring > 0 && !ring_pays(n, hs, xs, batch)) n_ring = 0;
+    if (n_ring > 0 && !ring_pays(n, hs, xs, batch, gate_up)) n_ring = 0;
     if (n_ring == n) return launch_all(op, n, hs, xs, ys, batch, stream, true, gate_up, rec);
     if (n_ring > 0) {
       std::vector<tq_handle> h2[2];
@@ -874,7 +837,7 @@ static int tq_matvec_impl(tq_handle h, const void* x, void* y, int batch, void* 
   if (int rc = check_call("tq_matvec", 1, &h, &x, &y, batch)) return rc;
   return launch(Op::kMatvec, 1, &h, &x, &y, batch, (hipStream_t)stream,
                 !dot_kernel_takes(batch, h->m.packing != 0, h->m.long_runs != 0, h->m.dict_words, h->m.x_dwords) && ring_eligible(h, x) &&
-                    ring_pays(1, &h, &x, batch));
+                    ring_pays(1, &h, &x, batch, false));
 }
 
 static int tq_matvec_multi_impl(int n, const tq_handle* hs, const void* const* xs, void* const* ys, int batch, void* stream) {
@@ -1079,11 +1042,16 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
     bool can = true;
     for (uint32_t k = 0; k < n_stages && can; ++k) {
       const int f = (int)first[k], cnt = (int)(first[k + 1] - first[k]);
+      if (cnt > kMaxAssign) {
+        can = false;
+        break;
+      }
       uint32_t wgs[kMaxAssign];
-      const uint64_t worst = assign_workgroups(cnt, hs + f, p.grid, wgs);
+      const BandCounts counts(cnt, hs + f);
+      const uint64_t worst = assign_workgroups(cnt, counts.m, p.grid, wgs);
       can = worst != 0;
       whole += worst;
-      even += even_cut_cost(cnt, hs + f, p.grid);
+      even += even_cut_cost(cnt, counts.m, p.grid);
       uint32_t at = k * p.grid;
       for (int i = 0; i < cnt && can; ++i) {
         line[f + i] = at;

@@ -43,7 +43,7 @@ namespace tq {
 // exact: hence the turns in multiply_ready.)
 constexpr int kRingWaves = 16, kRingWavesGated = 12;
 constexpr uint32_t kRingMaxSeg = 256;
-constexpr int kRingMinBandsPerCu = 24;   // tq_set_ring_min_bands_per_cu's default, see ring_pays
+constexpr int kRingMinBandsPerCu = 24;   // tq_set_ring_min_bands_per_cu's default: the choice by estimate (tq_choice.h)
 constexpr uint32_t ring_x_tile(int rows) { return kUnitPanels * kRingMaxSeg * rows * 2; }   // bytes: 4 panels x 256 columns x batch rows of bf16
 
 // 8 * swizzle(lane): lanes 2 (4) apart start on the same bank when a ring is 128 (64) bytes

@@ -106,4 +106,24 @@ inline uint64_t assign_workgroups(int n, const BandCount* m, uint64_t grid, uint
   return worst;
 }
 
+// What the busiest workgroup does when the line is cut into `grid` equal parts instead: its part to within half a band,
+// and, with several matrices, a second start (offsets, activations, barriers) in workgroups that get the end of one
+// matrix and the start of the next, worth about kRestartCost of the line (4 us, in which a compute unit streams 100 KB of
+// codes: one LLaMA-3.2-1B layer, 7 matrices, 24.9 us when 6 of the 256 workgroups start twice, 18.4 us in whole workgroups).
+constexpr uint64_t kRestartCost = 6000;
+constexpr int kMaxAssign = 32;   // most matrices that are given whole workgroups
+inline uint64_t even_cut_cost(int n, const BandCount* m, uint64_t grid) {
+  uint64_t total = 0, cols_max = 0;
+  for (int i = 0; i < n; ++i) {
+    total += (uint64_t)m[i].n_bands * m[i].cols;
+    cols_max = std::max<uint64_t>(cols_max, m[i].cols);
+  }
+  return total / grid + cols_max / 2 + (n > 1 ? kRestartCost : 0);
+}
+// Whether a launch of n <= kMaxAssign matrices is cut in whole workgroups, wgs[i] of `most` at most for matrix i, or into `grid` parts.
+inline bool cut_in_workgroups(int n, const BandCount* m, uint64_t most, uint64_t grid, uint32_t* wgs) {
+  const uint64_t worst = assign_workgroups(n, m, most, wgs);
+  return worst && worst <= even_cut_cost(n, m, grid);
+}
+
 }  // namespace tq

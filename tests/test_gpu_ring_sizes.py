@@ -66,3 +66,35 @@ def test_small_shares_at_the_batches_that_take_the_small_rings(rows, cols, seg_c
             assert np.isfinite(got).all() and (np.abs(got - ref).max(axis=1) <= TOL * np.abs(ref).max(axis=1)).all()
     finally:
         m.close()
+
+
+def test_callers_own_line_between_the_batched_kernels():
+    """tq_set_ring_min_bands_per_cu: bands per compute unit from which on a launch goes to the ring kernel, half as many above 8 rows
+    of x; a matrix that only the runs kernel takes shows by a launch of its own.  Both ways give the product."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 16 * (2 * n_cu + 1)
+    specs = [small_case(rows, 256, seed=1), small_case(40, 300, seed=2)]
+    Ws = [make_weights(s) for s in specs]
+    refs = [O.quantize_rows(W) for W in Ws]
+    mats = [tq.Matrix(tq.tq_encode(W, seg_cols=64, max_entries=600)) for W in Ws]
+    try:
+        for line, batch, launches in ((0, 3, 2), (1, 3, 2), (2, 8, 2), (3, 8, 1), (3, 9, 2), (5, 16, 2), (6, 16, 1), (1 << 31, 16, 1)):
+            xs, ys, want = [], [], []
+            for s, (Q, scales) in zip(specs, refs):
+                bits, x = make_activations(s, batch)
+                xs.append(torch.from_numpy(bits.view(np.int16).copy()).cuda())
+                ys.append(torch.full((batch, s.rows), float("nan"), dtype=torch.float32, device="cuda"))
+                want.append(O.gemv_f64(Q, scales, x))
+            tq.tq_set_ring_min_bands_per_cu(line)
+            step = tq.Step([m.handle for m in mats], [x.data_ptr() for x in xs], [y.data_ptr() for y in ys], batch)
+            assert step.info["n_launches"] == launches, (line, batch)
+            step.launch(_stream())
+            torch.cuda.synchronize()
+            step.close()
+            for y, ref in zip(ys, want):
+                got = y.cpu().numpy().astype(np.float64)
+                assert np.isfinite(got).all() and (np.abs(got - ref).max(axis=1) <= TOL * np.abs(ref).max(axis=1)).all()
+    finally:
+        tq.tq_set_ring_min_bands_per_cu(24)
+        for m in mats:
+            m.close()
