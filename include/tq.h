@@ -140,10 +140,10 @@ int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);
  * at batch 2; a matrix whose rows are too long for that image to fit the LDS beside the dictionary - more than 8192
  * columns with a full dictionary, more with a smaller one - goes on as batch 3 does, slower but to the same result);
  * batch 3..16 run an MFMA kernel (the batch is the N dimension).  Of those there are three.  Two keep the last 64 or 128 bytes of
- * every segment in LDS and multiply while they decode; how far apart the lanes of a matrix are, which tq_info's lane_spread
- * tells of the container, they are brought closer on the device where their codes leave room for it.  The ring kernel
- * takes matrices whose lanes are then within 33 columns, and has the activations of a quad (4 segments) in LDS as well: for
- * rows that are a whole number of units (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x
+ * every segment in LDS and multiply while they decode, for which its lanes have to stay close together; where they are further
+ * apart in the container (tq_info's lane_spread), they are brought together on the device as far as their codes leave room for
+ * it.  The ring kernel takes lanes within 33 columns and has the activations of a quad (4 segments) in LDS as well: for rows
+ * that are a whole number of units (cols a multiple of 4 * seg_cols), with seg_cols a multiple of 32 up to 256 and x
  * 16-byte aligned, in calls where an estimate of both kernels' times says that it is the faster one (many bands of 16 rows
  * per compute unit, few sums to add; tq_set_ring_min_bands_per_cu puts a line of the caller's in its place).  The runs kernel
  * takes its activations from global memory: any other shape of at least 8 columns, any x, lanes within 65 columns.

@@ -61,7 +61,6 @@ static_assert(kSmallRingStep <= kSmallRingGroup, "ring schedule");
 constexpr int ring_step(int bytes) { return bytes == kSmallRingBytes ? kSmallRingStep : kRingStep; }
 constexpr int ring_group(int bytes) { return bytes == kSmallRingBytes ? kSmallRingGroup : kRingGroup; }
 constexpr int ring_piece(int bytes) { return bytes == kSmallRingBytes ? kSmallRingPiece : kRingPiece; }
-constexpr uint32_t kRingSpreadCareful = kRingBytes - 8 - 8 + 1;   // of a schedule that looks after every chunk (no kernel takes it; the host test of the bound does)
 // Whether a lane that stands at column pos holds bytes of a piece it has not stored (see append_chunk_ring): a unit whose
 // segments end inside pieces stores those at every look - those only, never the piece that begins at pos.
 TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }

@@ -90,7 +90,7 @@ static void assign() {
   std::printf("%d cuts\n", n);
 }
 
-// The ring kernels' decode of one unit by its schedule, column numbers in place of bytes: a piece of a lane's ring holds the
+// k_matvec_runs' decode of one unit by its schedule, in both sizes of its rings, column numbers in place of bytes: a piece of a lane's ring holds the
 // columns it was stored with, and every group a look multiplies has to hold the lane's own columns of the run in their places
 // and zeros (number 0) elsewhere.
 struct LaneStream {
@@ -100,7 +100,8 @@ struct LaneStream {
 struct Unit {
   std::vector<LaneStream> lanes;
   uint32_t n_chunks, n_win8;   // windows are taken up to n_win8, in whole groups
-  bool ragged, careful;
+  bool ragged;
+  uint32_t bytes;              // of a lane's ring
 };
 
 // Largest distance between two lanes that are both unfinished after the same number of chunks, as the validator takes it.
@@ -123,15 +124,15 @@ static uint32_t spread_of(const std::vector<LaneStream>& lanes, uint32_t n_chunk
 // Chunks [c0, c_end) of the unit.  taken[lane][column] counts how often a column was multiplied; returns the places that held
 // something else than they should.  always_store: the leftover goes to the ring whether there is one or not.
 static int decode(const Unit& u, uint32_t c0, uint32_t c_end, bool always_store, std::vector<std::vector<int>>& taken) {
-  const uint32_t kG = u.careful ? 1 : tq::kRingGroup, kLook = u.careful ? 1 : tq::kRingStep;
+  const uint32_t kG = tq::ring_group(u.bytes), kLook = tq::ring_step(u.bytes), kP = tq::ring_piece(u.bytes);
   struct Lane {
     uint32_t pos = 0, first = 0;                 // first: the column the run starts at
-    uint32_t ring[tq::kRingBytes] = {}, carry[8] = {};
+    uint32_t ring[tq::kRingBytes] = {}, carry[8] = {};   // (the first u.bytes of it)
   };
   std::vector<Lane> lanes(u.lanes.size());
   uint32_t done = 0;
   int wrong = 0;
-  auto store = [&](Lane& l, uint32_t col, const uint32_t* v) { std::memcpy(l.ring + (col & 0x78u), v, 32); };
+  auto store = [&](Lane& l, uint32_t col, const uint32_t* v) { std::memcpy(l.ring + (col & (u.bytes - 8)), v, 32); };
   const uint32_t zeros[8] = {};
   auto append = [&](size_t i, uint32_t chunk) {
     Lane& l = lanes[i];
@@ -154,7 +155,7 @@ static int decode(const Unit& u, uint32_t c0, uint32_t c_end, bool always_store,
       if (lanes[i].pos < std::min(u.lanes[i].panel_len, done + 8 * kG)) return;
     for (size_t i = 0; i < lanes.size(); ++i)
       for (uint32_t col = done; col < std::min(done + 8 * kG, u.lanes[i].panel_len); ++col) {   // (activations are zero behind the panel)
-        const uint32_t got = lanes[i].ring[col % tq::kRingBytes], want = col >= lanes[i].first && col < lanes[i].pos ? col + 1 : 0;
+        const uint32_t got = lanes[i].ring[col % u.bytes], want = col >= lanes[i].first && col < lanes[i].pos ? col + 1 : 0;
         wrong += got != want;
         taken[i][col] += want != 0;
       }
@@ -174,13 +175,13 @@ static int decode(const Unit& u, uint32_t c0, uint32_t c_end, bool always_store,
     for (Lane& l : lanes)
       for (uint32_t col = done; col < (l.pos & ~7u); col += 8) store(l, col, zeros);
   }
-  const uint32_t len = c_end - c0, pieces = (len + tq::kRingPiece - 1) / tq::kRingPiece;
+  const uint32_t len = c_end - c0, pieces = (len + kP - 1) / kP;
   uint32_t at = c0;
   for (uint32_t p = 0; p < pieces; ++p) {
     const uint32_t n = len / pieces + (p < len % pieces ? 1 : 0);
     for (uint32_t k = 0; k < n; ++k) {
       for (size_t i = 0; i < lanes.size(); ++i) append(i, at + k);
-      if (k % kLook == kLook - 1 && (n >= (uint32_t)tq::kRingPiece - 1 ? k + 1 < (uint32_t)tq::kRingPiece : k + 1 < n)) multiply_ready(false);
+      if (k % kLook == kLook - 1 && (n >= kP - 1 ? k + 1 < kP : k + 1 < n)) multiply_ready(false);
     }
     multiply_ready(false);
     at += n;
@@ -206,7 +207,7 @@ static int decode(const Unit& u, uint32_t c0, uint32_t c_end, bool always_store,
   return wrong;
 }
 
-// Streams whose lanes come to exactly the distance a form of the decode takes and stay there for a while: a fast lane, a slow
+// Streams whose lanes come to exactly the distance a size of the ring takes and stay there for a while: a fast lane, a slow
 // one, others in between; whole panels, and a shorter one in every ragged unit; units as a whole and cut into runs.
 static void ring() {
   uint64_t state = 88172645463325252ull;
@@ -216,12 +217,13 @@ static void ring() {
   };
   int at_limit[2] = {0, 0}, units = 0, planted[2] = {0, 0};
   for (int trial = 0; trial < 20000; ++trial) {
-    const bool careful = trial & 1, ragged = trial % 8 != 0;
-    const uint32_t limit = careful ? tq::kRingSpreadCareful : tq::kRingSpread;
+    const int form = trial & 1;
+    const bool ragged = trial % 8 != 0;
+    const uint32_t limit = form ? tq::kSmallRingSpread : tq::kRingSpread;
     const uint32_t seg = ragged ? 16 * (16 + random(49)) : 32 * (8 + random(25));   // 256..1024
     const uint32_t shorter = ragged ? 1 + random(seg) : seg, hold = random(40), wobble = random(3);
     Unit u;
-    u.careful = careful;
+    u.bytes = form ? tq::kSmallRingBytes : tq::kRingBytes;
     u.ragged = ragged;
     u.lanes.assign(6, LaneStream{seg, {}});
     if (ragged) u.lanes[4].panel_len = u.lanes[5].panel_len = shorter;
@@ -256,10 +258,10 @@ static void ring() {
     }
     u.n_chunks = 0;
     for (const LaneStream& l : u.lanes) u.n_chunks = std::max<uint32_t>(u.n_chunks, l.advance.size());
-    const uint32_t group = 8 * (careful ? 1 : tq::kRingGroup), spread = spread_of(u.lanes, u.n_chunks);
+    const uint32_t group = 8 * tq::ring_group(u.bytes), spread = spread_of(u.lanes, u.n_chunks);
     u.n_win8 = (seg + group - 1) / group * group;
     if (spread > limit) continue;
-    at_limit[careful] += spread == limit && ragged;
+    at_limit[form] += spread == limit && ragged;
     ++units;
     for (int cuts = 0; cuts < 3; ++cuts) {
       std::vector<uint32_t> cut = {0, u.n_chunks};
@@ -270,18 +272,17 @@ static void ring() {
       for (size_t c = 0; c + 1 < cut.size(); ++c)
         if (cut[c] < cut[c + 1]) {
           const int wrong = decode(u, cut[c], cut[c + 1], false, taken);
-          CHECK(wrong == 0, "trial %d, spread %u (%s), segments of %u and %u, chunks %u..%u of %u: %d columns wrong", trial, spread,
-                careful ? "careful" : "fast", seg, shorter, cut[c], cut[c + 1], u.n_chunks, wrong);
+          CHECK(wrong == 0, "trial %d, spread %u, ring of %u, segments of %u and %u, chunks %u..%u of %u: %d columns wrong", trial, spread, u.bytes, seg, shorter, cut[c], cut[c + 1], u.n_chunks, wrong);
         }
       for (size_t i = 0; i < taken.size(); ++i)
         for (size_t col = 0; col < taken[i].size(); ++col) CHECK(taken[i][col] == 1, "trial %d, lane %zu, column %zu taken %d times", trial, i, col, taken[i][col]);
     }
     std::vector<std::vector<int>> taken;
     for (const LaneStream& l : u.lanes) taken.emplace_back(l.panel_len, 0);
-    planted[careful] += decode(u, 0, u.n_chunks, true, taken) != 0;
+    planted[form] += decode(u, 0, u.n_chunks, true, taken) != 0;
   }
   CHECK(at_limit[0] > 500 && at_limit[1] > 500, "%d, %d ragged units at the limits", at_limit[0], at_limit[1]);
-  // the streams reach the edge: a store of the empty leftover is found in both forms
+  // the streams reach the edge: a store of the empty leftover is found in both sizes
   CHECK(planted[0] > 0 && planted[1] > 0, "%d, %d units with the planted mistake wrong", planted[0], planted[1]);
   std::printf("%d units decoded, %d and %d ragged ones at the limits, %d and %d wrong with the mistake\n", units, at_limit[0], at_limit[1], planted[0], planted[1]);
 }

@@ -37,7 +37,7 @@ def test_whole_workgroups_per_matrix_for_every_width(driver):
 
 
 def test_ring_decode_at_the_distances_it_takes(driver):
-    """Lanes exactly as far apart as the fast and the careful form allow, also in segments that end inside a piece."""
+    """Lanes exactly as far apart as rings of 128 and of 64 bytes allow, also in segments that end inside a piece."""
     out = driver("ring")
     print(out)
     assert "units decoded" in out
