@@ -88,7 +88,7 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   std::vector<uint32_t> wide_units;
   n_threads = std::max(1u, std::min(n_threads, 16u));
   n_threads = (unsigned)std::min<uint64_t>(n_threads, n_units);
-  const uint32_t pad_advance = h.lmax > 2 ? 4u : 2u;   // columns a pad code moves a lane's activation index in the product kernel
+  const uint32_t pad_advance = h.lmax > 2 ? 4u : 1u;   // columns a pad moves a lane's activation index in the product kernel
   auto check_units = [&](uint64_t ub, uint64_t ue) {
     uint64_t real = 0;
     uint32_t over = 0, wide = 0;

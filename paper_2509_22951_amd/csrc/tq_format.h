@@ -105,9 +105,10 @@ class Threads {
 
 // What validation learns about a container beyond the header.
 struct BlobFacts {
-  uint32_t max_lane_reach;   // largest (segment length + 2 * pad codes) of any lane stream: how many columns past the start
-                             // of its segment a lane's activation index can get when every pad code advances it by two
-                             // (by four in containers whose runs may be longer than 2: what the pad code's place says)
+  uint32_t max_lane_reach;   // largest (segment length + pad codes) of any lane stream: how many columns past the start of its
+                             // segment a lane's activation index can get on the device, where every pad is code 0, a single
+                             // byte, and levelled lanes have fewer of them (in containers whose runs may be longer than 2
+                             // a pad stays the container's and counts four times: what the pad code's place says)
   uint32_t max_lane_spread;  // the 64 lanes of a unit take their chunks in step; after any number of chunks, the lanes whose
                              // segment is not yet complete have reached different columns of it: the largest difference
                              // between two of them, over all units and all chunk counts

@@ -392,7 +392,7 @@ __device__ __forceinline__ uint32_t word_offset_hi(uint32_t pair) {
   asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(a) : "v"(two), "v"(pair));
   return a;
 }
-// min(1, high byte of the low / high code): 1 for a two-weight entry (code >= 256, the pad code included), 0 for a single
+// min(1, high byte of the low / high code): 1 for a two-weight entry (code >= 256), 0 for a single (a pad too, code 0)
 __device__ __forceinline__ uint32_t is_pair_lo(uint32_t pair) {
   uint32_t a;
   const uint32_t one = 1;

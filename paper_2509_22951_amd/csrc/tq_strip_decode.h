@@ -88,8 +88,8 @@ typedef __attribute__((address_space(3))) uint64_t lds_u64;
 // Append the runs of one chunk to the lane's strip: the string goes to LDS as it is, with one 8-byte store at the
 // byte the lane has reached (LDS stores need no alignment on this target); what it writes past its own n bytes is
 // overwritten by the chunks that follow, or falls into the 8 spare bytes every strip has after its segment.
-// wpos = LDS address of the next byte of the segment, limit = address of the segment's end.  Pad codes (entry 0,
-// counted as 2 bytes by the code test) only follow a complete segment: the clamp keeps the lane at its end.
+// wpos = LDS address of the next byte of the segment, limit = address of the segment's end.  Pads (code 0 on the
+// device, a byte each) only follow a complete segment: the clamp keeps the lane at its end.
 __device__ __forceinline__ void append_chunk(uint2 c, uint32_t limit, uint32_t& wpos) {
   uint32_t s0, s1, n;
   chunk_string(c, s0, s1, n);
@@ -236,7 +236,7 @@ __device__ __forceinline__ uint4 mask_x_fragment(uint4 v, uint32_t cols, uint32_
 }
 
 // The dictionary's byte image goes to LDS as it is.  kThreads: of the workgroup, or the most it may have (n_threads then says how
-// many it has); a full dictionary is one round of loads.
+// many it has); a full dictionary is one round of loads, two where a workgroup has half its threads (the tile kernels with wide segments).
 constexpr uint32_t kImageBytes = 61440;
 template <int kThreads>
 __device__ __forceinline__ void stage_image(const DevMat& m, int tid, uint4* lds_dict, int n_threads = kThreads) {

@@ -19,13 +19,22 @@ def _classifier():
     return exe
 
 
-def ring_class(blob):
-    """2: k_matvec_ring and k_matvec_runs with rings of either size, 1: k_matvec_runs with rings of 128 bytes, 0: the whole-strip
-    kernel (what the creation decides, by its own function)."""
+def _classify(blob):
     with tempfile.NamedTemporaryFile() as f:
         f.write(blob)
         f.flush()
-        return int(subprocess.run([_classifier(), f.name], check=True, capture_output=True, text=True, timeout=60).stdout)
+        return [int(v) for v in subprocess.run([_classifier(), f.name], check=True, capture_output=True, text=True, timeout=60).stdout.split()]
+
+
+def ring_class(blob):
+    """2: k_matvec_ring and k_matvec_runs with rings of either size, 1: k_matvec_runs with rings of 128 bytes, 0: the whole-strip
+    kernel (what the creation decides, by its own function)."""
+    return _classify(blob)[0]
+
+
+def lane_reach(blob):
+    """Columns past the start of its segment that a lane reaches in the activation image of the dot-product kernel."""
+    return _classify(blob)[1]
 
 
 def _steps(rng, seg_cols, limit, spare):
@@ -74,8 +83,8 @@ def bytes_at_the_limit(seed, cols, seg_cols, limit, spare=True, rows=16):
     return Q
 
 
-def drifting(seed, cols, seg_cols, limit, opts, spare=True, rows=16, entries=288):
-    """bytes_at_the_limit as a container -> (weights, scales, container).  entries: of the dictionary (the first 288 are used)."""
+def drifting(seed, cols, seg_cols, limit, opts, spare=True, rows=16):
+    """bytes_at_the_limit as a container -> (weights, scales, container)."""
     Qb = bytes_at_the_limit(seed, cols, seg_cols, limit, spare, rows)
     pairs = np.array([[p, p + 32] for p in range(64, 96)], np.uint8).view(np.int8)
     d = tq.tq_encode_quantized(pairs, np.ones(32, np.float32), max_entries=288, dictionary="frequency")

@@ -1,4 +1,5 @@
-// Host-only: which of the ring kernels a container's matrix may take on the device, as it is decided when it is loaded (ring_class).
+// Host-only: which of the ring kernels a container's matrix may take on the device, as it is decided when it is loaded (ring_class),
+// and how far its lanes get in the activation image of the dot-product kernel (max_lane_reach).
 #include <cstdio>
 #include <vector>
 #include "../include/tq.h"
@@ -17,7 +18,7 @@ int main(int argc, char** argv) {
     std::vector<uint32_t> wide;
     if (tq::validate_blob(blob.data(), blob.size(), &h, &facts, &wide, 4) != TQ_OK) return std::printf("%s\n", tq_last_error_string()), 1;
     std::unique_ptr<uint16_t[]> codes;
-    std::printf("%u\n", tq::ring_class(blob.data(), h, wide, 4, codes));
+    std::printf("%u %u\n", tq::ring_class(blob.data(), h, wide, 4, codes), facts.max_lane_reach);
   }
   return 0;
 }
