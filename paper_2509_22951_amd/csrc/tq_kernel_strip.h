@@ -50,10 +50,11 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
     {
       const uint32_t strip = m.seg_cols + 8;   // bytes between the strips of two lanes
       const uint32_t my_strip = lds_address(tiles) + (uint32_t)wave * a.tile_area + (uint32_t)lane * strip;
-      uint4 xa[kMfmaGroup];   // activation fragments of the first MFMA group of the unit being decoded
+      constexpr int kG = kXFast ? kMfmaGroup : kMfmaGroupAny;
+      uint4 xa[kG];   // activation fragments of the first MFMA group of the unit being decoded
       decode_run_to_tile<kLong>(m, u0, u1, lane, my_strip, [&](uint32_t, uint32_t quad) {
 #pragma unroll
-        for (int k = 0; k < kMfmaGroup; ++k)
+        for (int k = 0; k < kG; ++k)
           xa[k] = load_x_fragment<kXFast>(xrow, x_cols, pk * (quad * kUnitPanels + (uint32_t)kg) * m.seg_cols + 8 * k);
       }, [&](uint32_t band, uint32_t quad) {
         const uint32_t col0 = quad * kUnitPanels * m.seg_cols;                            // first (byte) column of the unit

@@ -348,22 +348,27 @@ __device__ __forceinline__ f32x4 fold_sums(const f32x4 (&part)[4]) {
 }
 
 constexpr int kMfmaGroup = 8;   // MFMA steps per group: the activation fragments of the next group load while this one runs
+// The same where x is taken element by element: a fragment is 8 registers on its way, and groups of 8 spill 56 (runs of up to 4 bytes:
+// 105) of them.  us, runs of up to 4 bytes, groups of 8 -> 4: 458 x 4140 in segments of 16 batch 3 129 -> 61, 2048 x 1024 and two narrow
+// matrices batch 3 172 -> 84, 1024 x 8192 batch 8 69 -> 60.
+constexpr int kMfmaGroupAny = 4;
 
 // The MFMA steps of one decoded unit: step w multiplies bytes [8 w, 8 w + 8) of every lane's strip (16 rows x 4 panels
 // x 8 columns, converted to bf16) with the activations of those 32 columns.  n_win is wave-uniform.
-// Four accumulators so that consecutive MFMAs do not wait for each other; groups of kMfmaGroup steps whose weight
+// Four accumulators so that consecutive MFMAs do not wait for each other; groups of kG steps whose weight
 // reads are all issued before the first conversion and whose activation fragments were requested a group earlier
 // (the first group by the caller, into xa).
 // kPacked: the strips hold packed 4-bit weights; a step then takes 4 bytes of every strip (8 columns again), n_win counts
 // those steps, and cols and xcol are columns of the weight matrix (twice the byte columns).
 template <bool kFast, bool kRagged, bool kPacked>
 __device__ __forceinline__ f32x4 multiply_unit(f32x4 acc, uint32_t my_strip, global_cu16* xrow, uint32_t cols, uint32_t xcol, uint32_t n_win,
-                                               uint4 (&xa)[kMfmaGroup]) {
+                                               uint4 (&xa)[kFast ? kMfmaGroup : kMfmaGroupAny]) {
+  constexpr int kG = kFast ? kMfmaGroup : kMfmaGroupAny;
   f32x4 part[4] = {acc, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-  uint4 xb[kMfmaGroup];
-  auto request = [&](uint4 (&xf)[kMfmaGroup], uint32_t w0) {
+  uint4 xb[kG];
+  auto request = [&](uint4 (&xf)[kG], uint32_t w0) {
 #pragma unroll
-    for (int k = 0; k < kMfmaGroup; ++k) xf[k] = load_x_fragment<kFast>(xrow, cols, xcol + 8 * (w0 + k));
+    for (int k = 0; k < kG; ++k) xf[k] = load_x_fragment<kFast>(xrow, cols, xcol + 8 * (w0 + k));
   };
   auto weights = [&](uint32_t w) {   // the 8 weights of step w as bf16
     if constexpr (kPacked) {
@@ -373,27 +378,27 @@ __device__ __forceinline__ f32x4 multiply_unit(f32x4 acc, uint32_t my_strip, glo
       return i8x8_to_bf16x8(make_uint2(a8.x, a8.y));
     }
   };
-  auto run_group = [&](const uint4 (&xf)[kMfmaGroup], uint32_t w0) {
-    if (w0 + kMfmaGroup <= n_win) {   // whole group
-      bf16x8 a8[kMfmaGroup];
+  auto run_group = [&](const uint4 (&xf)[kG], uint32_t w0) {
+    if (w0 + kG <= n_win) {   // whole group
+      bf16x8 a8[kG];
       if constexpr (kPacked) {
 #pragma unroll
-        for (int k = 0; k < kMfmaGroup; ++k) a8[k] = weights(w0 + k);
+        for (int k = 0; k < kG; ++k) a8[k] = weights(w0 + k);
       } else {
-        u32x2 raw[kMfmaGroup];
+        u32x2 raw[kG];
 #pragma unroll
-        for (int k = 0; k < kMfmaGroup; ++k) raw[k] = *(lds_cu64*)(size_t)(my_strip + 8 * (w0 + k));
+        for (int k = 0; k < kG; ++k) raw[k] = *(lds_cu64*)(size_t)(my_strip + 8 * (w0 + k));
 #pragma unroll
-        for (int k = 0; k < kMfmaGroup; ++k) a8[k] = i8x8_to_bf16x8(make_uint2(raw[k].x, raw[k].y));
+        for (int k = 0; k < kG; ++k) a8[k] = i8x8_to_bf16x8(make_uint2(raw[k].x, raw[k].y));
       }
 #pragma unroll
-      for (int k = 0; k < kMfmaGroup; ++k) {
+      for (int k = 0; k < kG; ++k) {
         const uint4 x8 = kRagged ? mask_x_fragment<kFast>(xf[k], cols, xcol + 8 * (w0 + k)) : xf[k];
         part[k & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8[k], __builtin_bit_cast(bf16x8, x8), part[k & 3], 0, 0, 0);
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < kMfmaGroup; ++k) {
+      for (int k = 0; k < kG; ++k) {
         if (w0 + k < n_win) {
           const uint4 x8 = kRagged ? mask_x_fragment<kFast>(xf[k], cols, xcol + 8 * (w0 + k)) : xf[k];
           part[k & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(weights(w0 + k), __builtin_bit_cast(bf16x8, x8), part[k & 3], 0, 0, 0);
@@ -402,11 +407,11 @@ __device__ __forceinline__ f32x4 multiply_unit(f32x4 acc, uint32_t my_strip, glo
     }
   };
   // xa holds the first group already: it was requested before the unit's last piece of chunks was decoded
-  for (uint32_t w = 0; w < n_win; w += 2 * kMfmaGroup) {
-    request(xb, w + kMfmaGroup);
+  for (uint32_t w = 0; w < n_win; w += 2 * kG) {
+    request(xb, w + kG);
     run_group(xa, w);
-    request(xa, w + 2 * kMfmaGroup);
-    run_group(xb, w + kMfmaGroup);
+    request(xa, w + 2 * kG);
+    run_group(xb, w + kG);
   }
   return (part[0] + part[1]) + (part[2] + part[3]);
 }
