@@ -30,8 +30,9 @@ TQ_HD ListingOutput listing_output(uint32_t base, uint32_t tokens, uint64_t n_va
   return {first - lo, lo, tokens ? hi : lo};
 }
 
-// The schedule of the ring kernels.  A lane keeps kRingBytes of its segment; every kRingStep chunks the wavefront looks whether
-// all unfinished lanes have passed the next kRingGroup windows of 8 columns, and multiplies them if so.
+// The schedule of the ring kernels.  A lane keeps the last kRingBytes of its segment; every kRingStep chunks the wavefront looks
+// whether all unfinished lanes have passed the next kRingGroup windows of 8 columns, and multiplies them if so.  (These are
+// k_matvec_runs' large rings; the small ones, further down, are its other size and k_matvec_ring's only one.)
 constexpr int kRingBytes = 128;
 constexpr int kRingPiece = 12;    // chunks per piece of the code stream (two register sets)
 constexpr int kRingStep = 4;      // chunks between two looks at the lanes' progress
@@ -66,8 +67,8 @@ constexpr int ring_piece(int bytes) { return bytes == kSmallRingBytes ? kSmallRi
 TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }
 
 // Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
-// that the largest share (bands x columns) is as small as possible, to within an eighth of the widest row.  Returns that
-// share, or 0 when there are more matrices than workgroups (or a matrix is too tall for the kernels' cut).
+// that the largest share (bands x columns) is as small as possible, to within an eighth of the widest row, and the others' too
+// as far as there are workgroups.  Returns the largest share, or 0 when there are more matrices than workgroups (or a matrix is too tall for the kernels' cut).
 struct BandCount {
   uint32_t n_bands, cols;   // of a matrix, both at least 1
 };
@@ -79,26 +80,28 @@ inline uint64_t assign_workgroups(int n, const BandCount* m, uint64_t grid, uint
     total += (uint64_t)m[i].n_bands * m[i].cols;
     cols_max = std::max<uint64_t>(cols_max, m[i].cols);
   }
-  auto needed = [&](uint64_t share) {   // workgroups when none takes more than `share`
+  auto needed = [&](uint64_t share) {   // workgroups when none takes more than `share`, or a single band
     uint64_t sum = 0;
     for (int i = 0; i < n; ++i) {
-      const uint64_t per = share / m[i].cols;   // >= 1
+      const uint64_t per = std::max<uint64_t>(1, share / m[i].cols);
       sum += (m[i].n_bands + per - 1) / per;
     }
     return sum;
   };
-  uint64_t lo = std::max(cols_max, (total + grid - 1) / grid), hi = lo;
-  while (needed(hi) > grid) hi *= 2;
-  if (hi > lo) {   // needed(lo) > grid >= needed(hi), and so it stays; hi - lo >= 2 inside the loop, so that it shrinks every time
-    const uint64_t close = std::max<uint64_t>(1, cols_max / 8);   // (an eighth of a row below 8 columns is nothing)
-    for (lo = hi / 2; hi - lo > close;) {
-      const uint64_t mid = lo + (hi - lo) / 2;
-      (mid >= cols_max && needed(mid) <= grid ? hi : lo) = mid;
-    }
+  // Shares of a wide matrix are a band at least; where workgroups are left then, the shares of the narrower ones shrink further (16
+  // bands of 7424 columns beside 800 of 256: 44 workgroups of up to 29 bands would meet the largest share, 256 cut the 800 into 3 or 4).
+  const uint64_t even = (total + grid - 1) / grid;
+  uint64_t lo = even, hi = std::max(cols_max, even);
+  while (needed(hi) > grid) lo = hi, hi *= 2;
+  if (needed(lo) <= grid) hi = lo;
+  // needed(lo) > grid >= needed(hi), and so it stays; hi - lo >= 2 inside the loop, so that it shrinks every time
+  while (hi - lo > std::max<uint64_t>(1, hi > cols_max ? cols_max / 8 : hi / 16)) {   // (an eighth of a row below 8 columns is nothing)
+    const uint64_t mid = lo + (hi - lo) / 2;
+    (needed(mid) <= grid ? hi : lo) = mid;
   }
   uint64_t worst = 0;
   for (int i = 0; i < n; ++i) {
-    const uint64_t bands = m[i].n_bands, per = hi / m[i].cols;
+    const uint64_t bands = m[i].n_bands, per = std::max<uint64_t>(1, hi / m[i].cols);
     wgs[i] = (uint32_t)((bands + per - 1) / per);
     worst = std::max(worst, (bands + wgs[i] - 1) / wgs[i] * m[i].cols);
   }

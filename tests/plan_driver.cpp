@@ -84,6 +84,16 @@ static void assign() {
       }
   for (uint32_t bands : {1u, 255u, 257u, 1000u, 8016u, (1u << 23) - 1})
     for (uint32_t cols : {1u, 7u, 8u, 9u, 63u, 3072u, 8191u, 1u << 20}) one({{bands, cols}}, 256);
+  // a matrix of few wide bands leaves workgroups over: they go to the narrow ones, whose shares come near the even one
+  for (uint32_t cols : {1u, 61u, 256u, 1023u})
+    for (uint32_t bands : {100u, 548u, 800u, 20000u}) {
+      const tq::BandCount two[2] = {{16, 9344}, {bands, cols}};
+      uint32_t w[2];
+      tq::assign_workgroups(2, two, 256, w);
+      const uint64_t even = (16ull * 9344 + (uint64_t)bands * cols + 255) / 256, share = (uint64_t)((bands + w[1] - 1) / w[1]) * cols;
+      CHECK(w[0] <= 16 && w[0] + w[1] <= 256, "%u + %u workgroups", w[0], w[1]);
+      CHECK(even > 9344 || share <= std::max<uint64_t>(cols, even + even / 8 + cols), "%u bands of %u: %u workgroups, share %lu, even %lu", bands, cols, w[1], share, even);
+    }
   uint32_t wgs[4];
   const tq::BandCount tall = {1u << 23, 4}, three[3] = {{5, 4}, {5, 4}, {5, 4}};
   CHECK(tq::assign_workgroups(1, &tall, 256, wgs) == 0 && tq::assign_workgroups(3, three, 2, wgs) == 0, "refused cuts");
