@@ -112,12 +112,12 @@ inline double runs_time(int n, const BatchedMatrix* m, uint64_t n_cu, int batch,
   const double cold = std::min(1., std::max(0., ((double)bytes - 144e6) / 192e6));
   const double rows = batch <= 4 ? t.rows4 : batch <= 8 ? t.rows8 : t.rows9 + t.row * (batch - 9);
   auto job = [&](int i, double b) {
-    const double unit = (packed ? 2. : 1.) * m[i].seg_cols / 256;
-    return t.matrix + b * m[i].n_quads * (t.piece + rows * (1 + t.hbm * cold) * unit);
+    const double units = (packed ? 2. : 1.) * unit_columns(m[i].cols, m[i].seg_cols) / 1024;   // of a band
+    return t.matrix + b * (t.piece * m[i].n_quads + rows * (1 + t.hbm * cold) * units);
   };
   uint32_t wgs[kMaxAssign];
   BandCount count[kMaxAssign];
-  for (int i = 0; i < n && i < kMaxAssign; ++i) count[i] = {m[i].n_bands, m[i].cols};
+  for (int i = 0; i < n && i < kMaxAssign; ++i) count[i] = {m[i].n_bands, unit_columns(m[i].cols, m[i].seg_cols)};   // (as the launch counts them)
   if (n > kMaxAssign || !cut_in_workgroups(n, count, std::min(n_cu, bands), grid, wgs)) return t.start + longest_share(n, m, grid, job);
   double us = 0;
   for (int i = 0; i < n; ++i) us = std::max(us, job(i, (m[i].n_bands + wgs[i] - 1) / wgs[i]));

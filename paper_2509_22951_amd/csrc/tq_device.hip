@@ -13,7 +13,8 @@
 //      (two activation rows are handled the same way, with both rows in the image and one dot product per row;
 //      packed 4-bit weights: four weights per entry as fp8, two conversions and two dot products per code and row),
 //   4. for batches of 3..16 rows and for tq_decompress the lanes append their run bytes to per-lane storage in LDS
-//      instead - a ring of 64 or 128 bytes (k_matvec_ring, k_matvec_runs: multiplied by bf16 MFMA, batch = N, while the decode goes on) or
+//      instead - a ring of 64 bytes (k_matvec_ring, k_matvec_runs; 128 in some of the latter's launches: multiplied by bf16 MFMA,
+//      batch = N, while the decode goes on) or
 //      a strip holding the whole segment (k_matvec_mfma: multiplied when the unit is complete; k_decompress: copied
 //      out row-major).
 // The expanded matrix never exists in HBM on the tq_matvec path.
@@ -518,11 +519,11 @@ int fire(const PreparedLaunch& p, hipStream_t stream) {
   return TQ_OK;
 }
 
-// (of matrices on the cost line; n <= kMaxAssign)
+// The bands of n <= kMaxAssign matrices and what one costs: its columns, or, by_units, what its units cost (unit_columns).
 struct BandCounts {
   BandCount m[kMaxAssign];
-  BandCounts(int n, const tq_handle* hs) {
-    for (int i = 0; i < n; ++i) m[i] = {hs[i]->m.n_bands, hs[i]->m.cols};
+  BandCounts(int n, const tq_handle* hs, bool by_units = false) {
+    for (int i = 0; i < n; ++i) m[i] = {hs[i]->m.n_bands, by_units ? unit_columns(hs[i]->m.cols, hs[i]->m.seg_cols) : hs[i]->m.cols};
   }
 };
 
@@ -583,9 +584,9 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   p.grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)hs[0]->n_cu, bands, cost / band_cost_max}));
   const bool packed = hs[0]->m.packing != 0;   // (all matrices of a product launch hold their weights the same way: launch_all sees to that)
   const bool long_runs = hs[0]->m.long_runs != 0;   // (likewise)
-  auto cut_by_workgroup = [&] {
+  auto cut_by_workgroup = [&](bool by_units) {
     uint32_t wgs[kMaxAssign];
-    if (n > kMaxAssign || !cut_in_workgroups(n, BandCounts(n, hs).m, std::min<uint64_t>(hs[0]->n_cu, bands), p.grid, wgs)) return;
+    if (n > kMaxAssign || !cut_in_workgroups(n, BandCounts(n, hs, by_units).m, std::min<uint64_t>(hs[0]->n_cu, bands), p.grid, wgs)) return;
     a.by_workgroup = 1;
     p.grid = 0;
     for (int i = 0; i < n; ++i) {
@@ -604,7 +605,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
                : packed ? (batch == 2 ? (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2> : (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1>)
                : batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 2> : (const void*)k_matvec<kDotPiece, kDotWaves, false, 1>;
     p.block = (packed ? kDotWavesPacked : kDotWaves) * 64;
-    cut_by_workgroup();
+    cut_by_workgroup(false);
   } else if (ring) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size: the kernel ORs piece offsets into its
     // address) | the activation tile of one quad.
@@ -637,7 +638,7 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     else if (batch <= 4) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4>;
     else if (batch <= 8) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2>;
     else p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1>;
-    cut_by_workgroup();
+    cut_by_workgroup(true);
   } else {
     // Tile decode.  LDS: 16-bit dictionary image | one tile (64 strips) per wavefront, which the batched product reuses
     // for its partial sums (per wavefront two slots of 1 KB and their two band numbers).

@@ -17,11 +17,11 @@ namespace tq {
 // shifted into place, zeros behind it.
 // Batches of up to 8 rows take two windows per load, up to 4 rows four (fold_sums).
 // Measured, us, buffers warm in the caches (in brackets: the whole-strip kernel, which took these launches before): 4099 x
-// 2999 batch 5 19.7 (41), one LLaMA-3.2-3B layer batch 8 42.2 (56), batch 4 41.8, batch 16 55.7, 8192 x 3072 packed batch 4 14.1.
-// Launches that fill k_matvec_ring go there: eight such layers, batch 8, 230 us there, 250 here; the gated pairs of eight
-// blocks, batch 16, 128 there, 253 here.  What they differ in is x.  Counters of the eight layers at batch 8, M cycles
-// summed over the compute units, there / here: busy 122 / 136, address unit of the vector memory path busy 58 / 109 (39 / 89 M
-// cache accesses), vector instructions issued 86 / 90, LDS pipe busy 71 / 68.  The 16-byte pieces of up to 16 rows of x keep
+// 2999 batch 5 17.5 (41), one LLaMA-3.2-3B layer batch 8 35.8 (56), batch 4 33.7, batch 16 52.0, 8192 x 3072 packed batch 4 14.1.
+// Launches that fill k_matvec_ring go there (tq_choice.h): eight such layers, batch 8, 215 us there, 248 here, batch 16 228 and 484;
+// the gated pairs of eight blocks, batch 16, 107 and 239.  What they differ in is x.  Counters of the eight layers at batch 8, M
+// cycles summed over the compute units, there / here: busy 109 / 133, address unit of the vector memory path busy 64 / 107 (39 / 88 M
+// cache accesses), vector instructions issued 86 / 89, LDS pipe busy 74 / 68.  The 16-byte pieces of up to 16 rows of x keep
 // the address unit busy four fifths of the time here; with 16 rows in place of 8 there are twice as many of them.
 constexpr int kRunWaves = 12;        // 60 KB of dictionary and 12 rings of 8 KB fill the LDS
 constexpr int kRunSmallUnits = 6;    // units per workgroup up to which the rings are 64 bytes (batches above 4, one weight per byte)

@@ -108,6 +108,13 @@ inline uint64_t assign_workgroups(int n, const BandCount* m, uint64_t grid, uint
   return worst;
 }
 
+// What a band of `cols` columns costs k_matvec_runs, in columns: a unit takes a wavefront as long as its widest segment is, whether it
+// has one panel or four.  (Seven matrices, among them 2432 x 64 and 8192 x 1024, batch 9: 65 us cut by columns, 30 like this.)
+inline uint32_t unit_columns(uint32_t cols, uint32_t seg_cols) {
+  const uint32_t quad = kUnitPanels * seg_cols, whole = (cols - 1) / quad * quad;
+  return whole + kUnitPanels * std::min(seg_cols, cols - whole);
+}
+
 // What the busiest workgroup does when the line is cut into `grid` equal parts instead: its part to within half a band,
 // and, with several matrices, a second start (offsets, activations, barriers) in workgroups that get the end of one
 // matrix and the start of the next, worth about kRestartCost of the line (4 us, in which a compute unit streams 100 KB of

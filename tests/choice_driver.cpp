@@ -91,6 +91,12 @@ static const Timed timed[] = {
 };
 static bool choices() {
   bool ok = true;
+  // what a matrix of narrow bands costs beside wide ones (packed, batch 5, gated pairs; 31.9 us on the runs kernel alone)
+  const uint32_t shape[][2] = {{3830, 3302}, {64, 32}, {422, 6}, {256, 1920}, {15360, 512}, {1044, 28}, {2, 1024}};
+  std::vector<BatchedMatrix> mixed;
+  for (const auto& s : shape) mixed.push_back(matrix(s[0], s[1], 128, 0));
+  const double us = tq::runs_time(7, mixed.data(), 256, 5, true);
+  if (us < 24 || us > 40) std::printf("seven matrices: %.1f us by the estimate\n", us), ok = false;
   for (const Timed& t : timed) {
     std::vector<BatchedMatrix> m(t.n, matrix(t.rows, t.cols / (t.packed ? 2 : 1), t.seg, t.mbytes * 1000000ull / t.n));
     const double ring = tq::ring_time((int)t.n, m.data(), 256, t.batch, t.packed, t.gate), runs = tq::runs_time((int)t.n, m.data(), 256, t.batch, t.packed);

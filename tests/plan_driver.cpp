@@ -94,6 +94,12 @@ static void assign() {
       CHECK(w[0] <= 16 && w[0] + w[1] <= 256, "%u + %u workgroups", w[0], w[1]);
       CHECK(even > 9344 || share <= std::max<uint64_t>(cols, even + even / 8 + cols), "%u bands of %u: %u workgroups, share %lu, even %lu", bands, cols, w[1], share, even);
     }
+  for (uint32_t seg : {16u, 128u, 256u, 1024u})   // by the widest segment of every unit
+    for (uint32_t cols = 1; cols < 9 * seg; ++cols) {
+      uint32_t want = 0;
+      for (uint32_t q = 0; q < cols; q += 4 * seg) want += 4 * std::min(seg, cols - q);
+      CHECK(tq::unit_columns(cols, seg) == want && want >= cols, "%u columns in segments of %u: %u", cols, seg, tq::unit_columns(cols, seg));
+    }
   uint32_t wgs[4];
   const tq::BandCount tall = {1u << 23, 4}, three[3] = {{5, 4}, {5, 4}, {5, 4}};
   CHECK(tq::assign_workgroups(1, &tall, 256, wgs) == 0 && tq::assign_workgroups(3, three, 2, wgs) == 0, "refused cuts");
