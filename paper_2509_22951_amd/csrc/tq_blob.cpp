@@ -92,47 +92,47 @@ int validate_blob(const void* blob, size_t bytes, Header* hdr_out, BlobFacts* fa
   auto check_units = [&](uint64_t ub, uint64_t ue) {
     uint64_t real = 0;
     uint32_t over = 0, wide = 0;
-    std::vector<uint32_t> mine;                 // the units of this range that level_unit has to see
-    std::vector<uint32_t> reach_lo, reach_hi;   // per chunk count: least / greatest column reached by an unfinished lane
-    std::vector<uint32_t> reach_on;             // the greatest column any lane reaches, finished lanes going on by one a code
+    std::vector<uint32_t> mine;   // the units of this range that level_unit has to see
+    const uint32_t n_entries = h.n_entries;
+    const bool pairs = h.lmax <= 2;   // (a run is 1 byte, or 2 from code 256 on)
     for (uint64_t u = ub; u < ue && first_bad.load(std::memory_order_relaxed) == UINT64_MAX; ++u) {
       const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
-      const uint32_t steps = (uoff[u + 1] - uoff[u]) * kChunkCodes;
-      const uint16_t* cb = codes + (uint64_t)uoff[u] * kChunkWords;
-      bool ok = true;
-      reach_lo.assign(steps / kChunkCodes, UINT32_MAX);
-      reach_hi.assign(steps / kChunkCodes, 0);
-      reach_on.assign(steps / kChunkCodes, 0);
-      for (uint32_t l = 0; l < 64 && ok; ++l) {
-        const uint32_t want = segment_len(h, band, quad, l);
-        uint32_t sum = 0, pads = 0;
-        for (uint32_t k = 0; k < steps; ++k) {
-          const uint32_t c = cb[(uint64_t)(k / kChunkCodes) * kChunkWords + l * kChunkCodes + k % kChunkCodes];
-          if (c > h.n_entries) { ok = false; break; }
-          if (c == h.n_entries) {
-            ++pads;
+      const uint32_t n_chunks = uoff[u + 1] - uoff[u];
+      const uint16_t* c = codes + (uint64_t)uoff[u] * kChunkWords;
+      uint32_t want[64], sum[64] = {}, pads[64] = {};
+      for (uint32_t l = 0; l < 64; ++l) want[l] = segment_len(h, band, quad, l);
+      bool ok = true, apart = false, going = true;   // going: some segment is not complete yet
+      for (uint32_t k = 0; k < n_chunks && ok; ++k) {
+        uint32_t lo = UINT32_MAX, hi = 0, on = 0;   // least / greatest column reached by an unfinished lane; by any, finished ones going on by one a code
+        for (uint32_t l = 0; l < 64; ++l, c += kChunkCodes) {
+          if ((pads[l] == 0) & (c[0] < n_entries) & (c[1] < n_entries) & (c[2] < n_entries) & (c[3] < n_entries)) {
+            sum[l] += pairs ? 4u + (c[0] >= 256) + (c[1] >= 256) + (c[2] >= 256) + (c[3] >= 256)
+                            : run_length(h, c[0]) + run_length(h, c[1]) + run_length(h, c[2]) + run_length(h, c[3]);
           } else {
-            if (pads) { ok = false; break; }   // a real code after a pad
-            sum += run_length(h, c);
-          }
-          if (k % kChunkCodes == kChunkCodes - 1) {   // a whole chunk taken
-            reach_on[k / kChunkCodes] = std::max(reach_on[k / kChunkCodes], sum + pads);
-            if (sum < want) {                         // segment not complete
-              reach_lo[k / kChunkCodes] = std::min(reach_lo[k / kChunkCodes], sum);
-              reach_hi[k / kChunkCodes] = std::max(reach_hi[k / kChunkCodes], sum);
+            for (uint32_t j = 0; j < kChunkCodes; ++j) {
+              if (c[j] > n_entries || (c[j] < n_entries && pads[l])) ok = false;   // no code, or a real one after a pad
+              else if (c[j] == n_entries) ++pads[l];
+              else sum[l] += run_length(h, c[j]);
             }
           }
+          on = std::max(on, sum[l] + pads[l]);
+          if (sum[l] < want[l]) {
+            lo = std::min(lo, sum[l]);
+            hi = std::max(hi, sum[l]);
+          }
         }
-        if (sum != want) ok = false;
-        real += steps - pads;
-        over = std::max(over, want + pad_advance * pads);
+        going = going && lo != UINT32_MAX;
+        if (ok && going) {
+          wide = std::max(wide, hi - lo);
+          apart = apart || on > lo + kSmallRingSpread;
+        }
       }
-      bool apart = false;
-      for (size_t k = 0; ok && k < reach_lo.size() && reach_lo[k] != UINT32_MAX; ++k) {   // (until all are finished)
-        wide = std::max(wide, reach_hi[k] - reach_lo[k]);
-        apart = apart || reach_on[k] > reach_lo[k] + kSmallRingSpread;
+      for (uint32_t l = 0; l < 64; ++l) {
+        ok = ok && sum[l] == want[l];
+        real += (uint64_t)n_chunks * kChunkCodes - pads[l];
+        over = std::max(over, want[l] + pad_advance * pads[l]);
       }
-      if (apart) mine.push_back((uint32_t)u);
+      if (ok && apart) mine.push_back((uint32_t)u);
       if (!ok) {
         uint64_t cur = first_bad.load();
         while (u < cur && !first_bad.compare_exchange_weak(cur, u)) {}

@@ -388,7 +388,9 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   // The units whose lanes are further apart than the ring kernels take are brought closer together (level_unit).
   const uint32_t* blob_uoff = (const uint32_t*)((const uint8_t*)blob + h.off_uoff);
   std::unique_ptr<uint16_t[]> level;
+  wide_units = close_gaps(wide_units);
   m.ring = ring_class(blob, h, wide_units, hw ? hw : 1, level);
+  if (!m.ring) wide_units.clear();
   m.packing = h.packing;
   m.long_runs = long_runs ? 1u : 0u;
   m.class2 = h.class_end[1];
@@ -444,18 +446,21 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
     return e == hipErrorOutOfMemory ? TQ_E_OOM : TQ_E_HIP;
   }
   e = hipMemcpy(base + o_uoff, src + h.off_uoff, h.uoff_bytes, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(base + o_codes, src + h.off_codes, h.code_bytes, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(base + o_scales, src + h.off_scales, h.scale_bytes, hipMemcpyHostToDevice);
-  if (m.ring) {
-    // (units in a row go up together: they are the first of the matrix a dictionary starts with)
-    size_t at = 0;
-    for (size_t i = 0, j; i < wide_units.size() && e == hipSuccess; i = j) {
-      for (j = i + 1; j < wide_units.size() && wide_units[j] == wide_units[j - 1] + 1;) ++j;
-      const uint64_t first = blob_uoff[wide_units[i]], n = blob_uoff[wide_units[j - 1] + 1] - first;
-      e = hipMemcpy(base + o_codes + first * kChunkWords * 2, level.get() + at, n * kChunkWords * 2, hipMemcpyHostToDevice);
-      at += n * kChunkWords;
-    }
+  // the codes, every run of levelled units in place of the container's
+  uint64_t done = 0, at = 0;   // chunks uploaded; of them from `level`
+  auto upload = [&](const void* from, uint64_t n) {
+    if (n && e == hipSuccess) e = hipMemcpy(base + o_codes + done * kChunkWords * 2, from, n * kChunkWords * 2, hipMemcpyHostToDevice);
+    done += n;
+  };
+  for (size_t i = 0, j; i < wide_units.size(); i = j) {
+    for (j = i + 1; j < wide_units.size() && wide_units[j] == wide_units[j - 1] + 1;) ++j;
+    upload(src + h.off_codes + done * kChunkWords * 2, blob_uoff[wide_units[i]] - done);
+    const uint64_t n = blob_uoff[wide_units[j - 1] + 1] - done;
+    upload(level.get() + at * kChunkWords, n);
+    at += n;
   }
+  upload(src + h.off_codes + done * kChunkWords * 2, h.n_chunks - done);
   if (!long_runs && e == hipSuccess) {
     const uint64_t n16 = h.code_bytes / 16;
     hipLaunchKernelGGL(k_replace_pads, dim3((unsigned)std::min<uint64_t>((n16 + 255) / 256, 4096)), dim3(256), 0, nullptr, (uint4*)(base + o_codes), n16, h.pad_code);

@@ -18,6 +18,11 @@ static uint32_t rnd(uint32_t n) {
   state ^= state << 13, state ^= state >> 7, state ^= state << 17;
   return (uint32_t)(state % n);
 }
+static uint16_t* scratch(uint32_t n_chunks) {
+  static std::vector<uint16_t> room;
+  room.assign(tq::level_scratch(n_chunks), 0xFFFF);
+  return room.data();
+}
 
 // Many units at once: the same codes as one by one, a unit that cannot be levelled refuses them all, and several threads
 // take part (process time against the clock, where there are processors for it).
@@ -46,7 +51,7 @@ static bool many() {
   Codes want;
   for (uint32_t u : wide) {
     Codes c((size_t)(uoff[u + 1] - uoff[u]) * tq::kChunkWords);
-    if (!tq::level_unit(codes.data() + (size_t)uoff[u] * tq::kChunkWords, uoff[u + 1] - uoff[u], n_entries, word.data(), tq::kSmallRingSpread, c.data())) return std::printf("refused\n"), false;
+    if (!tq::level_unit(codes.data() + (size_t)uoff[u] * tq::kChunkWords, uoff[u + 1] - uoff[u], n_entries, word.data(), tq::kSmallRingSpread, c.data(), scratch(uoff[u + 1] - uoff[u]))) return std::printf("refused\n"), false;
     want.insert(want.end(), c.begin(), c.end());
   }
   std::unique_ptr<uint16_t[]> out;
@@ -57,6 +62,15 @@ static bool many() {
   with.insert(std::lower_bound(with.begin(), with.end(), n_units / 2), n_units / 2);
   if (tq::level_units(codes.data(), uoff.data(), with, n_entries, word.data(), tq::kSmallRingSpread, 4, out)) return std::printf("taken with a unit that cannot be levelled\n"), false;
   if (!tq::level_units(codes.data(), uoff.data(), {}, n_entries, word.data(), tq::kSmallRingSpread, 4, out)) return std::printf("none refused\n"), false;
+  const std::vector<uint32_t> closed = tq::close_gaps({1, 2, 4, 10, 17, 30, 36});
+  if (closed != std::vector<uint32_t>{1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 17, 30, 31, 32, 33, 34, 35, 36} || !tq::close_gaps({}).empty()) return std::printf("gaps\n"), false;
+  // a unit that is close together: its own codes, zeros for its pads
+  Codes plain(4 * tq::kChunkWords, (uint16_t)n_entries), same(plain.size());
+  for (uint32_t l = 0; l < 64; ++l)
+    for (uint32_t k = 0; k < 8 + l % 8; ++k) plain[(size_t)(k / 4) * tq::kChunkWords + 4 * l + k % 4] = (uint16_t)rnd(n_entries);
+  if (!tq::level_unit(plain.data(), 4, n_entries, word.data(), tq::kSmallRingSpread, same.data(), scratch(4))) return std::printf("close unit refused\n"), false;
+  for (size_t k = 0; k < plain.size(); ++k)
+    if (same[k] != (plain[k] == n_entries ? 0 : plain[k])) return std::printf("close unit changed\n"), false;
   double shared = 0;
   for (int k = 0; k < 5 && shared < 1.5; ++k) {
     const std::clock_t c0 = std::clock();
@@ -95,7 +109,7 @@ int main() {
     auto at = [](uint32_t l, uint32_t k) { return (size_t)(k / 4) * tq::kChunkWords + 4 * l + k % 4; };
     for (uint32_t l = 0; l < 64; ++l)
       for (uint32_t k = 0; k < lane[l].size(); ++k) in[at(l, k)] = lane[l][k];
-    if (!tq::level_unit(in.data(), n_chunks, n_entries, word.data(), limit, out.data())) {
+    if (!tq::level_unit(in.data(), n_chunks, n_entries, word.data(), limit, out.data(), scratch(n_chunks))) {
       ++refused;
       by_chance += turn == seg;   // (a lane that is ahead can wait; of two with the same share of pairs the other may be later on)
       continue;

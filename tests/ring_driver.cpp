@@ -13,6 +13,11 @@ static uint32_t rnd(uint32_t n) {
   state ^= state << 13, state ^= state >> 7, state ^= state << 17;
   return (uint32_t)(state % n);
 }
+static uint16_t* scratch(uint32_t n_chunks) {
+  static std::vector<uint16_t> room;
+  room.assign(tq::level_scratch(n_chunks), 0xFFFF);
+  return room.data();
+}
 
 // k_matvec_ring: whole units, lanes that have finished go on by a column a code.
 // advance[chunk][lane]: columns; len[lane]: of its segment, `seg` or 0.  Returns the places that held something else.
@@ -181,7 +186,7 @@ int main() {
       for (uint32_t k = 0; k < lane[l].size(); ++k) in[at(l, k)] = lane[l][k];
     auto columns = [&](uint32_t most) {   // of the unit brought within `most` columns; empty: it cannot be
       std::vector<std::vector<uint32_t>> advance;
-      if (!tq::level_unit(in.data(), n_chunks, n_entries, word.data(), most, out.data())) return advance;
+      if (!tq::level_unit(in.data(), n_chunks, n_entries, word.data(), most, out.data(), scratch(n_chunks))) return advance;
       advance.assign(n_chunks, std::vector<uint32_t>(64, 0));
       for (uint32_t l = 0; l < 64; ++l)
         for (uint32_t k = 0; k < 4 * n_chunks; ++k) advance[k / 4][l] += out[at(l, k)] >= 256 ? 2 : 1;
