@@ -12,13 +12,15 @@ from test_gpu_work_split import TOL, _gated, _stream
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("cols,seg_cols,opts", [(2048, 256, {}), (384, 96, {}), (1024, 128, {"pack": True})], ids=["256", "96", "packed"])
-@pytest.mark.parametrize("limit,spare,kind", [(32, True, 2), (33, True, 2), (34, True, 2), (40, True, 2), (32, False, 2), (33, False, 2), (34, False, 1), (40, False, 1)])
+SHAPES = [(2048, 256, {}), (384, 96, {}), (1024, 128, {"pack": True})]
+LANES = [(32, True, 2), (33, True, 2), (34, True, 2), (40, True, 2), (32, False, 2), (33, False, 2), (34, False, 1), (40, False, 1)]
+
+
+# (lanes without a code to spare need room for the codes that close the distance again)
+@pytest.mark.parametrize("cols,seg_cols,opts,limit,spare,kind", [s + l for s in SHAPES for l in LANES if l[1] or s[1] >= 3 * l[0] + 8])
 def test_lanes_around_the_limit_of_the_small_ring(cols, seg_cols, opts, limit, spare, kind):
     """Lanes that can wait are brought within 33 columns when the matrix is loaded, whatever they were, and take the ring kernel; so do
     lanes that cannot but are no further apart; beyond that the runs kernel takes the matrix, with rings of 128 bytes."""
-    if not spare and seg_cols < 3 * limit + 8:
-        pytest.skip("a segment too short for such lanes")
     Q, scales, blob = drifting(1, cols, seg_cols, limit, opts, spare)
     assert ring_class(blob) == kind
     m = tq.Matrix(blob)
