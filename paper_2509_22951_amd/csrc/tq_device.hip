@@ -277,10 +277,15 @@ int static_table_of(int device, StepEntry** out) {   // `device` is the current 
 // Every kernel of the library that takes its dictionary at LDS address 0.
 const void* const kLdsKernels[] = {
     (const void*)k_matvec<kDotPiece, kDotWaves, false, 1>,
+    (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, false, false, true>,
     (const void*)k_matvec<kDotPiece, kDotWaves, false, 2>,
+    (const void*)k_matvec<kDotPiece, kDotWaves, false, 2, false, false, true>,
     (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1>,
+    (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1, false, false, true>,
     (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2>,
+    (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2, false, false, true>,
     (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, true>,
+    (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, true, false, true>,
     (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 1, false, true>,
     (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 2, false, true>,
     (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1, false, true>,
@@ -295,14 +300,22 @@ const void* const kLdsKernels[] = {
     (const void*)k_matvec_mfma<false, false, true>,
     (const void*)k_matvec_mfma<true, true, true>,
     (const void*)k_matvec_mfma<false, true, true>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1>,
-    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1>,
-    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2>,
-    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1, true>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1, false>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1, true>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2, false>,
+    (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2, true>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2, true>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4, true>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1, true>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2, true>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4, false>,
+    (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4, true>,
     (const void*)k_matvec_ring<kRingWaves, 16, false>,
     (const void*)k_matvec_ring<kRingWaves, 8, false>,
     (const void*)k_matvec_ring<kRingWaves, 16, true>,
@@ -536,6 +549,28 @@ struct BandCounts {
 // bytes), and those narrower than one activation fragment.
 bool runs_eligible(const tq_matrix* t) { return t->m.ring && (t->m.packing ? 2 : 1) * t->m.cols >= 8; }
 
+// kOne: every workgroup serves one matrix.
+template <bool kOne>
+const void* dot_kernel(bool packed, bool long_runs, int batch) {
+  if (long_runs) return (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, true, false, kOne>;
+  if (packed)
+    return batch == 2 ? (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2, false, false, kOne>
+                      : (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1, false, false, kOne>;
+  return batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 2, false, false, kOne> : (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, false, false, kOne>;
+}
+// less: rings of 64 bytes.
+template <bool kOne>
+const void* runs_kernel(bool packed, bool less, int batch) {
+  if (less) return batch <= 8 ? (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2, kOne> : (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1, kOne>;
+  if (packed)
+    return batch <= 4   ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4, kOne>
+           : batch <= 8 ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2, kOne>
+                        : (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1, kOne>;
+  return batch <= 4   ? (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4, kOne>
+         : batch <= 8 ? (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2, kOne>
+                      : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1, kOne>;
+}
+
 // One kernel launch for hs[0..n), all on one device, total cost below 2^32; n <= kMaxMulti, or n <= kMaxStep when the
 // launch is recorded for a prepared step (rec: its jobs then go to the step's device table, not into the arguments).
 // kMatvec: xs/ys are the activations and outputs; kDecompress: ys are the int8 output matrices, xs is not used.
@@ -586,16 +621,22 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
   }
   // Every workgroup's share of the cost line is at least one band of the most expensive kind, and there is one
   // workgroup per CU at most.
-  p.grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)hs[0]->n_cu, bands, cost / band_cost_max}));
+  p.grid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>({(uint64_t)hs[0]->n_cu, bands, cost / band_cost_max, kMaxParts}));
+  a.share = (uint32_t)(cost / p.grid);
+  a.share_rest = (uint32_t)(cost % p.grid);
+  a.parts_inverse = 1.f / (float)p.grid;
   const bool packed = hs[0]->m.packing != 0;   // (all matrices of a product launch hold their weights the same way: launch_all sees to that)
   const bool long_runs = hs[0]->m.long_runs != 0;   // (likewise)
   auto cut_by_workgroup = [&](bool by_units) {
     uint32_t wgs[kMaxAssign];
-    if (n > kMaxAssign || !cut_in_workgroups(n, BandCounts(n, hs, by_units).m, std::min<uint64_t>(hs[0]->n_cu, bands), p.grid, wgs)) return;
+    if (n > kMaxAssign || hs[0]->n_cu > kJobMapWorkgroups || !cut_in_workgroups(n, BandCounts(n, hs, by_units).m, std::min<uint64_t>(hs[0]->n_cu, bands), p.grid, wgs)) return;
+    for (int i = 0; i < n; ++i)
+      if (hs[i]->m.n_bands / wgs[i] >= kMaxWorkgroupBands) return;
     a.by_workgroup = 1;
     p.grid = 0;
     for (int i = 0; i < n; ++i) {
-      a.u.cost_long[i] = p.grid;
+      a.u.cost_long[i] = line_word(p.grid, hs[i]->m.n_bands / wgs[i]);
+      for (uint32_t g = p.grid; g < p.grid + wgs[i]; ++g) a.u.cost_long[kJobMapAt + g / 4] |= (uint32_t)i << g % 4 * 8;
       p.grid += wgs[i];
     }
     a.u.cost_long[n] = p.grid;
@@ -606,11 +647,9 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
       set_error("the matrices of this call together need " + std::to_string(p.lds) + " bytes of LDS (largest dictionary plus longest row)");
       return TQ_E_UNSUPPORTED;
     }
-    p.kernel = long_runs ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 1, true>
-               : packed ? (batch == 2 ? (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 2> : (const void*)k_matvec<kDotPiecePacked, kDotWavesPacked, true, 1>)
-               : batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWaves, false, 2> : (const void*)k_matvec<kDotPiece, kDotWaves, false, 1>;
-    p.block = (packed ? kDotWavesPacked : kDotWaves) * 64;
     cut_by_workgroup(false);
+    p.kernel = a.by_workgroup ? dot_kernel<true>(packed, long_runs, batch) : dot_kernel<false>(packed, long_runs, batch);
+    p.block = (packed ? kDotWavesPacked : kDotWaves) * 64;
   } else if (ring) {
     // LDS: 16-bit dictionary image | one ring per lane (aligned to its size: the kernel ORs piece offsets into its
     // address) | the activation tile of one quad.
@@ -639,11 +678,8 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     const bool less = small && !packed && batch > 4 && units <= (uint64_t)kRunSmallUnits * p.grid;
     p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
     p.lds = dict16 + (size_t)p.block * (less ? kSmallRingBytes : kRingBytes) + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
-    if (less) p.kernel = batch <= 8 ? (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 2> : (const void*)k_matvec_runs<kSmallRingBytes, kRunWaves, false, 1>;
-    else if (batch <= 4) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 4> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 4>;
-    else if (batch <= 8) p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 2> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 2>;
-    else p.kernel = packed ? (const void*)k_matvec_runs<kRingBytes, kRunWavesPacked, true, 1> : (const void*)k_matvec_runs<kRingBytes, kRunWaves, false, 1>;
     cut_by_workgroup(true);
+    p.kernel = a.by_workgroup ? runs_kernel<true>(packed, less, batch) : runs_kernel<false>(packed, less, batch);
   } else {
     // Tile decode.  LDS: 16-bit dictionary image | one tile (64 strips) per wavefront, which the batched product reuses
     // for its partial sums (per wavefront two slots of 1 KB and their two band numbers).
@@ -1055,7 +1091,8 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
       uint32_t wgs[kMaxAssign];
       const BandCounts counts(cnt, hs + f);
       const uint64_t worst = assign_workgroups(cnt, counts.m, p.grid, wgs);
-      can = worst != 0;
+      can = worst != 0 && (uint64_t)n_stages * p.grid <= kLineMask;
+      for (int i = 0; i < cnt && can; ++i) can = hs[f + i]->m.n_bands / wgs[i] < kMaxWorkgroupBands;
       whole += worst;
       even += even_cut_cost(cnt, counts.m, p.grid);
       uint32_t at = k * p.grid;
@@ -1067,7 +1104,9 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
     line[n] = n_stages * p.grid;   // (workgroups left over in a stage count as its last matrix's)
     if (can && whole <= even) {
       a.by_workgroup = 1;
-      std::copy(line.begin(), line.end(), a.u.cost_long);
+      a.share = p.grid;
+      for (int i = 0; i < n; ++i) a.u.cost_long[i] = line_word(line[i], hs[i]->m.n_bands / (line[i + 1] - line[i]));
+      a.u.cost_long[n] = line[n];
     }
     rec.launches.push_back(p);
   }

@@ -5,26 +5,9 @@
 
 namespace tq {
 // Staging is split in two so that the loads of the dictionary, of the activations and of the first code chunks are
-// all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS.
+// all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS; the dictionary's loads write LDS
+// themselves (request_to_lds).
 constexpr uint32_t kSplitWaves = 4;    // k_matvec splits units between wavefronts in shares that leave each unit at least this many
-
-template <int kThreads, int kDictRegs>   // kDictRegs x kThreads x 16 bytes per round (128 KB: the whole dictionary in one)
-__device__ __forceinline__ void issue_dictionary(const DevMat& m, uint32_t base, int tid, uint4 (&v)[kDictRegs]) {
-  const uint4* src = (const uint4*)m.dict_bf16;
-  const uint32_t n4 = m.dict_words / 4;
-#pragma unroll
-  for (int k = 0; k < kDictRegs; ++k) v[k] = global_load(src + min(base + k * kThreads + tid, n4 - 1));
-}
-template <int kThreads, int kDictRegs>
-__device__ __forceinline__ void commit_dictionary(const DevMat& m, uint32_t base, int tid, const uint4 (&v)[kDictRegs], uint32_t* lds_dict) {
-  uint4* dst = (uint4*)lds_dict;
-  const uint32_t n4 = m.dict_words / 4;
-#pragma unroll
-  for (int k = 0; k < kDictRegs; ++k) {
-    const uint32_t i = base + k * kThreads + tid;
-    if (i < n4) dst[i] = v[k];
-  }
-}
 
 // LDS image of one activation row: dword (panel * x_span + c) = (x[panel * seg_cols + c], x[panel * seg_cols + c + 1])
 // as two bf16, zero past the end of the row; the gap dwords between panels and the tail are zero.
@@ -36,17 +19,19 @@ __device__ __forceinline__ void issue_activations(const DevMat& m, const uint16_
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
     const uint32_t j = first_pair + k * kThreads + tid, col = 2 * j;
+    lo[k] = hi[k] = 0u;
+    if (2 * (first_pair + k * kThreads) >= m.cols) continue;   // (the same for all: rows are mostly shorter than a round of loads)
     if (kAligned) {   // x is 4-byte aligned and cols is even
       lo[k] = col < m.cols ? x_load<kCoherent>((const uint32_t*)x + j) : 0u;
     } else {
       lo[k] = (col < m.cols ? x_load<kCoherent>(x + col) : 0u) | (col + 1 < m.cols ? x_load<kCoherent>(x + col + 1) << 16 : 0u);
     }
-    hi[k] = 0u;
   }
   if ((tid & 63) == 63) {
 #pragma unroll
     for (int k = 0; k < kXRegs; ++k) {
       const uint32_t col = 2 * (first_pair + k * kThreads + tid) + 2;
+      if (2 * (first_pair + k * kThreads) >= m.cols) continue;
       if (col < m.cols) hi[k] = x_load<kCoherent>(x + col);
     }
   }
@@ -57,6 +42,7 @@ __device__ __forceinline__ void commit_activations(const DevMat& m, uint32_t fir
   const uint32_t gap = m.x_span - m.seg_cols;
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
+    if (2 * (first_pair + k * kThreads) >= image_cols) continue;
     const uint32_t col = 2 * (first_pair + k * kThreads + tid);
     // the next lane's pair (wave shift by one lane; the last lane keeps what it loaded itself)
     const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)hi[k], (int)lo[k], 0x130, 0xf, 0xf, false);
@@ -65,6 +51,43 @@ __device__ __forceinline__ void commit_activations(const DevMat& m, uint32_t fir
       lds_x[i] = lo[k];
       lds_x[i + 1] = lo[k] >> 16 | next << 16;
     }
+  }
+}
+// The same for x at 8-byte aligned addresses and rows of whole 4 columns: thread t of a round handles 4 columns, with one load and one
+// store.  v: the 4 columns; hi: the one behind them, loaded by the last lane of a wavefront only.
+template <int kThreads, int kXRegs, bool kCoherent>   // 2 * kXRegs registers as above, kXRegs x kThreads x 4 columns per round
+__device__ __forceinline__ void issue_activations_wide(const DevMat& m, const uint16_t* __restrict__ x, uint32_t first, int tid, uint32_t (&v)[2 * kXRegs],
+                                                       uint32_t (&hi)[2 * kXRegs]) {
+#pragma unroll
+  for (int k = 0; k < kXRegs; ++k) {
+    v[2 * k] = v[2 * k + 1] = hi[k] = 0u;
+    if (first + k * kThreads * 4 >= m.cols) continue;   // (the same for all)
+    const uint32_t col = first + 4 * (k * kThreads + tid);
+    if (col < m.cols) {
+      if constexpr (kCoherent) {
+        const uint64_t w = __hip_atomic_load((__attribute__((address_space(1))) const uint64_t*)(x + col), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v[2 * k] = (uint32_t)w;
+        v[2 * k + 1] = (uint32_t)(w >> 32);
+      } else {
+        const uint2 w = global_load((const uint2*)(x + col));
+        v[2 * k] = w.x;
+        v[2 * k + 1] = w.y;
+      }
+    }
+    if ((tid & 63) == 63 && col + 4 < m.cols) hi[k] = x_load<kCoherent>(x + col + 4);
+  }
+}
+template <int kThreads, int kXRegs>
+__device__ __forceinline__ void commit_activations_wide(const DevMat& m, uint32_t first, int tid, const uint32_t (&v)[2 * kXRegs], const uint32_t (&hi)[2 * kXRegs],
+                                                        uint32_t* lds_x, uint32_t image_cols) {
+  const uint32_t gap = m.x_span - m.seg_cols;
+#pragma unroll
+  for (int k = 0; k < kXRegs; ++k) {
+    if (first + k * kThreads * 4 >= image_cols) continue;
+    const uint32_t col = first + 4 * (k * kThreads + tid), lo = v[2 * k], up = v[2 * k + 1];
+    const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)hi[k], (int)lo, 0x130, 0xf, 0xf, false);   // the next lane's first two
+    if (col < image_cols)   // (image_cols and seg_cols are multiples of 16: the 4 columns lie in one panel)
+      *(u32x4*)&lds_x[col + gap * __umulhi(col, m.seg_magic)] = u32x4{lo, __builtin_amdgcn_alignbyte(up, lo, 2), up, __builtin_amdgcn_alignbyte(next, up, 2)};
   }
 }
 template <int kThreads, int kDwords = 1>   // kDwords: dwords per column of the image (2: two rows of packed weights)
@@ -162,6 +185,8 @@ __device__ __forceinline__ void issue_activations_packed(const DevMat& m, const 
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
     const uint32_t j = first + k * kThreads + tid;
+    v[k] = 0u;
+    if (first + k * kThreads >= m.cols) continue;
     if (kAligned) v[k] = j < m.cols ? x_load<kCoherent>((const uint32_t*)x + j) : 0u;   // x is 4-byte aligned
     else v[k] = j < m.cols ? x_load<kCoherent>(x + 2 * j) | x_load<kCoherent>(x + 2 * j + 1) << 16 : 0u;
   }
@@ -172,6 +197,7 @@ __device__ __forceinline__ void commit_activations_packed(const DevMat& m, uint3
   const uint32_t gap = m.x_span - m.seg_cols;
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
+    if (first + k * kThreads >= image_cols) continue;
     const uint32_t j = first + k * kThreads + tid;
     if (j < image_cols) lds_x[j + gap * __umulhi(j, m.seg_magic)] = v[k];
   }
@@ -216,6 +242,7 @@ __device__ __forceinline__ void commit_activations_packed_two(const DevMat& m, u
   const uint32_t gap = m.x_span - m.seg_cols;
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
+    if (first + k * kThreads >= image_cols) continue;
     const uint32_t j = first + k * kThreads + tid;
     if (j < image_cols) {
       const uint32_t i = 2 * (j + gap * __umulhi(j, m.seg_magic));
@@ -243,6 +270,8 @@ __device__ __forceinline__ void issue_activations_two(const DevMat& m, const uin
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
     const uint32_t j = first_pair + k * kThreads + tid, col = 2 * j;
+    r0[k] = r1[k] = 0u;
+    if (2 * (first_pair + k * kThreads) >= m.cols) continue;
     if (kAligned) {
       r0[k] = col < m.cols ? x_load<kCoherent>((const uint32_t*)x + j) : 0u;
       r1[k] = col < m.cols ? x_load<kCoherent>((const uint32_t*)x1 + j) : 0u;
@@ -258,6 +287,7 @@ __device__ __forceinline__ void commit_activations_two(const DevMat& m, uint32_t
   const uint32_t gap = m.x_span - m.seg_cols;
 #pragma unroll
   for (int k = 0; k < kXRegs; ++k) {
+    if (2 * (first_pair + k * kThreads) >= image_cols) continue;
     const uint32_t col = 2 * (first_pair + k * kThreads + tid);
     if (col < image_cols) {   // image_cols and seg_cols are even: both columns lie in one panel
       const uint32_t i = col + gap * __umulhi(col, m.seg_magic);
@@ -312,7 +342,13 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // so the result does not depend on timing.
 // kStaged: the jobs form stages (MatvecArgs::stage_first); the workgroups take the stages in turn, each one's bands cut
 // into equal shares as above, with a grid-wide hand-over between two stages; the dictionary stays in LDS across them.
-template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false>
+// kOne: every workgroup serves one job (a launch whose matrices have whole workgroups), found in the arguments' map: no loop over jobs,
+// which the compiler prepares for with some 200 instructions ahead of the first load.  A small launch is bound by what its wavefronts do
+// before they decode: every instruction of a wavefront with one neighbour on its SIMD is 2 to 4 ns, a round trip to memory only 160.
+// 2048 x 2048, batch 1, us after the first wavefront's start, before -> now (no search and no 64-bit divisions either, 4 columns of x to a
+// load, the dictionary through request_to_lds, behind the first codes): its job known 1.5 -> 0.6, everything requested 3.7 -> 2.4, decode
+// from 6.1 -> 3.9, end of a pass 10.1 -> 8.7; one LLaMA-3.2-1B layer 18.3 -> 17.2.
+template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false, bool kOne = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   static_assert(kB == 1 || kB == 2, "one activation row or two");
   static_assert(!kLong || (kB == 1 && !kPacked), "runs of 3 and 4 bytes: one activation row of one-weight-per-byte matrices");
@@ -328,7 +364,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   // two rows, 2 units 9.7 / 12.2, 3 units 11.7 / 11.5; packed, 12 wavefronts, 3 units 10.3 / 11.2, 4 units 11.1 / 10.6.)
   constexpr bool kSplit = !kLong && !(kPacked && kB == 2);   // (two rows of packed weights leave no LDS for the counts)
   constexpr int kCount = 12;   // chunks per round of that count
-  constexpr int kThreads = kWaves * 64, kDictRegs = (kStaged ? 48 : 128) / kWaves, kXRegs = 64 / kWaves;   // (staged: one dictionary for many stages, so few registers)
+  constexpr int kThreads = kWaves * 64, kXRegs = 64 / kWaves;
   if constexpr (!kStaged) touch_arguments();
   extern __shared__ uint4 lds4[];
   uint32_t* lds_dict = (uint32_t*)lds4;
@@ -351,10 +387,21 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   auto enter_stage = [&](Cursor& c) {
     const int first = kStaged ? (int)((const_u32*)a.stage_first)[c.stage] : 0;
     c.end = kStaged ? (int)((const_u32*)a.stage_first)[c.stage + 1] : a.n;
-    const uint32_t cost_first = cost_at(a, first);
-    const uint64_t total = cost_at(a, c.end) - cost_first;
-    c.lo = cost_first + (uint32_t)(total * blockIdx.x / gridDim.x);
-    c.hi = cost_first + (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+    if (kOne || (kStaged && a.by_workgroup)) {
+      c.lo = (kStaged ? c.stage * a.share : 0u) + blockIdx.x;
+      c.hi = c.lo + 1;
+      if constexpr (kOne) {
+        c.i = mapped_job(a);
+        return;
+      }
+    } else if constexpr (kStaged) {
+      const uint32_t cost_first = cost_at(a, first);
+      const uint64_t total = cost_at(a, c.end) - cost_first;
+      c.lo = cost_first + (uint32_t)(total * blockIdx.x / gridDim.x);
+      c.hi = cost_first + (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+    } else {
+      even_share(a, c.lo, c.hi);
+    }
     c.i = first_job(a, first, c.end, c.lo, lane);
   };
   auto settle = [&](Cursor& c) {   // moves on, over stages the workgroup has no share in, to a job it has; false at the end
@@ -419,7 +466,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       w_ends = unit_end <= c_end;
       const uint32_t len = min(unit_end, c_end) - wc;
       w_left = (len + kPiece - 1) / kPiece;
-      w_base = len / w_left;
+      w_base = piece_length(len, w_left);
       w_rem = len - w_base * w_left;
       ++wu;
     }
@@ -510,7 +557,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   enter_stage(at);
   uint32_t arrived = 0;   // kStaged: the stages this workgroup has announced to have behind it
   uint32_t entry_at = 0, entry_next = 0, entry_later = 0;
-  bool have = settle(at), have_next = false, have_later = false, planned = false;
+  bool have = kOne || settle(at), have_next = false, have_later = false, planned = false;
   if (kStaged && have) {
     entry_at = request_entry(at.i);
     next = at;
@@ -546,7 +593,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     if constexpr (kStaged) open_entry(entry_at, job, m);
     else fetch_job(a, at.i, job, m);
     uint32_t band_lo, band_hi;
-    share_of_bands(a, m, cost_at(a, at.i), cost_at(a, at.i + 1), at.lo, at.hi, band_lo, band_hi);
+    share_of_bands(a, kOne || (kStaged && a.by_workgroup), m, at.i, at.lo, at.hi, band_lo, band_hi);
     if (kStaged && at.stage > arrived) {
       wait_for_stores();
       stage_arrive(a, at.stage);
@@ -554,6 +601,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       arrived = at.stage;
     }
     if (band_lo >= band_hi) {
+      if constexpr (kOne) return;
       look_further();
       planned = false;
       advance();
@@ -566,12 +614,13 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     const uint32_t xa_lane = lds_address(lds_x) + 4u * kImage * m.x_span * (uint32_t)(lane >> 4);
     const uint32_t xa_quad = 16u * kImage * m.x_span;
     const bool x_aligned = (kPacked || m.cols % 2 == 0) && ((uintptr_t)job.x % 4 == 0);   // (cols even: a second row is aligned like the first)
+    const bool x_wide = !kPacked && kB == 1 && m.cols % 4 == 0 && (uintptr_t)job.x % 8 == 0;
     if (!planned) uoff_lane = request_offsets(m, band_lo, band_hi);
     {   // one activation row, or two: larger batches run the MFMA kernels
       const uint16_t* xb = job.x;
       float* yb = job.y;
-      // Dictionary and activations are requested first: their addresses wait for nothing but the description.
-      uint4 dv[kDictRegs];
+      // Activations and dictionary are requested first: their addresses wait for nothing but the description.  (A further matrix's
+      // dictionary goes to LDS when the one before it is no longer in use.)
       uint32_t xlo[kXRegs], xhi[kXRegs];
       auto request_activations = [&] {
         if constexpr (kPacked) {
@@ -585,12 +634,15 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
           if (x_aligned) issue_activations_two<true, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
           else issue_activations_two<false, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
         } else {
-          if (x_aligned) issue_activations<true, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
+          if (x_wide) issue_activations_wide<kThreads, kXRegs / 2, kStaged>(m, xb, 0, tid, xlo, xhi);
+          else if (x_aligned) issue_activations<true, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
           else issue_activations<false, kThreads, kXRegs, kStaged>(m, xb, 0, tid, xlo, xhi);
         }
       };
-      if (new_dict) issue_dictionary<kThreads, kDictRegs>(m, 0, tid, dv);
       if constexpr (!kStaged) request_activations();   // (staged: they may still be in the making)
+      const bool dict_first = new_dict && !lds_used;
+      constexpr uint32_t kDictAhead = 4;   // rounds of the dictionary that are on their way while the unit offsets arrive; the others behind the first codes
+      if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, 0, kDictAhead);
       if (!planned) {
         plan_run(m, band_lo, band_hi);
         if (u0 < u1) load_piece(m, cwa, sa, na);
@@ -598,6 +650,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         load_piece(m, cwa, sa, na, false, false);
       }
       if (tail_shared) request_count(m, part);
+      if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, kDictAhead);
       if constexpr (kStaged) {   // while the other workgroups arrive
         if (lds_used && wait_for == kNoStage) __syncthreads();   // (the counts of the job before are no longer read)
         if (split) count_columns(m);
@@ -611,6 +664,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         __syncthreads();
       }
       lds_used = true;
+      if (new_dict && !dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict);
       if constexpr (kStaged) request_activations();
       look_further();
       uint32_t uoff_next = 0, next_lo = 0, next_hi = 0;
@@ -618,20 +672,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         Job next_job;
         DevMat next_m;
         open_entry(entry_next, next_job, next_m);
-        share_of_bands(a, next_m, cost_at(a, next.i), cost_at(a, next.i + 1), next.lo, next.hi, next_lo, next_hi);
+        share_of_bands(a, a.by_workgroup, next_m, next.i, next.lo, next.hi, next_lo, next_hi);
         if (next_lo < next_hi) uoff_next = request_offsets(next_m, next_lo, next_hi);
       }
       {
         zero_activation_gaps<kThreads, kImage>(m, tid, lds_x, n_slots);
         if (tid < 2 * kWaves) slot_band[tid] = -1;
-        if (new_dict) {
-          commit_dictionary<kThreads, kDictRegs>(m, 0, tid, dv, lds_dict);
-          for (uint32_t base = kDictRegs * kThreads; base < m.dict_words / 4; base += kDictRegs * kThreads) {
-            issue_dictionary<kThreads, kDictRegs>(m, base, tid, dv);
-            commit_dictionary<kThreads, kDictRegs>(m, base, tid, dv, lds_dict);
-          }
-        }
-        if (!kStaged && split) count_columns(m);   // (after the dictionary, which was requested first)
         if constexpr (kPacked && kB == 2) {
           commit_activations_packed_two<kThreads, kXRegs>(m, 0, tid, xlo, xhi, lds_x, image_cols);
           for (uint32_t first = kXRegs * kThreads; first < image_cols; first += kXRegs * kThreads) {
@@ -658,6 +704,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             else issue_activations_two<false, kThreads, kXRegs, kStaged>(m, xb, first, tid, xlo, xhi);
             commit_activations_two<kThreads, kXRegs>(m, first, tid, xlo, xhi, lds_x, image_cols);
           }
+        } else if (x_wide) {
+          commit_activations_wide<kThreads, kXRegs / 2>(m, 0, tid, xlo, xhi, lds_x, image_cols);
+          for (uint32_t first = 2 * kXRegs * kThreads; first < image_cols; first += 2 * kXRegs * kThreads) {
+            issue_activations_wide<kThreads, kXRegs / 2, kStaged>(m, xb, first, tid, xlo, xhi);
+            commit_activations_wide<kThreads, kXRegs / 2>(m, first, tid, xlo, xhi, lds_x, image_cols);
+          }
         } else {
           commit_activations<kThreads, kXRegs>(m, 0, tid, xlo, xhi, lds_x, image_cols);
           for (uint32_t first = kXRegs * kThreads; 2 * first < image_cols; first += kXRegs * kThreads) {
@@ -666,7 +718,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             commit_activations<kThreads, kXRegs>(m, first, tid, xlo, xhi, lds_x, image_cols);
           }
         }
+        if (!kStaged && split) count_columns(m);   // (last: its chunks were requested after everything else)
       }
+      if (new_dict) lds_arrived();
       __syncthreads();
       float slot_scale = 0.f;   // row scales of the bands in this wavefront's two slots: the first one's in lanes 0..31
       if (u0 < u1) {
@@ -796,12 +850,13 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       // wavefront sees to its own two slots, whose row scales it still holds; lanes are (slot, activation row, row).
       {
         const int slots = lane < 2 * kWaves ? slot_band[lane] : -1;
-        uint64_t same[2];
+        static_assert(2 * kWaves <= 32, "a bit per slot");
+        uint32_t same[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const int band = __builtin_amdgcn_readlane(slots, 2 * wave + j);
-          same[j] = __builtin_amdgcn_ballot_w64(slots == band && slots >= 0);
-          if (same[j] & ((1ull << (2 * wave + j)) - 1)) same[j] = 0;   // an earlier slot of the band does it
+          same[j] = (uint32_t)__builtin_amdgcn_ballot_w64(slots == band && slots >= 0);
+          if (same[j] & ((1u << (2 * wave + j)) - 1)) same[j] = 0;   // an earlier slot of the band does it
         }
         const int j = lane >> 5, b = lane >> 4 & 1, r16 = lane & 15;
         if (b < kB && (same[0] | same[1])) {
@@ -825,6 +880,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         }
       }
     }
+    if constexpr (kOne) return;
     advance();
   }
   if constexpr (kStaged) {

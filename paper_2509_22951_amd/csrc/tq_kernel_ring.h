@@ -114,7 +114,7 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
       wc = unit_offset(m, u);
       const uint32_t len = unit_offset(m, u + 1) - wc;
       w_left = (len + kP - 1) / kP;
-      w_base = len / w_left;
+      w_base = piece_length(len, w_left);
       w_rem = len - w_base * w_left;
     }
     n = w_base + (w_rem ? 1u : 0u);
@@ -227,27 +227,25 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t rings = a.x_off, xtile = a.slot_off;   // LDS addresses (the LDS segment starts at 0)
-  const uint64_t total = cost_at(a, a.n);
-  const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+  uint32_t lo, hi;
+  even_share(a, lo, hi);
   const uint32_t* staged = nullptr;
   const int bn = lane & 15, kg = lane >> 4;   // B operand: batch row and k-group (panel) of this lane
   const uint32_t ring = rings + (uint32_t)wave * (64 * kRing) + (uint32_t)lane * kRing;
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
-    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb) break;
+    if (hi <= cost_at(a, i)) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
     uint32_t band_lo, band_hi;
-    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
+    share_of_bands(a, false, m, i, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     constexpr uint32_t pk = kPacked ? 2u : 1u;             // columns of the weight matrix per stored byte
     const uint32_t nq = m.n_quads, n_win = pk * m.seg_cols / 8;   // activation windows (8 columns) per segment
     __syncthreads();   // the previous matrix's dictionary and activation tile are no longer in use
-    if (m.dict != staged) {
-      stage_image<kRingThreads>(m, tid, lds4);
-      staged = m.dict;
-    }
+    const bool new_dict = m.dict != staged;
+    if (new_dict) stage_image(m, lane, wave, kWaves, lds4);
+    staged = m.dict;
     // Bands are handed out one at a time, per quad, through a counter in LDS: wavefront w starts with band w of the
     // workgroup's range and claims the next free one while it decodes the last piece of chunks of the one in work.
     // (An even split up front leaves wavefronts waiting at the end of every quad: for the slowest, and for the one more
@@ -304,6 +302,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
         if (q || pass_lo != band_lo) __syncthreads();   // everybody has finished the previous quad: its activation tile can go
         if (!kGateUp && tid == 0) *next_band_counter = kWaves;   // bands 0 .. kWaves - 1 are the wavefronts' first ones
         commit_tile();
+        if (new_dict && q == 0 && pass_lo == band_lo) lds_arrived();
         if (q + 1 < nq || pass_hi < band_hi) request_tile(q + 1 < nq ? q + 1 : 0);
         __syncthreads();
         // Sums of lane l: rows 4 * (l / 16) + v of the band, batch row l % 16.  The scales of the next band are requested

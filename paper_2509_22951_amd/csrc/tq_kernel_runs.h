@@ -44,10 +44,14 @@ __device__ __forceinline__ u32x4 drop_elements(u32x4 v, uint32_t by) {
 // a lane has not written itself counts as zeros.  x: the activations, row_first: where the
 // batch row of this lane's B operand starts; part: the sums of the band in work.  on_unit(band, quad) is called when a unit has been multiplied.
 // kFold: windows per B operand (fold_sums).
-template <int kRing, bool kPacked, int kFold, typename OnUnit>
-__device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, uint32_t start,
+// ready() is called once, when the first codes have been requested (they are on their way while it waits for the dictionary), and returns `start`.
+template <int kRing, bool kPacked, int kFold, typename Ready, typename OnUnit>
+__device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, uint32_t u1, uint32_t c0, uint32_t c_end, bool started, Ready&& ready,
                                                 global_cu16* x, uint32_t row_first, int lane, uint32_t ring, f32x4 (&part)[4], OnUnit&& on_unit) {
-  if (u0 >= u1 || c0 >= c_end) return;
+  if (u0 >= u1 || c0 >= c_end) {
+    (void)ready();
+    return;
+  }
   constexpr int kP = ring_piece(kRing), kG = ring_group(kRing), kLook = ring_step(kRing), kParts = (kP + kLook - 1) / kLook;
   constexpr uint32_t pk = kPacked ? 2u : 1u;   // columns of the weight matrix per stored byte, windows per 8-byte piece of the ring
   constexpr uint32_t kLoads = kG * pk / kFold;
@@ -68,7 +72,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
       const uint32_t unit_end = unit_offset(m, wu + 1), len = min(unit_end, c_end) - wc;
       w_ends = unit_end <= c_end;
       w_left = (len + kP - 1) / kP;
-      w_base = len / w_left;
+      w_base = piece_length(len, w_left);
       w_rem = len - w_base * w_left;
       ++wu;
     }
@@ -195,6 +199,9 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   auto ring_piece = [&](uint32_t col) { return (lds_u64*)(size_t)(ring | ((col ^ sw8) & (kRing - 8u))); };
   enter_unit();
   next_piece(sa, na, ea);
+#pragma unroll
+  for (int j = 0; j < kParts; ++j) load_part(cwa, sa, na, j);
+  const uint32_t start = ready();
   if (started) {   // the groups that every lane has passed are others' work; of the next ones, what a lane has passed is zeros here
     pos = min(start, seg_len);
     while (done + 8 * kG < n_win8 && __builtin_amdgcn_ballot_w64(pos < min(seg_len, done + 8 * kG)) == 0) done += 8 * kG;
@@ -202,8 +209,6 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
       if (col < (pos & ~7u)) *ring_piece(col) = 0;
   }
   request_x();
-#pragma unroll
-  for (int j = 0; j < kParts; ++j) load_part(cwa, sa, na, j);
   while (na) {   // two register sets: one is decoded while the other is filled
     next_piece(sb, nb, eb);
     decode_piece(First{}, cwa, na, ea, cwb, sb, nb);
@@ -236,28 +241,32 @@ constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a u
                                         // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
 constexpr uint32_t kRunSplitMinSmall = 9;   // with rings of 64 bytes, whose pieces are 9 chunks (11 / 9, us: 1024 x 1024 batch 8 10.8 / 10.1, 2048 x 2048 12.9 /
                                             // 12.5, 700 x 1999 15.9 / 16.7; batch 16 14.3 / 14.5)
-template <int kRing, int kWaves, bool kPacked, int kFold>
+// kOne: as in k_matvec (4099 x 2999 batch 5 18.1 -> 16.9 us, one LLaMA-3.2-3B layer batch 8 36.7 -> 35.4, with the first codes requested ahead of
+// the dictionary).
+template <int kRing, int kWaves, bool kPacked, int kFold, bool kOne>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
-  constexpr int kRunThreads = kWaves * 64, kCount = 12;
+  constexpr int kCount = 12;
   touch_arguments();
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint64_t total = cost_at(a, a.n);
-  const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+  uint32_t lo = blockIdx.x, hi = blockIdx.x + 1;
+  if constexpr (!kOne) even_share(a, lo, hi);
   const uint32_t* staged = nullptr;
   const uint32_t rings = a.x_off;   // LDS address (the LDS segment starts at 0)
   const uint32_t ring = rings + (uint32_t)wave * (64 * kRing) + (uint32_t)lane * kRing;
   uint16_t* lds_count = (uint16_t*)((uint8_t*)lds4 + rings + kWaves * 64 * kRing);   // [kWaves][64]
   bool lds_used = false;
-  for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
-    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb) break;
+  for (int i = kOne ? mapped_job(a) : first_job(a, 0, a.n, lo, lane); kOne || i < a.n; ++i) {
+    if (!kOne && hi <= cost_at(a, i)) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
     uint32_t band_lo, band_hi;
-    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
-    if (band_lo >= band_hi) continue;
+    share_of_bands(a, kOne, m, i, lo, hi, band_lo, band_hi);
+    if (band_lo >= band_hi) {
+      if constexpr (kOne) return;
+      continue;
+    }
     const uint32_t nq = m.n_quads, unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
     EvenRun run;
     const bool split = (kFold == 1 && !kPacked ? 3 : 2) * n_units <= kWaves;
@@ -272,32 +281,44 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
       run.head = run.tail = false;
     }
     const bool new_dict = m.dict != staged;
+    staged = m.dict;
     if (lds_used) __syncthreads();   // the previous matrix's dictionary, counts and partial sums are no longer in use
     lds_used = true;
-    if (new_dict) stage_image<kRunThreads>(m, tid, lds4);
-    if (split) {
-      u16x2 pairs = {0, 0};
-      if (run.tail) {
-        for (uint32_t from = run.part; from < run.c_end; from += kCount) {
-          uint2 cw[kCount];
+    // Called when the wavefront's first codes are on their way: the dictionary behind them, then the columns that its part of a unit
+    // passes.  Returns the columns of the run's first unit that earlier wavefronts pass.
+    auto ready = [&]() -> uint32_t {
+      uint2 cw[kCount];
+      auto request_count = [&](uint32_t from) {
 #pragma unroll
-          for (int k = 0; k < kCount; ++k) cw[k] = load_chunk(m.codes, min(from + k, run.c_end - 1), lane);
+        for (int k = 0; k < kCount; ++k) cw[k] = load_chunk(m.codes, min(from + k, run.c_end - 1), lane);
+      };
+      if (split && run.tail) request_count(run.part);
+      if (new_dict) stage_image(m, lane, wave, kWaves, lds4);
+      if (split) {
+        u16x2 pairs = {0, 0};
+        if (run.tail) {
+          for (uint32_t from = run.part;;) {
 #pragma unroll
-          for (int k = 0; k < kCount; ++k)
-            if (from + k < run.c_end) pairs = count_pairs(count_pairs(pairs, cw[k].x), cw[k].y);
+            for (int k = 0; k < kCount; ++k)
+              if (from + k < run.c_end) pairs = count_pairs(count_pairs(pairs, cw[k].x), cw[k].y);
+            from += kCount;
+            if (from >= run.c_end) break;
+            request_count(from);
+          }
+        }
+        lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (run.c_end - run.part) + pairs.x + pairs.y);   // (an empty run passes nothing)
+      }
+      if (new_dict) lds_arrived();
+      if (split || new_dict) __syncthreads();
+      uint32_t start = 0;
+      if (run.head) {
+        for (int w = wave - 1; w >= 0; --w) {
+          start += lds_count[w * 64 + lane];
+          if (run.start_of(w) <= run.unit_start) break;
         }
       }
-      lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (run.c_end - run.part) + pairs.x + pairs.y);   // (an empty run passes nothing)
-    }
-    if (split || new_dict) __syncthreads();
-    staged = m.dict;
-    uint32_t start = 0;   // head: the columns of the first unit that earlier wavefronts pass
-    if (run.head) {
-      for (int w = wave - 1; w >= 0; --w) {
-        start += lds_count[w * 64 + lane];
-        if (run.start_of(w) <= run.unit_start) break;
-      }
-    }
+      return start;
+    };
     BandSums sums;
     sums.start(run.u0, nq, run.head);
     f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -310,10 +331,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     global_cu16* x = (global_cu16*)job.x;
     // lanes past the batch repeat its last row: their sums are never stored
     const uint32_t row_first = min((uint32_t)(lane & 15) % (16 / kFold), (uint32_t)a.batch - 1) * (kPacked ? 2 : 1) * m.cols;
-    decode_run_ring<kRing, kPacked, kFold>(m, run.u0, run.u1, run.c0, run.c_end, run.head, start, x, row_first, lane, ring, part, on_unit);
+    decode_run_ring<kRing, kPacked, kFold>(m, run.u0, run.u1, run.c0, run.c_end, run.head, ready, x, row_first, lane, ring, part, on_unit);
     if (run.tail) sums.finish(a, job, m, (run.u1 - 1) / nq, false, fold_sums<kFold>(part), lane);
     __syncthreads();   // every wavefront is done with its ring: the partial sums go over the ring area
     sums.combine(a, job, m, rings, wave, kWaves, lane);
+    if constexpr (kOne) return;
   }
 }
 

@@ -10,19 +10,18 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
   extern __shared__ uint4 lds4[];
   uint8_t* tiles = (uint8_t*)lds4 + a.x_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_threads = blockDim.x, n_waves = n_threads >> 6;
-  const uint64_t total = cost_at(a, a.n);
-  const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+  const int n_waves = blockDim.x >> 6;
+  uint32_t lo, hi;
+  even_share(a, lo, hi);
   const uint32_t* staged = nullptr;
   const int bn = lane & 15, kg = lane >> 4;   // B operand: batch row and k-group of this lane
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
-    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb) break;
+    if (hi <= cost_at(a, i)) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
     uint32_t band_lo, band_hi;
-    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
+    share_of_bands(a, false, m, i, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads;
     const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
@@ -30,7 +29,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_matvec_mfma(MatvecArgs a) {
     const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / n_waves);
     __syncthreads();   // the previous matrix's dictionary and partial sums are no longer in use
     if (m.dict != staged) {
-      stage_image<kThreads>(m, tid, lds4, n_threads);
+      stage_image(m, lane, wave, n_waves, lds4);
+      lds_arrived();
       staged = m.dict;
     }
     __syncthreads();
@@ -82,18 +82,17 @@ __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
   extern __shared__ uint4 lds4[];
   uint8_t* tiles = (uint8_t*)lds4 + a.x_off;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_threads = blockDim.x, n_waves = n_threads >> 6;
-  const uint64_t total = cost_at(a, a.n);
-  const uint32_t lo = (uint32_t)(total * blockIdx.x / gridDim.x), hi = (uint32_t)(total * (blockIdx.x + 1) / gridDim.x);
+  const int n_waves = blockDim.x >> 6;
+  uint32_t lo, hi;
+  even_share(a, lo, hi);
   const uint32_t* staged = nullptr;
   for (int i = first_job(a, 0, a.n, lo, lane); i < a.n; ++i) {
-    const uint32_t cb = cost_at(a, i), ce = cost_at(a, i + 1);
-    if (hi <= cb) break;
+    if (hi <= cost_at(a, i)) break;
     Job job;
     DevMat m;
     fetch_job(a, i, job, m);
     uint32_t band_lo, band_hi;
-    share_of_bands(a, m, cb, ce, lo, hi, band_lo, band_hi);
+    share_of_bands(a, false, m, i, lo, hi, band_lo, band_hi);
     if (band_lo >= band_hi) continue;
     const uint32_t nq = m.n_quads;
     const uint32_t unit_lo = band_lo * nq, n_units = (band_hi - band_lo) * nq;
@@ -101,7 +100,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_decompress(MatvecArgs a) {
     const uint32_t u1 = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / n_waves);
     if (m.dict != staged) {
       __syncthreads();   // nobody reads the previous dictionary any more
-      stage_image<kThreads>(m, tid, lds4, n_threads);
+      stage_image(m, lane, wave, n_waves, lds4);
+      lds_arrived();
       staged = m.dict;
       __syncthreads();
     }

@@ -8,6 +8,7 @@
 
 #include "../../include/tq.h"
 #include "tq_format.h"
+#include "tq_plan.h"
 
 namespace tq {
 
@@ -95,6 +96,8 @@ struct MatvecArgs {
   uint32_t tile_area;         // bytes of LDS per wavefront in the tile kernels (the same for every matrix of the launch)
   uint16_t gate_up;           // 1: rows 2r and 2r + 1 are a gate and an up projection; y[b][r] = silu(row 2r) * (row 2r + 1)
   uint16_t by_workgroup;      // 1: the cost line counts workgroups (see share_of_bands)
+  uint32_t share, share_rest; // the cost line in even parts (even_part), one per workgroup; by_workgroup: share is the workgroups of a stage
+  float parts_inverse;
   const StepEntry* table;     // device table of the n jobs, or null: then j and first below hold them
   // A staged step (one launch for products that depend on each other): the jobs come in n_stages groups, jobs
   // stage_first[s] .. stage_first[s + 1] - 1 form stage s, and no workgroup starts a stage before every workgroup has
@@ -194,16 +197,36 @@ __device__ __forceinline__ DevMat load_description(const DevMat* p) {
 }
 
 // Point i of the launch's cost line (the two forms of the arguments keep it at the same place).
-__device__ __forceinline__ uint32_t cost_at(const MatvecArgs& a, int i) { return a.u.cost_long[i]; }
+__device__ __forceinline__ uint32_t cost_at(const MatvecArgs& a, int i) {
+  const uint32_t v = a.u.cost_long[i];
+  return a.by_workgroup ? v & kLineMask : v;
+}
+
+// A launch whose matrices have whole workgroups (kMaxAssign of them at most, one workgroup per compute unit) says in its arguments which
+// matrix a workgroup serves, a byte each, behind the cost line: no search.
+constexpr int kJobMapAt = kMaxAssign + 4, kJobMapWorkgroups = 256;   // (dwords of the cost line that such a launch does not use)
+static_assert(kJobMapAt + kJobMapWorkgroups / 4 <= kMaxMulti + 1 && kMaxAssign <= 256, "the map lies in the unused part of the shorter line");
+__device__ __forceinline__ int mapped_job(const MatvecArgs& a) {
+  return (int)(a.u.cost_long[kJobMapAt + blockIdx.x / 4] >> (blockIdx.x % 4 * 8) & 255u);
+}
+
+// The workgroup's part of a cost line that counts weights.
+__device__ __forceinline__ void even_share(const MatvecArgs& a, uint32_t& lo, uint32_t& hi) {
+  lo = even_part(a.share, a.share_rest, a.parts_inverse, blockIdx.x);
+  hi = even_part(a.share, a.share_rest, a.parts_inverse, blockIdx.x + 1);
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  hi = __builtin_amdgcn_readfirstlane(hi);
+}
 
 // The lines of the kernel arguments a launch of few matrices looks at - head and cost line, first job, first description -
 // requested together: taken as they are needed, each costs a round trip of its own (0.3 us) before the first load of
 // the matrix can start.
 __device__ __forceinline__ void touch_arguments() {
   const const_u32* k = (const const_u32*)__builtin_amdgcn_kernarg_segment_ptr();
-  constexpr size_t job = offsetof(MatvecArgs, u.in.j) / 4, desc = offsetof(MatvecArgs, u.in.first) / 4;
+  constexpr size_t line = offsetof(MatvecArgs, u.cost_long) / 4, job = offsetof(MatvecArgs, u.in.j) / 4, desc = offsetof(MatvecArgs, u.in.first) / 4;
   const uint32_t v0 = k[0], v1 = k[16], v2 = k[job], v3 = k[desc], v4 = k[desc + 16], v5 = k[desc + sizeof(DevMat) / 4 - 1];
-  asm volatile("" ::"s"(v0), "s"(v1), "s"(v2), "s"(v3), "s"(v4), "s"(v5));
+  const uint32_t v6 = k[line + kJobMapAt + (blockIdx.x & (kJobMapWorkgroups - 1)) / 4];
+  asm volatile("" ::"s"(v0), "s"(v1), "s"(v2), "s"(v3), "s"(v4), "s"(v5), "s"(v6));
 }
 
 // First job of [first, end) that ends behind point `lo` of the cost line.  A step has up to kMaxStep jobs: looking at
@@ -224,13 +247,16 @@ __device__ __forceinline__ int first_job(const MatvecArgs& a, int first, int end
 // The bands of matrix m, at [cb, ce) of the cost line, that belong to the share [lo, hi) of a workgroup.
 // Cost line in weights: a band goes to the share that holds its middle; a workgroup may get the end of one matrix and the
 // start of the next.  Cost line in workgroups (launches of few matrices, see assign_workgroups): [lo, hi) is one
-// workgroup, inside one matrix, which has its bands split evenly over its ce - cb workgroups.
-__device__ __forceinline__ void share_of_bands(const MatvecArgs& a, const DevMat& m, uint32_t cb, uint32_t ce, uint32_t lo, uint32_t hi,
+// workgroup, inside one matrix (job i), which has its bands split evenly over its ce - cb workgroups.
+__device__ __forceinline__ void share_of_bands(const MatvecArgs& a, bool by_workgroup, const DevMat& m, int i, uint32_t lo, uint32_t hi,
                                                uint32_t& band_lo, uint32_t& band_hi) {
-  if (a.by_workgroup) {
-    band_lo = (lo - cb) * m.n_bands / (ce - cb);
-    band_hi = (hi - cb) * m.n_bands / (ce - cb);
+  const uint32_t first = a.u.cost_long[i], next = a.u.cost_long[i + 1];
+  if (by_workgroup) {
+    const uint32_t cb = first & kLineMask, ce = next & kLineMask, bands = first >> kLineBits, rest = m.n_bands - bands * (ce - cb);
+    band_lo = workgroup_band(bands, rest, lo - cb);
+    band_hi = workgroup_band(bands, rest, hi - cb);
   } else {
+    const uint32_t cb = first, ce = next;
     const uint32_t bc = m.cols;
     band_lo = lo <= cb ? 0u : (lo - cb + bc / 2) / bc;
     band_hi = hi >= ce ? m.n_bands : min(m.n_bands, (hi - cb + bc / 2) / bc);
@@ -328,6 +354,34 @@ __device__ __forceinline__ void stage_end(const MatvecArgs& a) {
     if (__builtin_amdgcn_readfirstlane(before) == gridDim.x - 1)
       for (uint32_t i = threadIdx.x; i < sync_words(gridDim.x); i += 64) __hip_atomic_store(sync + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// n16 pieces of 16 bytes from global memory to LDS by the loads that write LDS themselves: no registers, no store instructions, and all of
+// a wavefront's requests on their way at once.  (120 KB into 8 wavefronts' workgroups on every compute unit, until the barrier: 1.05 us, through
+// registers 1.45; the 64 bytes a clock that a compute unit takes are 0.85.)  In round r wavefront `wave` of n_waves takes kilobyte r * n_waves + wave.  lds_arrived(),
+// then a barrier, before anyone reads.
+__device__ __forceinline__ void request_to_lds(const void* src, uint32_t n16, int lane, int wave, int n_waves, void* lds, uint32_t first_round = 0,
+                                               uint32_t end_round = 0x10000u) {
+  typedef __attribute__((address_space(1))) const uint32_t global_cu32;
+  typedef __attribute__((address_space(3))) uint32_t lds_mu32;
+  // (whole rounds without a look at the lanes, the address a uniform base plus the lane's offset: four scalar instructions a request)
+  const uint32_t step = (uint32_t)n_waves * 64, whole = min(n16 / 64, end_round * (uint32_t)n_waves);   // kilobytes that all lanes have
+  uint32_t c = first_round * (uint32_t)n_waves + (uint32_t)wave;
+  const uint64_t at = (uint64_t)src + (uint64_t)c * 1024;
+  const uint32_t at_lo = __builtin_amdgcn_readfirstlane((uint32_t)at), at_hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
+  uint64_t from = (uint64_t)at_hi << 32 | at_lo;
+  uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds + c * 1024);
+  for (; c < whole; c += (uint32_t)n_waves) {
+    __builtin_amdgcn_global_load_lds((global_cu32*)from + 4 * lane, (lds_mu32*)(size_t)to, 16, 0, 0);
+    from += step * 16;
+    to += step * 16;
+  }
+  if (c == n16 / 64 && c < end_round * (uint32_t)n_waves && (uint32_t)lane < n16 % 64)
+    __builtin_amdgcn_global_load_lds((global_cu32*)from + 4 * lane, (lds_mu32*)(size_t)to, 16, 0, 0);
+}
+__device__ __forceinline__ void lds_arrived() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) alone.  (The builtin, not inline assembly: the compiler sees that these loads are done)
+  asm volatile("" ::: "memory");
 }
 
 // Byte address inside LDS of a pointer into the workgroup's dynamic shared memory.

@@ -14,6 +14,38 @@
 
 namespace tq {
 
+// Where part k of `parts` begins on a line of `total` points, floor(total * k / parts), from share = total / parts, rest = total % parts
+// and parts_inverse = 1.f / parts: the host divides (a 64-bit division is a hundred instructions, and two of them stood ahead of the first load
+// of a wavefront).  Exact for parts and k up to kMaxParts: rest * k + .5 is a whole float and a half, and lies at least half a part's
+// share from the next whole number of parts.
+constexpr uint32_t kMaxParts = 1024;
+TQ_HD uint32_t even_part(uint32_t share, uint32_t rest, float parts_inverse, uint32_t k) {
+  return share * k + (uint32_t)(((float)(rest * k) + .5f) * parts_inverse);
+}
+
+// `bands` of them for every one of w workgroups, and one more for the first `rest`: the first band of workgroup k.
+TQ_HD uint32_t workgroup_band(uint32_t bands, uint32_t rest, uint32_t k) { return bands * k + (k < rest ? k : rest); }
+
+// len / parts for the few parts that a unit's chunks are cut into: units of 256 columns are 33 to 36 chunks long, in pieces of 6 to 12.
+TQ_HD uint32_t piece_length(uint32_t len, uint32_t parts) {
+  if (len >= 1u << 15) return len / parts;
+  switch (parts) {
+    case 1: return len;
+    case 2: return len >> 1;
+    case 3: return len * 43691u >> 17;
+    case 4: return len >> 2;
+    case 5: return len * 52429u >> 18;
+    default: return len / parts;
+  }
+}
+
+// A launch (or stage) whose matrices have whole workgroups keeps in one word per matrix where its workgroups start on the line of all of
+// them, and how many bands each of them has at least.
+constexpr int kLineBits = 18;   // a staged step's line: one workgroup per compute unit and stage, up to 896 * 256
+constexpr uint32_t kLineMask = (1u << kLineBits) - 1;
+constexpr uint32_t kMaxWorkgroupBands = 1u << (32 - kLineBits);
+TQ_HD uint32_t line_word(uint32_t start, uint32_t bands) { return bands << kLineBits | start; }
+
 // What a block of a listing stream writes: `tokens` tokens start in it, `base` start before it, token t stands for the values
 // [4 t, 4 t + 4) of n_values (the last one of the stream possibly for fewer).  The block's tokens sit in LDS from dword
 // base % 4 on, so that its output lies there as it lies in memory relative to 16-byte pieces.

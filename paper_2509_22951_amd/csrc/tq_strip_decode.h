@@ -141,7 +141,7 @@ __device__ __forceinline__ void decode_run_to_tile(const DevMat& m, uint32_t u0,
       }
       const uint32_t len = unit_offset(m, wu + 1) - wc;
       w_left = (len + kPiece - 1) / kPiece;
-      w_base = len / w_left;
+      w_base = piece_length(len, w_left);
       w_rem = len - w_base * w_left;
       ++wu;
     }
@@ -235,21 +235,9 @@ __device__ __forceinline__ uint4 mask_x_fragment(uint4 v, uint32_t cols, uint32_
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// The dictionary's byte image goes to LDS as it is.  kThreads: of the workgroup, or the most it may have (n_threads then says how
-// many it has); a full dictionary is one round of loads, two where a workgroup has half its threads (the tile kernels with wide segments).
-constexpr uint32_t kImageBytes = 61440;
-template <int kThreads>
-__device__ __forceinline__ void stage_image(const DevMat& m, int tid, uint4* lds_dict, int n_threads = kThreads) {
-  constexpr int kRegs = (kImageBytes / 16 + kThreads - 1) / kThreads;
-  const uint32_t n = m.dict16_bytes / 16;
-  for (uint32_t base = tid; base < n; base += kRegs * n_threads) {
-    uint4 v[kRegs];
-#pragma unroll
-    for (int k = 0; k < kRegs; ++k) v[k] = global_load((const uint4*)m.dict + min(base + k * n_threads, n - 1));
-#pragma unroll
-    for (int k = 0; k < kRegs; ++k)
-      if (base + k * n_threads < n) lds_dict[base + k * n_threads] = v[k];
-  }
+// The dictionary's byte image goes to LDS as it is; the caller's barrier follows.
+__device__ __forceinline__ void stage_image(const DevMat& m, int lane, int wave, int n_waves, uint4* lds_dict) {
+  request_to_lds(m.dict, m.dict16_bytes / 16, lane, wave, n_waves, lds_dict);
 }
 
 // The sums of the bands of a wavefront's run of units [u0, u1), as MFMA accumulators: register v of lane l is row

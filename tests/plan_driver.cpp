@@ -106,6 +106,38 @@ static void assign() {
   std::printf("%d cuts\n", n);
 }
 
+// The cuts that the kernels multiply out: parts of a cost line as the division gives them, bands of a workgroup in order and even, pieces of a
+// unit's chunks, and the word that holds a workgroup's place and its bands.
+static void cuts() {
+  uint64_t state = 88172645463325252ull;
+  auto rnd = [&](uint32_t n) {
+    state ^= state << 13, state ^= state >> 7, state ^= state << 17;
+    return (uint32_t)(state % n);
+  };
+  for (uint32_t parts = 1; parts <= tq::kMaxParts; ++parts)
+    for (uint32_t rest = 0; rest < parts; rest += parts < 300 ? 1 : 1 + rnd(7))
+      for (uint32_t k = 0; k <= parts; ++k) {
+        const uint64_t share = rnd(2) ? rnd(1000) : 0xFFFFFFFFull / parts - 1, total = share * parts + rest;
+        const uint32_t got = tq::even_part((uint32_t)share, rest, 1.f / (float)parts, k);
+        CHECK(got == total * k / parts, "part %u of %u, rest %u: %u", k, parts, rest, got);
+      }
+  for (int trial = 0; trial < 100000; ++trial) {
+    const uint32_t w = 1 + rnd(256), n = w + rnd(trial % 2 ? 50 : 1u << 21), bands = n / w;
+    uint32_t at = 0;
+    for (uint32_t k = 0; k < w; ++k) {
+      const uint32_t lo = tq::workgroup_band(bands, n - bands * w, k), hi = tq::workgroup_band(bands, n - bands * w, k + 1);
+      CHECK(lo == at && hi - lo >= bands && hi - lo <= bands + 1, "%u bands, workgroup %u of %u: %u..%u", n, k, w, lo, hi);
+      at = hi;
+    }
+    CHECK(at == n, "%u of %u bands", at, n);
+    const uint32_t start = rnd(tq::kLineMask + 1), few = rnd(tq::kMaxWorkgroupBands), word = tq::line_word(start, few);
+    CHECK((word & tq::kLineMask) == start && word >> tq::kLineBits == few, "%u, %u", start, few);
+  }
+  for (uint32_t parts = 1; parts <= 64; ++parts)
+    for (uint32_t len = parts; len < 70000; len += len < 40000 ? 1 : 97) CHECK(tq::piece_length(len, parts) == len / parts, "%u chunks in %u pieces", len, parts);
+  std::printf("cuts of lines, bands and units\n");
+}
+
 // k_matvec_runs' decode of one unit by its schedule, in both sizes of its rings, column numbers in place of bytes: a piece of a lane's ring holds the
 // columns it was stored with, and every group a look multiplies has to hold the lane's own columns of the run in their places
 // and zeros (number 0) elsewhere.
@@ -307,6 +339,7 @@ int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
   else if (!std::strcmp(what, "assign")) assign();
+  else if (!std::strcmp(what, "cuts")) cuts();
   else if (!std::strcmp(what, "ring")) ring();
   else return 2;
   return 0;

@@ -36,6 +36,11 @@ def test_whole_workgroups_per_matrix_for_every_width(driver):
     assert "cuts" in driver("assign")
 
 
+def test_cuts_that_the_kernels_multiply_out(driver):
+    """Parts of a cost line, bands of a workgroup, pieces of a unit: what the divisions they stand for give."""
+    assert "cuts of lines" in driver("cuts")
+
+
 def test_ring_decode_at_the_distances_it_takes(driver):
     """Lanes exactly as far apart as rings of 128 and of 64 bytes allow, also in segments that end inside a piece."""
     out = driver("ring")
