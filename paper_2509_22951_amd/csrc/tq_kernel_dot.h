@@ -364,6 +364,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   // two rows, 2 units 9.7 / 12.2, 3 units 11.7 / 11.5; packed, 12 wavefronts, 3 units 10.3 / 11.2, 4 units 11.1 / 10.6.)
   constexpr bool kSplit = !kLong && !(kPacked && kB == 2);   // (two rows of packed weights leave no LDS for the counts)
   constexpr int kCount = 12;   // chunks per round of that count
+  // Packed weights are bound by issue and the LDS pipe and gain most from wavefronts that end together (see pace; us, eight LLaMA-3.2-3B layers 87 -> 83,
+  // one 17.7 -> 16.0, batch 2 104 -> 98, four in 16 stages 171 -> 164); plain ones in large launches 1 % (eight layers 154 -> 153, staged at
+  // batch 2 221 -> 218), where a workgroup serves one matrix they lose as much (a 1B layer 17.2 -> 17.5, a 3B layer batch 2 26.1 -> 26.8).
+  constexpr bool kPaced = kPacked || (!kOne && (kB == 2 || !kStaged));
   constexpr int kThreads = kWaves * 64, kXRegs = 64 / kWaves;
   if constexpr (!kStaged) touch_arguments();
   extern __shared__ uint4 lds4[];
@@ -827,13 +831,16 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
           }
         };
         while (na) {
+          if constexpr (kPaced) pace(sa - c0, c_end - c0);
           next_piece(m, sb, nb, eb);
           load_piece(m, cwb, sb, nb);
           run_piece(cwa, na, ea);
+          if constexpr (kPaced) pace(sb - c0, c_end - c0);
           next_piece(m, sa, na, ea);
           load_piece(m, cwa, sa, na);
           run_piece(cwb, nb, eb);
         }
+        if constexpr (kPaced) __builtin_amdgcn_s_setprio(0);
         if (u1 % nq || tail_shared) finish_band(false);   // the run ends inside a band (a band that ends with the run was finished above)
       }
       planned = kStaged && next_lo < next_hi;

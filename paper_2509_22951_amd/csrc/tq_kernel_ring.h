@@ -224,6 +224,9 @@ template <int kWaves, int kRows, bool kPacked, bool kGateUp = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
   constexpr int kRing = kSmallRingBytes, kRingThreads = kWaves * 64, kGateUpBands = (32 + kWaves - 1) / kWaves;
   constexpr uint32_t kRingXTile = ring_x_tile(kRows);
+  // A wavefront's bands are fixed then, and the others wait for it at the end of the quad (us, packed gated pairs of eight LLaMA-3.2-3B blocks:
+  // batch 8 76.9 -> 75.3, batch 16 79.7 -> 78.0; with one weight per byte nothing).
+  constexpr bool kPaced = kGateUp && kPacked;
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t rings = a.x_off, xtile = a.slot_off;   // LDS addresses (the LDS segment starts at 0)
@@ -323,6 +326,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
             for (int k = 0; k < kGateUpBands; ++k)   // (a sum of selected values: indexed, the array would go to memory)
 #pragma unroll
               for (int v = 0; v < 4; ++v) acc[k][v] += mine == (uint32_t)k ? sums[v] : 0.f;
+            if constexpr (kPaced) {   // a level for every band done
+              if (mine == 0) __builtin_amdgcn_s_setprio(2);
+              else if (mine == 1) __builtin_amdgcn_s_setprio(1);
+              else __builtin_amdgcn_s_setprio(0);
+            }
             return;
           }
 #pragma unroll
@@ -336,7 +344,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
           }
           request_scales(next_band);
         };
+        if constexpr (kPaced) __builtin_amdgcn_s_setprio(3);
         decode_units_ring<kRows, kPacked>(m, q, band0, claim, lane, ring, xfrag, finish_unit);
+        if constexpr (kPaced) __builtin_amdgcn_s_setprio(0);
       }
       if constexpr (kGateUp) {
 #pragma unroll

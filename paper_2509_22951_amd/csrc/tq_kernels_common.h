@@ -425,6 +425,16 @@ __device__ __forceinline__ EvenRun even_run(uint32_t uoff_lane, uint32_t unit_lo
   return r;
 }
 
+// Of the wavefronts of a SIMD that could go on the oldest is served, so that the first is done with its run when the last has a third of its own
+// left, and works alone from then on.  A wavefront that has come further than half its run, three quarters, seven eighths takes a
+// lower priority than those that have not: they end together.
+__device__ __forceinline__ void pace(uint32_t done, uint32_t total) {
+  if (2 * done < total) __builtin_amdgcn_s_setprio(3);
+  else if (4 * done < 3 * total) __builtin_amdgcn_s_setprio(2);
+  else if (8 * done < 7 * total) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
 // Pointer forms on purpose: the compiler tracks the outstanding LDS read and places the wait before the first use.
 __device__ __forceinline__ uint32_t lds_read32(uint32_t addr) { return *(lds_cu32*)(size_t)addr; }
 template <int kOff>

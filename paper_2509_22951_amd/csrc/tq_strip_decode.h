@@ -198,14 +198,18 @@ __device__ __forceinline__ void decode_run_to_tile(const DevMat& m, uint32_t u0,
   bool ea, eb;
   next_piece(sa, na, ea);
   load_piece(cwa, sa, na);
-  while (na) {
+  const uint32_t run_first = sa, run_n = run_last + 1 - run_first;
+  while (na) {   // (paced, us: four LLaMA-3.2-3B layers expanded 185.9 -> 181.5, a layer of 2048 and 5632 35.8 -> 33.4)
+    pace(sa - run_first, run_n);
     next_piece(sb, nb, eb);
     load_piece(cwb, sb, nb);
     decode_piece(cwa, na, ea);
+    pace(sb - run_first, run_n);
     next_piece(sa, na, ea);
     load_piece(cwa, sa, na);
     decode_piece(cwb, nb, eb);
   }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 typedef __attribute__((address_space(1))) const uint16_t global_cu16;
