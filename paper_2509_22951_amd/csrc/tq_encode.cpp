@@ -4,11 +4,16 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
+
+#include <sys/mman.h>
 
 #include "../../include/tq.h"
 #include "tq_format.h"
@@ -26,21 +31,83 @@ unsigned pick_threads(uint32_t asked) {
   return std::max(1u, std::min(n, 16u));
 }
 
-template <typename F>
-void parallel_for(uint64_t n, unsigned n_threads, F&& body) {  // body(begin, end, thread_index)
-  n_threads = (unsigned)std::min<uint64_t>(n_threads, std::max<uint64_t>(n, 1));
-  if (n_threads <= 1) {
-    body(0, n, 0);
-    return;
+// The threads of one call, started once: the caller is number 0, the others wait between the phases of its work, first for a few
+// microseconds by looking, then asleep.  (Started anew for each of three phases, 16 threads cost 0.6 of the 2.1 ms that a 2048 x 2048 matrix
+// takes.)  Where one cannot be started the constructor throws, and those that run are waited for.
+class Crew {
+ public:
+  explicit Crew(unsigned n) : n_(std::max(1u, n)) {
+    try {
+      for (unsigned t = 1; t < n_; ++t) threads_.start([this, t] { work(t); });
+    } catch (...) {
+      finish();
+      throw;
+    }
   }
-  Threads th;
-  uint64_t per = (n + n_threads - 1) / n_threads;
-  for (unsigned t = 0; t < n_threads; ++t) {
-    uint64_t b = std::min<uint64_t>(n, t * per), e = std::min<uint64_t>(n, b + per);
-    th.start([=, &body] { body(b, e, t); });
+  ~Crew() { finish(); }
+  unsigned size() const { return n_; }
+  // body(t) on every thread but the caller's, which goes on; until wait() has returned, body and what it refers to stay as they are.
+  void start(std::function<void(unsigned)> body) {
+    body_ = std::move(body);
+    left_.store(n_ - 1, std::memory_order_relaxed);
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      phase_.fetch_add(1, std::memory_order_release);
+    }
+    wake_.notify_all();
   }
-  th.join();
-}
+  void wait() {
+    for (unsigned looks = 0; left_.load(std::memory_order_acquire); ++looks)
+      if (looks > kLooks) std::this_thread::yield();
+  }
+  // body(t) on every thread, the caller's among them
+  void run(const std::function<void(unsigned)>& body) {
+    start(body);
+    const Waits all(*this);
+    body(0);
+  }
+  // Waits for the others where its block ends, whatever way that is left.
+  class Waits {
+   public:
+    explicit Waits(Crew& crew) : crew_(crew) {}
+    ~Waits() { crew_.wait(); }
+
+   private:
+    Crew& crew_;
+  };
+
+ private:
+  static constexpr unsigned kLooks = 4000;
+  void work(unsigned t) {
+    for (unsigned seen = 0;;) {
+      for (unsigned looks = 0; looks < kLooks && phase_.load(std::memory_order_acquire) == seen; ++looks) {}
+      if (phase_.load(std::memory_order_acquire) == seen) {
+        std::unique_lock<std::mutex> lock(mutex_);
+        wake_.wait(lock, [&] { return phase_.load(std::memory_order_acquire) != seen; });
+      }
+      ++seen;
+      if (stop_.load(std::memory_order_relaxed)) return;
+      body_(t);
+      left_.fetch_sub(1, std::memory_order_release);
+    }
+  }
+  void finish() {
+    stop_.store(true, std::memory_order_relaxed);
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      phase_.fetch_add(1, std::memory_order_release);
+    }
+    wake_.notify_all();
+    threads_.join();
+  }
+  const unsigned n_;
+  std::function<void(unsigned)> body_;
+  std::atomic<unsigned> phase_{0}, left_{0};
+  std::atomic<bool> stop_{false};
+  std::mutex mutex_;
+  std::condition_variable wake_;
+  Threads threads_;   // (last: the others are there before the first thread looks at them)
+};
 
 // Dictionary of runs of up to 4 bytes, in the order LZW creates them (the container's code space is that order sorted by
 // run length: final_codes()).  Codes 0..255 are the single bytes; a two-byte run is found through a direct table over
@@ -152,7 +219,8 @@ class RunDict {
     return t;
   }
 
-  // parse<true> for runs of at most 2 (lmax 2), with `pairs` kept as pair_table() would give it.
+  // parse<true> for runs of at most 2 (lmax 2), with `pairs` kept as pair_table() would give it (pair_, which only longer runs and an
+  // inherited dictionary are looked up in, is left as it is).
   uint32_t parse_growing_pairs(const uint8_t* p, uint32_t len, uint16_t* pairs, uint16_t* out) {
     uint32_t i = 0, n = 0;
     while (i + 1 < len) {
@@ -165,9 +233,10 @@ class RunDict {
         continue;
       }
       out[n++] = p[i];
-      if (!full()) {
+      if (size() < max_) {
         pairs[key] = (uint16_t)size();
-        add(p[i], p[i + 1]);
+        bytes_.push_back(key);
+        len_.push_back(2);
       }
       ++i;
     }
@@ -248,17 +317,48 @@ struct UnitRange {
   std::vector<uint16_t> cnt;
 };
 
+// Room for the codes of all units while their number is not known: for as many as there are bytes.  In large pages, each the size of 512 ordinary
+// ones whose first writes would come from all threads at once (2048 x 2048: 0.5 of 1.75 ms), up to 64 MB; beyond that in ordinary ones, of
+// which those that are not written cost nothing.
+class CodeRoom {
+ public:
+  explicit CodeRoom(size_t words) {
+    constexpr size_t kLarge = 2u << 20, kMost = 64u << 20;
+    const size_t bytes = std::max<size_t>(words * 2, 2), whole = (size_t)round_up(bytes, kLarge);
+    if (bytes < 2 * kLarge || whole > kMost) {
+      p_ = (uint16_t*)std::malloc(bytes);
+    } else if ((p_ = (uint16_t*)std::aligned_alloc(kLarge, whole))) {
+      (void)madvise(p_, whole, MADV_HUGEPAGE);   // (a wish: without it the pages are ordinary ones)
+    }
+    if (!p_) throw std::bad_alloc();
+    next_ = p_;
+  }
+  CodeRoom(const CodeRoom&) = delete;
+  CodeRoom& operator=(const CodeRoom&) = delete;
+  ~CodeRoom() { std::free(p_); }
+  uint16_t* take(size_t words) {
+    uint16_t* p = next_;
+    next_ += words;
+    return p;
+  }
+
+ private:
+  uint16_t *p_ = nullptr, *next_ = nullptr;
+};
+
 // The code section of a contiguous range of units, in the container's layout (the offsets follow when all ranges are known).
 struct CodedRange {
   uint64_t u_begin = 0, u_end = 0, n_real = 0;
-  std::unique_ptr<uint16_t[]> words;   // not initialised: a page that is not written costs nothing
+  uint16_t* words = nullptr;
   size_t used = 0;                     // words
   std::vector<uint32_t> chunks;        // per unit
-  // longest: of the segments' lengths (a matrix narrower than its segments would otherwise ask for many times its size)
-  void start(uint64_t begin, uint64_t end, uint32_t longest) {
+  // Words that n_units may need.  longest: of the segments' lengths (a matrix narrower than its segments would otherwise ask for many
+  // times its size)
+  static size_t most_words(uint64_t n_units, uint32_t longest) { return (size_t)n_units * 64 * ((longest + kChunkCodes - 1) / kChunkCodes * kChunkCodes); }
+  void start(uint64_t begin, uint64_t end, uint32_t longest, CodeRoom& room) {
     u_begin = begin;
     u_end = end;
-    words.reset(new uint16_t[(size_t)(end - begin) * 64 * ((longest + kChunkCodes - 1) / kChunkCodes * kChunkCodes)]);
+    words = room.take(most_words(end - begin, longest));
     chunks.reserve(end - begin);
   }
   // lane l's codes at lanes + l * kMaxSegCols (room to pad them to whole chunks of the longest)
@@ -269,7 +369,7 @@ struct CodedRange {
       n_real += cnt[l];
     }
     const uint32_t n = (mx + kChunkCodes - 1) / kChunkCodes;
-    uint16_t* to = words.get() + used;
+    uint16_t* to = words + used;
     for (uint32_t l = 0; l < 64; ++l) {
       uint16_t* src = lanes + (size_t)l * kMaxSegCols;
       std::fill(src + cnt[l], src + n * kChunkCodes, pad);
@@ -360,9 +460,41 @@ bool pack_nibbles(const uint8_t* Q, uint32_t rows, uint32_t cols, std::vector<ui
   return true;
 }
 
-// Q: the byte matrix rows x cols that is coded (for packing 1 the packed one).
+// The bands of the matrix that is coded, where they are made while the dictionary already grows over the first of them.
+class Bands {
+ public:
+  // make(band): the rows of a band, by any thread
+  Bands(uint32_t n, std::function<void(uint32_t)> make) : n_(n), make_(std::move(make)), made_(new std::atomic<bool>[n]) {
+    for (uint32_t b = 0; b < n; ++b) made_[b].store(false, std::memory_order_relaxed);
+  }
+  void make_all() {
+    while (make_next()) {}
+  }
+  void wait_for(uint32_t band) {
+    while (!made_[band].load(std::memory_order_acquire))
+      if (!make_next()) std::this_thread::yield();
+  }
+
+ private:
+  bool make_next() {
+    const uint32_t b = next_.fetch_add(1, std::memory_order_relaxed);
+    if (b >= n_) return false;
+    make_(b);
+    made_[b].store(true, std::memory_order_release);
+    return true;
+  }
+  const uint32_t n_;
+  std::function<void(uint32_t)> make_;
+  std::unique_ptr<std::atomic<bool>[]> made_;
+  std::atomic<uint32_t> next_{0};
+};
+
+// The threads that are worth starting for a matrix: no more than it has bands.
+unsigned crew_size(unsigned n_threads, uint32_t rows) { return std::min<unsigned>(n_threads, (rows + kUnitRows - 1) / kUnitRows); }
+
+// Q: the byte matrix rows x cols that is coded (for packing 1 the packed one).  bands: null, or the crew's other threads are making its bands.
 int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_pad, uint32_t rows, uint32_t cols,
-                            const tq_encode_opts* opts, void** blob_out, size_t* bytes_out) {
+                            const tq_encode_opts* opts, Crew& crew, Bands* bands, void** blob_out, size_t* bytes_out) {
   uint32_t max_entries, lmax, seg_cols;
   unsigned n_threads;
   if (int rc = check_opts(opts, &max_entries, &lmax, &seg_cols, &n_threads)) return rc;
@@ -400,14 +532,19 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
       return TQ_E_INVALID_ARG;
     }
   }
-  auto segment_start = [&](uint64_t u, uint32_t lane) {
-    const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
+  auto segment_start = [&](uint32_t band, uint32_t quad, uint32_t lane) {
     return (uint64_t)(band * kUnitRows + (lane & 15)) * cols + (uint64_t)(quad * kUnitPanels + (lane >> 4)) * seg_cols;
   };
-  auto segment_length = [&](uint64_t u, uint32_t lane) { return segment_len(h, (uint32_t)(u / h.n_quads), (uint32_t)(u % h.n_quads), lane); };
+  auto all_bands = [&] {   // everything is quantized
+    if (!bands) return;
+    bands->make_all();
+    crew.wait();
+    bands = nullptr;
+  };
 
   const bool by_frequency = opts && opts->dictionary == TQ_DICT_FREQUENCY;
   if (by_frequency && !(opts && opts->dict_from) && lmax >= 2 && max_entries > 256) {
+    all_bands();
     // The most frequent pairs of neighbouring bytes, counted at every offset inside a segment, segments in the order
     // they are parsed in; ties go to the pair seen first.
     std::vector<uint64_t> count(65536, 0), first(65536, 0);
@@ -438,16 +575,20 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   std::vector<uint16_t> pairs = lmax <= 2 ? dict.pair_table() : std::vector<uint16_t>();
   uint16_t segment[kMaxSegCols];
   uint64_t u = 0;
-  for (; !by_frequency && u < n_units && !dict.full(); ++u)
+  for (; !by_frequency && u < n_units && !dict.full(); ++u) {
+    const uint32_t band = (uint32_t)(u / h.n_quads), quad = (uint32_t)(u % h.n_quads);
+    if (bands) bands->wait_for(band);
     for (uint32_t lane = 0; lane < 64; ++lane) {
       const size_t before = grown.codes.size();
-      if (const uint32_t len = segment_length(u, lane)) {
-        const uint64_t start = segment_start(u, lane);
+      if (const uint32_t len = segment_len(h, band, quad, lane)) {
+        const uint64_t start = segment_start(band, quad, lane);
         if (lmax == 2) grown.codes.insert(grown.codes.end(), segment, segment + dict.parse_growing_pairs(Q + start, len, pairs.data(), segment));
         else dict.parse<true>(Q, start, start + len, grown.codes);
       }
       grown.cnt.push_back((uint16_t)(grown.codes.size() - before));
     }
+  }
+  all_bands();
   const uint64_t u_frozen = u;
   const uint32_t n_entries = dict.size();
   const uint16_t pad = (uint16_t)n_entries;
@@ -458,17 +599,21 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   dict.final_codes(&final_of, &words, h.class_end);
 
   // Phase 2 (parallel): the dictionary no longer changes, units are independent.
+  n_threads = crew.size();
+  const uint32_t longest = std::min(seg_cols, cols);
+  CodeRoom room(CodedRange::most_words(n_units, longest));
   std::vector<CodedRange> ranges(1 + n_threads);
   {
     auto code_unit = [&](uint64_t uu, uint16_t* lanes, std::vector<uint16_t>& buffer, CodedRange& r) {
       uint32_t cnt[64];
+      const uint32_t band = (uint32_t)(uu / h.n_quads), quad = (uint32_t)(uu % h.n_quads);
       for (uint32_t lane = 0; lane < 64; lane += 4) {
         const uint8_t* p[4];
         uint16_t* out[4];
         uint32_t len[4], n[4];
         for (uint32_t k = 0; k < 4; ++k) {
-          len[k] = segment_length(uu, lane + k);
-          p[k] = Q + (len[k] ? segment_start(uu, lane + k) : 0);
+          len[k] = segment_len(h, band, quad, lane + k);
+          p[k] = Q + (len[k] ? segment_start(band, quad, lane + k) : 0);
           out[k] = lanes + (size_t)(lane + k) * kMaxSegCols;
         }
         if (lmax <= 2 && len[0] && len[0] == len[1] && len[1] == len[2] && len[2] == len[3]) {
@@ -489,36 +634,40 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
       }
       r.add_unit(lanes, cnt, pad);
     };
-    const uint64_t rest = n_units - u_frozen, per = (rest + n_threads - 1) / std::max(1u, n_threads);
+    // Laying out a unit that is parsed already is about a third of the work of another: the caller's share is smaller by that.
+    const uint64_t rest = n_units - u_frozen, done = u_frozen / 3, all = rest + done;
+    auto range_start = [&](unsigned t) { return t == 0 ? 0 : std::min(rest, std::max(all * t / n_threads, done) - done); };   // of thread t, behind u_frozen
     // (what can fail for want of memory is taken here: nothing throws inside the threads but the long-run buffer's growth)
     const size_t lane_words = (size_t)64 * kMaxSegCols;
     std::unique_ptr<uint16_t[]> lanes(new uint16_t[lane_words * (1 + n_threads)]);
     std::vector<std::vector<uint16_t>> buffers(1 + n_threads);
-    const uint32_t longest = std::min(seg_cols, cols);
-    ranges[0].start(0, u_frozen, longest);
+    ranges[0].start(0, u_frozen, longest, room);
     for (unsigned t = 0; t < n_threads; ++t) {
-      const uint64_t b = std::min<uint64_t>(n_units, u_frozen + t * per), e = std::min<uint64_t>(n_units, b + per);
-      ranges[1 + t].start(b, e, longest);
+      const uint64_t b = u_frozen + range_start(t), e = t + 1 == n_threads ? n_units : u_frozen + range_start(t + 1);
+      ranges[1 + t].start(b, e, longest, room);
       if (lmax > 2) buffers[1 + t].reserve(kMaxSegCols);
     }
-    Threads th;
-    for (unsigned t = 0; t < n_threads; ++t)
-      if (ranges[1 + t].u_begin < ranges[1 + t].u_end) th.start([&, t] {
-        CodedRange& r = ranges[1 + t];
-        for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) code_unit(uu, lanes.get() + lane_words * (1 + t), buffers[1 + t], r);
-      });
-    const uint16_t* src = grown.codes.data();
-    for (uint64_t uu = 0; uu < u_frozen; ++uu) {   // the units parsed above
-      uint32_t cnt[64];
-      for (uint32_t l = 0; l < 64; ++l) {
-        cnt[l] = grown.cnt[uu * 64 + l];
-        uint16_t* out = lanes.get() + (size_t)l * kMaxSegCols;
-        for (uint32_t k = 0; k < cnt[l]; ++k) out[k] = final_of[src[k]];
-        src += cnt[l];
+    // (range t + 1 is thread t's; the caller begins with the units parsed above)
+    auto code_range = [&](unsigned t) {
+      CodedRange& r = ranges[1 + t];
+      for (uint64_t uu = r.u_begin; uu < r.u_end; ++uu) code_unit(uu, lanes.get() + lane_words * (1 + t), buffers[1 + t], r);
+    };
+    crew.run([&](unsigned t) {
+      if (t == 0) {
+        const uint16_t* src = grown.codes.data();
+        for (uint64_t uu = 0; uu < u_frozen; ++uu) {
+          uint32_t cnt[64];
+          for (uint32_t l = 0; l < 64; ++l) {
+            cnt[l] = grown.cnt[uu * 64 + l];
+            uint16_t* out = lanes.get() + (size_t)l * kMaxSegCols;
+            for (uint32_t k = 0; k < cnt[l]; ++k) out[k] = final_of[src[k]];
+            src += cnt[l];
+          }
+          ranges[0].add_unit(lanes.get(), cnt, pad);
+        }
       }
-      ranges[0].add_unit(lanes.get(), cnt, pad);
-    }
-    th.join();
+      code_range(t);
+    });
   }
 
   // Unit offsets in chunks: a unit is its longest lane stream, rounded up to whole chunks.
@@ -570,12 +719,12 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   {
     uint16_t* codes = (uint16_t*)(blob + h.off_codes);
     auto copy = [&](const CodedRange& r) {
-      if (r.u_begin < r.u_end) std::memcpy(codes + (uint64_t)uoff[r.u_begin] * kChunkWords, r.words.get(), r.used * 2);
+      if (r.u_begin < r.u_end) std::memcpy(codes + (uint64_t)uoff[r.u_begin] * kChunkWords, r.words, r.used * 2);
     };
-    Threads th;
-    for (size_t i = 1; i < ranges.size(); ++i)
-      if (ranges[i].u_begin < ranges[i].u_end) th.start([&, i] { copy(ranges[i]); });
-    copy(ranges[0]);
+    crew.run([&](unsigned t) {
+      if (t == 0) copy(ranges[0]);
+      copy(ranges[1 + t]);
+    });
   }
   *blob_out = owned.release();
   *bytes_out = (size_t)h.total_bytes;
@@ -594,9 +743,7 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
       set_error("tq_encode: null pointer or empty matrix");
       return TQ_E_INVALID_ARG;
     }
-    const unsigned nt = pick_threads(opts ? opts->n_threads : 0);
     const uint32_t rows_pad = (uint32_t)round_up(rows, kUnitRows);
-    std::unique_ptr<uint8_t[]> Q(new uint8_t[(size_t)rows * cols]);
     std::vector<float> scales(rows_pad, 0.f);
     // Per row (quantize_row), with qmax = 2^(bits - 1) - 1 (paper section 3: a fixed range of levels set by the number of
     // bits; 127 at 8 bits).
@@ -609,16 +756,26 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
       set_error("tq_encode: TQ_PACK_NIBBLES takes bits 2..4");
       return TQ_E_INVALID_ARG;
     }
-    const float qmax = (float)((1u << ((opts && opts->bits ? opts->bits : 8u) - 1)) - 1u);
-    parallel_for(rows, nt, [&](uint64_t rb, uint64_t re, unsigned) {
-      for (uint64_t r = rb; r < re; ++r) scales[r] = quantize_row(w + r * cols, cols, qmax, Q.get() + r * cols);
-    });
-    if (packed) {
-      std::vector<uint8_t> P;
-      if (!pack_nibbles(Q.get(), rows, cols, &P)) return TQ_E_INVALID_ARG;
-      return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, blob, blob_bytes);
+    if (packed && cols % 2) {
+      set_error("tq_encode: packing needs an even number of columns");
+      return TQ_E_INVALID_ARG;
     }
-    return encode_quantized_matrix(Q.get(), scales, rows, cols, opts, blob, blob_bytes);
+    const float qmax = (float)((1u << ((opts && opts->bits ? opts->bits : 8u) - 1)) - 1u);
+    const uint32_t width = packed ? cols / 2 : cols;   // stored bytes of a row
+    std::unique_ptr<uint8_t[]> Q(new uint8_t[(size_t)rows * width]);
+    Crew crew(crew_size(pick_threads(opts ? opts->n_threads : 0), rows));
+    std::unique_ptr<uint8_t[]> unpacked(packed ? new uint8_t[(size_t)rows * cols] : nullptr);
+    Bands bands(rows_pad / kUnitRows, [&](uint32_t band) {
+      for (uint32_t r = band * kUnitRows; r < std::min(rows, (band + 1) * kUnitRows); ++r) {
+        uint8_t* q = packed ? unpacked.get() + (size_t)r * cols : Q.get() + (size_t)r * cols;
+        scales[r] = quantize_row(w + (size_t)r * cols, cols, qmax, q);
+        if (packed)   // (the quantizer's values fit: qmax is at most 7)
+          for (uint32_t c = 0; c < width; ++c) Q[(size_t)r * width + c] = (uint8_t)((q[2 * c] & 15) | (q[2 * c + 1] & 15) << 4);
+      }
+    });
+    const Crew::Waits all(crew);   // (the bands and what they are made of stay until no thread is at them)
+    crew.start([&](unsigned) { bands.make_all(); });
+    return encode_quantized_matrix(Q.get(), scales, rows, width, opts, crew, &bands, blob, blob_bytes);
   } catch (const std::bad_alloc&) {
     set_error("tq_encode: out of host memory");
     return TQ_E_OOM;
@@ -642,9 +799,11 @@ extern "C" int tq_encode_quantized(const int8_t* q, const float* scales_in, uint
     if (opts && opts->packing == TQ_PACK_NIBBLES) {
       std::vector<uint8_t> P;
       if (!pack_nibbles(Q, rows, cols, &P)) return TQ_E_INVALID_ARG;
-      return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, blob, blob_bytes);
+      Crew crew(crew_size(pick_threads(opts->n_threads), rows));
+      return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, crew, nullptr, blob, blob_bytes);
     }
-    return encode_quantized_matrix(Q, scales, rows, cols, opts, blob, blob_bytes);
+    Crew crew(crew_size(pick_threads(opts ? opts->n_threads : 0), rows));
+    return encode_quantized_matrix(Q, scales, rows, cols, opts, crew, nullptr, blob, blob_bytes);
   } catch (const std::bad_alloc&) {
     set_error("tq_encode_quantized: out of host memory");
     return TQ_E_OOM;
