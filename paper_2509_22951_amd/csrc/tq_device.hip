@@ -57,6 +57,26 @@ static __device__ __align__(256) unsigned char scratch[kStaticTableBytes];
 
 namespace {
 
+// The marks of a matrix's units (see mark_index), from its codes as the kernels read them.  A wavefront per unit.
+template <typename T>
+__global__ __launch_bounds__(256) void k_mark_units(const uint2* codes, const uint32_t* uoff, T* marks, uint32_t n_units) {
+  const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (uint32_t u = blockIdx.x * 4 + wave; u < n_units; u += gridDim.x * 4) {
+    const uint32_t begin = ((const_u32*)uoff)[u], end = ((const_u32*)uoff)[u + 1];
+    T* mark = marks + mark_index(u, begin) * 64 + lane;
+    u16x2 pairs = {0, 0};
+    for (uint32_t from = begin; from + kMarkChunks < end; from += kMarkChunks) {   // (a mark at the unit's end is no place to start)
+#pragma unroll
+      for (uint32_t k = 0; k < kMarkChunks; ++k) {
+        const uint2 c = load_chunk(codes, from + k, (int)lane);
+        pairs = count_pairs(count_pairs(pairs, c.x), c.y);
+      }
+      mark += 64;
+      *mark = (T)(pairs.x + pairs.y);
+    }
+  }
+}
+
 // What the table writer needs per job: where the matrix description lives in device memory, and the buffers.
 struct JobRef {
   const DevMat* m;
@@ -228,11 +248,10 @@ hipError_t release_dictionary(DictCopy* d) {
 }
 
 constexpr uint32_t kSlotBytes = 2 * kDotWavesMax * 2 * 16 * 4 + 2 * kDotWavesMax * 4;   // (two activation rows at most)
-// slots, their band numbers and, but for two rows of packed weights, the column counts of units shared between wavefronts
-constexpr uint32_t dot_slot_bytes(int waves, int rows, bool counts) { return 2 * waves * rows * 16 * 4 + 2 * waves * 4 + (counts ? waves * 64 * 2 : 0); }
-static_assert(dot_slot_bytes(kDotWaves, 1, true) <= kSlotBytes && dot_slot_bytes(kDotWaves, 2, true) <= kSlotBytes &&
-              dot_slot_bytes(kDotWavesStaged, 2, true) <= kSlotBytes && dot_slot_bytes(kDotWavesPacked, 1, true) <= kSlotBytes &&
-              dot_slot_bytes(kDotWavesPacked, 2, false) <= kSlotBytes, "LDS behind the activation image");
+// slots and their band numbers
+constexpr uint32_t dot_slot_bytes(int waves, int rows) { return 2 * waves * rows * 16 * 4 + 2 * waves * 4; }
+static_assert(dot_slot_bytes(kDotWaves, 2) <= kSlotBytes && dot_slot_bytes(kDotWavesStaged, 2) <= kSlotBytes &&
+              dot_slot_bytes(kDotWavesPacked, 2) <= kSlotBytes, "LDS behind the activation image");
 
 // LDS plan of the product kernel for a set of matrices: dictionary | activation image | partial-sum slots.
 bool plan_matvec_lds(uint32_t dict_words_max, uint32_t x_dwords_max, uint32_t* x_off, uint32_t* slot_off, size_t* total) {
@@ -447,7 +466,8 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   if (long_runs) m.dict_words = dict->dict_words_bf16;
   m.dict16_bytes = dict->image_bytes;
 
-  const uint64_t sz_uoff = round_up(h.uoff_bytes, kSectionAlign), sz_codes = round_up(h.code_bytes, kSectionAlign),
+  const uint64_t n_units = (uint64_t)h.n_bands * h.n_quads;
+  const uint64_t sz_uoff = round_up(marks_at(n_units) + (long_runs ? 0 : marks_size(n_units, h.n_chunks, h.seg_cols)), kSectionAlign), sz_codes = round_up(h.code_bytes, kSectionAlign),
                  sz_scales = round_up(h.scale_bytes, kSectionAlign);
   const uint64_t o_uoff = 0, o_codes = o_uoff + sz_uoff, o_scales = o_codes + sz_codes, o_desc = o_scales + sz_scales,
                  total = o_desc + round_up(sizeof(DevMat), kSectionAlign);
@@ -478,6 +498,15 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
     const uint64_t n16 = h.code_bytes / 16;
     hipLaunchKernelGGL(k_replace_pads, dim3((unsigned)std::min<uint64_t>((n16 + 255) / 256, 4096)), dim3(256), 0, nullptr, (uint4*)(base + o_codes), n16, h.pad_code);
     e = hipGetLastError();
+    if (e == hipSuccess) {
+      const dim3 grid((unsigned)std::min<uint64_t>((n_units + 3) / 4, 16384)), block(256);
+      const uint2* codes = (const uint2*)(base + o_codes);
+      const uint32_t* uoff = (const uint32_t*)(base + o_uoff);
+      uint8_t* marks = base + o_uoff + marks_at(n_units);
+      if (h.seg_cols <= kMarkByteCols) hipLaunchKernelGGL(k_mark_units<uint8_t>, grid, block, 0, nullptr, codes, uoff, marks, (uint32_t)n_units);
+      else hipLaunchKernelGGL(k_mark_units<uint16_t>, grid, block, 0, nullptr, codes, uoff, (uint16_t*)marks, (uint32_t)n_units);
+      e = hipGetLastError();
+    }
   }
   m.dict = dict->dev;
   m.dict_bf16 = dict->dev_bf16;
@@ -670,14 +699,14 @@ int launch(Op op, int n, const tq_handle* hs, const void* const* xs, void* const
     else p.kernel = packed ? (const void*)k_matvec_ring<kRingWaves, 16, true> : (const void*)k_matvec_ring<kRingWaves, 16, false>;
     p.block = (unsigned)waves * 64;
   } else if (op == Op::kMatvec && runs) {
-    // LDS: 16-bit dictionary image | one ring per lane (aligned to its size) | a count per lane
+    // LDS: 16-bit dictionary image | one ring per lane (aligned to its size)
     const size_t dict16 = round_up((uint64_t)dict_words_max * 2, kRingBytes);
     a.x_off = (uint32_t)dict16;
     uint64_t units = 0;
     for (int i = 0; i < n; ++i) units += (uint64_t)hs[i]->m.n_bands * hs[i]->m.n_quads;
     const bool less = small && !packed && batch > 4 && units <= (uint64_t)kRunSmallUnits * p.grid;
     p.block = (packed ? kRunWavesPacked : kRunWaves) * 64;
-    p.lds = dict16 + (size_t)p.block * (less ? kSmallRingBytes : kRingBytes) + (size_t)p.block * 2;   // + the column counts of units shared between wavefronts
+    p.lds = dict16 + (size_t)p.block * (less ? kSmallRingBytes : kRingBytes);
     cut_by_workgroup(true);
     p.kernel = a.by_workgroup ? runs_kernel<true>(packed, less, batch) : runs_kernel<false>(packed, less, batch);
   } else {

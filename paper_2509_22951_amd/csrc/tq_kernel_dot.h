@@ -7,7 +7,6 @@ namespace tq {
 // Staging is split in two so that the loads of the dictionary, of the activations and of the first code chunks are
 // all in flight together before anything waits: issue_* only loads into registers, commit_* writes LDS; the dictionary's loads write LDS
 // themselves (request_to_lds).
-constexpr uint32_t kSplitWaves = 4;    // k_matvec splits units between wavefronts in shares that leave each unit at least this many
 
 // LDS image of one activation row: dword (panel * x_span + c) = (x[panel * seg_cols + c], x[panel * seg_cols + c + 1])
 // as two bf16, zero past the end of the row; the gap dwords between panels and the tail are zero.
@@ -347,23 +346,23 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // before they decode: every instruction of a wavefront with one neighbour on its SIMD is 2 to 4 ns, a round trip to memory only 160.
 // 2048 x 2048, batch 1, us after the first wavefront's start, before -> now (no search and no 64-bit divisions either, 4 columns of x to a
 // load, the dictionary through request_to_lds, behind the first codes): its job known 1.5 -> 0.6, everything requested 3.7 -> 2.4, decode
-// from 6.1 -> 3.9, end of a pass 10.1 -> 8.7; one LLaMA-3.2-1B layer 18.3 -> 17.2.
+// from 6.1 -> 3.9, end of a pass 10.1 -> 8.7 (7.7 with marks, see kSplit); one LLaMA-3.2-1B layer 18.3 -> 17.2.
 template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false, bool kOne = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   static_assert(kB == 1 || kB == 2, "one activation row or two");
   static_assert(!kLong || (kB == 1 && !kPacked), "runs of 3 and 4 bytes: one activation row of one-weight-per-byte matrices");
   constexpr int kImage = kPacked && kB == 2 ? 2 : 1;   // dwords of the activation image per column
-  // kSplit: a share of few units is cut into equal runs of chunks, wherever a run starts inside a unit.  (Whole units
-  // leave wavefronts idle: a 2048 x 2048 matrix gives a workgroup two units for its eight wavefronts.)  Where a lane
-  // stands at the start of such a run is the number of columns the wavefronts before it pass in that unit; each counts
-  // its own part while the dictionary is on its way and leaves the counts in LDS, so nothing waits for device memory a
-  // second time.  (2048 x 2048, batch 1: 12.3 -> 10.1 us, decode 5.9 -> 1.9 us of it.)  The counts and the sums of the
-  // shared bands cost 2 to 4 us, most where the codes come from HBM: they pay in shares of kWaves / kSplitWaves units and no
-  // more.  (us, split / whole units, from HBM | from the caches: 8 wavefronts, 1 unit 9.3 / 9.8 | 8.6 / 9.4, 2 units 10.1 / 10.9 |
-  // 9.1 / 10.5, 3 units 11.9 / 10.7 | 10.5 / 10.1, 6 units (8192 x 3072) 15.7 / 12.5 | 13.6 / 11.6, 15 units 22.1 / 19.0 | 19.1 / 17.1;
-  // two rows, 2 units 9.7 / 12.2, 3 units 11.7 / 11.5; packed, 12 wavefronts, 3 units 10.3 / 11.2, 4 units 11.1 / 10.6.)
-  constexpr bool kSplit = !kLong && !(kPacked && kB == 2);   // (two rows of packed weights leave no LDS for the counts)
-  constexpr int kCount = 12;   // chunks per round of that count
+  // kSplit: a share of few units is cut into equal runs of chunks, wherever a run starts inside a unit.  (Whole units leave wavefronts
+  // idle: a 2048 x 2048 matrix gives a workgroup two units for its eight wavefronts.)  Where a lane stands at the start of such a run the
+  // matrix's marks say, to within 7 chunks that are counted while the dictionary is on its way (request_place).  (Counted from the codes of
+  // the whole unit, each wavefront its part and the counts exchanged through LDS, it took as long again as the decode and paid in shares of up
+  // to two units: 2048 x 2048 8.74 -> 7.67 us, 3072 x 3072 10.7 -> 9.1.)
+  // What is left of the cost is the sums of bands that are shared.  It pays where whole units leave a quarter of the wavefronts' time idle;
+  // packed ones, which fewer chunks keep busier, where they leave half of the wavefronts without any.  us, whole units -> split, batch 1: 3 units
+  // (3072 x 3072) 10.7 -> 9.1, 6 units (8192 x 3072) 12.0 -> 11.8, 9 units 15.0 -> 13.8, 12 units 15.9 -> 15.5, 14 units (8192 x 7168) 16.3 -> 16.7, 14
+  // to 16 (a LLaMA-3.2-1B layer) 17.1 -> 17.9; batch 2: 6 units 13.8 -> 13.3, 12 units 19.1 -> 18.1; packed: 6 units 9.7 -> 9.5, batch 2 11.0 -> 10.5; 9
+  // units 10.9 -> 11.5, batch 2 12.3 -> 12.8.
+  constexpr bool kSplit = !kLong;
   // Packed weights are bound by issue and the LDS pipe and gain most from wavefronts that end together (see pace; us, eight LLaMA-3.2-3B layers 87 -> 83,
   // one 17.7 -> 16.0, batch 2 104 -> 98, four in 16 stages 171 -> 164); plain ones in large launches 1 % (eight layers 154 -> 153, staged at
   // batch 2 221 -> 218), where a workgroup serves one matrix they lose as much (a 1B layer 17.2 -> 17.5, a 3B layer batch 2 26.1 -> 26.8).
@@ -376,7 +375,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   float* slot_val = (float*)((uint8_t*)lds4 + a.slot_off);           // [2 * kWaves][kB][16]
   int* slot_band = (int*)(slot_val + 2 * kWaves * kB * 16);          // [2 * kWaves]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint16_t* lds_count = (uint16_t*)(slot_band + 2 * kWaves);         // kSplit: [kWaves][64] columns of a shared unit, per lane
   const uint32_t* staged = nullptr;
   const uint32_t n_stages = kStaged ? a.n_stages : 1u;
   constexpr uint32_t kNoStage = 0xFFFFFFFFu;
@@ -444,10 +442,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   };
   // This wavefront's run of a job: the chunks [c0, c_end) of the units [u0, u1).
   uint32_t uoff_lane = 0;
-  uint32_t unit_lo = 0, u0 = 0, u1 = 0, c0 = 0, c_end = 0, unit_start = 0, split_lo = 0, split_n = 0, part = 0;
-  bool in_lanes = false, split = false, head_shared = false, tail_shared = false;   // the run starts / ends inside a unit
+  uint32_t unit_lo = 0, u0 = 0, u1 = 0, c0 = 0, c_end = 0, unit_start = 0, passed = 0;   // (passed: columns of its first unit that earlier wavefronts take)
+  bool in_lanes = false, head_shared = false, tail_shared = false;   // the run starts / ends inside a unit
   uint2 cwa[kPiece], cwb[kPiece];
-  uint2 counted[kCount];   // first chunks of the unit the run leaves unfinished
+  Place place;
   auto offset_of = [&](const DevMat& m, uint32_t u) {
     if (in_lanes) return (uint32_t)__builtin_amdgcn_readlane(uoff_lane, u - unit_lo);
     return unit_offset(m, u);
@@ -494,16 +492,14 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     unit_lo = band_lo * m.n_quads;
     const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
     in_lanes = n_units < kLaneUnits;
-    split = kSplit && kSplitWaves * n_units <= kWaves;
-    static_assert(kWaves / kSplitWaves < kLaneUnits, "the offsets of a split share are in the lanes");
+    const bool split = kSplit && in_lanes && (kPacked ? 2 * n_units <= kWaves : 4 * n_units <= 3 * kWaves * ((n_units + kWaves - 1) / kWaves));
     // (values of the two ways meet in local variables and are assigned once: assigned in each branch, the compiler keeps
     // them in memory)
     uint32_t first = unit_lo + (uint32_t)((uint64_t)n_units * wave / kWaves), end = unit_lo + (uint32_t)((uint64_t)n_units * (wave + 1) / kWaves);
-    uint32_t lo = 0, hi = 0, start = 0, shared_from = 0, all_lo = 0, all_n = 0;
+    uint32_t lo = 0, hi = 0, start = 0;
     bool head = false, tail = false;
     if (split) {   // few units per wavefront: see kSplit above
-      all_lo = offset_of(m, unit_lo);
-      all_n = offset_of(m, unit_lo + n_units) - all_lo;
+      const uint32_t all_lo = offset_of(m, unit_lo), all_n = offset_of(m, unit_lo + n_units) - all_lo;
       lo = all_lo + all_n * wave / kWaves;
       hi = all_lo + all_n * (wave + 1) / kWaves;
       const uint64_t lanes = (2ull << n_units) - 1;   // lanes 0 .. n_units hold the offsets
@@ -511,10 +507,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       const uint32_t last = unit_lo + (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane < max(hi, lo + 1)) & lanes) - 1;
       end = lo < hi ? last + 1 : first;
       start = offset_of(m, first);
-      const uint32_t last_start = offset_of(m, last), last_end = offset_of(m, last + 1);
-      head = lo > start;
-      tail = lo < hi && hi < last_end;
-      shared_from = tail ? max(lo, last_start) : hi;
+      head = lo < hi && lo > start;
+      tail = lo < hi && hi < offset_of(m, last + 1);
     } else if (first < end) {
       lo = offset_of(m, first);
       hi = offset_of(m, end);
@@ -524,9 +518,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     c0 = lo;
     c_end = hi;
     unit_start = start;
-    part = shared_from;
-    split_lo = all_lo;
-    split_n = all_n;
     head_shared = head;
     tail_shared = tail;
     wu = u0;
@@ -535,26 +526,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     na = 0;
     ea = false;
     if (u0 < u1) next_piece(m, sa, na, ea);
-  };
-  // Columns every lane passes in this wavefront's part of the unit it leaves unfinished: where the wavefronts after it
-  // start.  (Run lengths follow from the codes alone; an empty run passes nothing.)
-  auto request_count = [&](const DevMat& m, uint32_t from) {
-#pragma unroll
-    for (int k = 0; k < kCount; ++k) counted[k] = load_chunk(m.codes, min(from + k, c_end - 1), lane);
-  };
-  auto count_columns = [&](const DevMat& m) {
-    u16x2 pairs = {0, 0};
-    if (tail_shared) {
-      for (uint32_t from = part;;) {
-#pragma unroll
-        for (int k = 0; k < kCount; ++k)
-          if (from + k < c_end) pairs = count_pairs(count_pairs(pairs, counted[k].x), counted[k].y);
-        from += kCount;
-        if (from >= c_end) break;
-        request_count(m, from);
-      }
-    }
-    lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (c_end - part) + pairs.x + pairs.y);
   };
   Cursor at, next;   // (next: one job further, kStaged only)
   at.stage = 0;
@@ -653,11 +624,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       } else if (u0 < u1) {
         load_piece(m, cwa, sa, na, false, false);
       }
-      if (tail_shared) request_count(m, part);
+      if (head_shared) request_place(m, u0, unit_start, c0, lane, place);
       if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, kDictAhead);
       if constexpr (kStaged) {   // while the other workgroups arrive
-        if (lds_used && wait_for == kNoStage) __syncthreads();   // (the counts of the job before are no longer read)
-        if (split) count_columns(m);
+        if (head_shared) passed = columns_passed(place, unit_start, c0);
       }
       // the previous dictionary, activation image and slots are no longer in use; staged: nor is anyone still writing
       // the activations (the wait ends with the same barrier)
@@ -722,7 +692,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             commit_activations<kThreads, kXRegs>(m, first, tid, xlo, xhi, lds_x, image_cols);
           }
         }
-        if (!kStaged && split) count_columns(m);   // (last: its chunks were requested after everything else)
+        if (!kStaged && head_shared) passed = columns_passed(place, unit_start, c0);   // (last: requested after everything else)
       }
       if (new_dict) lds_arrived();
       __syncthreads();
@@ -732,14 +702,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         bool whole = q == 0 && !head_shared;             // the current band started inside this wavefront's run
         float a0 = 0.f, a1 = 0.f;
         uint32_t xa = xa_lane + q * xa_quad;
-        if (head_shared) {   // the columns of this unit that earlier wavefronts take
-          uint32_t passed = 0;
-          for (int w = wave - 1; w >= 0; --w) {
-            passed += lds_count[w * 64 + lane];
-            if (split_lo + split_n * w / kWaves <= unit_start) break;
-          }
-          xa += 4u * kImage * passed;
-        }
+        if (head_shared) xa += 4u * kImage * passed;
         // the scales of the band in work are requested when the band starts (the array is padded to whole bands)
         float scale = global_load(m.scales + band * kUnitRows + (lane & 15));
         auto finish_band = [&](bool complete) {

@@ -227,12 +227,14 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
   }
 }
 
-// kSplit: as in k_matvec, a share of few units is cut into equal runs of chunks, and each wavefront counts the columns its
-// part of a unit passes while the dictionary is on its way.  A lone wavefront takes 8 us for a unit of 33 chunks, but the
+// kSplit: as in k_matvec, a share of few units is cut into equal runs of chunks, and the marks say where the lanes stand at the start of one
+// (4099 x 2999 batch 5 17.8 -> 15.4 us against counts of each wavefront's part, exchanged through LDS).  A lone wavefront takes 8 us for a unit of 33 chunks, but the
 // windows around a cut are multiplied on both sides of it, each time with zeros for the other side's columns: shares that
 // leave less than half the wavefronts idle (above 8 batch rows, where the operands are twice as many loads: two thirds) are
 // faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 -> 15.0, 700 x 1999 batch 5 20.2 -> 16.6; 6 units of
-// packed weights for 8 wavefronts 18.0 -> 23.2; batch 16, 6 units for 12 wavefronts: 4099 x 2999 27.7 -> 33.8, 8192 x 3072 22.7 -> 26.4.)
+// packed weights for 8 wavefronts 18.0 -> 23.2; batch 16, 6 units for 12 wavefronts: 4099 x 2999 27.7 -> 33.8, 8192 x 3072 22.7 -> 26.4.  That
+// is with counts; with marks, beyond the line: 8192 x 3072 batch 16 21.4 -> 22.7, 4096 x 8192 batch 5 17.5 -> 19.3, batch 16 21.7 -> 26.8, 8192 x 3072 packed batch 4
+// 12.0 -> 13.5; only 9 units gain, 12288 x 3072 batch 3 20.0 -> 19.3, batch 8 20.8 -> 19.9.)
 // Rings of 64 bytes take such shares (kRunSmallUnits): groups of two windows leave half as much around a cut to be multiplied
 // twice, and in ragged units.  us, rings of 128 -> 64 bytes: 4099 x 2999 batch 5 19.7 -> 18.6, 700 x 1999 batch 8 17.6 -> 16.7, batch 16 26.2 ->
 // 22.9, 2048 x 2048 batch 16 15.5 -> 14.3, 3072 x 3072 batch 16 18.8 -> 16.4; larger shares equal or slower (16384 x 3072 batch 8 21.2 -> 22.6), and
@@ -245,7 +247,6 @@ constexpr uint32_t kRunSplitMinSmall = 9;   // with rings of 64 bytes, whose pie
 // the dictionary).
 template <int kRing, int kWaves, bool kPacked, int kFold, bool kOne>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
-  constexpr int kCount = 12;
   touch_arguments();
   extern __shared__ uint4 lds4[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -254,7 +255,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   const uint32_t* staged = nullptr;
   const uint32_t rings = a.x_off;   // LDS address (the LDS segment starts at 0)
   const uint32_t ring = rings + (uint32_t)wave * (64 * kRing) + (uint32_t)lane * kRing;
-  uint16_t* lds_count = (uint16_t*)((uint8_t*)lds4 + rings + kWaves * 64 * kRing);   // [kWaves][64]
   bool lds_used = false;
   for (int i = kOne ? mapped_job(a) : first_job(a, 0, a.n, lo, lane); kOne || i < a.n; ++i) {
     if (!kOne && hi <= cost_at(a, i)) break;
@@ -282,40 +282,18 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     }
     const bool new_dict = m.dict != staged;
     staged = m.dict;
-    if (lds_used) __syncthreads();   // the previous matrix's dictionary, counts and partial sums are no longer in use
+    if (lds_used) __syncthreads();   // the previous matrix's dictionary and partial sums are no longer in use
     lds_used = true;
-    // Called when the wavefront's first codes are on their way: the dictionary behind them, then the columns that its part of a unit
-    // passes.  Returns the columns of the run's first unit that earlier wavefronts pass.
+    // Called when the wavefront's first codes are on their way: the dictionary behind them.  Returns the columns of the run's first unit
+    // that earlier wavefronts pass.
     auto ready = [&]() -> uint32_t {
-      uint2 cw[kCount];
-      auto request_count = [&](uint32_t from) {
-#pragma unroll
-        for (int k = 0; k < kCount; ++k) cw[k] = load_chunk(m.codes, min(from + k, run.c_end - 1), lane);
-      };
-      if (split && run.tail) request_count(run.part);
+      Place place;
+      if (run.head) request_place(m, run.u0, run.unit_start, run.c0, lane, place);
       if (new_dict) stage_image(m, lane, wave, kWaves, lds4);
-      if (split) {
-        u16x2 pairs = {0, 0};
-        if (run.tail) {
-          for (uint32_t from = run.part;;) {
-#pragma unroll
-            for (int k = 0; k < kCount; ++k)
-              if (from + k < run.c_end) pairs = count_pairs(count_pairs(pairs, cw[k].x), cw[k].y);
-            from += kCount;
-            if (from >= run.c_end) break;
-            request_count(from);
-          }
-        }
-        lds_count[wave * 64 + lane] = (uint16_t)(kChunkCodes * (run.c_end - run.part) + pairs.x + pairs.y);   // (an empty run passes nothing)
-      }
-      if (new_dict) lds_arrived();
-      if (split || new_dict) __syncthreads();
-      uint32_t start = 0;
-      if (run.head) {
-        for (int w = wave - 1; w >= 0; --w) {
-          start += lds_count[w * 64 + lane];
-          if (run.start_of(w) <= run.unit_start) break;
-        }
+      const uint32_t start = run.head ? columns_passed(place, run.unit_start, run.c0) : 0u;
+      if (new_dict) {
+        lds_arrived();
+        __syncthreads();
       }
       return start;
     };

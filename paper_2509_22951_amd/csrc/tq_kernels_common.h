@@ -162,6 +162,7 @@ __device__ __forceinline__ uint4 global_load(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ uint32_t global_load(const uint32_t* p) { return *(__attribute__((address_space(1))) const uint32_t*)p; }
+__device__ __forceinline__ uint32_t global_load(const uint8_t* p) { return *(__attribute__((address_space(1))) const uint8_t*)p; }
 __device__ __forceinline__ uint32_t global_load(const uint16_t* p) { return *(__attribute__((address_space(1))) const uint16_t*)p; }
 __device__ __forceinline__ float global_load(const float* p) { return *(__attribute__((address_space(1))) const float*)p; }
 __device__ __forceinline__ void global_store(float* p, float v) { *(__attribute__((address_space(1))) float*)p = v; }
@@ -394,34 +395,55 @@ __device__ __forceinline__ u16x2 count_pairs(u16x2 acc, uint32_t codes) {
   return acc + __builtin_elementwise_min(high, u16x2{1, 1});
 }
 
+// Where the lanes stand at chunk c0 of the unit that starts at chunk unit_start < c0: the mark before it, and the up to kMarkChunks - 1
+// chunks between (requested together, and looked at when they have arrived).
+struct Place {
+  uint32_t mark;
+  uint2 c[kMarkChunks - 1];
+};
+__device__ __forceinline__ void request_place(const DevMat& m, uint32_t unit, uint32_t unit_start, uint32_t c0, int lane, Place& p) {
+  const uint32_t k = (c0 - unit_start) / kMarkChunks, from = unit_start + k * kMarkChunks;
+  p.mark = 0;
+  if (k) {
+    const uint64_t at = (mark_index(unit, unit_start) + k) * mark_bytes(m.seg_cols);
+    const uint8_t* marks = (const uint8_t*)m.uoff + marks_at((uint64_t)m.n_bands * m.n_quads) + at;
+    p.mark = m.seg_cols <= kMarkByteCols ? global_load(marks + lane) : global_load((const uint16_t*)marks + lane);
+  }
+#pragma unroll
+  for (uint32_t j = 0; j < kMarkChunks - 1; ++j) p.c[j] = load_chunk(m.codes, min(from + j, c0 - 1), lane);
+}
+__device__ __forceinline__ uint32_t columns_passed(const Place& p, uint32_t unit_start, uint32_t c0) {
+  const uint32_t n = (c0 - unit_start) % kMarkChunks;
+  u16x2 pairs = {0, 0};
+#pragma unroll
+  for (uint32_t j = 0; j < kMarkChunks - 1; ++j)
+    if (j < n) pairs = count_pairs(count_pairs(pairs, p.c[j].x), p.c[j].y);
+  return kChunkCodes * (c0 - unit_start) + p.mark + pairs.x + pairs.y;
+}
+
 // One of n_waves equal runs of chunks of a share of n_units < 64 units: chunks [c0, c_end) of the units [u0, u1).
 // uoff_lane: lane k holds the offset of the share's unit k, lanes from n_units on that of its end.
 struct EvenRun {
   uint32_t u0, u1, c0, c_end;
   bool head, tail;       // the run starts / ends inside a unit
   uint32_t unit_start;   // of unit u0
-  uint32_t part;         // tail: where the run's part of the unit it leaves unfinished begins (else c_end)
-  uint32_t all_lo, all_n, n_runs;
-  __device__ __forceinline__ uint32_t start_of(int wave) const { return all_lo + all_n * min((uint32_t)wave, n_runs) / n_runs; }
 };
 __device__ __forceinline__ EvenRun even_run(uint32_t uoff_lane, uint32_t unit_lo, uint32_t n_units, int wave, int n_waves, uint32_t min_chunks) {
   EvenRun r;
-  r.all_lo = __builtin_amdgcn_readlane(uoff_lane, 0);
-  r.all_n = __builtin_amdgcn_readlane(uoff_lane, n_units) - r.all_lo;
-  r.n_runs = min((uint32_t)n_waves, (r.all_n + min_chunks - 1) / min_chunks);   // the wavefronts behind that many have none
-  r.c0 = r.start_of(wave);
-  r.c_end = r.start_of(wave + 1);
+  const uint32_t all_lo = __builtin_amdgcn_readlane(uoff_lane, 0), all_n = __builtin_amdgcn_readlane(uoff_lane, n_units) - all_lo;
+  const uint32_t n_runs = min((uint32_t)n_waves, (all_n + min_chunks - 1) / min_chunks);   // the wavefronts behind that many have none
+  r.c0 = all_lo + all_n * min((uint32_t)wave, n_runs) / n_runs;
+  r.c_end = all_lo + all_n * min((uint32_t)wave + 1, n_runs) / n_runs;
   const uint64_t lanes = (2ull << n_units) - 1;   // lanes 0 .. n_units hold the offsets
   const uint32_t first = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane <= r.c0) & lanes) - 1;
   const uint32_t last = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(uoff_lane < max(r.c_end, r.c0 + 1)) & lanes) - 1;
-  const uint32_t last_start = __builtin_amdgcn_readlane(uoff_lane, last), last_end = __builtin_amdgcn_readlane(uoff_lane, min(last + 1, 63u));
+  const uint32_t last_end = __builtin_amdgcn_readlane(uoff_lane, min(last + 1, 63u));
   const bool empty = r.c0 >= r.c_end;
   r.u0 = unit_lo + first;
   r.u1 = empty ? r.u0 : unit_lo + last + 1;
   r.unit_start = __builtin_amdgcn_readlane(uoff_lane, first);
   r.head = !empty && r.c0 > r.unit_start;
   r.tail = !empty && r.c_end < last_end;
-  r.part = r.tail ? max(r.c0, last_start) : r.c_end;
   return r;
 }
 

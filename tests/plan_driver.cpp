@@ -335,12 +335,43 @@ static void ring() {
   std::printf("%d units decoded, %d and %d ragged ones at the limits, %d and %d wrong with the mistake\n", units, at_limit[0], at_limit[1], planted[0], planted[1]);
 }
 
+// Marks of units of any lengths: no two in one place, none outside the room for them, none over the offsets.
+static void marks() {
+  unsigned long total = 0;
+  uint32_t state = 12345;
+  auto next = [&](uint32_t n) { return (state = state * 1664525u + 1013904223u) / 65536u % n; };
+  for (uint32_t longest : {1u, 7u, 8u, 9u, 17u, 36u, 260u}) {
+    for (int turn = 0; turn < 60; ++turn) {
+      const uint32_t n_units = 1 + next(300);
+      uint32_t at = 0;
+      uint64_t behind = 0;   // places up to here are taken
+      for (uint32_t u = 0; u < n_units; ++u) {
+        const uint32_t len = 1 + next(longest);
+        for (uint32_t k = 1; k * tq::kMarkChunks < len; ++k, ++total) {
+          const uint64_t place = tq::mark_index(u, at) + k;
+          CHECK(!(place < behind), "unit %u mark %u", u, k);
+          behind = place + 1;
+        }
+        at += len;
+      }
+      for (uint32_t seg_cols : {16u, 496u, 512u, 1024u}) {
+        CHECK(!(behind * tq::mark_bytes(seg_cols) > tq::marks_size(n_units, at, seg_cols)), "%u units", n_units);
+        const uint32_t most = seg_cols / 2;   // pairs of a lane
+        CHECK(!(tq::mark_bytes(seg_cols) == 64 ? most > 255 : most > 65535), "%u columns", seg_cols);
+      }
+      CHECK(!(tq::marks_at(n_units) < 4 * ((uint64_t)n_units + 1) || tq::marks_at(n_units) % 2), "%u units", n_units);
+    }
+  }
+  std::printf("%lu marks\n", total);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
   else if (!std::strcmp(what, "assign")) assign();
   else if (!std::strcmp(what, "cuts")) cuts();
   else if (!std::strcmp(what, "ring")) ring();
+  else if (!std::strcmp(what, "marks")) marks();
   else return 2;
   return 0;
 }

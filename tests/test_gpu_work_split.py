@@ -68,6 +68,33 @@ def test_units_shared_between_wavefronts(rows, cols, seg_cols, batch, opts):
         job.m.close()
 
 
+# Runs that start inside a unit, at any chunk of it: at marks and between them, marks of two bytes (segments over 510 columns),
+# shares of one to one and a half units to a wavefront.
+STARTS = [
+    (16, 4096, 1024),     # one unit of 128 chunks or more, 16 marks
+    (37, 3000, 1008),     # three bands, the last one and the last panel ragged
+    (16, 1900, 496),      # the widest segments with marks of a byte
+    (16, 9 * 256, 64),    # nine units of 8 or 9 chunks: one mark or none
+    (16, 11 * 1024 - 3, 256),
+    (9000, 257, 512),     # one panel; two or three bands to a workgroup
+]
+
+
+@pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("batch", [1, 2, 3, 7, 16])
+@pytest.mark.parametrize("rows,cols,seg_cols", STARTS)
+def test_runs_that_start_inside_a_unit(rows, cols, seg_cols, batch, opts):
+    if opts and cols % 2:
+        cols += 1
+    job = _Job(rows, cols, batch, seed=rows + cols + batch, seg_cols=seg_cols, **opts)
+    try:
+        job.m.matvec(job.x.data_ptr(), job.y.data_ptr(), batch, _stream())
+        torch.cuda.synchronize()
+        job.check()
+    finally:
+        job.m.close()
+
+
 @pytest.mark.parametrize("n", [2, 7, 32, 33])   # 32: the most matrices that get whole workgroups
 def test_matrices_of_a_call_get_whole_workgroups(n):
     jobs = [_Job(16 * (1 + (37 * i) % 60) + i % 3, 256 * (1 + i % 4) + i % 2, 1, seed=100 + i, seg_cols=64, max_entries=600) for i in range(n)]

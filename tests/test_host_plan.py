@@ -46,3 +46,7 @@ def test_ring_decode_at_the_distances_it_takes(driver):
     out = driver("ring")
     print(out)
     assert "units decoded" in out
+
+
+def test_marks_of_units_of_any_lengths_never_share_a_place(driver):
+    assert "marks" in driver("marks")
