@@ -347,9 +347,14 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // 2048 x 2048, batch 1, us after the first wavefront's start, before -> now (no search and no 64-bit divisions either, 4 columns of x to a
 // load, the dictionary through request_to_lds, behind the first codes): its job known 1.5 -> 0.6, everything requested 3.7 -> 2.4, decode
 // from 6.1 -> 3.9, end of a pass 10.1 -> 8.7 (7.7 with marks, see kSplit); one LLaMA-3.2-1B layer 18.3 -> 17.2.
-template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false, bool kOne = false>
+// kShared: a staged step whose workgroups may share bands (shared_share).  A stage's largest share is then its units over the workgroups, rounded up, where
+// whole bands of 3 or 8 units leave some workgroups 6 units of 3.75, or 8 of 6.  us, whole bands -> shared, four LLaMA-3.2-3B layers in 16 stages 199.0 ->
+// 192.8, batch 2 209 -> 200, four 1B layers 165.5 -> 158.2; packed ones gained nothing (batch 1 160 -> 158, batch 2 87.3 -> 87.6, 1B 107.1 -> 107.7).  A kernel of its own:
+// with the choice made inside it, steps that share nothing lost 3 % (four layers of 1024 x 2048, batch 2, 122 -> 126).
+template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false, bool kOne = false, bool kShared = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   static_assert(kB == 1 || kB == 2, "one activation row or two");
+  static_assert(!kShared || (kStaged && !kPacked), "workgroups share bands in staged steps of one-weight-per-byte matrices");
   static_assert(!kLong || (kB == 1 && !kPacked), "runs of 3 and 4 bytes: one activation row of one-weight-per-byte matrices");
   constexpr int kImage = kPacked && kB == 2 ? 2 : 1;   // dwords of the activation image per column
   // kSplit: a share of few units is cut into equal runs of chunks, wherever a run starts inside a unit.  (Whole units leave wavefronts
@@ -436,9 +441,20 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   };
   // The unit offsets of a share of few units sit in the lanes: lane k has that of unit k, the lanes behind them the end.
   constexpr uint32_t kLaneUnits = 64;
-  auto request_offsets = [&](const DevMat& m, uint32_t band_lo, uint32_t band_hi) {
-    const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
-    return n_units < kLaneUnits ? global_load(m.uoff + band_lo * m.n_quads + min((uint32_t)lane, n_units)) : 0u;
+  auto request_offsets = [&](const DevMat& m, uint32_t share_lo, uint32_t share_hi) {
+    const uint32_t n_units = share_hi - share_lo;
+    return n_units < kLaneUnits ? global_load(m.uoff + share_lo + min((uint32_t)lane, n_units)) : 0u;
+  };
+  // The units of job i that a cursor's share holds.
+  auto share_of_units = [&](const DevMat& m, const Cursor& c, uint32_t& share_lo, uint32_t& share_hi) {
+    if constexpr (kShared) {
+      shared_share(a.u.cost_long[c.i], a.u.cost_long[c.i + 1], m.n_bands, m.n_quads, c.lo, share_lo, share_hi);
+    } else {
+      uint32_t band_lo, band_hi;
+      share_of_bands(a, kOne || (kStaged && a.by_workgroup), m, c.i, c.lo, c.hi, band_lo, band_hi);
+      share_lo = band_lo * m.n_quads;
+      share_hi = band_hi * m.n_quads;
+    }
   };
   // This wavefront's run of a job: the chunks [c0, c_end) of the units [u0, u1).
   uint32_t uoff_lane = 0;
@@ -486,11 +502,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   };
   uint32_t sa = 0, na = 0, sb, nb;
   bool ea = false, eb;
-  // Cuts the share [band_lo, band_hi) of a job and requests the first piece of the wavefront's run (ahead of the staging of
+  // Cuts the share of a job, its units [share_lo, share_hi), and requests the first piece of the wavefront's run (ahead of the staging of
   // dictionary and activations, so that a small launch does not wait for device memory twice in a row).
-  auto plan_run = [&](const DevMat& m, uint32_t band_lo, uint32_t band_hi) {
-    unit_lo = band_lo * m.n_quads;
-    const uint32_t n_units = (band_hi - band_lo) * m.n_quads;
+  auto plan_run = [&](const DevMat& m, uint32_t share_lo, uint32_t share_hi) {
+    unit_lo = share_lo;
+    const uint32_t n_units = share_hi - share_lo;
     in_lanes = n_units < kLaneUnits;
     const bool split = kSplit && in_lanes && (kPacked ? 2 * n_units <= kWaves : 4 * n_units <= 3 * kWaves * ((n_units + kWaves - 1) / kWaves));
     // (values of the two ways meet in local variables and are assigned once: assigned in each branch, the compiler keeps
@@ -567,15 +583,15 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     DevMat m;
     if constexpr (kStaged) open_entry(entry_at, job, m);
     else fetch_job(a, at.i, job, m);
-    uint32_t band_lo, band_hi;
-    share_of_bands(a, kOne || (kStaged && a.by_workgroup), m, at.i, at.lo, at.hi, band_lo, band_hi);
+    uint32_t share_lo, share_hi;
+    share_of_units(m, at, share_lo, share_hi);
     if (kStaged && at.stage > arrived) {
       wait_for_stores();
       stage_arrive(a, at.stage);
       wait_for = at.stage;
       arrived = at.stage;
     }
-    if (band_lo >= band_hi) {
+    if (share_lo >= share_hi) {
       if constexpr (kOne) return;
       look_further();
       planned = false;
@@ -590,7 +606,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     const uint32_t xa_quad = 16u * kImage * m.x_span;
     const bool x_aligned = (kPacked || m.cols % 2 == 0) && ((uintptr_t)job.x % 4 == 0);   // (cols even: a second row is aligned like the first)
     const bool x_wide = !kPacked && kB == 1 && m.cols % 4 == 0 && (uintptr_t)job.x % 8 == 0;
-    if (!planned) uoff_lane = request_offsets(m, band_lo, band_hi);
+    if (!planned) uoff_lane = request_offsets(m, share_lo, share_hi);
     {   // one activation row, or two: larger batches run the MFMA kernels
       const uint16_t* xb = job.x;
       float* yb = job.y;
@@ -619,7 +635,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       constexpr uint32_t kDictAhead = 4;   // rounds of the dictionary that are on their way while the unit offsets arrive; the others behind the first codes
       if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, 0, kDictAhead);
       if (!planned) {
-        plan_run(m, band_lo, band_hi);
+        plan_run(m, share_lo, share_hi);
         if (u0 < u1) load_piece(m, cwa, sa, na);
       } else if (u0 < u1) {
         load_piece(m, cwa, sa, na, false, false);
@@ -646,7 +662,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         Job next_job;
         DevMat next_m;
         open_entry(entry_next, next_job, next_m);
-        share_of_bands(a, a.by_workgroup, next_m, next.i, next.lo, next.hi, next_lo, next_hi);
+        share_of_units(next_m, next, next_lo, next_hi);
         if (next_lo < next_hi) uoff_next = request_offsets(next_m, next_lo, next_hi);
       }
       {
@@ -814,6 +830,14 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         uoff_lane = uoff_next;
         plan_run(next_m, next_lo, next_hi);
         if (u0 < u1) load_piece(next_m, cwa, sa, na, false, true);
+        // a band of the next stage that this workgroup begins and another ends: both add to its outputs, from zero on (nobody reads or
+        // writes these in this stage, and the arrival after it waits for these stores too)
+        if constexpr (kShared) {
+          const uint32_t row = next_hi / next_m.n_quads * kUnitRows + (uint32_t)lane;
+          if (next_hi % next_m.n_quads && wave == 0 && lane < (int)kUnitRows && row < next_m.rows)
+#pragma unroll
+            for (int b = 0; b < kB; ++b) y_store<true>(next_job.y + (size_t)b * next_m.rows + row, 0.f);
+        }
       }
       __syncthreads();
       // Combine the shared bands: the first slot of a band adds the later slots of the same band in slot order.  Every
@@ -845,7 +869,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
             const float other = __shfl_xor(t, 1);
             if (mine && !(r16 & 1) && row + 1 < m.rows) y_store<kStaged>(yb + (size_t)b * (m.rows / 2) + row / 2, silu_times(t, other));
           } else if (mine && row < m.rows) {
-            y_store<kStaged>(yb + (size_t)b * m.rows + row, t);
+            float* out = yb + (size_t)b * m.rows + row;
+            if (kShared && ((uint32_t)bnd * nq < share_lo || ((uint32_t)bnd + 1) * nq > share_hi)) y_add(out, t);   // another workgroup has the rest
+            else y_store<kStaged>(out, t);
           }
         }
       }

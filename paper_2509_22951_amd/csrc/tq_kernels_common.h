@@ -95,7 +95,7 @@ struct MatvecArgs {
   uint32_t x_off, slot_off;   // byte offsets in LDS of the activation image (or of the tiles) and of the partial-sum slots
   uint32_t tile_area;         // bytes of LDS per wavefront in the tile kernels (the same for every matrix of the launch)
   uint16_t gate_up;           // 1: rows 2r and 2r + 1 are a gate and an up projection; y[b][r] = silu(row 2r) * (row 2r + 1)
-  uint16_t by_workgroup;      // 1: the cost line counts workgroups (see share_of_bands)
+  uint16_t by_workgroup;      // 1: the cost line counts workgroups (see share_of_bands); kBySharedBands: and workgroups may share bands (staged steps, see shared_share)
   uint32_t share, share_rest; // the cost line in even parts (even_part), one per workgroup; by_workgroup: share is the workgroups of a stage
   float parts_inverse;
   const StepEntry* table;     // device table of the n jobs, or null: then j and first below hold them
@@ -184,6 +184,10 @@ template <bool kCoherent>
 __device__ __forceinline__ void y_store(float* p, float v) {
   if constexpr (kCoherent) __hip_atomic_store((__attribute__((address_space(1))) float*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else global_store(p, v);
+}
+
+__device__ __forceinline__ void y_add(float* p, float v) {   // at device scope, no return value
+  (void)__builtin_amdgcn_global_atomic_fadd_f32((__attribute__((address_space(1))) float*)p, v);
 }
 
 // A matrix description from device memory, through scalar loads.

@@ -46,6 +46,32 @@ constexpr uint32_t kLineMask = (1u << kLineBits) - 1;
 constexpr uint32_t kMaxWorkgroupBands = 1u << (32 - kLineBits);
 TQ_HD uint32_t line_word(uint32_t start, uint32_t bands) { return bands << kLineBits | start; }
 
+// Stages whose workgroups take equal numbers of units, not of whole bands: two of them may share a band, and both add their part of its sums
+// to outputs that were cleared in the stage before (two addends onto zero: the same sum in either order).  The word says so in its top bit.
+constexpr uint32_t kBySharedBands = 2, kShareUnits = 1u << 31;
+constexpr uint32_t kMaxSharedItems = kMaxWorkgroupBands / 2;
+// Workgroup `at` of the line, between the words of its matrix and of the next one: units [lo, hi) of the matrix.
+TQ_HD void shared_share(uint32_t word, uint32_t next_word, uint32_t n_bands, uint32_t n_quads, uint32_t at, uint32_t& lo, uint32_t& hi) {
+  const uint32_t first = word & kLineMask, wgs = (next_word & kLineMask) - first, items = (word & ~kShareUnits) >> kLineBits;
+  const uint32_t size = word & kShareUnits ? 1u : n_quads, total = word & kShareUnits ? n_bands * n_quads : n_bands;
+  lo = size * workgroup_band(items, total - items * wgs, at - first);
+  hi = size * workgroup_band(items, total - items * wgs, at - first + 1);
+}
+// Whether no band of a matrix is cut twice when `wgs` workgroups take equal numbers of its units, and each has some.
+inline bool bands_cut_once(uint32_t n_bands, uint32_t n_quads, uint32_t wgs) {
+  const uint64_t units = (uint64_t)n_bands * n_quads;
+  if (units > UINT32_MAX || units < wgs) return false;
+  const uint32_t items = (uint32_t)units / wgs, rest = (uint32_t)units % wgs;
+  uint32_t last = 0;   // the band cut last, plus 1
+  for (uint32_t k = 1; k < wgs; ++k) {
+    const uint32_t at = workgroup_band(items, rest, k);
+    if (at % n_quads == 0) continue;
+    if (at / n_quads + 1 == last) return false;
+    last = at / n_quads + 1;
+  }
+  return true;
+}
+
 // What a block of a listing stream writes: `tokens` tokens start in it, `base` start before it, token t stands for the values
 // [4 t, 4 t + 4) of n_values (the last one of the stream possibly for fewer).  The block's tokens sit in LDS from dword
 // base % 4 on, so that its output lies there as it lies in memory relative to 16-byte pieces.

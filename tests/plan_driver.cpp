@@ -365,6 +365,38 @@ static void marks() {
   std::printf("%lu marks\n", total);
 }
 
+// Workgroups that take equal numbers of units: every unit once, in order, no band in more than two shares where bands_cut_once says so.
+static void shared() {
+  unsigned long cuts = 0, once = 0;
+  uint32_t state = 99;
+  auto next = [&](uint32_t n) { return (state = state * 1664525u + 1013904223u) / 65536u % n; };
+  for (int turn = 0; turn < 20000; ++turn) {
+    const uint32_t n_quads = 1 + next(9), n_bands = 1 + next(turn % 4 ? 400 : 9000), wgs = 1 + next(256), units = n_bands * n_quads, first = next(800) * 256;
+    for (uint32_t kind : {0u, tq::kShareUnits}) {
+      const uint32_t items = (kind ? units : n_bands) / wgs;
+      if (items >= tq::kMaxSharedItems) continue;
+      const uint32_t word = tq::line_word(first, items) | kind, next_word = tq::line_word(first + wgs, 3) | (turn & 1 ? tq::kShareUnits : 0u);
+      std::vector<uint32_t> sharers(n_bands, 0);
+      uint32_t at = 0;
+      bool empty = false;
+      for (uint32_t k = 0; k < wgs; ++k, ++cuts) {
+        uint32_t lo, hi;
+        tq::shared_share(word, next_word, n_bands, n_quads, first + k, lo, hi);
+        CHECK(lo == at && hi >= lo && (kind || lo % n_quads == 0), "%u workgroups, %u bands of %u", wgs, n_bands, n_quads);
+        for (uint32_t b = lo / n_quads; lo < hi && b <= (hi - 1) / n_quads; ++b) ++sharers[b];
+        empty = empty || lo == hi;
+        at = hi;
+      }
+      CHECK(at == units, "%u of %u units", at, units);
+      if (!kind) continue;
+      const bool two = *std::max_element(sharers.begin(), sharers.end()) <= 2 && !empty;
+      CHECK(two == tq::bands_cut_once(n_bands, n_quads, wgs), "%u workgroups, %u bands of %u", wgs, n_bands, n_quads);
+      once += two;
+    }
+  }
+  std::printf("%lu shares, %lu matrices with bands cut once\n", cuts, once);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
@@ -372,6 +404,7 @@ int main(int argc, char** argv) {
   else if (!std::strcmp(what, "cuts")) cuts();
   else if (!std::strcmp(what, "ring")) ring();
   else if (!std::strcmp(what, "marks")) marks();
+  else if (!std::strcmp(what, "shared")) shared();
   else return 2;
   return 0;
 }

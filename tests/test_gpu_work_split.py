@@ -120,6 +120,50 @@ def test_matrices_of_a_call_get_whole_workgroups(n):
             j.m.close()
 
 
+# Stages whose workgroups take equal numbers of units: bands of 2, 3, 4 and 8 quads that two workgroups share, ragged last bands,
+# matrices beside each other.  (The first stage has a band for every workgroup, as clearing ahead needs it.)
+SHARED = [
+    [[(4096, 256)], [(2033, 2048)], [(5111, 768)], [(3000, 768), (1000, 768)]],       # shares of 4 of 8, 4 of 3; 3 of 3: whole bands
+    [[(4096, 256)], [(2048, 512), (3072, 512)], [(3072, 2000)], [(2048, 1000)]],      # 3 of 2, 6 of 8, 2 of 4
+]
+
+
+@pytest.mark.parametrize("opts", [{}, {"bits": 4, "pack": True}], ids=["bytes", "packed"])
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("one_place", [False, True], ids=["own outputs", "outputs in one place"])
+@pytest.mark.parametrize("shapes", SHARED)
+def test_bands_that_workgroups_of_a_stage_share(shapes, one_place, batch, opts):
+    jobs = [[_Job(r, c, batch, seed=7 * k + r + c, seg_cols=32 if opts else 64, **opts) for r, c in stage] for k, stage in enumerate(shapes)]
+    flat = [j for stage in jobs for j in stage]
+    stages = [k for k, stage in enumerate(jobs) for _ in stage]
+    try:
+        if one_place:     # a stage's outputs over those of the stage before: they must not be cleared while that one is in work
+            place = torch.empty(max(sum(j.y.numel() for j in stage) for stage in jobs), dtype=torch.float32, device="cuda")
+            for stage in jobs:
+                at = 0
+                for j in stage:
+                    j.y = place[at:at + j.y.numel()].view_as(j.y)
+                    at += j.y.numel()
+        step = tq.Step([j.m.handle for j in flat], [j.x.data_ptr() for j in flat], [j.y.data_ptr() for j in flat], batch, stages=stages)
+        assert step.info["persistent"] == 1
+        before = None
+        for _ in range(4):
+            for j in flat:
+                j.y.fill_(float("nan"))
+            step.launch(_stream())
+            torch.cuda.synchronize()
+            checked = jobs[-1] if one_place else flat
+            for j in checked:
+                j.check()
+            got = [j.y.clone() for j in checked]
+            assert before is None or all(torch.equal(a, b) for a, b in zip(before, got))     # the sums do not depend on timing
+            before = got
+        step.close()
+    finally:
+        for j in flat:
+            j.m.close()
+
+
 # More bands than compute units, fewer than 8 stored columns: whole workgroups per matrix at the narrow end.
 NARROW = [(6, {}), (3, {}), (1, {}), (10, {"bits": 4, "pack": True}), (14, {"bits": 4, "pack": True})]
 

@@ -50,3 +50,7 @@ def test_ring_decode_at_the_distances_it_takes(driver):
 
 def test_marks_of_units_of_any_lengths_never_share_a_place(driver):
     assert "marks" in driver("marks")
+
+
+def test_shares_of_units_cut_no_band_twice(driver):
+    assert "cut once" in driver("shared")
