@@ -243,8 +243,8 @@ constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a u
                                         // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
 constexpr uint32_t kRunSplitMinSmall = 9;   // with rings of 64 bytes, whose pieces are 9 chunks (11 / 9, us: 1024 x 1024 batch 8 10.8 / 10.1, 2048 x 2048 12.9 /
                                             // 12.5, 700 x 1999 15.9 / 16.7; batch 16 14.3 / 14.5)
-// kOne: as in k_matvec (4099 x 2999 batch 5 18.1 -> 16.9 us, one LLaMA-3.2-3B layer batch 8 36.7 -> 35.4, with the first codes requested ahead of
-// the dictionary).
+// kOne: as in k_matvec (one LLaMA-3.2-3B layer batch 8 36.7 -> 35.4 us; 4099 x 2999 batch 5, which has the loop over jobs, 18.1 -> 16.9 by the
+// first codes requested ahead of the dictionary alone).
 template <int kRing, int kWaves, bool kPacked, int kFold, bool kOne>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
   touch_arguments();
