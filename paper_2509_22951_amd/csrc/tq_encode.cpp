@@ -468,37 +468,46 @@ bool pack_nibbles(const uint8_t* Q, uint32_t rows, uint32_t cols, std::vector<ui
   return true;
 }
 
-// The bands of the matrix that is coded, where they are made while the dictionary already grows over the first of them.
+// The bands of the matrix that is coded, where they are made while the dictionary already grows over the first of them: in pieces of whole
+// bands, or of single rows where there are too few bands for the threads (16 x 262144 on 8 threads: see crew_size).
 class Bands {
  public:
-  // make(band): the rows of a band, by any thread
-  Bands(uint32_t n, std::function<void(uint32_t)> make) : n_(n), make_(std::move(make)), made_(new std::atomic<bool>[n]) {
-    for (uint32_t b = 0; b < n; ++b) made_[b].store(false, std::memory_order_relaxed);
+  // make(first, end): rows of one band, by any thread
+  Bands(uint32_t rows, unsigned n_threads, std::function<void(uint32_t, uint32_t)> make)
+      : rows_(rows), step_((uint64_t)kUnitRows * 2 * n_threads > rows ? 1u : kUnitRows), n_((rows + step_ - 1) / step_), make_(std::move(make)),
+        made_(new std::atomic<bool>[n_]) {
+    for (uint32_t k = 0; k < n_; ++k) made_[k].store(false, std::memory_order_relaxed);
   }
   void make_all() {
     while (make_next()) {}
   }
   void wait_for(uint32_t band) {
-    while (!made_[band].load(std::memory_order_acquire))
-      if (!make_next()) std::this_thread::yield();
+    const uint32_t first = band * (kUnitRows / step_), end = std::min(n_, first + kUnitRows / step_);
+    for (uint32_t k = first; k < end; ++k)
+      while (!made_[k].load(std::memory_order_acquire))
+        if (!make_next()) std::this_thread::yield();
   }
 
  private:
   bool make_next() {
-    const uint32_t b = next_.fetch_add(1, std::memory_order_relaxed);
-    if (b >= n_) return false;
-    make_(b);
-    made_[b].store(true, std::memory_order_release);
+    const uint32_t k = next_.fetch_add(1, std::memory_order_relaxed);
+    if (k >= n_) return false;
+    make_(k * step_, (uint32_t)std::min<uint64_t>(rows_, (uint64_t)(k + 1) * step_));
+    made_[k].store(true, std::memory_order_release);
     return true;
   }
-  const uint32_t n_;
-  std::function<void(uint32_t)> make_;
+  const uint32_t rows_, step_, n_;
+  std::function<void(uint32_t, uint32_t)> make_;
   std::unique_ptr<std::atomic<bool>[]> made_;
   std::atomic<uint32_t> next_{0};
 };
 
-// The threads that are worth starting for a matrix: no more than it has bands.
-unsigned crew_size(unsigned n_threads, uint32_t rows) { return std::min<unsigned>(n_threads, (rows + kUnitRows - 1) / kUnitRows); }
+// The threads that are worth starting for a matrix of rows x cols stored bytes: no more than it has units.  (Bands limit neither phase: with no
+// more threads than bands 16 x 262144 took 11.1 ms, with a carried dictionary 11.6; now 6.2 and 5.8, 8 threads.)
+unsigned crew_size(const tq_encode_opts* opts, uint32_t rows, uint32_t cols) {
+  const uint64_t unit_cols = (uint64_t)kUnitPanels * std::max(kMinSegCols, opts && opts->seg_cols ? opts->seg_cols : kDefaultSegCols);
+  return (unsigned)std::min<uint64_t>(pick_threads(opts ? opts->n_threads : 0), (rows + kUnitRows - 1) / kUnitRows * ((cols + unit_cols - 1) / unit_cols));
+}
 
 // Q: the byte matrix rows x cols that is coded (for packing 1 the packed one).  bands: null, or the crew's other threads are making its bands.
 int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_pad, uint32_t rows, uint32_t cols,
@@ -773,9 +782,9 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
     // (threads take bands as they come, so that all of them meet in the same pages: 8192 x 3072 in ordinary ones 8.7 to 11.4 ms, in large ones 5.4 to 8.3)
     const std::unique_ptr<void, Free> stored = large_room((size_t)rows * width), unpacked = packed ? large_room((size_t)rows * cols) : nullptr;
     uint8_t* const Q = (uint8_t*)stored.get();
-    Crew crew(crew_size(pick_threads(opts ? opts->n_threads : 0), rows));
-    Bands bands(rows_pad / kUnitRows, [&](uint32_t band) {
-      for (uint32_t r = band * kUnitRows; r < std::min(rows, (band + 1) * kUnitRows); ++r) {
+    Crew crew(crew_size(opts, rows, width));
+    Bands bands(rows, crew.size(), [&](uint32_t first, uint32_t end) {
+      for (uint32_t r = first; r < end; ++r) {
         uint8_t* q = (packed ? (uint8_t*)unpacked.get() : Q) + (size_t)r * cols;
         scales[r] = quantize_row(w + (size_t)r * cols, cols, qmax, q);
         if (packed)   // (the quantizer's values fit: qmax is at most 7)
@@ -808,10 +817,10 @@ extern "C" int tq_encode_quantized(const int8_t* q, const float* scales_in, uint
     if (opts && opts->packing == TQ_PACK_NIBBLES) {
       std::vector<uint8_t> P;
       if (!pack_nibbles(Q, rows, cols, &P)) return TQ_E_INVALID_ARG;
-      Crew crew(crew_size(pick_threads(opts->n_threads), rows));
+      Crew crew(crew_size(opts, rows, cols / 2));
       return encode_quantized_matrix(P.data(), scales, rows, cols / 2, opts, crew, nullptr, blob, blob_bytes);
     }
-    Crew crew(crew_size(pick_threads(opts ? opts->n_threads : 0), rows));
+    Crew crew(crew_size(opts, rows, cols));
     return encode_quantized_matrix(Q, scales, rows, cols, opts, crew, nullptr, blob, blob_bytes);
   } catch (const std::bad_alloc&) {
     set_error("tq_encode_quantized: out of host memory");

@@ -409,7 +409,8 @@ print("container of", len(tq.tq_encode_quantized(q, s, n_threads=1)))
 
 
 @pytest.mark.parametrize("rows,cols,opts", [(1, 2, {}), (16, 64, {}), (17, 300, {}), (500, 1000, {}), (500, 1000, {"max_entries": 300}), (515, 998, {"bits": 4, "pack": True}),
-                                            (130, 700, {"dictionary": "frequency"}), (300, 520, {"bits": 4, "lmax": 4})])
+                                            (130, 700, {"dictionary": "frequency"}), (300, 520, {"bits": 4, "lmax": 4}),
+                                            (16, 65536, {}), (16, 9000, {"bits": 4, "pack": True}), (40, 5000, {"max_entries": 300}), (16, 3000, {"lmax": 4})])
 def test_container_does_not_depend_on_the_number_of_threads(rows, cols, opts):
     """The dictionary grows over the first bands while other threads quantize the rest; one thread does one after the other."""
     w = (0.02 * np.random.default_rng(rows * cols).standard_normal((rows, cols))).astype(np.float32)

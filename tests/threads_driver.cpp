@@ -1,5 +1,6 @@
 // Host-only: the encoder and the validator when the system does not start a thread.  pthread_create is replaced by one that
-// refuses from the `allowed`-th call on; every call has to come back, with an error or with the same container.
+// refuses from the `allowed`-th call on; every call has to come back, with an error or with the same container.  And how many a
+// short and wide matrix is given.
 #include <dlfcn.h>
 #include <errno.h>
 #include <pthread.h>
@@ -47,6 +48,19 @@ int main() {
   allowed = 1 << 30;
   if (tq_validate_blob(want, want_bytes, nullptr) != TQ_OK) return std::printf("validate: %s\n", tq_last_error_string()), 1;
   tq_free_blob(want);
+  // One band of many units: its coding is work for every thread that was asked for, and so are its rows.
+  std::vector<float> wide((size_t)16 * 16384);
+  for (size_t i = 0; i < wide.size(); ++i) wide[i] = w[i % w.size()];
+  const std::vector<int8_t> wide_q(wide.size(), 1);
+  const std::vector<float> wide_s(16, 1.f);
+  for (int quantized = 0; quantized < 2; ++quantized) {
+    calls = 0;
+    void* blob = nullptr;
+    size_t bytes = 0;
+    const int rc = quantized ? tq_encode_quantized(wide_q.data(), wide_s.data(), 16, 16384, &o, &blob, &bytes) : tq_encode(wide.data(), 16, 16384, &o, &blob, &bytes);
+    tq_free_blob(blob);
+    if (rc != TQ_OK || calls != 3) return std::printf("16 x 16384 (%s): rc %d, %d threads beside the caller's\n", quantized ? "quantized" : "fp32", rc, calls), 1;
+  }
   std::printf("%d encodes came back without all of their threads\n", refused);
   return 0;
 }
