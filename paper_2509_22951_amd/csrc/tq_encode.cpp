@@ -718,12 +718,10 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   h.total_bytes = round_up(h.off_scales + h.scale_bytes, kSectionAlign);
 
   // Every byte is written below: the sections, and zeros between them (the pad entry is the first of those).
-  std::unique_ptr<uint8_t, void (*)(void*)> owned((uint8_t*)std::malloc(h.total_bytes), std::free);
-  uint8_t* blob = owned.get();
-  if (!blob) {
-    set_error("tq_encode: out of host memory");
-    return TQ_E_OOM;
-  }
+  // (in large pages, since all threads write it for the first time at once: 8192 x 3072 through the Python call 33 -> 17 ms on 8 threads; tq_free_blob
+  // frees it)
+  std::unique_ptr<void, Free> owned = large_room(h.total_bytes);
+  uint8_t* const blob = (uint8_t*)owned.get();
   auto put = [&](uint64_t at, const void* src, uint64_t n, uint64_t next) {
     std::memcpy(blob + at, src, n);
     std::memset(blob + at + n, 0, next - at - n);

@@ -418,3 +418,30 @@ def test_container_does_not_depend_on_the_number_of_threads(rows, cols, opts):
     for n_threads in (2, 3, 16):
         for _ in range(3):
             assert tq.tq_encode(w, n_threads=n_threads, **opts) == want
+
+
+def test_a_container_is_written_to_large_pages():
+    """All threads write it for the first time at once: 25 MB of ordinary pages are 6300 faults that queue behind each other."""
+    import subprocess
+    import sys
+    modes = "/sys/kernel/mm/transparent_hugepage/enabled"
+    if not os.path.exists(modes) or "[never]" in open(modes).read():
+        pytest.skip("no large pages on this system")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = """
+import ctypes, resource
+import numpy as np
+import paper_2509_22951_amd as tq
+lib = tq.load()
+q = np.random.default_rng(0).integers(-127, 128, (8192, 3072), dtype=np.int8)     # (fills the dictionary in its first units)
+s = np.ones(q.shape[0], np.float32)
+ptr, n = ctypes.c_void_p(), ctypes.c_size_t()
+before = resource.getrusage(resource.RUSAGE_SELF).ru_minflt
+assert lib.tq_encode_quantized(q.ctypes.data, s.ctypes.data, *q.shape, None, ctypes.byref(ptr), ctypes.byref(n)) == 0
+print(resource.getrusage(resource.RUSAGE_SELF).ru_minflt - before, n.value // 4096)
+lib.tq_free_blob(ptr)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-1000:]
+    faults, pages = map(int, r.stdout.split())
+    assert faults < pages / 2, (faults, pages)
