@@ -246,9 +246,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
     constexpr uint32_t pk = kPacked ? 2u : 1u;             // columns of the weight matrix per stored byte
     const uint32_t nq = m.n_quads, n_win = pk * m.seg_cols / 8;   // activation windows (8 columns) per segment
     __syncthreads();   // the previous matrix's dictionary and activation tile are no longer in use
-    const bool new_dict = m.dict != staged;
-    if (new_dict) stage_image(m, lane, wave, kWaves, lds4);
-    staged = m.dict;
     // Bands are handed out one at a time, per quad, through a counter in LDS: wavefront w starts with band w of the
     // workgroup's range and claims the next free one while it decodes the last piece of chunks of the one in work.
     // (An even split up front leaves wavefronts waiting at the end of every quad: for the slowest, and for the one more
@@ -296,6 +293,11 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
       }
     };
     request_tile(0);
+    if (m.dict != staged) {
+      stage_image(m, lane, wave, kWaves, lds4);
+      lds_arrived();
+      staged = m.dict;
+    }
     for (; pass_lo < band_hi; pass_lo = pass_hi) {
       pass_hi = min(band_hi, pass_lo + pass_bands);
       f32x4 acc[kGateUpBands];   // kGateUp: the sums of this wavefront's bands of the pass
@@ -305,7 +307,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_ring(MatvecArgs a) {
         if (q || pass_lo != band_lo) __syncthreads();   // everybody has finished the previous quad: its activation tile can go
         if (!kGateUp && tid == 0) *next_band_counter = kWaves;   // bands 0 .. kWaves - 1 are the wavefronts' first ones
         commit_tile();
-        if (new_dict && q == 0 && pass_lo == band_lo) lds_arrived();
         if (q + 1 < nq || pass_hi < band_hi) request_tile(q + 1 < nq ? q + 1 : 0);
         __syncthreads();
         // Sums of lane l: rows 4 * (l / 16) + v of the band, batch row l % 16.  The scales of the next band are requested

@@ -384,6 +384,10 @@ __device__ __forceinline__ void request_to_lds(const void* src, uint32_t n16, in
   if (c == n16 / 64 && c < end_round * (uint32_t)n_waves && (uint32_t)lane < n16 % 64)
     __builtin_amdgcn_global_load_lds((global_cu32*)from + 4 * lane, (lds_mu32*)(size_t)to, 16, 0, 0);
 }
+// Where requests depend on a condition (a dictionary that is new) inside a loop over jobs, the wait belongs into the same branch: with a condition of its
+// own the compiler takes the requests for unfinished on the way round it, and every barrier of the loop waits for all loads, those of the next
+// activation tile or of the next codes among them (us, wait behind the tile or the image -> with the requests: eight LLaMA-3.2-3B layers batch 8 218.5 -> 217.0, packed
+// 153.9 -> 151.5; four in 16 stages 192.6 -> 190.7, batch 2 200.0 -> 198.1).
 __device__ __forceinline__ void lds_arrived() {
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) alone.  (The builtin, not inline assembly: the compiler sees that these loads are done)
   asm volatile("" ::: "memory");
