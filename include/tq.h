@@ -50,7 +50,7 @@ typedef struct tq_encode_opts {
   uint32_t max_entries; /* dictionary size cap incl. the 256 single bytes; 256..TQ_MAX_ENTRIES_DEVICE;
                            0 = TQ_MAX_ENTRIES_DEVICE */
   uint32_t lmax;        /* longest run a dictionary entry may hold, 1..TQ_MAX_LMAX; 0 = TQ_DEFAULT_LMAX */
-  uint32_t n_threads;   /* host threads for the frozen-dictionary part of the parse; 0 = all cores (max 16) */
+  uint32_t n_threads;   /* host threads, at most 16 and at most one per unit; 0: one per core and per 2^17 weight bytes */
   uint32_t seg_cols;    /* columns per independently decodable segment (the tile width of the per-tile stream offsets):
                            multiple of 16 in 16..1024; 0 = TQ_DEFAULT_SEG_COLS (half of it with TQ_PACK_NIBBLES) */
   const void *dict_from;    /* NULL, or a container made earlier: its dictionary is taken over and LZW goes on from

@@ -469,7 +469,7 @@ bool pack_nibbles(const uint8_t* Q, uint32_t rows, uint32_t cols, std::vector<ui
 }
 
 // The bands of the matrix that is coded, where they are made while the dictionary already grows over the first of them: in pieces of whole
-// bands, or of single rows where there are too few bands for the threads (16 x 262144 on 8 threads: see crew_size).
+// bands, or of single rows where there are too few bands for the threads.
 class Bands {
  public:
   // make(first, end): rows of one band, by any thread
@@ -502,11 +502,15 @@ class Bands {
   std::atomic<uint32_t> next_{0};
 };
 
-// The threads that are worth starting for a matrix of rows x cols stored bytes: no more than it has units.  (Bands limit neither phase: with no
-// more threads than bands 16 x 262144 took 11.1 ms, with a carried dictionary 11.6; now 6.2 and 5.8, 8 threads.)
+// The threads of a matrix of rows x cols stored bytes: as many as the caller asks for, but no more than it has units; if it asks for none, one for every
+// kThreadBytes, since starting one costs its caller 20 us.  (Bands limit neither phase.  ms on 16 CPUs, no more threads than bands -> now:
+// 16 x 262144 4.35 -> 2.5, with a carried dictionary 4.8 -> 1.2; 256 x 256 0.45 -> 0.21, from int8 0.43 -> 0.19.  kThreadBytes of 2^15, 2^16, 2^17: 256 x 2048
+// 0.81, 0.61, 0.56; 64 x 8192 0.84, 0.63, 0.56; 1024 x 256 0.76, 0.72, 0.58; 2048 x 512 0.88, 0.85, 0.83.)
+constexpr uint64_t kThreadBytes = 1u << 17;
 unsigned crew_size(const tq_encode_opts* opts, uint32_t rows, uint32_t cols) {
   const uint64_t unit_cols = (uint64_t)kUnitPanels * std::max(kMinSegCols, opts && opts->seg_cols ? opts->seg_cols : kDefaultSegCols);
-  return (unsigned)std::min<uint64_t>(pick_threads(opts ? opts->n_threads : 0), (rows + kUnitRows - 1) / kUnitRows * ((cols + unit_cols - 1) / unit_cols));
+  const uint64_t units = (rows + (uint64_t)kUnitRows - 1) / kUnitRows * ((cols + unit_cols - 1) / unit_cols), asked = opts ? opts->n_threads : 0;
+  return (unsigned)std::min<uint64_t>(pick_threads((uint32_t)asked), asked ? units : std::max<uint64_t>(1, (uint64_t)rows * cols / kThreadBytes));
 }
 
 // Q: the byte matrix rows x cols that is coded (for packing 1 the packed one).  bands: null, or the crew's other threads are making its bands.
@@ -718,8 +722,8 @@ int encode_quantized_matrix(const uint8_t* Q, const std::vector<float>& scales_p
   h.total_bytes = round_up(h.off_scales + h.scale_bytes, kSectionAlign);
 
   // Every byte is written below: the sections, and zeros between them (the pad entry is the first of those).
-  // (in large pages, since all threads write it for the first time at once: 8192 x 3072 through the Python call 33 -> 17 ms on 8 threads; tq_free_blob
-  // frees it)
+  // (in large pages, since all threads write it for the first time at once: 8192 x 3072 through the Python call 33 -> 17 ms on 8 CPUs, 10.7 -> 4.1
+  // on 16; tq_free_blob frees it)
   std::unique_ptr<void, Free> owned = large_room(h.total_bytes);
   uint8_t* const blob = (uint8_t*)owned.get();
   auto put = [&](uint64_t at, const void* src, uint64_t n, uint64_t next) {
@@ -777,7 +781,8 @@ extern "C" int tq_encode(const float* w, uint32_t rows, uint32_t cols, const tq_
     }
     const float qmax = (float)((1u << ((opts && opts->bits ? opts->bits : 8u) - 1)) - 1u);
     const uint32_t width = packed ? cols / 2 : cols;   // stored bytes of a row
-    // (threads take bands as they come, so that all of them meet in the same pages: 8192 x 3072 in ordinary ones 8.7 to 11.4 ms, in large ones 5.4 to 8.3)
+    // (threads take bands as they come, so that all of them meet in the same pages: 8192 x 3072 in ordinary ones 8.7 to 11.4 ms, in large ones, the
+    // container's among them, 4.1)
     const std::unique_ptr<void, Free> stored = large_room((size_t)rows * width), unpacked = packed ? large_room((size_t)rows * cols) : nullptr;
     uint8_t* const Q = (uint8_t*)stored.get();
     Crew crew(crew_size(opts, rows, width));

@@ -48,7 +48,7 @@ int main() {
   allowed = 1 << 30;
   if (tq_validate_blob(want, want_bytes, nullptr) != TQ_OK) return std::printf("validate: %s\n", tq_last_error_string()), 1;
   tq_free_blob(want);
-  // One band of many units: its coding is work for every thread that was asked for, and so are its rows.
+  // One band of many units, four threads asked for: its coding is work for every thread that was asked for, and so are its rows.
   std::vector<float> wide((size_t)16 * 16384);
   for (size_t i = 0; i < wide.size(); ++i) wide[i] = w[i % w.size()];
   const std::vector<int8_t> wide_q(wide.size(), 1);
@@ -61,6 +61,13 @@ int main() {
     tq_free_blob(blob);
     if (rc != TQ_OK || calls != 3) return std::printf("16 x 16384 (%s): rc %d, %d threads beside the caller's\n", quantized ? "quantized" : "fp32", rc, calls), 1;
   }
+  // Nobody asks, and all of it is less work than starting a thread.
+  calls = 0;
+  o.n_threads = 0;
+  void* small = nullptr;
+  size_t small_bytes = 0;
+  if (tq_encode(w.data(), 256, 256, &o, &small, &small_bytes) != TQ_OK || calls != 0) return std::printf("256 x 256: %d threads started\n", calls), 1;
+  tq_free_blob(small);
   std::printf("%d encodes came back without all of their threads\n", refused);
   return 0;
 }
