@@ -1022,32 +1022,14 @@ static int tq_step_create_impl(int n, const tq_handle* hs, const void* const* xs
   }
 }
 
-// Whether the outputs of the products [f, end) of a stage can be cleared while the stage before, products [before, f), is in work, and added
-// to in their own: they are this device's memory, and in no one's place but their own among both stages' activations and outputs.
-static bool outputs_can_be_added_to(const tq_handle* hs, const void* const* xs, void* const* ys, int batch, int before, int f, int end) {
-  struct Range {
-    uintptr_t lo, hi;
-  };
-  auto x_of = [&](int i) {
-    const uintptr_t lo = (uintptr_t)xs[i];
-    return Range{lo, lo + (uintptr_t)batch * hs[i]->m.cols * (hs[i]->m.packing ? 2 : 1) * 2};
-  };
-  auto y_of = [&](int i) {
-    const uintptr_t lo = (uintptr_t)ys[i];
-    return Range{lo, lo + (uintptr_t)batch * hs[i]->m.rows * 4};
-  };
-  auto apart = [](Range a, Range b) { return a.hi <= b.lo || b.hi <= a.lo; };
-  for (int i = f; i < end; ++i) {
-    hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, ys[i]) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
-    if (at.type != hipMemoryTypeDevice || at.isManaged || at.device != hs[i]->device) return false;   // (float adds at device scope)
-    for (int j = before; j < end; ++j)
-      if (!apart(y_of(i), x_of(j)) || (j != i && !apart(y_of(i), y_of(j)))) return false;
+// Whether float adds at device scope work on p: this device's memory.
+static bool can_be_added_to(const void* p, int device) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
   }
-  return true;
+  return at.type == hipMemoryTypeDevice && !at.isManaged && at.device == device;
 }
 
 // A staged step: products that depend on each other in one prepared step.  When every matrix takes the dot-product
@@ -1137,74 +1119,20 @@ static int tq_step_create_staged_impl(int n, const tq_handle* hs, const void* co
                             : (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 1, false, true>;
     p.block = (packed ? kDotWavesPacked : kDotWavesStaged) * 64;
     p.grid = (unsigned)hs[0]->n_cu;   // one workgroup per compute unit (each takes the whole LDS): all resident together
-    // Whole workgroups per matrix in every stage, if that is the better cut over all stages.
-    // Or in equal numbers of units, where that takes a sixteenth off the largest share, no two outputs or activations of the stage and
-    // the one before are in one place, and every workgroup has work in the stage before (it clears what is added to).
-    std::vector<uint32_t> line((size_t)n + 1, 0);
-    std::vector<uint8_t> by_units((size_t)n, 0);
-    uint64_t whole = 0, even = 0;
-    bool can = true, shared = false, all_busy = false, wide_words = false;
-    for (uint32_t k = 0; k < n_stages && can; ++k) {
-      const int f = (int)first[k], cnt = (int)(first[k + 1] - first[k]);
-      if (cnt > kMaxAssign) {
-        can = false;
-        break;
-      }
-      uint32_t wgs[kMaxAssign];
-      const BandCounts counts(cnt, hs + f);
-      const uint64_t worst = assign_workgroups(cnt, counts.m, p.grid, wgs);
-      can = worst != 0 && (uint64_t)n_stages * p.grid <= kLineMask;
-      uint64_t largest = worst;
-      if (can && k && all_busy && !packed) {
-        BandCount units[kMaxAssign];
-        uint32_t unit_wgs[kMaxAssign];
-        bool fits = true;
-        for (int i = 0; i < cnt && fits; ++i) {
-          const DevMat& m = hs[f + i]->m;
-          fits = (uint64_t)m.n_bands * m.n_quads < 1u << 23;
-          units[i] = {m.n_bands * m.n_quads, std::max(1u, m.cols / m.n_quads)};
-        }
-        const uint64_t unit_worst = fits ? assign_workgroups(cnt, units, p.grid, unit_wgs) : 0;
-        fits = unit_worst && unit_worst * 17 < worst * 16;
-        for (int i = 0, left = (int)p.grid; i < cnt && fits; ++i) {
-          const uint32_t take = i + 1 < cnt ? unit_wgs[i] : (uint32_t)left;   // (those left over are the last matrix's)
-          left -= (int)unit_wgs[i];
-          fits = bands_cut_once(hs[f + i]->m.n_bands, hs[f + i]->m.n_quads, take) && units[i].n_bands / take < kMaxSharedItems;
-        }
-        if (fits && outputs_can_be_added_to(hs, xs, ys, batch, (int)first[k - 1], f, f + cnt)) {
-          std::copy(unit_wgs, unit_wgs + cnt, wgs);
-          std::fill(by_units.begin() + f, by_units.begin() + f + cnt, 1);
-          largest = unit_worst;
-          shared = true;
-        }
-      }
-      all_busy = can;
-      for (int i = 0, left = (int)p.grid; i < cnt && can; ++i) {
-        const uint32_t take = i + 1 < cnt ? wgs[i] : (uint32_t)left, items = hs[f + i]->m.n_bands * (by_units[f + i] ? hs[f + i]->m.n_quads : 1u);
-        left -= (int)wgs[i];
-        all_busy = all_busy && items >= take;
-        can = items / wgs[i] < kMaxWorkgroupBands;
-        wide_words = wide_words || items / wgs[i] >= kMaxSharedItems;
-      }
-      whole += largest;
-      even += even_cut_cost(cnt, counts.m, p.grid);
-      uint32_t at = k * p.grid;
-      for (int i = 0; i < cnt && can; ++i) {
-        line[f + i] = at;
-        at += wgs[i];
-      }
+    std::vector<StageItem> items;
+    items.reserve((size_t)n);
+    for (int i = 0; i < n; ++i) {
+      const DevMat& m = hs[i]->m;
+      const uint64_t x = (uint64_t)(uintptr_t)xs[i], y = (uint64_t)(uintptr_t)ys[i];
+      items.push_back({m.n_bands, m.n_quads, m.cols, x, x + (uint64_t)batch * m.cols * (m.packing ? 2 : 1) * 2, y, y + (uint64_t)batch * m.rows * 4});
     }
-    line[n] = n_stages * p.grid;   // (workgroups left over in a stage count as its last matrix's)
-    if (can && whole <= even && !(shared && wide_words)) {
-      a.by_workgroup = shared ? kBySharedBands : 1;
-      if (shared) p.kernel = batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 2, false, true, false, true>
-                                        : (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 1, false, true, false, true>;
+    const StageLine line = plan_stages(n, items.data(), first.data(), n_stages, p.grid, !packed, [&](int i) { return can_be_added_to(ys[i], hs[i]->device); });
+    if (!line.words.empty()) {
+      a.by_workgroup = line.shared ? kBySharedBands : 1;
+      if (line.shared) p.kernel = batch == 2 ? (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 2, false, true, false, true>
+                                             : (const void*)k_matvec<kDotPiece, kDotWavesStaged, false, 1, false, true, false, true>;
       a.share = p.grid;
-      for (int i = 0; i < n; ++i) {
-        const uint32_t items = hs[i]->m.n_bands * (by_units[i] ? hs[i]->m.n_quads : 1u) / (line[i + 1] - line[i]);
-        a.u.cost_long[i] = line_word(line[i], items) | (by_units[i] ? kShareUnits : 0u);
-      }
-      a.u.cost_long[n] = line[n];
+      std::copy(line.words.begin(), line.words.end(), a.u.cost_long);
     }
     rec.launches.push_back(p);
   }

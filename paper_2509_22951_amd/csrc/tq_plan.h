@@ -3,6 +3,7 @@
 #pragma once
 #include <algorithm>
 #include <cstdint>
+#include <vector>
 
 #include "tq_format.h"
 
@@ -142,11 +143,12 @@ inline uint64_t marks_size(uint64_t n_units, uint64_t n_chunks, uint32_t seg_col
 struct BandCount {
   uint32_t n_bands, cols;   // of a matrix, both at least 1
 };
+constexpr uint32_t kTallMatrix = 1u << 23;   // bands; (2^14 of them for every workgroup of 256 are more than line_word holds anyway)
 inline uint64_t assign_workgroups(int n, const BandCount* m, uint64_t grid, uint32_t* wgs) {
   if ((uint64_t)n > grid) return 0;
   uint64_t total = 0, cols_max = 0;
   for (int i = 0; i < n; ++i) {
-    if (m[i].n_bands >= 1u << 23) return 0;   // (share_of_bands multiplies band counts by workgroup counts)
+    if (m[i].n_bands >= kTallMatrix) return 0;
     total += (uint64_t)m[i].n_bands * m[i].cols;
     cols_max = std::max<uint64_t>(cols_max, m[i].cols);
   }
@@ -203,6 +205,92 @@ inline uint64_t even_cut_cost(int n, const BandCount* m, uint64_t grid) {
 inline bool cut_in_workgroups(int n, const BandCount* m, uint64_t most, uint64_t grid, uint32_t* wgs) {
   const uint64_t worst = assign_workgroups(n, m, most, wgs);
   return worst && worst <= even_cut_cost(n, m, grid);
+}
+
+// How a staged step that is one launch of `grid` workgroups cuts its stages.
+struct StageItem {   // a product of it: its matrix, where its activations and its outputs lie
+  uint32_t n_bands, n_quads, cols;
+  uint64_t x, x_end, y, y_end;
+};
+// Whether the outputs of the products [f, end) of a stage can be cleared while the stage before, products [before, f), is in work, and added
+// to in their own: addable(i) says that of the memory, and they are in no one's place but their own among both stages' activations and outputs.
+template <typename Addable>
+bool outputs_can_be_added_to(const StageItem* m, int before, int f, int end, Addable&& addable) {
+  for (int i = f; i < end; ++i) {
+    if (!addable(i)) return false;
+    for (int j = before; j < end; ++j) {
+      const bool x_apart = m[i].y_end <= m[j].x || m[j].x_end <= m[i].y, y_apart = m[i].y_end <= m[j].y || m[j].y_end <= m[i].y;
+      if (!x_apart || (j != i && !y_apart)) return false;
+    }
+  }
+  return true;
+}
+// Whole workgroups per matrix in every stage, if that is the better cut over all stages.  In equal numbers of units where may_share, that takes a
+// sixteenth off the stage's largest share, its outputs can be added to, and every workgroup has work in the stage before (it clears what is
+// added to).  first: the first product of every stage, and n.  words: of the line (line_word, shared_share), empty where the cost line in
+// weights is cut evenly.
+struct StageLine {
+  bool shared = false;
+  std::vector<uint32_t> words;
+};
+template <typename Addable>
+StageLine plan_stages(int n, const StageItem* m, const uint32_t* first, uint32_t n_stages, uint32_t grid, bool may_share, Addable&& addable) {
+  StageLine plan;
+  std::vector<uint32_t> line((size_t)n + 1, 0);
+  std::vector<uint8_t> by_units((size_t)n, 0);
+  uint64_t whole = 0, even = 0;
+  bool all_busy = false, wide_words = false;
+  if ((uint64_t)n_stages * grid > kLineMask) return plan;
+  for (uint32_t k = 0; k < n_stages; ++k) {
+    const int f = (int)first[k], cnt = (int)(first[k + 1] - first[k]);
+    if (cnt > kMaxAssign) return plan;
+    BandCount bands[kMaxAssign], units[kMaxAssign];
+    uint32_t wgs[kMaxAssign], unit_wgs[kMaxAssign];
+    bool few = true;
+    for (int i = 0; i < cnt; ++i) {
+      const StageItem& t = m[f + i];
+      bands[i] = {t.n_bands, t.cols};
+      units[i] = {t.n_bands * t.n_quads, std::max(1u, t.cols / t.n_quads)};
+      few = few && (uint64_t)t.n_bands * t.n_quads < kTallMatrix;
+    }
+    uint64_t largest = assign_workgroups(cnt, bands, grid, wgs);
+    if (!largest) return plan;
+    if (k && all_busy && may_share && few) {
+      const uint64_t unit_largest = assign_workgroups(cnt, units, grid, unit_wgs);
+      bool fits = unit_largest && unit_largest * 17 < largest * 16;
+      for (int i = 0, left = (int)grid; i < cnt && fits; ++i) {
+        const uint32_t take = i + 1 < cnt ? unit_wgs[i] : (uint32_t)left;   // (those left over are the last matrix's)
+        left -= (int)unit_wgs[i];
+        fits = bands_cut_once(m[f + i].n_bands, m[f + i].n_quads, take) && units[i].n_bands / take < kMaxSharedItems;
+      }
+      if (fits && outputs_can_be_added_to(m, (int)first[k - 1], f, f + cnt, addable)) {
+        std::copy(unit_wgs, unit_wgs + cnt, wgs);
+        std::fill(by_units.begin() + f, by_units.begin() + f + cnt, 1);
+        largest = unit_largest;
+        plan.shared = true;
+      }
+    }
+    all_busy = true;
+    uint32_t at = k * grid;
+    for (int i = 0, left = (int)grid; i < cnt; ++i) {
+      const uint32_t take = i + 1 < cnt ? wgs[i] : (uint32_t)left, items = by_units[f + i] ? units[i].n_bands : bands[i].n_bands;
+      left -= (int)wgs[i];
+      all_busy = all_busy && items >= take;
+      if (items / wgs[i] >= kMaxWorkgroupBands) return StageLine();
+      wide_words = wide_words || items / wgs[i] >= kMaxSharedItems;
+      line[f + i] = at;
+      at += wgs[i];
+    }
+    whole += largest;
+    even += even_cut_cost(cnt, bands, grid);
+  }
+  line[n] = n_stages * grid;   // (workgroups left over in a stage count as its last matrix's)
+  if (whole > even || (plan.shared && wide_words)) return StageLine();
+  plan.words.resize((size_t)n + 1);
+  for (int i = 0; i < n; ++i)
+    plan.words[i] = line_word(line[i], m[i].n_bands * (by_units[i] ? m[i].n_quads : 1u) / (line[i + 1] - line[i])) | (by_units[i] ? kShareUnits : 0u);
+  plan.words[n] = line[n];
+  return plan;
 }
 
 }  // namespace tq

@@ -397,6 +397,71 @@ static void shared() {
   std::printf("%lu shares, %lu matrices with bands cut once\n", cuts, once);
 }
 
+// Which stages of a staged step are cut by units: those that gain by it, whose outputs are in nobody's place, behind a stage in which every
+// workgroup has work.
+static void stages() {
+  struct Shape {
+    uint32_t rows, cols;
+  };
+  typedef std::vector<std::vector<Shape>> Stages;
+  // outputs and activations apart, quads of 4 segments of `seg` columns; x, y: from -> to moves an address
+  auto plan = [&](const Stages& shapes, uint32_t seg, bool may_share, int no_adds, int from, int to, bool to_x) {
+    std::vector<tq::StageItem> m;
+    std::vector<uint32_t> first;
+    uint64_t at = 1 << 20;
+    for (const auto& stage : shapes) {
+      first.push_back((uint32_t)m.size());
+      for (const Shape& t : stage) {
+        const uint64_t x = at, x_end = x + t.cols * 2, y = x_end + 64, y_end = y + t.rows * 4;
+        m.push_back({(t.rows + 15) / 16, (t.cols + 4 * seg - 1) / (4 * seg), t.cols, x, x_end, y, y_end});
+        at = y_end + 64;
+      }
+    }
+    first.push_back((uint32_t)m.size());
+    if (from >= 0) {   // product `from`'s outputs end inside product `to`'s activations or outputs
+      const uint64_t bytes = m[from].y_end - m[from].y;
+      m[from].y_end = (to_x ? m[to].x : m[to].y) + 4;
+      m[from].y = m[from].y_end - bytes;
+    }
+    const tq::StageLine line = tq::plan_stages((int)m.size(), m.data(), first.data(), (uint32_t)shapes.size(), 256, may_share, [&](int i) { return i != no_adds; });
+    std::vector<int> shared;   // the stages that are
+    for (size_t k = 0; k < shapes.size(); ++k)
+      if (!line.words.empty() && line.words[first[k]] & tq::kShareUnits) shared.push_back((int)k);
+    CHECK(line.shared == !shared.empty(), "%zu stages", shared.size());
+    return shared;
+  };
+  typedef std::vector<int> V;
+  int n = 0;
+  auto same = [&](const V& got, const V& want, const char* what) {
+    CHECK(got == want, "%s: %zu stages shared", what, got.size());
+    ++n;
+  };
+  // the shapes that the tests of the device take
+  const Stages a = {{{4096, 256}}, {{2033, 2048}}, {{5111, 768}}, {{3000, 768}, {1000, 768}}}, b = {{{4096, 256}}, {{2048, 512}, {3072, 512}}, {{3072, 2000}}, {{2048, 1000}}};
+  const Stages c = {{{4096, 256}}, {{2048, 2048}}, {{2048, 4096}}}, d = {{{4096, 256}}, {{2048, 2048}}, {{2048, 2048}}, {{2048, 2048}}};
+  same(plan(a, 64, true, -1, -1, -1, false), V{1, 2}, "a");
+  same(plan(b, 64, true, -1, -1, -1, false), V{1, 2, 3}, "b");
+  same(plan(c, 64, true, -1, -1, -1, false), V{1, 2}, "c");
+  same(plan(d, 64, true, -1, -1, -1, false), V{1, 2, 3}, "d");
+  // a LLaMA-3.2-3B layer: q, k, v and down; o and gate, up have whole bands
+  const Stages layer = {{{3072, 3072}, {1024, 3072}, {1024, 3072}}, {{3072, 3072}}, {{8192, 3072}, {8192, 3072}}, {{3072, 8192}}, {{3072, 3072}, {1024, 3072}, {1024, 3072}}};
+  const V of_layer = plan(layer, 256, true, -1, -1, -1, false);
+  CHECK(std::count(of_layer.begin(), of_layer.end(), 3) == 1 && std::count(of_layer.begin(), of_layer.end(), 0) == 0, "%zu stages of a layer", of_layer.size());
+  same(plan(d, 64, false, -1, -1, -1, false), V{}, "not a kernel that can");
+  // (stage 2 in whole bands leaves workgroups without work, and stage 3 with whole bands)
+  same(plan(d, 64, true, 2, -1, -1, false), V{1}, "outputs that cannot be added to");
+  for (bool x : {false, true}) {
+    same(plan(d, 64, true, -1, 2, 1, x), V{1}, "a stage's outputs over the stage before");
+    same(plan(d, 64, true, -1, 1, 2, x), x ? V{1, 2, 3} : V{1}, "a stage's outputs over the next one's outputs, or read by the next one");
+    same(plan(d, 64, true, -1, 3, 1, x), V{1, 2, 3}, "outputs over those of two stages before");
+    same(plan(b, 64, true, -1, 1, 2, x), V{2, 3}, "two outputs of a stage in one place");
+  }
+  same(plan(d, 64, true, -1, 2, 2, true), V{1}, "outputs over their own activations");
+  same(plan({{{16, 256}}, {{2048, 2048}}, {{2048, 2048}}}, 64, true, -1, -1, -1, false), V{}, "workgroups without work in the stage before");
+  same(plan({{{4096, 256}}, {{1024, 4096}}}, 64, true, -1, -1, -1, false), V{}, "bands that would be cut three times");
+  std::printf("%d plans of stages\n", n);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "listing")) listing();
@@ -405,6 +470,7 @@ int main(int argc, char** argv) {
   else if (!std::strcmp(what, "ring")) ring();
   else if (!std::strcmp(what, "marks")) marks();
   else if (!std::strcmp(what, "shared")) shared();
+  else if (!std::strcmp(what, "stages")) stages();
   else return 2;
   return 0;
 }

@@ -54,3 +54,8 @@ def test_marks_of_units_of_any_lengths_never_share_a_place(driver):
 
 def test_shares_of_units_cut_no_band_twice(driver):
     assert "cut once" in driver("shared")
+
+
+def test_stages_that_are_cut_by_units(driver):
+    """Overlapping outputs, memory that cannot be added to, idle workgroups, bands cut more than once: whole bands then."""
+    assert "plans of stages" in driver("stages")
