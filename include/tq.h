@@ -236,8 +236,9 @@ int tq_step_create(int n, const tq_handle *hs, const void *const *xs, void *cons
  * no runs longer than 2 bytes) the whole step is one kernel launch: one workgroup per compute unit walks the stages, the
  * dictionary stays in LDS across them, and between two stages the workgroups hand over through a table of words in device
  * memory, one per workgroup, which every launch finds and leaves zero (outputs and activations of such a step are stored
- * and loaded device-coherently; one that two workgroups add to is zero from the stage before its own on, where nothing in
- * either stage lies in its place).  That needs all workgroups resident together, which holds when nothing else occupies the
+ * and loaded device-coherently; one that two workgroups add to - in fp32, each its part of the sum, rounded once - is zero from
+ * the stage before its own on; that needs outputs in this device's memory with nothing of either stage in their place, so the
+ * last bits of a staged step's results depend on where its outputs lie).  That needs all workgroups resident together, which holds when nothing else occupies the
  * GPU's compute units while the step runs; a wait is bounded (tq_step_set_spin_limit; about two seconds by default): a
  * workgroup that gives up sets a fault flag, every other wait of that launch ends within 32 polls, the results must not
  * be used, tq_step_get_info reports fault = 1 from then on and later calls of tq_step_launch return TQ_E_HIP (a captured

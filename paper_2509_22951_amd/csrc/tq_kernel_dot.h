@@ -350,7 +350,10 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // kShared: a staged step whose workgroups may share bands (shared_share).  A stage's largest share is then its units over the workgroups, rounded up, where
 // whole bands of 3 or 8 units leave some workgroups 6 units of 3.75, or 8 of 6.  us, whole bands -> shared, four LLaMA-3.2-3B layers in 16 stages 199.0 ->
 // 192.8, batch 2 209 -> 200, four 1B layers 165.5 -> 158.2; packed ones gained nothing (batch 1 160 -> 158, batch 2 87.3 -> 87.6, 1B 107.1 -> 107.7).  A kernel of its own:
-// with the choice made inside it, steps that share nothing lost 3 % (four layers of 1024 x 2048, batch 2, 122 -> 126).
+// with the choice made inside it, steps that share nothing lost 3 % (four layers of 1024 x 2048, batch 2, 122 -> 126).  A shared band's sum is no longer one
+// sum in double: each workgroup's part is scaled in double and rounded, and the two are added in fp32, so its low bits depend on where the outputs
+// lie (which decides whether bands are shared).  Relative error of 15 staged steps of up to 4 layers against 64 bits, in the 2-norm: 5.45e-8, whole bands (longer
+// runs of fp32 sums in a wavefront) 5.84e-8, none of them further off; rounded before and after the scale, as whole sums are, 5.51e-8.
 template <int kPiece, int kWaves, bool kPacked, int kB, bool kLong = false, bool kStaged = false, bool kOne = false, bool kShared = false>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   static_assert(kB == 1 || kB == 2, "one activation row or two");
@@ -867,13 +870,15 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
           const int bnd = j ? __builtin_amdgcn_readlane(slots, 2 * wave + 1) : __builtin_amdgcn_readlane(slots, 2 * wave);
           const bool mine = (j ? same[1] : same[0]) != 0;
           const uint32_t row = (uint32_t)bnd * kUnitRows + r16;
-          const float t = sum * slot_scale;
+          const bool part = kShared && ((uint32_t)bnd * nq < share_lo || ((uint32_t)bnd + 1) * nq > share_hi);   // another workgroup has the rest
+          // (a part is rounded once, behind its scale, and their sum once: as often as a whole band's sum)
+          const float t = kShared && part ? (float)(total * (double)slot_scale) : sum * slot_scale;
           if (a.gate_up) {   // lanes 2r, 2r + 1 hold the gate and the up row of output r
             const float other = __shfl_xor(t, 1);
             if (mine && !(r16 & 1) && row + 1 < m.rows) y_store<kStaged>(yb + (size_t)b * (m.rows / 2) + row / 2, silu_times(t, other));
           } else if (mine && row < m.rows) {
             float* out = yb + (size_t)b * m.rows + row;
-            if (kShared && ((uint32_t)bnd * nq < share_lo || ((uint32_t)bnd + 1) * nq > share_hi)) y_add(out, t);   // another workgroup has the rest
+            if (part) y_add(out, t);
             else y_store<kStaged>(out, t);
           }
         }

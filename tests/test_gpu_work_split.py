@@ -164,6 +164,67 @@ def test_bands_that_workgroups_of_a_stage_share(shapes, one_place, batch, opts):
             j.m.close()
 
 
+class _Exact:
+    """Stages of 2048 x 2048 in segments of 64, four units of every band's eight for each of two workgroups, with activations at one column
+    of a segment and 3 powers of two between the quads: what a wavefront sums is exact, and what is rounded are the band's sums alone."""
+    SHAPES = [(4096, 256), (2048, 2048), (2048, 2048), (2048, 2048)]     # (plan_driver.cpp: stages 1, 2, 3 share)
+
+    def __init__(self, batch=1):
+        rng = np.random.default_rng(7)
+        self.batch, self.mats, self.xs, self.scale, self.total = batch, [], [], [], []
+        for rows, cols in self.SHAPES:
+            q = rng.integers(-127, 128, (rows, cols), dtype=np.int8)
+            scale = rng.uniform(0.5, 1.0, rows).astype(np.float32)
+            quads = np.array([0, 2, 4, 6, 1, 3, 5, 7])[: cols // 256]
+            x = np.zeros((batch, cols // 256, 4, 64), np.float32)
+            x[..., 9] = rng.integers(128, 256, x.shape[:3]) * rng.choice([-1, 1], x.shape[:3]) * 2.0 ** (-3 * quads)[:, None]
+            x = x.reshape(batch, cols)
+            self.total.append(x.astype(np.float64) @ q.T.astype(np.float64))
+            self.scale.append(scale)
+            self.mats.append(tq.Matrix(tq.tq_encode_quantized(q, scale, seg_cols=64)))
+            self.xs.append(torch.from_numpy(x).cuda().to(torch.bfloat16))
+
+    def run(self, ys):
+        step = tq.Step([m.handle for m in self.mats], [x.data_ptr() for x in self.xs], [y.data_ptr() for y in ys], self.batch, stages=list(range(len(self.mats))))
+        assert step.info["persistent"] == 1
+        step.launch(_stream())
+        torch.cuda.synchronize()
+        step.close()
+        return [y.cpu().numpy() for y in ys]
+
+    def whole(self, k):      # a band's sum in double, rounded once, times its scale
+        return self.total[k].astype(np.float32) * self.scale[k]
+
+    def error(self, k, y):
+        exact = self.total[k] * self.scale[k].astype(np.float64)
+        return np.linalg.norm(y - exact) / np.linalg.norm(exact)
+
+
+@pytest.mark.parametrize("batch", [1, 2])
+def test_bands_that_workgroups_share_are_rounded_no_further_than_whole_ones(batch):
+    """Two parts, each rounded once, and their sum, against a sum that is rounded before and after its scale: the same error (here 3.56e-8
+    for 3.56e-8; with the parts rounded before and after their scale 4.29e-8).  Where outputs cannot be added to the bands are whole: then
+    every bit is that of the sum in double."""
+    e = _Exact(batch)
+    try:
+        fresh = lambda **kw: [torch.full((batch, r), float("nan"), dtype=torch.float32, **kw) for r, _ in e.SHAPES]
+        got = e.run(fresh(device="cuda"))
+        assert np.array_equal(got[0], e.whole(0))
+        for k in (1, 2, 3):
+            assert not np.array_equal(got[k], e.whole(k))     # (two workgroups have been at it)
+        shared, whole = (np.mean([e.error(k, y[k]) for k in (1, 2, 3)]) for y in (got, [e.whole(k) for k in range(4)]))
+        assert shared <= 1.05 * whole, (shared, whole)        # (18432 roundings of one spread: 1 % of it)
+        host = e.run(fresh(pin_memory=True))
+        place = torch.full((batch, 4096), float("nan"), dtype=torch.float32, device="cuda").view(-1)
+        over = e.run([place[:batch * r].view(batch, r) for r, _ in e.SHAPES])
+        for k in (1, 2, 3):
+            assert np.array_equal(host[k], e.whole(k))
+        assert np.array_equal(over[3], e.whole(3))
+    finally:
+        for m in e.mats:
+            m.close()
+
+
 # More bands than compute units, fewer than 8 stored columns: whole workgroups per matrix at the narrow end.
 NARROW = [(6, {}), (3, {}), (1, {}), (10, {"bits": 4, "pack": True}), (14, {"bits": 4, "pack": True})]
 
