@@ -225,6 +225,54 @@ def test_bands_that_workgroups_share_are_rounded_no_further_than_whole_ones(batc
             m.close()
 
 
+def _chain():
+    """A stage whose activations are the shared outputs of the stage before: small whole numbers as fp32 are pairs (0, the number) of bf16."""
+    rng = np.random.default_rng(3)
+    shapes = [(4096, 256), (2048, 2048), (2048, 4096)]       # (plan_driver.cpp: stages 1 and 2 share)
+    q = [rng.integers(-1, 2, s, dtype=np.int8) for s in shapes]
+    q[2][:, rng.permutation(4096)[:3800]] = 0                # (148 or so of its columns meet a number: sums below 2^24)
+    x0, x1 = (np.where(np.arange(c) % 32 == 5, rng.integers(-1, 2, c), 0).astype(np.float32) for c in (256, 2048))
+    y1 = q[1].astype(np.int64) @ x1.astype(np.int64)
+    pairs = np.zeros(4096, np.int64)
+    pairs[1::2] = y1
+    assert np.abs(y1).max() < 256
+    refs = [q[0].astype(np.int64) @ x0.astype(np.int64), y1, q[2].astype(np.int64) @ pairs]
+    mats = [tq.Matrix(tq.tq_encode_quantized(w, np.ones(len(w), np.float32), seg_cols=64)) for w in q]
+    ys = [torch.full((r,), float("nan"), dtype=torch.float32, device="cuda") for r, _ in shapes]
+    xs = [torch.from_numpy(x0).cuda().to(torch.bfloat16), torch.from_numpy(x1).cuda().to(torch.bfloat16), ys[1]]
+    step = tq.Step([m.handle for m in mats], [x.data_ptr() for x in xs], [y.data_ptr() for y in ys], 1, stages=[0, 1, 2])
+    return mats, xs, ys, refs, step
+
+
+@pytest.mark.parametrize("replayed", [False, True], ids=["launched", "in a graph"])
+def test_a_stage_reads_what_two_workgroups_added_to_in_the_stage_before(replayed):
+    mats, xs, ys, refs, step = _chain()
+    try:
+        assert step.info["persistent"] == 1
+        graph = None
+        if replayed:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+                step.launch(torch.cuda.current_stream().cuda_stream)
+        for turn in range(6):
+            for y in ys:
+                y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            if replayed and turn % 3 != 2:
+                graph.replay()
+            else:
+                step.launch(_stream())          # (eager work between the replays)
+            torch.cuda.synchronize()
+            for y, ref in zip(ys, refs):
+                assert np.array_equal(y.cpu().numpy(), ref.astype(np.float32))
+        assert tq.tq_step_get_info(step.handle)["fault"] == 0
+        del graph
+    finally:
+        step.close()
+        for m in mats:
+            m.close()
+
+
 # More bands than compute units, fewer than 8 stored columns: whole workgroups per matrix at the narrow end.
 NARROW = [(6, {}), (3, {}), (1, {}), (10, {"bits": 4, "pack": True}), (14, {"bits": 4, "pack": True})]
 
