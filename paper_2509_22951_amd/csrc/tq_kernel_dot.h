@@ -345,7 +345,7 @@ __device__ __forceinline__ float silu_times(float gate, float up) { return gate 
 // which the compiler prepares for with some 200 instructions ahead of the first load.  A small launch is bound by what its wavefronts do
 // before they decode: every instruction of a wavefront with one neighbour on its SIMD is 2 to 4 ns, a round trip to memory only 160.
 // 2048 x 2048, batch 1, us after the first wavefront's start, before -> now (no search and no 64-bit divisions either, 4 columns of x to a
-// load, the dictionary through request_to_lds, behind the first codes where there is no loop): its job known 1.5 -> 0.6, everything requested 3.7 -> 2.4, decode
+// load, the dictionary through request_to_lds, behind the first codes): its job known 1.5 -> 0.6, everything requested 3.7 -> 2.4, decode
 // from 6.1 -> 3.9, end of a pass 10.1 -> 8.7 (7.7 with marks, see kSplit); one LLaMA-3.2-1B layer 18.3 -> 17.2.
 // kShared: a staged step whose workgroups may share bands (shared_share).  A stage's largest share is then its units over the workgroups, rounded up, where
 // whole bands of 3 or 8 units leave some workgroups 6 units of 3.75, or 8 of 6.  us, whole bands -> shared, four LLaMA-3.2-3B layers in 16 stages 199.0 ->
@@ -613,8 +613,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
     {   // one activation row, or two: larger batches run the MFMA kernels
       const uint16_t* xb = job.x;
       float* yb = job.y;
-      // Activations and dictionary are requested first: their addresses wait for nothing but the description.  (With a loop over jobs the
-      // dictionary goes to LDS when the one before it is no longer in use.)
+      // Activations and dictionary are requested first: their addresses wait for nothing but the description.  (A further matrix's
+      // dictionary goes to LDS when the one before it is no longer in use; in staged steps so does the first, see lds_arrived.)
       uint32_t xlo[kXRegs], xhi[kXRegs];
       auto request_activations = [&] {
         if constexpr (kPacked) {
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
         }
       };
       if constexpr (!kStaged) request_activations();   // (staged: they may still be in the making)
-      const bool dict_first = kOne && new_dict;   // (with a loop over jobs: see lds_arrived)
+      const bool dict_first = !kStaged && new_dict && !lds_used;
       constexpr uint32_t kDictAhead = 4;   // rounds of the dictionary that are on their way while the unit offsets arrive; the others behind the first codes
       if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, 0, kDictAhead);
       if (!planned) {
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       }
       lds_used = true;
       if constexpr (kStaged) request_activations();
-      if (!kOne && new_dict) {
+      if (new_dict && !dict_first) {
         request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict);
         lds_arrived();
       }

@@ -385,9 +385,11 @@ __device__ __forceinline__ void request_to_lds(const void* src, uint32_t n16, in
     __builtin_amdgcn_global_load_lds((global_cu32*)from + 4 * lane, (lds_mu32*)(size_t)to, 16, 0, 0);
 }
 // Where requests depend on a condition (a dictionary that is new) inside a loop over jobs, the wait belongs into the same branch: with a condition of its
-// own the compiler takes the requests for unfinished on the way round it, and every barrier of the loop waits for all loads, those of the next
+// own the compiler takes the requests for unfinished on the way round it, and the barriers of the loop wait for all loads, those of the next
 // activation tile or of the next codes among them (us, wait behind the tile or the image -> with the requests: eight LLaMA-3.2-3B layers batch 8 218.5 -> 217.0, packed
-// 153.9 -> 151.5; four in 16 stages 192.6 -> 190.7, batch 2 200.0 -> 198.1).
+// 153.9 -> 151.5; four in 16 stages 192.6 -> 190.7, batch 2 200.0 -> 198.1).  k_matvec without stages keeps them apart: its workgroups have one job or two, and
+// the first dictionary's first rounds ahead of the unit offsets are worth a little more (together -> apart: six LLaMA-3.2-1B layers 79.8 -> 79.4, eight 3B layers
+// batch 2 173.4 -> 172.8, packed ones 82.5 -> 82.6).
 __device__ __forceinline__ void lds_arrived() {
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) alone.  (The builtin, not inline assembly: the compiler sees that these loads are done)
   asm volatile("" ::: "memory");

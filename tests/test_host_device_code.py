@@ -37,7 +37,7 @@ def assembly(tmp_path_factory):
 
 @pytest.mark.parametrize("what,name,number", [
     ("products of up to 16 rows", r"_ZN2tq13k_matvec_ringI", 8),
-    ("dot products with a loop over jobs", r"_ZN2tq8k_matvecILi\d+ELi\d+ELb[01]ELi[12]ELb[01]ELb[01]ELb0E", 11),     # (kOne false)
+    ("staged steps", r"_ZN2tq8k_matvecILi\d+ELi\d+ELb[01]ELi[12]ELb0ELb1E", 6),
 ])
 def test_barriers_of_kernels_with_a_loop_wait_for_no_loads(assembly, what, name, number):
     found = {k: v for k, v in assembly.items() if re.match(name, k)}
