@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void k_mark_units(const uint2* codes, const ui
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (uint32_t u = blockIdx.x * 4 + wave; u < n_units; u += gridDim.x * 4) {
     const uint32_t begin = ((const_u32*)uoff)[u], end = ((const_u32*)uoff)[u + 1];
-    T* mark = marks + mark_index(u, begin) * 64 + lane;
+    T* mark = marks + mark_index(begin) * 64 + lane;
     u16x2 pairs = {0, 0};
     for (uint32_t from = begin; from + kMarkChunks < end; from += kMarkChunks) {   // (a mark at the unit's end is no place to start)
 #pragma unroll
@@ -469,7 +469,7 @@ static int tq_create_from_encoded_impl(const void* blob, size_t blob_bytes, tq_h
   m.dict16_bytes = dict->image_bytes;
 
   const uint64_t n_units = (uint64_t)h.n_bands * h.n_quads;
-  const uint64_t sz_uoff = round_up(marks_at(n_units) + (long_runs ? 0 : marks_size(n_units, h.n_chunks, h.seg_cols)), kSectionAlign), sz_codes = round_up(h.code_bytes, kSectionAlign),
+  const uint64_t sz_uoff = round_up(marks_at(n_units) + (long_runs ? 0 : marks_size(h.n_chunks, h.seg_cols)), kSectionAlign), sz_codes = round_up(h.code_bytes, kSectionAlign),
                  sz_scales = round_up(h.scale_bytes, kSectionAlign);
   const uint64_t o_uoff = 0, o_codes = o_uoff + sz_uoff, o_scales = o_codes + sz_codes, o_desc = o_scales + sz_scales,
                  total = o_desc + round_up(sizeof(DevMat), kSectionAlign);

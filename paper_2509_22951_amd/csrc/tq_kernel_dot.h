@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
       } else if (u0 < u1) {
         load_piece(m, cwa, sa, na, false, false);
       }
-      if (head_shared) request_place(m, u0, unit_start, c0, lane, place);
+      if (head_shared) request_place(m, unit_start, c0, lane, place);
       if (dict_first) request_to_lds(m.dict_bf16, m.dict_words / 4, lane, wave, kWaves, lds_dict, kDictAhead);
       if constexpr (kStaged) {   // while the other workgroups arrive
         if (head_shared) passed = columns_passed(place, unit_start, c0);

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {
     // that earlier wavefronts pass.
     auto ready = [&]() -> uint32_t {
       Place place;
-      if (run.head) request_place(m, run.u0, run.unit_start, run.c0, lane, place);
+      if (run.head) request_place(m, run.unit_start, run.c0, lane, place);
       if (new_dict) stage_image(m, lane, wave, kWaves, lds4);
       const uint32_t start = run.head ? columns_passed(place, run.unit_start, run.c0) : 0u;
       if (new_dict) {

@@ -411,11 +411,11 @@ struct Place {
   uint32_t mark;
   uint2 c[kMarkChunks - 1];
 };
-__device__ __forceinline__ void request_place(const DevMat& m, uint32_t unit, uint32_t unit_start, uint32_t c0, int lane, Place& p) {
+__device__ __forceinline__ void request_place(const DevMat& m, uint32_t unit_start, uint32_t c0, int lane, Place& p) {
   const uint32_t k = (c0 - unit_start) / kMarkChunks, from = unit_start + k * kMarkChunks;
   p.mark = 0;
   if (k) {
-    const uint64_t at = (mark_index(unit, unit_start) + k) * mark_bytes(m.seg_cols);
+    const uint64_t at = (mark_index(unit_start) + k) * mark_bytes(m.seg_cols);
     const uint8_t* marks = (const uint8_t*)m.uoff + marks_at((uint64_t)m.n_bands * m.n_quads) + at;
     p.mark = m.seg_cols <= kMarkByteCols ? global_load(marks + lane) : global_load((const uint16_t*)marks + lane);
   }

@@ -126,16 +126,17 @@ constexpr int ring_piece(int bytes) { return bytes == kSmallRingBytes ? kSmallRi
 TQ_HD bool ring_leftover(uint32_t pos) { return (pos & 7u) != 0; }
 
 // Marks: where every lane of a unit stands at each kMarkChunks-th chunk of it (the pairs it has passed; its columns are those and a column
-// a code), so that a wavefront can start inside a unit.  A mark is 64 values, one per lane, of a byte where segments are narrow enough.  Unit u,
-// whose first chunk is c, keeps that of its chunk k * kMarkChunks at mark_index(u, c) + k: units of any lengths never meet there, since the
-// quotient of the next unit's first chunk grows by at least that of this one's length, and the place of k = 0, which nobody needs, is spare.
+// a code), so that a wavefront can start inside a unit.  A mark is 64 values, one per lane, of a byte where segments are narrow enough.  A unit
+// whose first chunk is c keeps that of its chunk k * kMarkChunks, k >= 1, at mark_index(c) + k: units of any lengths never meet there, since its last one is
+// at most the quotient of the chunk behind it, and the next unit's first one lies above that.  (So marks are a 64th of the codes, or a 32nd, however
+// short the units are; with a place for k = 0 as well segments of 16 columns had 8 % of them.)
 constexpr uint32_t kMarkChunks = 8, kMarkByteCols = 510;   // (pairs of a lane: at most half the columns of its segment)
 constexpr uint32_t kMarkAlign = 256;
-TQ_HD uint64_t mark_index(uint32_t unit, uint32_t first_chunk) { return (uint64_t)unit + first_chunk / kMarkChunks; }
+TQ_HD uint64_t mark_index(uint32_t first_chunk) { return first_chunk / kMarkChunks; }
 TQ_HD uint32_t mark_bytes(uint32_t seg_cols) { return seg_cols <= kMarkByteCols ? 64 : 128; }
 // The marks lie behind the n_units + 1 unit offsets, at this many bytes from them.
 TQ_HD uint64_t marks_at(uint64_t n_units) { return ((n_units + 1) * 4 + kMarkAlign - 1) / kMarkAlign * kMarkAlign; }
-inline uint64_t marks_size(uint64_t n_units, uint64_t n_chunks, uint32_t seg_cols) { return (n_units + n_chunks / kMarkChunks + 1) * mark_bytes(seg_cols); }
+inline uint64_t marks_size(uint64_t n_chunks, uint32_t seg_cols) { return (n_chunks / kMarkChunks + 1) * mark_bytes(seg_cols); }
 
 // Whole workgroups for the matrices of a launch (or of a stage): wgs[i] of them for matrix i, `grid` at most together, such
 // that the largest share (bands x columns) is as small as possible, to within an eighth of the widest row, and the others' too

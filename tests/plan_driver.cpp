@@ -348,14 +348,15 @@ static void marks() {
       for (uint32_t u = 0; u < n_units; ++u) {
         const uint32_t len = 1 + next(longest);
         for (uint32_t k = 1; k * tq::kMarkChunks < len; ++k, ++total) {
-          const uint64_t place = tq::mark_index(u, at) + k;
+          const uint64_t place = tq::mark_index(at) + k;
           CHECK(!(place < behind), "unit %u mark %u", u, k);
           behind = place + 1;
         }
         at += len;
       }
       for (uint32_t seg_cols : {16u, 496u, 512u, 1024u}) {
-        CHECK(!(behind * tq::mark_bytes(seg_cols) > tq::marks_size(n_units, at, seg_cols)), "%u units", n_units);
+        CHECK(!(behind * tq::mark_bytes(seg_cols) > tq::marks_size(at, seg_cols)), "%u units", n_units);
+        CHECK(!(tq::marks_size(at, seg_cols) > at * 512ull / 64 * (tq::mark_bytes(seg_cols) / 64) + 128), "%u units of %u chunks", n_units, at);   // of the codes
         const uint32_t most = seg_cols / 2;   // pairs of a lane
         CHECK(!(tq::mark_bytes(seg_cols) == 64 ? most > 255 : most > 65535), "%u columns", seg_cols);
       }
