@@ -114,7 +114,9 @@ __device__ __forceinline__ void decode_units_ring(const DevMat& m, uint32_t quad
       wc = unit_offset(m, u);
       const uint32_t len = unit_offset(m, u + 1) - wc;
       w_left = (len + kP - 1) / kP;
-      w_base = piece_length(len, w_left);
+      // (the kernel for 16 rows and packed weights is at its register limit and loses by the branches of piece_length: us, with them -> a division, 30
+      // matrices of 1420 x 1536 55.4 -> 53.8, seven LLaMA-3.2-3B pairs of 8192 x 3072 and back 121.9 -> 120.5, batch 9 117.9 -> 117.2; the one for 8 rows gains by them, 71.8 -> 71.0)
+      w_base = kPacked && kRows == 16 ? len / w_left : piece_length(len, w_left);
       w_rem = len - w_base * w_left;
     }
     n = w_base + (w_rem ? 1u : 0u);
