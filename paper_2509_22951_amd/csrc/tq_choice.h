@@ -74,6 +74,8 @@ constexpr double kAddsPerUs = .105e6;   // floating-point additions to y that th
 // 14 %.  Which is the faster kernel by it costs 0.5 % over the better of both on average, and more than 5 % in one launch of 26; by
 // bands per compute unit (24, above 8 rows of x 12) it was 9 % and more than 5 % in one of 4, worst where narrow segments have
 // many sums to add (4 times the time), or few bands of many quads leave the ring kernel's wavefronts idle.
+// (The kernels have since become faster, the runs kernel by 4 % in the middle and up to 10 in small shares.  4,932 launches of whole units, 1 to 30 matrices: the
+// choice costs 1.2 % over the better kernel, more than 5 % in one of 11; with the kernels that the times were fitted to 1.1 %, one of 13.)
 inline double ring_time(int n, const BatchedMatrix* m, uint64_t n_cu, int batch, bool packed, bool gate_up) {
   static const RingTimes table[2][2] = {{{2.7, 1.1, 5.1, .56, .79, 1.0, 0., .039}, {1.9, 1.4, 4.6, .67, 1.06, 2.2, .04, 0.}},
                                         {{3.5, 1.25, 3.3, .37, .48, .5, .06, .04}, {1.8, 1.35, 2.6, .6, .76, 1.9, .06, 0.}}};

@@ -365,10 +365,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec(MatvecArgs a) {
   // matrix's marks say, to within 7 chunks that are counted while the dictionary is on its way (request_place).  (Counted from the codes of
   // the whole unit, each wavefront its part and the counts exchanged through LDS, it took as long again as the decode and paid in shares of up
   // to two units: 2048 x 2048 8.74 -> 7.67 us, 3072 x 3072 10.7 -> 9.1.)
-  // What is left of the cost is the sums of bands that are shared.  It pays where whole units leave a quarter of the wavefronts' time idle;
-  // packed ones, which fewer chunks keep busier, where they leave half of the wavefronts without any.  us, whole units -> split, batch 1: 3 units
+  // What is left of the cost is the sums of bands that are shared.  It pays where whole units leave a quarter of the wavefronts' time idle (of 8 wavefronts:
+  // 1 to 6 units, 9 to 12, 17 and 18); packed ones, which fewer chunks keep busier, where they leave half of the wavefronts without any.  us, whole units -> split, batch 1: 3 units
   // (3072 x 3072) 10.7 -> 9.1, 6 units (8192 x 3072) 12.0 -> 11.8, 9 units 15.0 -> 13.8, 12 units 15.9 -> 15.5, 14 units (8192 x 7168) 16.3 -> 16.7, 14
-  // to 16 (a LLaMA-3.2-1B layer) 17.1 -> 17.9; batch 2: 6 units 13.8 -> 13.3, 12 units 19.1 -> 18.1; packed: 6 units 9.7 -> 9.5, batch 2 11.0 -> 10.5; 9
+  // to 16 (a LLaMA-3.2-1B layer) 17.1 -> 17.9, 18 units (24576 x 3072) 20.8 -> 19.3; batch 2: 6 units 13.8 -> 13.3, 12 units 19.1 -> 18.1, 18 units 25.2 -> 22.7; packed: 6 units 9.7 -> 9.5, batch 2 11.0 -> 10.5; 9
   // units 10.9 -> 11.5, batch 2 12.3 -> 12.8.
   constexpr bool kSplit = !kLong;
   // Packed weights are bound by issue and the LDS pipe and gain most from wavefronts that end together (see pace; us, eight LLaMA-3.2-3B layers 87 -> 83,

@@ -228,7 +228,7 @@ __device__ __forceinline__ void decode_run_ring(const DevMat& m, uint32_t u0, ui
 }
 
 // kSplit: as in k_matvec, a share of few units is cut into equal runs of chunks, and the marks say where the lanes stand at the start of one
-// (4099 x 2999 batch 5 17.8 -> 15.4 us against counts of each wavefront's part, exchanged through LDS).  A lone wavefront takes 8 us for a unit of 33 chunks, but the
+// (4099 x 2999 batch 5 17.8 -> 15.8 us against counts of each wavefront's part, exchanged through LDS).  A lone wavefront takes 8 us for a unit of 33 chunks, but the
 // windows around a cut are multiplied on both sides of it, each time with zeros for the other side's columns: shares that
 // leave less than half the wavefronts idle (above 8 batch rows, where the operands are twice as many loads: two thirds) are
 // faster in whole units.  (us, whole units -> split: 2048 x 2048 batch 8 19.7 -> 15.0, 700 x 1999 batch 5 20.2 -> 16.6; 6 units of
@@ -243,7 +243,7 @@ constexpr uint32_t kRunSplitMin = 11;   // least chunks of a run, a third of a u
                                         // 13.7 / 13.0, 2048 x 2048 batch 8 16.3 / 16.3 / 16.0 / 15.0, 700 x 1999 batch 5 17.8 / 17.9 / 18.0 / 16.6)
 constexpr uint32_t kRunSplitMinSmall = 9;   // with rings of 64 bytes, whose pieces are 9 chunks (11 / 9, us: 1024 x 1024 batch 8 10.8 / 10.1, 2048 x 2048 12.9 /
                                             // 12.5, 700 x 1999 15.9 / 16.7; batch 16 14.3 / 14.5)
-// kOne: as in k_matvec (one LLaMA-3.2-3B layer batch 8 36.7 -> 35.4 us; 4099 x 2999 batch 5, which has the loop over jobs, 18.1 -> 16.9 by the
+// kOne: as in k_matvec (one LLaMA-3.2-3B layer batch 8 37.1 -> 36.5 us; 4099 x 2999 batch 5, which has the loop over jobs, 18.1 -> 16.9 by the
 // first codes requested ahead of the dictionary alone).
 template <int kRing, int kWaves, bool kPacked, int kFold, bool kOne>
 __global__ __launch_bounds__(kWaves * 64, 1) void k_matvec_runs(MatvecArgs a) {

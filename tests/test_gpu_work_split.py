@@ -40,18 +40,20 @@ class _Job:
 
 
 SHARES = [
-    # rows, cols, seg_cols: units of a workgroup's share (whole bands of quads) and their length
+    # rows, cols, seg_cols: units of a workgroup's share (whole bands of quads) and their length.  Units are shared between 8 wavefronts
+    # in shares of 1 to 6, 9 to 12, 17 and 18, between 12 (packed) in shares of up to 6.
     (16, 8, 16),          # one unit of two chunks for 8 or 12 wavefronts: most runs are empty
     (16, 250, 64),        # one unit
-    (16, 500, 64),        # two units (packed: one): the most that are shared between 8 wavefronts
-    (16, 700, 64),        # three units (packed: two): whole
-    (16, 1500, 64),       # six units (packed: three, the most that are shared between 12 wavefronts)
-    (16, 2000, 64),       # eight units (packed: four: whole)
-    (16, 3000, 64),       # one band of 12 units, the last one part empty
+    (16, 500, 64),        # two units (packed: one)
+    (16, 700, 64),        # three units (packed: two)
+    (16, 1500, 64),       # six units, the most of the first kind (packed: three)
+    (16, 2000, 64),       # eight units: a whole one each (packed: four)
+    (16, 3000, 64),       # one band of 12 units, the last one part empty (packed: six)
     (16, 4096, 32),       # one band of 32 units
     (16, 3968, 32),       # 31 units: one wavefront has one less
     (4099, 1500, 128),    # one or two bands of 3 units, ragged rows and columns
     (8192, 512, 32),      # two bands of 4 units: a whole unit each for 8 wavefronts
+    (16, 4600, 64),       # 18 units, two to a wavefront and two over
 ]
 
 
