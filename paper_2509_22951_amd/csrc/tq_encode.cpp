@@ -269,11 +269,15 @@ class RunDict {
   std::vector<uint8_t> len_;
 };
 
+// (packed values: the same number of weights per segment by default)
+uint32_t segment_width(const tq_encode_opts* o) {
+  return o && o->seg_cols ? o->seg_cols : o && o->packing == TQ_PACK_NIBBLES ? TQ_DEFAULT_SEG_COLS / 2 : TQ_DEFAULT_SEG_COLS;
+}
+
 int check_opts(const tq_encode_opts* o, uint32_t* max_entries, uint32_t* lmax, uint32_t* seg_cols, unsigned* n_threads) {
   *max_entries = (o && o->max_entries) ? o->max_entries : TQ_MAX_ENTRIES_DEVICE;
   *lmax = (o && o->lmax) ? o->lmax : TQ_DEFAULT_LMAX;
-  // (packed values: the same number of weights per segment by default)
-  *seg_cols = (o && o->seg_cols) ? o->seg_cols : (o && o->packing == TQ_PACK_NIBBLES) ? TQ_DEFAULT_SEG_COLS / 2 : TQ_DEFAULT_SEG_COLS;
+  *seg_cols = segment_width(o);
   *n_threads = pick_threads(o ? o->n_threads : 0);
   if (*lmax < 1 || *lmax > TQ_MAX_LMAX) {
     set_error("tq_encode: lmax must be 0 (default) or in [1, " + std::to_string(TQ_MAX_LMAX) + "]");
@@ -508,7 +512,7 @@ class Bands {
 // 0.81, 0.61, 0.56; 64 x 8192 0.84, 0.63, 0.56; 1024 x 256 0.76, 0.72, 0.58; 2048 x 512 0.88, 0.85, 0.83.)
 constexpr uint64_t kThreadBytes = 1u << 17;
 unsigned crew_size(const tq_encode_opts* opts, uint32_t rows, uint32_t cols) {
-  const uint64_t unit_cols = (uint64_t)kUnitPanels * std::max(kMinSegCols, opts && opts->seg_cols ? opts->seg_cols : kDefaultSegCols);
+  const uint64_t unit_cols = (uint64_t)kUnitPanels * std::max(kMinSegCols, segment_width(opts));   // (not checked yet)
   const uint64_t units = (rows + (uint64_t)kUnitRows - 1) / kUnitRows * ((cols + unit_cols - 1) / unit_cols), asked = opts ? opts->n_threads : 0;
   return (unsigned)std::min<uint64_t>(pick_threads((uint32_t)asked), asked ? units : std::max<uint64_t>(1, (uint64_t)rows * cols / kThreadBytes));
 }

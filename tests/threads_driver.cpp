@@ -61,6 +61,15 @@ int main() {
     tq_free_blob(blob);
     if (rc != TQ_OK || calls != 3) return std::printf("16 x 16384 (%s): rc %d, %d threads beside the caller's\n", quantized ? "quantized" : "fp32", rc, calls), 1;
   }
+  // Two values to a byte: segments of half as many bytes, so 16 x 4096 weights are four units.
+  calls = 0;
+  o.bits = 4;
+  o.packing = TQ_PACK_NIBBLES;
+  void* packed = nullptr;
+  size_t packed_bytes = 0;
+  if (tq_encode(wide.data(), 16, 4096, &o, &packed, &packed_bytes) != TQ_OK || calls != 3) return std::printf("16 x 4096 (packed): %d threads beside the caller's\n", calls), 1;
+  tq_free_blob(packed);
+  o.bits = o.packing = 0;
   // Nobody asks, and all of it is less work than starting a thread.
   calls = 0;
   o.n_threads = 0;
