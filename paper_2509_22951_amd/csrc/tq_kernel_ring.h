@@ -35,7 +35,7 @@ namespace tq {
 // multiples of 32 (packed 4-bit weights: 32..128 bytes), and 16-byte aligned activations.
 //
 // 16 wavefronts: with rings of 128 bytes there is LDS for 10, which keep the vector ALUs busy for 75 % of the time.  12 of gated pairs,
-// whose sums stay in registers (16 would spill them); of the plain forms the one for packed weights and 9 to 16 rows of x spills 11
+// whose sums stay in registers (16 would spill them); of the plain forms the one for packed weights and 9 to 16 rows of x spills 9
 // registers and is still faster with 16.  us, rings of 128 bytes -> 64 with 16 | 12 wavefronts: eight LLaMA-3.2-3B layers batch 4
 // 225 -> 203 | 222, batch 8 228 -> 208 | 223, batch 16 252 -> 228 | 239, packed weights batch 8 182 -> 151 | 169, batch 16 202 ->
 // 183 | 189; gated pairs of eight blocks batch 8 116 -> 103 | 99, batch 16 119 -> 113 | 102, packed batch 8 92 -> 80 | 77, batch 16
