@@ -119,7 +119,8 @@ int tq_validate_blob(const void *blob, size_t blob_bytes, tq_info *info);
 /*
  * blob: host.  Validates as tq_validate_blob does (so the kernels need no bounds checks on codes),
  * copies dictionary, offsets, codes and scales into device memory owned by the handle, on the
- * current HIP device.  Synchronous.  The caller may free blob on return.
+ * current HIP device, and beside them notes where the lanes of a unit stand at every 8th chunk (a 64th of the codes, a
+ * 32nd where segments are wider than 510 columns; not among the bytes of tq_get_info).  Synchronous.  The caller may free blob on return.
  * This is the "parameters stay compressed in memory" state of the paper's Background "Inference".
  */
 int tq_create_from_encoded(const void *blob, size_t blob_bytes, tq_handle *out);

@@ -123,7 +123,8 @@ def test_matrices_of_a_call_get_whole_workgroups(n):
 
 
 # Stages whose workgroups take equal numbers of units: bands of 2, 3, 4 and 8 quads that two workgroups share, ragged last bands,
-# matrices beside each other.  (The first stage has a band for every workgroup, as clearing ahead needs it.)
+# matrices beside each other.  (The first stage has a band for every workgroup, as clearing ahead needs it.  Which stages share is
+# plan_driver.cpp's to say; packed matrices never do, nor outputs in one place.)
 SHARED = [
     [[(4096, 256)], [(2033, 2048)], [(5111, 768)], [(3000, 768), (1000, 768)]],       # shares of 4 of 8, 4 of 3; 3 of 3: whole bands
     [[(4096, 256)], [(2048, 512), (3072, 512)], [(3072, 2000)], [(2048, 1000)]],      # 3 of 2, 6 of 8, 2 of 4
